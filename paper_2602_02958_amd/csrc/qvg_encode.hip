@@ -18,11 +18,12 @@
 // carry a rounding error, so the kernel keeps the three largest scores per token
 // (cluster index carried in the 7 low mantissa bits) and certifies the winner only
 // when it leads by more than a bound on that error,
-//     thr = 2^-14 * (||x||^2 / 2 + max_j ||c_j||^2),
-// which covers the 131 accumulation roundings of half an ulp each plus the index tag for both
-// scores (with more than 256 centroids the tag has 8 bits and the factor is 1.5 * 2^-14).  Otherwise the candidates are re-evaluated in fp64: the two leaders
-// cooperatively by the wavefront, or, if the third score is inside the band as well,
-// all K centroids with the channels summed in index order (the reference order).
+//     thr = 2^-14 * (||x||^2 / 2 + N),
+// N the largest ||c_j||^2 among the centroids that can be the nearest, which covers the 131
+// accumulation roundings of half an ulp each plus the index tag for both scores (with more than 256
+// centroids the tag has 8 bits and the factor is 1.5 * 2^-14).  Otherwise the candidates are
+// re-evaluated in fp64, cooperatively by the wavefront: the two leaders, or, if the third score is
+// inside the band as well, every centroid that a second look at the fp32 scores leaves possible.
 // Equal fp64 distances go to the lower index.
 #include "qvg_internal.hpp"
 
@@ -33,6 +34,7 @@ constexpr int kAsgWaves = kAsgThreads / 64;
 constexpr int kAsgTile = 64;                    // tokens per wavefront step (two MFMA column blocks)
 constexpr int kCPitch = 136;                    // bf16 elements per LDS centroid row (272 B): 128 + (hi, mid, lo of -||c||^2/2) + 5 zeros
 constexpr int kPrepThreads = 256;
+constexpr int kScanPairs = 24;                  // candidates up to which fp64 distances are taken two at a time
 
 __device__ __forceinline__ void insert3(float v, int idx, float &b1, float &b2, float &b3,
                                         int &i1, int &i2) {
@@ -66,6 +68,10 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// acc + a.lo b.lo + a.hi b.hi of two packed bf16 pairs: v_dot2_f32_bf16
+__device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float acc) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), acc, false);
 }
 template <bool V> struct BoolK { static constexpr bool value = V; };
 // (a & mask) | (b & ~mask): v_bfi_b32
@@ -209,6 +215,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
     extern __shared__ __align__(16) unsigned char smem[];
     bf16_t *lc = reinterpret_cast<bf16_t *>(smem);                       // [Kpad][kCPitch]
     bf16_t *lscr = lc + (size_t)Kpad * kCPitch;                          // [waves][128]
+    float *lsscr = reinterpret_cast<float *>(lscr + kAsgWaves * kHeadDim);   // [waves][Kpad]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5, col = lane & 31;
@@ -283,6 +290,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
     __syncthreads();
     const float cmax = norms_given ? a.cmax[h] : __uint_as_float(smax);
     bf16_t *scr = lscr + wave * kHeadDim;
+    float *sscr = lsscr + wave * Kpad;
     // token operand of the extra MFMA step: three ones against (hi, mid, lo), lanes 0..31 only
     // 7 tag bits name a row among 256; with more rows the tag takes 8 (and the band below widens)
     const uint32_t tagbits = K > 256 ? 0xFFu : 0x7Fu;
@@ -305,6 +313,92 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
             for (int kk = 0; kk < 8; ++kk)
                 dst[tb][kk] = (nn < N) ? *reinterpret_cast<const uint4 *>(xp + kk * 8) : make_uint4(0u, 0u, 0u, 0u);
         }
+    };
+    // fp64 squared distances of the token in `scr` to centroids ja and jb (wave-uniform indices), one
+    // per half of the wavefront: two rows of 16 lanes summed by DPP moves, the row sums read as
+    // scalars (no exchange through LDS).  Both go through the same operations, so equal rows give
+    // equal sums.
+    auto pair_dist = [&](int ja, int jb, double &Da, double &Db) {
+        const int cand = half ? jb : ja;
+        const uint2 xv = *reinterpret_cast<const uint2 *>(scr + col * 4);
+        const uint2 cv = *reinterpret_cast<const uint2 *>(lc + cand * kCPitch + col * 4);
+        const double e0 = (double)bf16_lo(xv.x) - (double)bf16_lo(cv.x);
+        const double e1 = (double)bf16_hi(xv.x) - (double)bf16_hi(cv.x);
+        const double e2 = (double)bf16_lo(xv.y) - (double)bf16_lo(cv.y);
+        const double e3 = (double)bf16_hi(xv.y) - (double)bf16_hi(cv.y);
+        double d = e0 * e0; d += e1 * e1; d += e2 * e2; d += e3 * e3;
+        d = sum16_f64(d);
+        Da = readlane_f64(d, 0) + readlane_f64(d, 16);
+        Db = readlane_f64(d, 32) + readlane_f64(d, 48);
+    };
+    // Nearest centroid of the token in `scr` when more than two may be: the fp32 scores once more, one
+    // centroid per lane, and fp64 distances only for those within `band` of the best (the bound on the
+    // error of a score holds for this sum as well: as many roundings, and no tag).  With all K
+    // distances in fp64 instead, these tokens were a third of the time of a QVG-Pro encode's later
+    // stages: 24 units x 4680 tokens, S = 4, K = 256, I = 3 took 1.06 ms, with this and the band
+    // below 0.81.
+    auto scan_rows = [&](float band) -> int {
+        float best = -INFINITY;
+#pragma unroll 1
+        for (int j = lane; j < K; j += 64) {
+            const bf16_t *cr = lc + j * kCPitch;
+            float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll 4
+            for (int kk = 0; kk < 16; ++kk) {
+                const uint4 xv = *reinterpret_cast<const uint4 *>(scr + kk * 8);
+                const uint4 cv = *reinterpret_cast<const uint4 *>(cr + kk * 8);
+                s0 = dot2(xv.x, cv.x, s0); s1 = dot2(xv.y, cv.y, s1);
+                s0 = dot2(xv.z, cv.z, s0); s1 = dot2(xv.w, cv.w, s1);
+            }
+            const uint2 nh = *reinterpret_cast<const uint2 *>(cr + kHeadDim);
+            const float s = (s0 + s1) + ((bf16_lo(nh.x) + bf16_hi(nh.x)) + bf16_lo(nh.y));
+            sscr[j] = s;
+            best = fmaxf(best, s);
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) best = fmaxf(best, __shfl_xor(best, off, 64));
+        // (lane l reads back what lane l wrote; !(a < b): a score that overflowed to NaN stays a candidate)
+        double bd = INFINITY; int bj = 0x7fffffff;
+        int left = kScanPairs;
+#pragma unroll 1
+        for (int j0 = 0; j0 < K; j0 += 64) {
+            uint64_t cm = __ballot(j0 + lane < K && !(sscr[j0 + lane < K ? j0 + lane : 0] < best - band));
+            left -= __builtin_popcountll(cm);
+            if (left < 0) break;
+            while (cm) {
+                const int ja = j0 + __builtin_ctzll(cm);
+                cm &= cm - 1;
+                const int jb = cm ? j0 + __builtin_ctzll(cm) : ja;
+                if (cm) cm &= cm - 1;
+                double Da, Db;
+                pair_dist(ja, jb, Da, Db);
+                if (Da < bd) { bd = Da; bj = ja; }                      // ascending indices: ties keep the lower
+                if (Db < bd) { bd = Db; bj = jb; }
+            }
+        }
+        if (left >= 0 && bj < K) return bj;
+        bd = INFINITY; bj = 0x7fffffff;
+        // many candidates (equal centroids): one per lane, the channels summed in index order
+        for (int j = lane; j < K; j += 64) {
+            const bf16_t *cr = lc + j * kCPitch;
+            double acc = 0.0;
+            for (int c = 0; c < kHeadDim; c += 2) {
+                const uint32_t xw = *reinterpret_cast<const uint32_t *>(scr + c);
+                const uint32_t cw = *reinterpret_cast<const uint32_t *>(cr + c);
+                const double f0 = (double)bf16_lo(xw) - (double)bf16_lo(cw);
+                acc += f0 * f0;
+                const double f1 = (double)bf16_hi(xw) - (double)bf16_hi(cw);
+                acc += f1 * f1;
+            }
+            if (acc < bd) { bd = acc; bj = j; }
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            const double od = shfl_xor_f64(bd, off);
+            const int oj = __shfl_xor(bj, off, 64);
+            if (od < bd || (od == bd && oj < bj)) { bd = od; bj = oj; }
+        }
+        return bj;
     };
     auto step_start = [&](int k) {
         return k < tiles_per_wave ? blk0 + (int64_t)(k * kAsgWaves + wave) * kAsgTile : N;
@@ -475,7 +569,16 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
                 insert3(p2, q2, c1, c2, c3, i1, i2);
                 insert3(p3, 0, c1, c2, c3, i1, i2);
             }
-            const float thr = (K > 256 ? 0x1.8p-14f : 0x1p-14f) * (0.5f * xn[tb] + cmax);
+            // Which centroids can matter: one that is at least as near as the leader lies within the
+            // leader's distance d of the token, so its norm is at most ||x|| + d.  The band therefore
+            // takes min(max ||c||^2, (||x|| + d)^2): with the unit's largest norm alone, one centroid on
+            // a few outlying tokens widened the band of every token (student-t data, 80 units x 10800
+            // tokens, K = 128, I = 3: 0.88 to 1.68 ms, by the draw, against 0.56 to 0.58).
+            // d^2 = ||x||^2 - 2 score, with 2^-10 of slack on both terms for the rounding of the score.
+            const float d2 = fmaxf(xn[tb] - 2.0f * c1, 0.0f) * (1.0f + 0x1p-10f) + xn[tb] * 0x1p-10f;
+            const float reach = (xn[tb] + d2 + 2.0f * __builtin_amdgcn_sqrtf(xn[tb] * d2)) * (1.0f + 0x1p-10f);
+            // (the last term: the tag of a score that is zero, where all norms are)
+            const float thr = (K > 256 ? 0x1.8p-14f : 0x1p-14f) * (0.5f * xn[tb] + fminf(cmax, reach)) + 0x1p-126f;
             int id = i1;
             const bool amb = valid[tb] && (i2 < K) && !(c1 - c2 > thr);
             const bool full = !(c1 - c3 > thr);
@@ -492,48 +595,15 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
                 }
                 __builtin_amdgcn_wave_barrier();
                 // the token's lane index is wave-uniform: plain lane reads, no exchange through LDS
-                const int d1 = __builtin_amdgcn_readlane(i1, tk), d2 = __builtin_amdgcn_readlane(i2, tk);
+                const int d1 = __builtin_amdgcn_readlane(i1, tk), d2i = __builtin_amdgcn_readlane(i2, tk);
                 const int fl = __builtin_amdgcn_readlane((int)full, tk);
                 int winner;
                 if (!fl) {
-                    const int cand = half ? d2 : d1;
-                    const uint2 xv = *reinterpret_cast<const uint2 *>(scr + col * 4);
-                    const uint2 cv = *reinterpret_cast<const uint2 *>(lc + cand * kCPitch + col * 4);
-                    const double e0 = (double)bf16_lo(xv.x) - (double)bf16_lo(cv.x);
-                    const double e1 = (double)bf16_hi(xv.x) - (double)bf16_hi(cv.x);
-                    const double e2 = (double)bf16_lo(xv.y) - (double)bf16_lo(cv.y);
-                    const double e3 = (double)bf16_hi(xv.y) - (double)bf16_hi(cv.y);
-                    double d = e0 * e0; d += e1 * e1; d += e2 * e2; d += e3 * e3;
-                    // the 32 lanes of a candidate: two rows of 16 summed by DPP moves, the two row
-                    // sums read as scalars (no exchange through LDS: each cost a round trip, ten
-                    // in a row per token).  Both candidates go through the same operations, so
-                    // equal rows give equal sums.
-                    d = sum16_f64(d);
-                    const double D1 = readlane_f64(d, 0) + readlane_f64(d, 16);
-                    const double D2 = readlane_f64(d, 32) + readlane_f64(d, 48);
-                    winner = (D2 < D1 || (D2 == D1 && d2 < d1)) ? d2 : d1;
+                    double D1, D2;
+                    pair_dist(d1, d2i, D1, D2);
+                    winner = (D2 < D1 || (D2 == D1 && d2i < d1)) ? d2i : d1;
                 } else {
-                    double bd = INFINITY; int bj = 0x7fffffff;
-                    for (int j = lane; j < K; j += 64) {
-                        const bf16_t *cr = lc + j * kCPitch;
-                        double acc = 0.0;
-                        for (int c = 0; c < kHeadDim; c += 2) {
-                            const uint32_t xw = *reinterpret_cast<const uint32_t *>(scr + c);
-                            const uint32_t cw = *reinterpret_cast<const uint32_t *>(cr + c);
-                            const double f0 = (double)bf16_lo(xw) - (double)bf16_lo(cw);
-                            acc += f0 * f0;
-                            const double f1 = (double)bf16_hi(xw) - (double)bf16_hi(cw);
-                            acc += f1 * f1;
-                        }
-                        if (acc < bd) { bd = acc; bj = j; }
-                    }
-#pragma unroll
-                    for (int off = 32; off >= 1; off >>= 1) {
-                        const double od = shfl_xor_f64(bd, off);
-                        const int oj = __shfl_xor(bj, off, 64);
-                        if (od < bd || (od == bd && oj < bj)) { bd = od; bj = oj; }
-                    }
-                    winner = bj;
+                    winner = scan_rows(__uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(thr), tk)));
                 }
                 if (col == tk) id = winner;
                 __builtin_amdgcn_wave_barrier();
@@ -565,7 +635,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
 }
 
 static size_t assign_smem_bytes(int Kpad) {
-    return (size_t)Kpad * kCPitch * 2 + (size_t)kAsgWaves * kHeadDim * 2;
+    return (size_t)Kpad * kCPitch * 2 + (size_t)kAsgWaves * (kHeadDim * 2 + Kpad * sizeof(float));
 }
 
 template <int B_, bool FUSED, int T_>
