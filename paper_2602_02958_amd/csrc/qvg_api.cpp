@@ -46,19 +46,22 @@ inline bool scales_aligned(const qvg_params *p, const void *sc) {
     return p->scale_format == QVG_SCALE_E4M3 || aligned16(sc);
 }
 
-struct EncodeWs { size_t assign; size_t cent[2]; size_t perm; size_t offs; size_t resid[2]; size_t total; };
+struct EncodeWs { size_t init_norms, norms; size_t cent[2]; size_t perm; size_t seg; size_t resid[2]; size_t total; };
 
-// with_assign: scratch of the assignment kernel; with_tables: two centroid tables for the Lloyd
-// loop; with_update: permutation and offsets of the update step
+// with_assign: split norms of the start tables (one per smoothing stage); with_tables: two centroid
+// tables for the Lloyd loop and the split norms of the newer one; with_update: the member lists
 EncodeWs encode_ws(const qvg_params *p, int64_t N, bool with_assign, bool with_tables, bool with_update = true) {
     EncodeWs w{};
     size_t o = 0;
-    if (with_assign) { w.assign = o; o += assign_workspace_bytes(p->n_heads, p->n_clusters); }
+    const size_t norms = round256((size_t)p->n_heads * k_padded(p->n_clusters) * sizeof(uint2));
+    // (one more word per unit than the norms take: the size that callers were told from the start)
+    if (with_assign) { w.init_norms = o; o += norms * (size_t)p->n_smooth_stages + round256((size_t)p->n_heads * sizeof(float)); }
     const size_t table = round256((size_t)p->n_heads * p->n_clusters * kHeadDim * sizeof(bf16_t));
-    if (with_tables) { w.cent[0] = o; o += table; w.cent[1] = o; o += table; }
+    if (with_tables) { w.norms = o; o += norms; w.cent[0] = o; o += table; w.cent[1] = o; o += table; }
     if (with_update) {
-        w.perm = o; o += round256((size_t)p->n_heads * (size_t)(N > 0 ? N : 1) * sizeof(int32_t));
-        w.offs = o; o += round256((size_t)p->n_heads * (p->n_clusters + 1) * sizeof(int32_t));
+        const int64_t block = member_block(p->n_heads, N), n_blocks = N > 0 ? (N + block - 1) / block : 1;
+        w.perm = o; o += round256((size_t)p->n_heads * (size_t)(n_blocks * block) * sizeof(uint16_t));
+        w.seg = o; o += round256((size_t)p->n_heads * (size_t)n_blocks * (size_t)p->n_clusters * sizeof(uint32_t));
     }
     // bf16 residual tensors that carry the data from one smoothing stage to the next
     if (with_assign && p->n_smooth_stages > 1) {
@@ -68,6 +71,15 @@ EncodeWs encode_ws(const qvg_params *p, int64_t N, bool with_assign, bool with_t
     }
     w.total = o;
     return w;
+}
+
+MemberLists member_lists(const qvg_params *p, int64_t N, unsigned char *ws, const EncodeWs &w) {
+    MemberLists l;
+    l.perm = reinterpret_cast<uint16_t *>(ws + w.perm);
+    l.seg = reinterpret_cast<uint32_t *>(ws + w.seg);
+    l.block = member_block(p->n_heads, N);
+    l.n_blocks = (int)((N + l.block - 1) / l.block);
+    return l;
 }
 
 int check_view(const void *base, int64_t stride_head, int64_t stride_token, int64_t N) {
@@ -105,7 +117,7 @@ int qvg_workspace_bytes(const qvg_params *p, int which_entry, int64_t n_tokens, 
     if (n_tokens < 0 || n_q < 0) return QVG_ERR_BAD_PARAM;
     switch (which_entry) {
         case QVG_ENTRY_ENCODE:
-            *out = n_tokens == 0 ? 0 : encode_ws(p, n_tokens, true, p->kmeans_iters > 0 || p->n_smooth_stages > 1,
+            *out = n_tokens == 0 ? 0 : encode_ws(p, n_tokens, true, p->kmeans_iters > 0,
                                                  p->kmeans_iters > 0).total;   // same call as qvg_encode_chunk
             return QVG_OK;
         case QVG_ENTRY_KMEANS_UPDATE:
@@ -152,13 +164,18 @@ int qvg_kmeans_assign(const qvg_params *p, int64_t n_tokens, const void *x, int6
     if (!workspace || workspace_bytes < w.total) return QVG_ERR_WORKSPACE;
     if (!aligned16(workspace)) return QVG_ERR_ALIGN;
     AssignArgs a{};
-    assign_workspace_split(static_cast<unsigned char *>(workspace) + w.assign, p->n_heads, p->n_clusters, &a.nh3, &a.cmax);
+    const int64_t table = (int64_t)p->n_clusters * kHeadDim;
+    uint2 *nh3 = reinterpret_cast<uint2 *>(static_cast<unsigned char *>(workspace) + w.init_norms);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if (launch_half_norms(static_cast<const bf16_t *>(centroids), table, p->n_heads, 1, p->n_clusters, nh3, s) != hipSuccess)
+        return QVG_ERR_LAUNCH;
+    a.nh3 = nh3; a.nh3_stride = k_padded(p->n_clusters);
     a.x = static_cast<const bf16_t *>(x); a.stride_head = stride_head; a.stride_token = stride_token;
-    a.n_tokens = n_tokens; a.cent = static_cast<const bf16_t *>(centroids);
+    a.n_tokens = n_tokens; a.cent = static_cast<const bf16_t *>(centroids); a.cent_stride = table;
     a.H = p->n_heads; a.K = p->n_clusters; a.B = p->group_size; a.T = p->n_stages;
     a.ids = ids_out; a.codes = nullptr; a.scales = nullptr; a.out_stride = n_tokens; a.fused = 0;
     a.ids_step = 1; a.ids_off = 0; a.id_wide = id_wide(p);
-    return launch_assign(a, static_cast<hipStream_t>(stream)) == hipSuccess ? QVG_OK : QVG_ERR_LAUNCH;
+    return launch_assign(a, s) == hipSuccess ? QVG_OK : QVG_ERR_LAUNCH;
 }
 
 int qvg_kmeans_update(const qvg_params *p, int64_t n_tokens, const void *x, int64_t stride_head,
@@ -176,15 +193,16 @@ int qvg_kmeans_update(const qvg_params *p, int64_t n_tokens, const void *x, int6
     if (!workspace || workspace_bytes < w.total) return QVG_ERR_WORKSPACE;
     if (!aligned16(workspace)) return QVG_ERR_ALIGN;
     unsigned char *ws = static_cast<unsigned char *>(workspace);
+    hipStream_t s = static_cast<hipStream_t>(stream);
     UpdateArgs u{};
     u.x = static_cast<const bf16_t *>(x); u.stride_head = stride_head; u.stride_token = stride_token;
-    u.n_tokens = n_tokens; u.ids = ids; u.ids_stride = n_tokens; u.ids_step = 1; u.ids_off = 0;
-    u.id_wide = id_wide(p);
-    u.cent_prev = static_cast<const bf16_t *>(cent_prev);
+    u.n_tokens = n_tokens; u.lists = member_lists(p, n_tokens, ws, w);
+    u.cent_prev = static_cast<const bf16_t *>(cent_prev); u.prev_stride = (int64_t)p->n_clusters * kHeadDim;
     u.cent_out = static_cast<bf16_t *>(cent_out); u.counts_out = counts_out;
-    u.perm = reinterpret_cast<int32_t *>(ws + w.perm); u.offsets = reinterpret_cast<int32_t *>(ws + w.offs);
     u.H = p->n_heads; u.K = p->n_clusters;
-    return launch_update(u, static_cast<hipStream_t>(stream)) == hipSuccess ? QVG_OK : QVG_ERR_LAUNCH;
+    if (launch_member_lists(ids, n_tokens, n_tokens, p->n_heads, p->n_clusters, id_wide(p), u.lists, s) != hipSuccess)
+        return QVG_ERR_LAUNCH;
+    return launch_update(u, s) == hipSuccess ? QVG_OK : QVG_ERR_LAUNCH;
 }
 
 int qvg_encode_chunk(const qvg_params *p, int64_t n_tokens, const void *x, int64_t stride_head,
@@ -219,72 +237,64 @@ int qvg_encode_chunk(const qvg_params *p, int64_t n_tokens, const void *x, int64
     const int I = p->kmeans_iters;
     const int fmt = format_of(p);
     const int S = p->n_smooth_stages;
-    const EncodeWs w = encode_ws(p, n_tokens, true, I > 0 || S > 1, I > 0);
+    const EncodeWs w = encode_ws(p, n_tokens, true, I > 0, I > 0);
     if (!workspace || workspace_bytes < w.total) return QVG_ERR_WORKSPACE;
     if (!aligned16(workspace)) return QVG_ERR_ALIGN;
     unsigned char *ws = static_cast<unsigned char *>(workspace);
-    uint2 *nh3; float *cmax;
-    assign_workspace_split(ws + w.assign, p->n_heads, p->n_clusters, &nh3, &cmax);
+    const int64_t table = (int64_t)p->n_clusters * kHeadDim, kpad = k_padded(p->n_clusters);
+    // every stage's start table is known: one launch takes all their norms
+    uint2 *init_norms = reinterpret_cast<uint2 *>(ws + w.init_norms);
+    if (launch_half_norms(static_cast<const bf16_t *>(init_centroids), S * table, p->n_heads, S, p->n_clusters, init_norms, s) != hipSuccess)
+        return QVG_ERR_LAUNCH;
     // input of the current smoothing stage: the caller's view first, then dense residual tensors
     const bf16_t *xin = static_cast<const bf16_t *>(x);
     int64_t sh = stride_head, stt = stride_token;
     for (int stage = 0; stage < S; ++stage) {
-        const bf16_t *cur = static_cast<const bf16_t *>(init_centroids) + (size_t)stage * p->n_clusters * kHeadDim;
-        const int64_t init_stride = (int64_t)S * p->n_clusters * kHeadDim;     // init [H][S][K][d]
         AssignArgs a{};
         a.x = xin; a.stride_head = sh; a.stride_token = stt;
         a.n_tokens = n_tokens; a.H = p->n_heads; a.K = p->n_clusters; a.B = p->group_size;
         a.T = p->n_stages; a.ids = ids_out; a.out_stride = out_stride_head_tokens; a.fused = 0;
-        a.ids_step = S; a.ids_off = stage; a.nh3 = nh3; a.cmax = cmax; a.id_wide = id_wide(p);
+        a.ids_step = S; a.ids_off = stage; a.id_wide = id_wide(p);
+        // the caller's start tables are [H][S][K][d], the Lloyd loop's are dense
+        a.cent = static_cast<const bf16_t *>(init_centroids) + stage * table; a.cent_stride = S * table;
+        a.nh3 = init_norms + stage * kpad; a.nh3_stride = S * kpad;
         bf16_t *buf[2] = {reinterpret_cast<bf16_t *>(ws + w.cent[0]), reinterpret_cast<bf16_t *>(ws + w.cent[1])};
-        if (S > 1) {
-            // the kernels want a dense [H][K][d] table; the caller's start tables are [H][S][K][d]
-            if (hipMemcpy2DAsync(buf[1], row, cur, (size_t)init_stride * sizeof(bf16_t), row,
-                                 (size_t)p->n_heads, hipMemcpyDeviceToDevice, s) != hipSuccess)
-                return QVG_ERR_LAUNCH;
-            cur = buf[1];
-        }
         if (I > 0) {
             UpdateArgs u{};
             u.x = a.x; u.stride_head = sh; u.stride_token = stt; u.n_tokens = n_tokens;
-            u.ids = ids_out; u.ids_stride = out_stride_head_tokens; u.ids_step = S; u.ids_off = stage;
-            u.counts_out = nullptr; u.id_wide = id_wide(p);
-            u.perm = reinterpret_cast<int32_t *>(ws + w.perm); u.offsets = reinterpret_cast<int32_t *>(ws + w.offs);
-            u.H = p->n_heads; u.K = p->n_clusters;
+            u.counts_out = nullptr; u.H = p->n_heads; u.K = p->n_clusters;
+            u.lists = member_lists(p, n_tokens, ws, w);
+            u.nh3 = reinterpret_cast<uint2 *>(ws + w.norms);
             for (int it = 0; it < I; ++it) {
-                a.cent = cur;
+                a.lists = u.lists;
                 if (launch_assign(a, s) != hipSuccess) return QVG_ERR_LAUNCH;
-                u.cent_prev = cur; u.cent_out = buf[it & 1];
+                u.cent_prev = a.cent; u.prev_stride = a.cent_stride; u.cent_out = buf[it & 1];
                 if (launch_update(u, s) != hipSuccess) return QVG_ERR_LAUNCH;
-                cur = buf[it & 1];
+                a.cent = u.cent_out; a.cent_stride = table;
+                a.nh3 = u.nh3; a.nh3_stride = kpad;
             }
+            a.lists = MemberLists{};
         }
         // this stage's table goes out as H rows of K*d bf16 with the caller's pitch: the stage's
         // last assignment writes them while it stages the table (no copy of its own)
-        bf16_t *cdst = static_cast<bf16_t *>(centroids_out) + (size_t)stage * p->n_clusters * kHeadDim;
-        if (!(cur == cdst && cent_out_stride_head == (int64_t)p->n_clusters * kHeadDim)) {
+        bf16_t *cdst = static_cast<bf16_t *>(centroids_out) + stage * table;
+        if (!(a.cent == cdst && a.cent_stride == cent_out_stride_head)) {
             a.cent_copy = cdst; a.cent_copy_stride = cent_out_stride_head;
         }
         if (stage + 1 < S) {
-            // final assignment of this stage, then the bf16 residual becomes the next input
-            a.cent = cur;
+            // final assignment of this stage; the bf16 residual it leaves is the next stage's input
+            a.resid = reinterpret_cast<bf16_t *>(ws + w.resid[stage & 1]);
             if (launch_assign(a, s) != hipSuccess) return QVG_ERR_LAUNCH;
-            ResidualArgs r{};
-            r.x = xin; r.stride_head = sh; r.stride_token = stt; r.n_tokens = n_tokens;
-            r.cent = cur; r.ids = ids_out; r.ids_stride = out_stride_head_tokens; r.ids_step = S; r.ids_off = stage;
-            r.out = reinterpret_cast<bf16_t *>(ws + w.resid[stage & 1]); r.H = p->n_heads; r.K = p->n_clusters;
-            r.id_wide = id_wide(p);
-            if (launch_residual(r, s) != hipSuccess) return QVG_ERR_LAUNCH;
-            xin = r.out; sh = n_tokens * kHeadDim; stt = kHeadDim;
+            xin = a.resid; sh = n_tokens * kHeadDim; stt = kHeadDim;
         } else if (fmt == 0) {
-            a.cent = cur; a.codes = codes_out; a.scales = static_cast<f16_t *>(scales_out); a.fused = 1;
+            a.codes = codes_out; a.scales = static_cast<f16_t *>(scales_out); a.fused = 1;
             if (launch_assign(a, s) != hipSuccess) return QVG_ERR_LAUNCH;
         } else {
             // the other stored formats: assignment, then the quantization kernel
-            a.cent = cur;
             if (launch_assign(a, s) != hipSuccess) return QVG_ERR_LAUNCH;
             QuantArgs q{};
-            q.x = xin; q.stride_head = sh; q.stride_token = stt; q.n_tokens = n_tokens; q.cent = cur;
+            q.x = xin; q.stride_head = sh; q.stride_token = stt; q.n_tokens = n_tokens;
+            q.cent = a.cent; q.cent_stride = a.cent_stride;
             q.ids = ids_out; q.ids_step = S; q.ids_off = stage; q.codes = codes_out; q.scales = scales_out;
             q.out_stride = out_stride_head_tokens; q.H = p->n_heads; q.K = p->n_clusters; q.B = p->group_size;
             q.T = p->n_stages; q.fmt = fmt; q.id_wide = id_wide(p);
@@ -333,7 +343,7 @@ int qvg_encode_chunk_static(const qvg_params *p, int64_t n_tokens, const void *x
     if (st != QVG_OK) return st;
     if (n_tokens < 0 || n_tokens > kMaxTokensPerChunk) return QVG_ERR_BAD_PARAM;
     // the same workspace layout as qvg_encode_chunk, placed in the static array
-    const size_t need = n_tokens == 0 ? 0 : encode_ws(p, n_tokens, true, p->kmeans_iters > 0 || p->n_smooth_stages > 1,
+    const size_t need = n_tokens == 0 ? 0 : encode_ws(p, n_tokens, true, p->kmeans_iters > 0,
                                                       p->kmeans_iters > 0).total;
     if (need > (size_t)QVG_STATIC_SCRATCH_BYTES) return QVG_ERR_SCRATCH_LIMIT;
     void *ws = nullptr;

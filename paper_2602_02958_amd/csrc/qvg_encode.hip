@@ -25,15 +25,13 @@
 // re-evaluated in fp64, cooperatively by the wavefront: the two leaders, or, if the third score is
 // inside the band as well, every centroid that a second look at the fp32 scores leaves possible.
 // Equal fp64 distances go to the lower index.
-#include "qvg_internal.hpp"
+#include "qvg_kmeans.hpp"
 
 namespace qvg {
 
-constexpr int kAsgThreads = 256;
-constexpr int kAsgWaves = kAsgThreads / 64;
-constexpr int kAsgTile = 64;                    // tokens per wavefront step (two MFMA column blocks)
 constexpr int kCPitch = 136;                    // bf16 elements per LDS centroid row (272 B): 128 + (hi, mid, lo of -||c||^2/2) + 5 zeros
 constexpr int kPrepThreads = 256;
+constexpr int kPrepRows = kPrepThreads / 16;     // 16 lanes per centroid
 constexpr int kScanPairs = 24;                  // candidates up to which fp64 distances are taken two at a time
 
 __device__ __forceinline__ void insert3(float v, int idx, float &b1, float &b2, float &b3,
@@ -44,31 +42,6 @@ __device__ __forceinline__ void insert3(float v, int idx, float &b1, float &b2, 
 }
 
 __device__ __forceinline__ double shfl_xor_f64(double v, int m) { return __shfl_xor(v, m, 64); }
-// Sum over each aligned group of 16 lanes, every lane getting the total, by data-parallel-primitive
-// moves (VALU; the general lane exchange goes through the LDS pipe and its latency, four times in
-// a row per table piece).  Pairings: lane ^ 1, lane ^ 2, then the mirror images inside 8 and
-// inside 16 lanes, whose partners hold what lane ^ 4 and lane ^ 8 hold, so the sums are those of
-// the xor butterfly bit for bit.
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, false);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ double sum16_f64(double v) {
-    v += dpp_f64<0xB1>(v);       // quad_perm [1,0,3,2]
-    v += dpp_f64<0x4E>(v);       // quad_perm [2,3,0,1]
-    v += dpp_f64<0x141>(v);      // row_half_mirror
-    v += dpp_f64<0x140>(v);      // row_mirror
-    return v;
-}
-__device__ __forceinline__ double readlane_f64(double v, int lane) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
 // acc + a.lo b.lo + a.hi b.hi of two packed bf16 pairs: v_dot2_f32_bf16
 __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float acc) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), acc, false);
@@ -84,49 +57,32 @@ __device__ __forceinline__ uint32_t vgpr_const(uint32_t c) {
     return v;
 }
 
-// ---------------------------------------------------------------------------------------------
-// Per centroid: nh = fp32(-||c||^2 / 2) from an fp64 sum, split into three bf16 pieces by
-// truncation (8 significant bits each, so hi + mid + lo == nh exactly); rows K..Kpad-1 get a
-// huge negative value so that they never win.  Per unit: an upper bound of max ||c||^2.
-// One workgroup per unit, 16 lanes per row.
-// ---------------------------------------------------------------------------------------------
+// The split norms of start tables (see split_half_norm); the tables of later Lloyd iterations get
+// theirs from the update kernel that makes them.  16 lanes per centroid, grid: x = rows, y = table of
+// the unit, z = unit.
 __global__ __launch_bounds__(kPrepThreads)
-void centroid_prep_kernel(const bf16_t *cent, int K, int Kpad, uint2 *nh3, float *cmax_out) {
-    __shared__ uint32_t smax;
-    const int h = blockIdx.x, tid = threadIdx.x;
-    if (tid == 0) smax = 0u;
-    __syncthreads();
-    const bf16_t *cg = cent + (int64_t)h * K * kHeadDim;
-    for (int i = tid; i < Kpad * 16; i += kPrepThreads) {          // Kpad*16 is a multiple of 64: whole waves
-        const int row = i >> 4, c16 = i & 15;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (row < K) v = *reinterpret_cast<const uint4 *>(cg + (int64_t)row * kHeadDim + c16 * 8);
-        double s = 0.0;
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+void half_norm_kernel(const bf16_t *cent, int64_t cent_stride, int K, int Kpad, uint2 *nh3) {
+    const int row = (int)blockIdx.x * kPrepRows + (int)(threadIdx.x >> 4), c16 = threadIdx.x & 15;
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    if (row < K)
+        v = *reinterpret_cast<const uint4 *>(cent + (int64_t)blockIdx.z * cent_stride +
+                                             ((int64_t)blockIdx.y * K + row) * kHeadDim + c16 * 8);
+    double s = 0.0;
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const double lo = (double)bf16_lo(w[e]), hi = (double)bf16_hi(w[e]);
-            s += lo * lo; s += hi * hi;
-        }
-        s = sum16_f64(s);
-        if (c16 == 0) {
-            float nh = -3.0e38f;
-            if (row < K) {
-                nh = (float)(-0.5 * s);
-                // upper bound of ||c||^2 in fp32 (one ulp up), kept as its bit pattern
-                const float up = (float)s * (1.0f + 0x1p-22f);
-                atomicMax(&smax, __float_as_uint(up));
-            }
-            const float hi = __uint_as_float(__float_as_uint(nh) & 0xffff0000u);
-            const float r1 = nh - hi;
-            const float mid = __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
-            const float lo = __uint_as_float(__float_as_uint(r1 - mid) & 0xffff0000u);
-            nh3[(int64_t)h * Kpad + row] =
-                make_uint2((__float_as_uint(hi) >> 16) | (__float_as_uint(mid) & 0xffff0000u), __float_as_uint(lo) >> 16);
-        }
+    for (int e = 0; e < 4; ++e) {
+        const double lo = (double)bf16_lo(w[e]), hi = (double)bf16_hi(w[e]);
+        s += lo * lo; s += hi * hi;
     }
-    __syncthreads();
-    if (tid == 0) cmax_out[h] = __uint_as_float(smax);
+    s = sum16_f64(s);
+    if (row < K && c16 == 0)
+        nh3[((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * Kpad + row] = split_half_norm(s);
+}
+
+hipError_t launch_half_norms(const bf16_t *cent, int64_t cent_stride, int H, int tables, int K, uint2 *nh3, hipStream_t s) {
+    hipLaunchKernelGGL(half_norm_kernel, dim3((unsigned)((K + kPrepRows - 1) / kPrepRows), (unsigned)tables, (unsigned)H),
+                       dim3(kPrepThreads), 0, s, cent, cent_stride, K, k_padded(K), nh3);
+    return hipGetLastError();
 }
 
 // T rounds of Eq. 2 (b = 2: scale = max|r|, levels -1, 0, 1) on the 64 residuals r[] a lane
@@ -208,10 +164,9 @@ __device__ __forceinline__ void quantize_token(float *r, int T, bool valid, int 
 // grid: x = unit, y = block of 256 * tiles_per_wave tokens.  With the unit as the fastest grid
 // index and H a multiple of 8, all blocks of a unit run on one XCD and share its table in L2.
 // T_: number of quantization rounds of the fused pass when known at compile time (0: a.T)
-template <int B_, bool FUSED, bool NORMS_GIVEN, int T_>
+template <int B_, bool FUSED, int T_>
 __global__ __launch_bounds__(kAsgThreads, 2)
 void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
-    constexpr bool norms_given = NORMS_GIVEN;
     extern __shared__ __align__(16) unsigned char smem[];
     bf16_t *lc = reinterpret_cast<bf16_t *>(smem);                       // [Kpad][kCPitch]
     bf16_t *lscr = lc + (size_t)Kpad * kCPitch;                          // [waves][128]
@@ -223,21 +178,23 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
     const int K = a.K;
     const int64_t N = a.n_tokens;
 
-    // ---- stage the centroid table (rows K.. are zero).  The norms either come from the
-    // preparation kernel (norms_given: many workgroups per unit would each repeat the fp64 sums)
-    // or are taken here while a row passes through (few workgroups per unit: one launch less): nh = fp32(-||c||^2 / 2) from an fp64 sum, split into three bf16 pieces by truncation
-    // (8 significant bits each, so hi + mid + lo == nh exactly) that go into the row's padding;
-    // rows K..Kpad-1 get a huge negative value so that they never win.  The largest ||c||^2 of the
-    // unit (one ulp up) is needed for the error band of the certification.
+    // ---- stage the centroid table (rows K.. are zero) and, in each row's padding, the split of its
+    // -||c||^2 / 2; rows K..Kpad-1 get a huge negative value so that they never win.  The largest
+    // ||c||^2 of the unit (one ulp up) is needed for the error band of the certification.
     __shared__ uint32_t smax;
     if (tid == 0) smax = 0u;
-    __syncthreads();
-    const bf16_t *cg = a.cent + (int64_t)h * K * kHeadDim;
+    const bf16_t *cg = a.cent + (int64_t)h * a.cent_stride;
+    uint2 nh[kMaxClusters / kAsgThreads];
+#pragma unroll
+    for (int u = 0; u < kMaxClusters / kAsgThreads; ++u) {
+        const int row = tid + u * kAsgThreads;
+        nh[u] = make_uint2(__float_as_uint(-3.0e38f) >> 16, 0u);
+        if (row < K) nh[u] = a.nh3[(int64_t)h * a.nh3_stride + row];
+    }
     // Eight 16-byte pieces per thread are requested before the first is used: taken one at a time
-    // (load, store to LDS, norm) every piece waits a whole memory round trip (0.85 us measured),
+    // (load, store to LDS) every piece waits a whole memory round trip (0.85 us measured),
     // which was most of what a workgroup with a single 256-token step spent on a 256-row table.
     constexpr int kStageBatch = 8;
-    uint32_t up_max = 0u;          // this lane's largest ||c||^2 bound so far (bit pattern): one LDS atomic after the loop
     for (int i0 = tid; i0 < Kpad * 16; i0 += kAsgThreads * kStageBatch) {      // Kpad*16 is a multiple of the block: whole waves
         uint4 vb[kStageBatch];
 #pragma unroll
@@ -256,41 +213,28 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
             if (row < K && a.cent_copy && blockIdx.y == 0)              // the table's way out to the caller, for free
                 *reinterpret_cast<uint4 *>(a.cent_copy + (int64_t)h * a.cent_copy_stride + (int64_t)row * kHeadDim + c16 * 8) = v;
             *reinterpret_cast<uint4 *>(lc + row * kCPitch + c16 * 8) = v;
-            if (norms_given) continue;                                  // uniform
-            double sq = 0.0;
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const double lo = (double)bf16_lo(w[e]), hi = (double)bf16_hi(w[e]);
-                sq += lo * lo; sq += hi * hi;
-            }
-            sq = sum16_f64(sq);
-            if (c16 == 0) {
-                float nh = -3.0e38f;
-                if (row < K) {
-                    nh = (float)(-0.5 * sq);
-                    const float up = (float)sq * (1.0f + 0x1p-22f);      // upper bound of ||c||^2 in fp32, as its bit pattern
-                    up_max = max(up_max, __float_as_uint(up));
-                }
-                const float hi = __uint_as_float(__float_as_uint(nh) & 0xffff0000u);
-                const float r1 = nh - hi;
-                const float mid = __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
-                const float lo = __uint_as_float(__float_as_uint(r1 - mid) & 0xffff0000u);
-                *reinterpret_cast<uint4 *>(lc + row * kCPitch + kHeadDim) =
-                    make_uint4((__float_as_uint(hi) >> 16) | (__float_as_uint(mid) & 0xffff0000u), __float_as_uint(lo) >> 16, 0u, 0u);
-            }
         }
     }
-    if (!norms_given && up_max != 0u) atomicMax(&smax, up_max);
-    if (norms_given)
-        for (int row = tid; row < Kpad; row += kAsgThreads) {
-            const uint2 p = a.nh3[(int64_t)h * Kpad + row];
-            *reinterpret_cast<uint4 *>(lc + row * kCPitch + kHeadDim) = make_uint4(p.x, p.y, 0u, 0u);
+    __syncthreads();                                                    // smax is zero
+#pragma unroll
+    for (int u = 0; u < kMaxClusters / kAsgThreads; ++u) {
+        const int row = tid + u * kAsgThreads;
+        if (row < Kpad) *reinterpret_cast<uint4 *>(lc + row * kCPitch + kHeadDim) = make_uint4(nh[u].x, nh[u].y, 0u, 0u);
+        float up = 0.0f;                                                // upper bound of ||c||^2 in fp32
+        if (row < K) up = -2.0f * ((bf16_lo(nh[u].x) + bf16_hi(nh[u].x)) + bf16_lo(nh[u].y)) * (1.0f + 0x1p-22f);
+        if (u * kAsgThreads < Kpad) {                                   // uniform
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) up = fmaxf(up, __shfl_xor(up, off, 64));
+            if (lane == 0) atomicMax(&smax, __float_as_uint(up));
         }
+    }
     __syncthreads();
-    const float cmax = norms_given ? a.cmax[h] : __uint_as_float(smax);
+    const float cmax = __uint_as_float(smax);
     bf16_t *scr = lscr + wave * kHeadDim;
     float *sscr = lsscr + wave * Kpad;
+    __shared__ uint16_t lid[FUSED ? 1 : kMaxTilesPerWave * kAsgThreads];    // the tokens' ids, for the member lists
+    if (!FUSED && a.lists.perm)
+        for (int i = tid; i < tiles_per_wave * kAsgThreads; i += kAsgThreads) lid[i] = 0xffffu;   // tokens of steps past the end; each wavefront clears its own
     // token operand of the extra MFMA step: three ones against (hi, mid, lo), lanes 0..31 only
     // 7 tag bits name a row among 256; with more rows the tag takes 8 (and the band below widens)
     const uint32_t tagbits = K > 256 ? 0xFFu : 0x7Fu;
@@ -611,7 +555,23 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
 
             const int64_t hn = (int64_t)h * a.out_stride + n[tb];
             if (valid[tb] && half == 0) store_id(a.ids, hn * a.ids_step + a.ids_off, a.id_wide, (uint32_t)id);
-            if (!FUSED) continue;
+            if (!FUSED) {
+                if (a.lists.perm && half == 0) lid[(k * kAsgWaves + wave) * kAsgTile + tb * 32 + col] = valid[tb] ? (uint16_t)id : 0xffffu;
+                if (a.resid && valid[tb]) {                              // Eq. 5, rounded to bf16: the next smoothing stage's input
+                    const bf16_t *crow = lc + id * kCPitch + half * 64;
+                    bf16_t *rp = a.resid + ((int64_t)h * N + n[tb]) * kHeadDim + half * 64;
+#pragma unroll
+                    for (int kk = 0; kk < 8; ++kk) {
+                        float xf[8], cf[8];
+                        unpack_bf16x8(xa[tb][kk], xf);
+                        unpack_bf16x8(*reinterpret_cast<const uint4 *>(crow + kk * 8), cf);
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) xf[i] -= cf[i];
+                        *reinterpret_cast<uint4 *>(rp + kk * 8) = pack_bf16x8(xf);
+                    }
+                }
+                continue;
+            }
 
             // ---- Eq. 5: residual against the assigned centroid, then the T rounds ----
             float r[64];
@@ -632,45 +592,40 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
             __builtin_amdgcn_sched_barrier(0);       // keep the two tokens' passes apart: each needs most registers
         }
     }
+    if (!FUSED && a.lists.perm) {                    // the member lists of this workgroup's tokens
+        __syncthreads();                             // every id is in lid, the table is not needed any more
+        const int64_t blk = (int64_t)h * a.lists.n_blocks + blockIdx.y;
+        block_member_sort(lid, tiles_per_wave, K, reinterpret_cast<int *>(smem), a.lists.perm + blk * a.lists.block,
+                          a.lists.seg + blk * K);
+    }
 }
 
 static size_t assign_smem_bytes(int Kpad) {
     return (size_t)Kpad * kCPitch * 2 + (size_t)kAsgWaves * (kHeadDim * 2 + Kpad * sizeof(float));
 }
 
+// 256-token steps per workgroup: more of them amortise the table staging once there are enough
+// workgroups to fill the chip several times over
+int assign_tiles_per_wave(int H, int64_t n_tokens) {
+    const int64_t steps = (n_tokens + kAsgWaves * kAsgTile - 1) / (kAsgWaves * kAsgTile);
+    int tpw = 1;
+    while (tpw < kMaxTilesPerWave && (steps / (2 * tpw)) * H >= 2048) tpw *= 2;
+    return tpw;
+}
+
 template <int B_, bool FUSED, int T_>
 static hipError_t launch_assign_t(const AssignArgs &a, hipStream_t s) {
-    const int Kpad = (a.K + 63) & ~63;
+    const int Kpad = k_padded(a.K);
     const size_t smem = assign_smem_bytes(Kpad);
-    static LdsHighWater lds_limit[2] = {};
-    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&assign_kernel<B_, FUSED, true, T_>), smem, lds_limit[0]);
+    static LdsHighWater lds_limit = {};
+    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&assign_kernel<B_, FUSED, T_>), smem, lds_limit);
     if (e != hipSuccess) return e;
-    e = ensure_dynamic_lds(reinterpret_cast<const void *>(&assign_kernel<B_, FUSED, false, T_>), smem, lds_limit[1]);
-    if (e != hipSuccess) return e;
-    // tokens per workgroup: 256 per step; more steps per workgroup amortise the table staging
-    // once there are enough workgroups to fill the chip several times over
-    const int64_t steps = (a.n_tokens + kAsgWaves * kAsgTile - 1) / (kAsgWaves * kAsgTile);
-    int tpw = 1;
-    while (tpw < 4 && (steps / (2 * tpw)) * a.H >= 2048) tpw *= 2;
-    const int64_t gy = (steps + tpw - 1) / tpw;
+    const int tpw = assign_tiles_per_wave(a.H, a.n_tokens);
+    const int64_t gy = (a.n_tokens + kAsgThreads * tpw - 1) / (kAsgThreads * tpw);
     if (gy > 65535) return hipErrorInvalidValue;
-    // the centroid norms: by a kernel of their own when there are many workgroups (each would
-    // repeat the fp64 sums of its unit's table); inside the assignment kernel when there are few
-    // (the extra launch then costs more than the repeated sums: 0.165 -> 0.154 ms per cfg2 encode;
-    // the bound scales with the table size, measured at K = 64 and K = 512)
-    const bool norms_given = (int64_t)a.H * gy * a.K > 2048 * 64;
-    if (norms_given) {
-        hipLaunchKernelGGL(centroid_prep_kernel, dim3((unsigned)a.H), dim3(kPrepThreads), 0, s, a.cent, a.K, Kpad,
-                           a.nh3, a.cmax);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (norms_given)
-        hipLaunchKernelGGL((assign_kernel<B_, FUSED, true, T_>), dim3((unsigned)a.H, (unsigned)gy), dim3(kAsgThreads), smem, s, a,
-                           Kpad, tpw);
-    else
-        hipLaunchKernelGGL((assign_kernel<B_, FUSED, false, T_>), dim3((unsigned)a.H, (unsigned)gy), dim3(kAsgThreads), smem, s, a,
-                           Kpad, tpw);
+    if (a.lists.perm && (a.lists.block != kAsgThreads * tpw || a.lists.n_blocks != gy)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((assign_kernel<B_, FUSED, T_>), dim3((unsigned)a.H, (unsigned)gy), dim3(kAsgThreads), smem, s, a,
+                       Kpad, tpw);
     return hipGetLastError();
 }
 
@@ -694,16 +649,6 @@ hipError_t launch_assign(const AssignArgs &a, hipStream_t s) {
         case 64: return launch_fused<64>(a, s);
         default: return launch_fused<128>(a, s);
     }
-}
-
-size_t assign_workspace_bytes(int H, int K) {
-    const size_t Kpad = (size_t)((K + 63) & ~63);
-    return ((size_t)H * Kpad * sizeof(uint2) + 255) / 256 * 256 + ((size_t)H * sizeof(float) + 255) / 256 * 256;
-}
-void assign_workspace_split(void *ws, int H, int K, uint2 **nh3, float **cmax) {
-    const size_t Kpad = (size_t)((K + 63) & ~63);
-    *nh3 = static_cast<uint2 *>(ws);
-    *cmax = reinterpret_cast<float *>(static_cast<unsigned char *>(ws) + ((size_t)H * Kpad * sizeof(uint2) + 255) / 256 * 256);
 }
 
 }  // namespace qvg

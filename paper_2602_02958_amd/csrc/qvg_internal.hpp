@@ -164,49 +164,73 @@ struct DecodeArgs {
 };
 hipError_t launch_decode(const DecodeArgs &a, hipStream_t s);
 
+// Scratch of the k-means passes.  Per centroid the matrix cores want nh = fp32(-||c||^2 / 2) as three
+// bf16 pieces (truncated, 8 significant bits each: hi + mid + lo == nh exactly), .x = hi | mid << 16,
+// .y = lo; one row of Kpad entries per unit.
+__host__ __device__ inline int k_padded(int K) { return (K + 63) & ~63; }
+__device__ __forceinline__ uint2 split_half_norm(double sumsq) {
+    const float nh = (float)(-0.5 * sumsq);
+    const float hi = __uint_as_float(__float_as_uint(nh) & 0xffff0000u);
+    const float r1 = nh - hi;
+    const float mid = __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
+    const float lo = __uint_as_float(__float_as_uint(r1 - mid) & 0xffff0000u);
+    return make_uint2((__float_as_uint(hi) >> 16) | (__float_as_uint(mid) & 0xffff0000u), __float_as_uint(lo) >> 16);
+}
+
+// Member lists.  The tokens of a unit are split into blocks of `block` (the tokens of one workgroup of
+// the assignment); inside a block they are sorted by cluster, equal ids in token order:
+//   perm [H][n_blocks * block] u16   index inside the block
+//   seg  [H][n_blocks][K] u32        first position | end << 16 of the cluster inside the block
+// The members of a cluster in token order are its segments of block 0, 1, ...
+struct MemberLists {
+    uint16_t *perm; uint32_t *seg;
+    int block, n_blocks;
+};
+// tokens per assignment workgroup = 256 x this
+int assign_tiles_per_wave(int H, int64_t n_tokens);
+inline int member_block(int H, int64_t n_tokens) { return 256 * assign_tiles_per_wave(H, n_tokens); }
+
 struct AssignArgs {
     const bf16_t *x; int64_t stride_head, stride_token; int64_t n_tokens;
-    const bf16_t *cent; int H; int K; int B; int T;
+    const bf16_t *cent; int64_t cent_stride;   // unit h's table at cent + h * cent_stride elements
+    int H; int K; int B; int T;
     uint8_t *ids;            // always written
     uint8_t *codes; f16_t *scales;   // written when fused != 0
     int64_t out_stride;      // tokens between consecutive units in ids / codes / scales
     int ids_step, ids_off;   // a token has ids_step id bytes; this pass writes byte ids_off (smoothing stage)
     int fused;
-    uint2 *nh3; float *cmax; // scratch of assign_workspace_bytes(H, K): split -||c||^2/2 per row, max ||c||^2 per unit
+    const uint2 *nh3; int64_t nh3_stride;      // split -||c||^2/2 per row, unit h at nh3 + h * nh3_stride
     bf16_t *cent_copy; int64_t cent_copy_stride;   // optional: the table also goes here, unit h at h * stride elements
                                                    // (written by the unit's first workgroup while it stages the table)
+    MemberLists lists;       // lists.perm: optional, the member lists of this assignment (not with fused)
+    bf16_t *resid;           // optional (not with fused): bf16(x - c) of every token, dense [H][N][128] (Eq. 5)
     int id_wide;             // ids are 16-bit words (K > 256)
 };
-// launches the centroid preparation and the assignment (fused with quantization when a.fused)
 hipError_t launch_assign(const AssignArgs &a, hipStream_t s);
-size_t assign_workspace_bytes(int H, int K);
-void assign_workspace_split(void *ws, int H, int K, uint2 **nh3, float **cmax);
+// the split norms of `tables` consecutive tables per unit: cent [H][..][K][d] with the given unit stride,
+// nh3 [H][tables][Kpad]
+hipError_t launch_half_norms(const bf16_t *cent, int64_t cent_stride, int H, int tables, int K, uint2 *nh3, hipStream_t s);
 
 struct UpdateArgs {
     const bf16_t *x; int64_t stride_head, stride_token; int64_t n_tokens;
-    const uint8_t *ids; int64_t ids_stride;      // tokens between consecutive units in ids
-    int ids_step, ids_off;                       // id bytes per token, byte read by this pass
-    const bf16_t *cent_prev; bf16_t *cent_out; int32_t *counts_out;
-    int32_t *perm; int32_t *offsets;     // workspace: [H][N] and [H][K+1]
+    const bf16_t *cent_prev; int64_t prev_stride;    // unit h at cent_prev + h * prev_stride elements
+    bf16_t *cent_out;                                // dense [H][K][d]
+    uint2 *nh3;                                      // optional: split norms of the new table, [H][Kpad]
+    int32_t *counts_out;
+    MemberLists lists;
     int H; int K;
-    int id_wide;                         // ids are 16-bit words (K > 256)
 };
 hipError_t launch_update(const UpdateArgs &a, hipStream_t s);
 
-// out[h][n][:] = bf16( x[h][n][:] - cent[h][ids[h][n]][:] ), one fp32 subtraction (Eq. 5), for the
-// next smoothing stage.  out is dense [H][N][128].
-struct ResidualArgs {
-    const bf16_t *x; int64_t stride_head, stride_token; int64_t n_tokens;
-    const bf16_t *cent; const uint8_t *ids; int64_t ids_stride; int ids_step, ids_off;
-    bf16_t *out; int H; int K; int id_wide;
-};
-hipError_t launch_residual(const ResidualArgs &a, hipStream_t s);
+// member lists of a given assignment, ids [H][ids_stride]; ids at or above K are left out
+hipError_t launch_member_lists(const uint8_t *ids, int64_t ids_stride, int64_t n_tokens, int H, int K, int id_wide,
+                               const MemberLists &lists, hipStream_t s);
 
 // Eq. 5 and the T rounds of Eq. 2 for a given assignment, for every stored format (the fused
 // assignment kernel covers 2-bit levels with binary16 scales only).
 struct QuantArgs {
     const bf16_t *x; int64_t stride_head, stride_token; int64_t n_tokens;
-    const bf16_t *cent;                    // [H][K][d]
+    const bf16_t *cent; int64_t cent_stride;   // unit h's table at cent + h * cent_stride elements
     const uint8_t *ids; int ids_step, ids_off;
     uint8_t *codes; void *scales; int64_t out_stride;     // tokens between units in ids / codes / scales
     int H; int K; int B; int T; int fmt; int id_wide;

@@ -1,136 +1,48 @@
 // k-means update step (paper Sec. 4.1: the centroid is the mean of its group).
 //
 // The mean is defined with a fixed summation order - members in token order, fp64 -
-// so that the result does not depend on scheduling.  Two kernels:
-//   rank:  a stable counting sort of the token indices of one unit by cluster id
-//          (16 wavefronts, each histogramming and then placing its own contiguous range
-//          of tokens, ballot-built peer masks keeping equal ids in token order);
-//   mean:  one wavefront per centroid adds its members in fp64, divides by the count, rounds
-//          to fp32 and then to bf16: in token order for short lists, in interleaved partial
-//          sums for long ones (four per wavefront; the longest lists are spread over the
-//          wavefronts of the block) when a test on the members' exponents shows that no
-//          addition can round (then every order gives the same bits).
-//          A group without members keeps its previous centroid.
-// Also here: the residual pass that turns one smoothing stage's output into the next one's
-// input (Eq. 5 on whole tensors, result rounded to bf16).
-#include "qvg_internal.hpp"
+// so that the result does not depend on scheduling.  The assignment leaves the unit's tokens sorted
+// by cluster inside blocks of 256..1024 tokens (MemberLists), so that a cluster's members in token
+// order are its segments of block 0, 1, ...  One wavefront per centroid adds them in fp64, divides by
+// the count, rounds to fp32 and then to bf16: in token order for short lists, in interleaved partial
+// sums for long ones (four per wavefront; the longest lists are spread over the wavefronts of the
+// block) when a test on the members' exponents shows that no addition can round (then every order
+// gives the same bits).  A group without members keeps its previous centroid.  The wavefront also
+// leaves the split norm of its new centroid for the next assignment.
+//
+// A Lloyd iteration is therefore two launches.  A third one, a counting sort of the whole unit by a
+// single workgroup (1024 threads), took 6.5 to 8 us of every iteration at 2 to 24 units of 4096 to
+// 4680 tokens and 15 us at 80 units of 10800; sorting where the ids are made costs the assignment
+// about 1 us.
+#include "qvg_kmeans.hpp"
 
 namespace qvg {
 
-constexpr int kRankThreads = 1024;
-constexpr int kRankWaves = kRankThreads / 64;      // the tokens of a unit are split into 16 ranges
-constexpr int kRankKeep = 8;                        // ids a lane keeps in registers between passes
-constexpr int kRankK = kMaxClusters;                // histogram width
-
-// Stable counting sort of token indices by cluster id, one workgroup per unit.
-// Wavefront w owns the w-th contiguous range of tokens: it histograms the range, and after
-// the scan (start of cluster k = tokens of lower clusters + tokens of k in earlier ranges) it
-// places the range 64 tokens at a time.  Inside a step, lanes with equal ids are ranked by
-// lane number (ballot-built peer masks), so equal ids keep their token order.
+// Member lists of ids that come from the caller: one workgroup per block of tokens.
 template <bool WIDE>                       // 16-bit ids (more than 256 centroids)
-__global__ __launch_bounds__(kRankThreads)
-void kmeans_rank_kernel(UpdateArgs a) {
-    __shared__ int cnt[kRankWaves][kRankK];   // histogram per range, then running cursor
-    __shared__ int total[kRankK];
-    const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int K = a.K;
-    const int64_t N = a.n_tokens;
-    const int64_t id0 = (int64_t)h * a.ids_stride * a.ids_step + a.ids_off;   // token n at element id0 + n * step
-    const int64_t step = a.ids_step;
-    auto id_of = [&](int64_t n) { return (int)load_id(a.ids, id0 + n * step, WIDE ? 1 : 0); };
-    int32_t *perm = a.perm + (int64_t)h * N;
-    int32_t *offs = a.offsets + (int64_t)h * (K + 1);
+__global__ __launch_bounds__(kAsgThreads)
+void member_list_kernel(const uint8_t *ids, int64_t ids_stride, int64_t n_tokens, int K, MemberLists lists) {
+    __shared__ uint16_t lid[kMaxTilesPerWave * kAsgThreads];
+    __shared__ __align__(16) int scratch[kAsgWaves * kMaxClusters + 8];
+    const int h = blockIdx.x;
+    const int64_t t0 = (int64_t)blockIdx.y * lists.block;
+    for (int i = threadIdx.x; i < lists.block; i += kAsgThreads) {
+        uint32_t id = 0xffffu;
+        if (t0 + i < n_tokens) { id = load_id(ids, (int64_t)h * ids_stride + t0 + i, WIDE ? 1 : 0); if (id >= (uint32_t)K) id = 0xffffu; }
+        lid[i] = (uint16_t)id;
+    }
+    __syncthreads();
+    const int64_t blk = (int64_t)h * lists.n_blocks + blockIdx.y;
+    block_member_sort(lid, lists.block / kAsgThreads, K, scratch, lists.perm + blk * lists.block, lists.seg + blk * K);
+}
 
-    const int Kp = (K + 63) & ~63;            // only the first Kp columns of the histograms are used
-    for (int k = lane; k < Kp; k += 64) cnt[w][k] = 0;
-    __syncthreads();
-    // range of this wavefront, a multiple of 64 tokens long
-    const int64_t per = ((N + kRankWaves * 64 - 1) / (kRankWaves * 64)) * 64;
-    const int64_t beg = (int64_t)w * per;
-    const int64_t end = (beg + per < N) ? beg + per : N;
-    const int steps = (int)((per + 63) / 64);
-    const bool keep = steps <= kRankKeep;
-    int kept[kRankKeep];
-    // ids at or above K cannot come from the assignment; such tokens are left out (id = -1)
-    if (keep) {
-#pragma unroll
-        for (int i = 0; i < kRankKeep; ++i) {
-            const int64_t n = beg + (int64_t)i * 64 + lane;
-            int id = -1;
-            if (i < steps && n < end) { id = id_of(n); if (id >= K) id = -1; }
-            kept[i] = id;
-        }
-#pragma unroll
-        for (int i = 0; i < kRankKeep; ++i) if (kept[i] >= 0) atomicAdd(&cnt[w][kept[i]], 1);
-    } else {
-        for (int64_t n = beg + lane; n < end; n += 64) { const int id = id_of(n); if (id < K) atomicAdd(&cnt[w][id], 1); }
-    }
-    __syncthreads();
-    if (tid < kRankK) {
-        int t = 0;
-        if (tid < K) for (int r = 0; r < kRankWaves; ++r) t += cnt[r][tid];
-        total[tid] = t;
-    }
-    __syncthreads();
-    constexpr int kPerLane = kRankK / 64;
-    if (tid < 64) {                       // exclusive scan of total[0..kRankK-1] by one wavefront
-        int v[kPerLane], run = 0;
-#pragma unroll
-        for (int i = 0; i < kPerLane; ++i) { v[i] = total[lane * kPerLane + i]; run += v[i]; }
-        int incl = run;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += o;
-        }
-        int start = incl - run;
-#pragma unroll
-        for (int i = 0; i < kPerLane; ++i) { total[lane * kPerLane + i] = start; start += v[i]; }
-    }
-    __syncthreads();
-    if (tid < Kp) {
-        // cursor of (range r, cluster tid) = start of the cluster + members in earlier ranges
-        int run = total[tid], c = 0;
-        for (int r = 0; r < kRankWaves; ++r) { const int t = cnt[r][tid]; cnt[r][tid] = run; run += t; c += t; }
-        if (tid < K) {
-            offs[tid] = total[tid];
-            if (a.counts_out) a.counts_out[(int64_t)h * K + tid] = c;
-            if (tid == K - 1) offs[K] = total[tid] + c;
-        }
-    }
-    __syncthreads();
-
-    int nxt = -1;
-    if (!keep && beg + lane < end) { nxt = id_of(beg + lane); if (nxt >= K) nxt = -1; }
-    for (int i = 0; i < steps; ++i) {
-        const int64_t n = beg + (int64_t)i * 64 + lane;
-        int id;
-        if (keep) {
-            id = -1;
-#pragma unroll
-            for (int j = 0; j < kRankKeep; ++j) if (j == i) id = kept[j];
-        } else {
-            id = nxt;
-            const int64_t nn = n + 64;
-            nxt = -1;
-            if (nn < end) { nxt = id_of(nn); if (nxt >= K) nxt = -1; }
-        }
-        const bool valid = id >= 0;
-        uint64_t peers = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < 9; ++b) {
-            if (b == 8 && !WIDE) break;                             // the ninth bit only with 16-bit ids
-            const uint64_t m = __ballot((id >> b) & 1);
-            peers &= ((id >> b) & 1) ? m : ~m;
-        }
-        if (valid) {
-            const int rank = __builtin_popcountll(peers & ((1ull << lane) - 1ull));
-            const int start = cnt[w][id];             // read by all peers before the write below
-            perm[start + rank] = (int32_t)n;
-            if (rank == 0) cnt[w][id] = start + __builtin_popcountll(peers);
-        }
-        __builtin_amdgcn_wave_barrier();
-    }
+hipError_t launch_member_lists(const uint8_t *ids, int64_t ids_stride, int64_t n_tokens, int H, int K, int id_wide,
+                               const MemberLists &lists, hipStream_t s) {
+    if (lists.n_blocks == 0) return hipSuccess;
+    const dim3 grid((unsigned)H, (unsigned)lists.n_blocks);
+    if (id_wide) hipLaunchKernelGGL(member_list_kernel<true>, grid, dim3(kAsgThreads), 0, s, ids, ids_stride, n_tokens, K, lists);
+    else hipLaunchKernelGGL(member_list_kernel<false>, grid, dim3(kAsgThreads), 0, s, ids, ids_stride, n_tokens, K, lists);
+    return hipGetLastError();
 }
 
 constexpr int kMeanThreads = 256;           // 4 wavefronts
@@ -139,6 +51,47 @@ constexpr int kMeanParallelMin = 96;        // member lists at least this long t
 constexpr int kMeanCoopMin = 192;           // lists at least this long are summed by the whole block
                                             // (with one centroid per block: every order-free list)
 constexpr int kMeanSmallGrid = 2048;        // up to this many centroids in a launch: one block each
+
+// A cluster's members in up to 64 consecutive blocks of its unit: lane b holds block b's part.
+struct Segments {
+    int pre;           // members in the blocks before this one
+    int delta;         // member m of this block is entry delta + m of the unit's perm
+    int n;             // members in all of these blocks (uniform)
+};
+struct ListView {      // one unit's lists
+    const uint16_t *perm; const uint32_t *seg;
+    int block, n_blocks, K, probe;      // probe: first step of the search, the largest power of two below min(n_blocks, 64)
+};
+__device__ __forceinline__ ListView list_view(const MemberLists &l, int K, int h) {
+    ListView v;
+    v.perm = l.perm + (int64_t)h * l.n_blocks * l.block;
+    v.seg = l.seg + (int64_t)h * l.n_blocks * K;
+    v.block = l.block; v.n_blocks = l.n_blocks; v.K = K;
+    v.probe = 32;
+    while (v.probe > 0 && v.probe >= l.n_blocks) v.probe >>= 1;
+    return v;
+}
+__device__ __forceinline__ Segments load_segments(const ListView &v, int j, int b0, int lane) {
+    const int b = b0 + lane;
+    const uint32_t w = b < v.n_blocks ? v.seg[(int64_t)b * v.K + j] : 0u;
+    const int start = (int)(w & 0xffffu), cnt = (int)(w >> 16) - start;
+    const int incl = scan64(cnt);
+    Segments s;
+    s.pre = incl - cnt;
+    s.delta = b * v.block + start - s.pre;
+    s.n = __builtin_amdgcn_readlane(incl, 63);
+    return s;
+}
+// token index of member m (0 .. s.n - 1; a larger m gives some valid token) of the blocks b0 ..
+__device__ __forceinline__ int member_token(const ListView &v, const Segments &s, int b0, int m) {
+    m = m < s.n ? m : s.n - 1;
+    int b = 0;                             // last block that starts at or before m: it is not empty
+    for (int step = v.probe; step; step >>= 1) {                         // uniform
+        const int p = __shfl(s.pre, b + step, 64);
+        if (b + step < 64 && p <= m) b += step;
+    }
+    return (b0 + b) * v.block + (int)v.perm[(int64_t)__shfl(s.delta, b, 64) + m];
+}
 
 typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
 
@@ -150,51 +103,56 @@ __device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
 }
 
 // Order-free partial sums of a member list: the wavefront takes the groups of 64 members
-// first, first + step, .. of perm[beg .. end); lane = member slot (4) x 8 channels, 8 rows in
+// first, first + step, .. of the list; lane = member slot (4) x 8 channels, 8 rows in
 // flight per lane (ROWS = 16 where registers do not matter).  s: the lane's partial sums of its 8 channels; amax / amin: per 16-bit half the
 // largest magnitude bits and the smallest non-zero magnitude bits minus one (0xffff: none).
 template <int ROWS>
-__device__ __forceinline__ void mean_partial(const bf16_t *xb, int64_t stride_token, const int32_t *perm, int beg,
-                                             int end, int first, int step, int lane, double s[8], uint32_t amax[4],
+__device__ __forceinline__ void mean_partial(const bf16_t *xb, int64_t stride_token, const ListView &v, int j,
+                                             Segments sg, int first, int step, int lane, double s[8], uint32_t amax[4],
                                              uint32_t amin[4]) {
     const int slot = lane >> 4;
     constexpr bool AHEAD = ROWS > 8;       // member indices requested a group ahead (two more registers)
-    int base = beg + 64 * first;
-    int nxt = (AHEAD && base + lane < end) ? perm[base + lane] : 0;
-    for (; base < end; base += 64 * step) {
-        int mine;                                                        // 64 member indices, one coalesced load
-        if (AHEAD) {
-            mine = nxt;
-            const int nb = base + 64 * step;
-            nxt = (nb + lane < end) ? perm[nb + lane] : 0;
-        } else {
-            mine = (base + lane < end) ? perm[base + lane] : 0;
-        }
-        const int cntm = (end - base < 64) ? end - base : 64;
-        // slot s takes members s, s + 4, s + 8, .. of the group: ROWS rows in flight per lane
-        for (int i0 = 0; 4 * i0 < cntm; i0 += ROWS) {
-            uint4 row[ROWS];
-#pragma unroll
-            for (int i = 0; i < ROWS; ++i) {
-                const int u = 4 * (i0 + i) + slot;
-                const int idx = __shfl(mine, u & 63, 64);
-                row[i] = (u < cntm) ? *reinterpret_cast<const uint4 *>(xb + (int64_t)idx * stride_token)
-                                    : make_uint4(0u, 0u, 0u, 0u);
+    for (int b0 = 0;;) {
+        int base = 64 * first;
+        int nxt = (AHEAD && base < sg.n) ? member_token(v, sg, b0, base + lane) : 0;
+        for (; base < sg.n; base += 64 * step) {
+            int mine;                                                    // 64 member indices
+            if (AHEAD) {
+                mine = nxt;
+                const int nb = base + 64 * step;
+                if (nb < sg.n) nxt = member_token(v, sg, b0, nb + lane);
+            } else {
+                mine = member_token(v, sg, b0, base + lane);
             }
+            const int cntm = (sg.n - base < 64) ? sg.n - base : 64;
+            // slot s takes members s, s + 4, s + 8, .. of the group: ROWS rows in flight per lane
+            for (int i0 = 0; 4 * i0 < cntm; i0 += ROWS) {
+                uint4 row[ROWS];
 #pragma unroll
-            for (int i = 0; i < ROWS; ++i) {
-                const uint32_t w[4] = {row[i].x, row[i].y, row[i].z, row[i].w};
+                for (int i = 0; i < ROWS; ++i) {
+                    const int u = 4 * (i0 + i) + slot;
+                    const int idx = __shfl(mine, u & 63, 64);
+                    row[i] = (u < cntm) ? *reinterpret_cast<const uint4 *>(xb + (int64_t)idx * stride_token)
+                                        : make_uint4(0u, 0u, 0u, 0u);
+                }
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    s[2 * e] += (double)bf16_lo(w[e]);
-                    s[2 * e + 1] += (double)bf16_hi(w[e]);
-                    const uint32_t mag = w[e] & 0x7fff7fffu;
-                    const ushort2_t one = {1, 1};
-                    amax[e] = pk_max_u16(amax[e], mag);
-                    amin[e] = pk_min_u16(amin[e], __builtin_bit_cast(uint32_t, (ushort2_t)(__builtin_bit_cast(ushort2_t, mag) - one)));   // zero -> 0xffff
+                for (int i = 0; i < ROWS; ++i) {
+                    const uint32_t w[4] = {row[i].x, row[i].y, row[i].z, row[i].w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        s[2 * e] += (double)bf16_lo(w[e]);
+                        s[2 * e + 1] += (double)bf16_hi(w[e]);
+                        const uint32_t mag = w[e] & 0x7fff7fffu;
+                        const ushort2_t one = {1, 1};
+                        amax[e] = pk_max_u16(amax[e], mag);
+                        amin[e] = pk_min_u16(amin[e], __builtin_bit_cast(uint32_t, (ushort2_t)(__builtin_bit_cast(ushort2_t, mag) - one)));   // zero -> 0xffff
+                    }
                 }
             }
         }
+        b0 += 64;
+        if (b0 >= v.n_blocks) break;                                     // uniform: more than 64 blocks per unit
+        sg = load_segments(v, j, b0, lane);
     }
 }
 
@@ -213,31 +171,45 @@ __device__ __forceinline__ bool mean_exact(uint32_t mx, uint32_t mn, int lg) {
     return ok;
 }
 
+// a new centroid's two channels of this lane: rounded to bf16, stored, and the split of its norm
+__device__ __forceinline__ void store_centroid(const UpdateArgs &a, int h, int j, int lane, uint32_t packed) {
+    *reinterpret_cast<uint32_t *>(a.cent_out + ((int64_t)h * a.K + j) * kHeadDim + lane * 2) = packed;
+    if (a.nh3) {                                                         // uniform
+        const double lo = (double)bf16_lo(packed), hi = (double)bf16_hi(packed);
+        const double n2 = sum64_f64(lo * lo + hi * hi);
+        if (lane == 0) a.nh3[(int64_t)h * k_padded(a.K) + j] = split_half_norm(n2);
+    }
+}
+
 // the defining order: members in token order, two channels per lane, 16 rows in flight
-__device__ __forceinline__ void mean_token_order(const bf16_t *xu, int64_t stride_token, const int32_t *perm, int beg,
-                                                 int end, int lane, bf16_t *out) {
+__device__ __forceinline__ uint32_t mean_token_order(const bf16_t *xu, int64_t stride_token, const ListView &v, int j,
+                                                     Segments sg, int n, int lane) {
     double s0 = 0.0, s1 = 0.0;
     const bf16_t *xb = xu + lane * 2;
-    for (int base = beg; base < end; base += 64) {
-        // 64 member indices with one coalesced load, then broadcast lane by lane
-        const int mine = (base + lane < end) ? perm[base + lane] : 0;
-        const int cntm = (end - base < 64) ? end - base : 64;
-        for (int u0 = 0; u0 < cntm; u0 += 16) {
-            uint32_t wv[16];
+    for (int b0 = 0;;) {
+        for (int base = 0; base < sg.n; base += 64) {
+            // 64 member indices at once, then broadcast lane by lane
+            const int mine = member_token(v, sg, b0, base + lane);
+            const int cntm = (sg.n - base < 64) ? sg.n - base : 64;
+            for (int u0 = 0; u0 < cntm; u0 += 16) {
+                uint32_t wv[16];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int idx = __shfl(mine, u0 + u, 64);
-                wv[u] = (u0 + u < cntm)
-                    ? *reinterpret_cast<const uint32_t *>(xb + (int64_t)idx * stride_token) : 0u;
+                for (int u = 0; u < 16; ++u) {
+                    const int idx = __shfl(mine, u0 + u, 64);
+                    wv[u] = (u0 + u < cntm)
+                        ? *reinterpret_cast<const uint32_t *>(xb + (int64_t)idx * stride_token) : 0u;
+                }
+#pragma unroll
+                for (int u = 0; u < 16; ++u)
+                    if (u0 + u < cntm) { s0 += (double)bf16_lo(wv[u]); s1 += (double)bf16_hi(wv[u]); }
             }
-#pragma unroll
-            for (int u = 0; u < 16; ++u)
-                if (u0 + u < cntm) { s0 += (double)bf16_lo(wv[u]); s1 += (double)bf16_hi(wv[u]); }
         }
+        b0 += 64;
+        if (b0 >= v.n_blocks) break;                                     // uniform
+        sg = load_segments(v, j, b0, lane);
     }
-    const double c = (double)(end - beg);
-    const float m0 = (float)(s0 / c), m1 = (float)(s1 / c);
-    *reinterpret_cast<uint32_t *>(out + lane * 2) = pack_bf16x2(m0, m1);
+    const double c = (double)n;
+    return pack_bf16x2((float)(s0 / c), (float)(s1 / c));
 }
 
 // One wavefront per centroid, CPB = four centroids per block (or CPB = 1, see below).  The defined result is the fp64 sum of
@@ -266,37 +238,43 @@ void kmeans_mean_kernel(UpdateArgs a) {
     constexpr int kCoopMin = CPB == 1 ? kMeanParallelMin : kMeanCoopMin;
     __shared__ double part[kMeanWaves][kHeadDim];
     __shared__ uint32_t pmx[kMeanWaves][kHeadDim / 2], pmn[kMeanWaves][kHeadDim / 2];
+    __shared__ int list_len[kMeanWaves];
     const int h = blockIdx.y, lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j0 = blockIdx.x * CPB;
     const int j = j0 + wave;
     const int K = a.K;
-    const int64_t N = a.n_tokens;
-    const int32_t *offs = a.offsets + (int64_t)h * (K + 1);
-    const int32_t *perm = a.perm + (int64_t)h * N;
     const bf16_t *xu = a.x + (int64_t)h * a.stride_head;
     const int slot = lane >> 4, c8 = lane & 15;
-    // the block's list boundaries with one load per wavefront (lane i: start of centroid j0 + i);
-    // used after the wavefront's own list
-    const int myoff = (lane <= CPB && j0 + lane <= K) ? offs[j0 + lane] : 0;
+    const ListView v = list_view(a.lists, K, h);
+    const bool own = wave < CPB && j < K;
+
+    Segments sg = {0, 0, 0};
+    int n = 0;                                                           // members of the wavefront's own centroid
+    if (own) {
+        sg = load_segments(v, j, 0, lane);
+        n = sg.n;
+        for (int b0 = 64; b0 < v.n_blocks; b0 += 64) n += load_segments(v, j, b0, lane).n;
+        if (a.counts_out && lane == 0) a.counts_out[(int64_t)h * K + j] = n;
+    }
+    if (lane == 0) list_len[wave] = n;
+    __syncthreads();
 
     // ---- the wavefront's own centroid, unless its list is left to the whole block ----
-    if (wave < CPB && j < K) {
-        const int beg = offs[j], end = offs[j + 1];                      // wave-uniform: scalar loads
-        const int64_t co = ((int64_t)h * K + j) * kHeadDim;
-        if (end == beg) {
-            *reinterpret_cast<uint32_t *>(a.cent_out + co + lane * 2) = *reinterpret_cast<const uint32_t *>(a.cent_prev + co + lane * 2);
-        } else if (end - beg < kCoopMin) {
+    if (own && n < kCoopMin) {
+        if (n == 0) {
+            store_centroid(a, h, j, lane, *reinterpret_cast<const uint32_t *>(a.cent_prev + (int64_t)h * a.prev_stride + (int64_t)j * kHeadDim + lane * 2));
+        } else {
             bool done = false;
-            if (CPB > 1 && end - beg >= kMeanParallelMin) {
+            if (CPB > 1 && n >= kMeanParallelMin) {
                 double s[8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) s[i] = 0.0;
                 uint32_t amax[4] = {0u, 0u, 0u, 0u}, amin[4] = {~0u, ~0u, ~0u, ~0u};
-                mean_partial<ROWS>(xu + c8 * 8, a.stride_token, perm, beg, end, 0, 1, lane, s, amax, amin);
+                mean_partial<ROWS>(xu + c8 * 8, a.stride_token, v, j, sg, 0, 1, lane, s, amax, amin);
                 // the four slots hold partial results of the same channels: lanes l, l^16, l^32, l^48
                 int lg = 0;
-                while ((1 << lg) < end - beg) ++lg;                          // ceil(log2 n)
+                while ((1 << lg) < n) ++lg;                                  // ceil(log2 n)
                 bool ok = true;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -309,38 +287,36 @@ void kmeans_mean_kernel(UpdateArgs a) {
                     ok = ok && mean_exact(mx, mn, lg);
                 }
                 if (__all(ok)) {
+                    // every slot's lanes end up with the total of their 8 channels; lane (slot, c8) keeps
+                    // channels 8 c8 + 2 slot, + 1 and hands them to lane 4 c8 + slot
+                    uint32_t pk = 0u;
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        s[i] += __shfl_xor(s[i], 16, 64);
-                        s[i] += __shfl_xor(s[i], 32, 64);
+                    for (int e = 0; e < 4; ++e) {
+                        double t0 = s[2 * e], t1 = s[2 * e + 1];
+                        t0 += __shfl_xor(t0, 16, 64); t0 += __shfl_xor(t0, 32, 64);
+                        t1 += __shfl_xor(t1, 16, 64); t1 += __shfl_xor(t1, 32, 64);
+                        if (slot == e) pk = pack_bf16x2((float)(t0 / (double)n), (float)(t1 / (double)n));
                     }
-                    if (slot == 0) {
-                        const double c = (double)(end - beg);
-                        float m[8];
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) m[i] = (float)(s[i] / c);
-                        *reinterpret_cast<uint4 *>(a.cent_out + co + c8 * 8) = pack_bf16x8(m);
-                    }
+                    store_centroid(a, h, j, lane, __shfl(pk, (lane & 3) * 16 + (lane >> 2), 64));
                     done = true;
                 }
             }
-            if (!done) mean_token_order(xu, a.stride_token, perm, beg, end, lane, a.cent_out + co);
+            if (!done) store_centroid(a, h, j, lane, mean_token_order(xu, a.stride_token, v, j, sg, n, lane));
         }
     }
 
     // ---- the block's longest lists, one after the other, by all wavefronts (every wavefront of
     // the block takes the same branches: the list lengths are read by all of them) ----
-    const int mylen = __shfl_down(myoff, 1, 64) - myoff;                 // all lanes take part in the exchange
-    const uint64_t coop = __ballot(lane < CPB && j0 + lane < K && mylen >= kCoopMin);   // the same in every wavefront
-    for (uint64_t todo = coop; todo; todo &= todo - 1) {
-        const int t = __builtin_ctzll(todo);
+    for (int t = 0; t < CPB; ++t) {
+        const int nt = __builtin_amdgcn_readfirstlane(list_len[t]);
+        if (nt < kCoopMin) continue;                                     // uniform over the block
         const int jt = j0 + t;
-        const int beg = __shfl(myoff, t, 64), end = __shfl(myoff, t + 1, 64);
         double s[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) s[i] = 0.0;
         uint32_t amax[4] = {0u, 0u, 0u, 0u}, amin[4] = {~0u, ~0u, ~0u, ~0u};
-        mean_partial<ROWS>(xu + c8 * 8, a.stride_token, perm, beg, end, wave, kMeanWaves, lane, s, amax, amin);
+        const Segments st = load_segments(v, jt, 0, lane);
+        mean_partial<ROWS>(xu + c8 * 8, a.stride_token, v, jt, st, wave, kMeanWaves, lane, s, amax, amin);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {          // harmless if an addition rounds: then the result is discarded
             s[i] += __shfl_xor(s[i], 16, 64);
@@ -372,50 +348,21 @@ void kmeans_mean_kernel(UpdateArgs a) {
                 mn = pk_min_u16(mn, pmn[w][lane]);
             }
             int lg = 0;
-            while ((1 << lg) < end - beg) ++lg;
-            const int64_t co = ((int64_t)h * K + jt) * kHeadDim;
+            while ((1 << lg) < nt) ++lg;
+            uint32_t pk;
             if (__all(mean_exact(mx, mn, lg))) {
-                const double c = (double)(end - beg);
-                *reinterpret_cast<uint32_t *>(a.cent_out + co + lane * 2) = pack_bf16x2((float)(s0 / c), (float)(s1 / c));
+                const double c = (double)nt;
+                pk = pack_bf16x2((float)(s0 / c), (float)(s1 / c));
             } else {
-                mean_token_order(xu, a.stride_token, perm, beg, end, lane, a.cent_out + co);
+                pk = mean_token_order(xu, a.stride_token, v, jt, st, nt, lane);
             }
+            store_centroid(a, h, jt, lane, pk);
         }
         __syncthreads();                      // the partial results are overwritten by the next list
     }
 }
 
-// Residual for the next smoothing stage: 16 lanes per token, 8 channels each.
-__global__ __launch_bounds__(256)
-void residual_kernel(ResidualArgs a) {
-    const int h = blockIdx.y;
-    const int64_t n = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
-    const int c8 = threadIdx.x & 15;
-    if (n >= a.n_tokens) return;
-    int id = (int)load_id(a.ids, ((int64_t)h * a.ids_stride + n) * a.ids_step + a.ids_off, a.id_wide);
-    if (id >= a.K) id = a.K - 1;
-    const uint4 xv = *reinterpret_cast<const uint4 *>(a.x + (int64_t)h * a.stride_head + n * a.stride_token + c8 * 8);
-    const uint4 cv = *reinterpret_cast<const uint4 *>(a.cent + ((int64_t)h * a.K + id) * kHeadDim + c8 * 8);
-    float xf[8], cf[8], r[8];
-    unpack_bf16x8(xv, xf);
-    unpack_bf16x8(cv, cf);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) r[i] = xf[i] - cf[i];
-    *reinterpret_cast<uint4 *>(a.out + ((int64_t)h * a.n_tokens + n) * kHeadDim + c8 * 8) = pack_bf16x8(r);
-}
-
-hipError_t launch_residual(const ResidualArgs &a, hipStream_t s) {
-    if (a.n_tokens == 0) return hipSuccess;
-    dim3 grid((unsigned)((a.n_tokens + 15) / 16), (unsigned)a.H);
-    hipLaunchKernelGGL(residual_kernel, grid, dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
 hipError_t launch_update(const UpdateArgs &a, hipStream_t s) {
-    if (a.id_wide) hipLaunchKernelGGL(kmeans_rank_kernel<true>, dim3((unsigned)a.H), dim3(kRankThreads), 0, s, a);
-    else hipLaunchKernelGGL(kmeans_rank_kernel<false>, dim3((unsigned)a.H), dim3(kRankThreads), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     if ((int64_t)a.K * a.H <= kMeanSmallGrid) {
         hipLaunchKernelGGL((kmeans_mean_kernel<1, 16>), dim3((unsigned)a.K, (unsigned)a.H), dim3(kMeanThreads), 0, s, a);
     } else {

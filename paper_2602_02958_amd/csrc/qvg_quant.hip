@@ -28,7 +28,7 @@ void quantize_kernel(QuantArgs a, int passes) {
     const int gl = B / 8;                          // lanes per group: 2, 4, 8 or 16
     const float qmax = (BITS == 4) ? 7.0f : 1.0f;
     constexpr int kCodeBytes = kHeadDim * BITS / 8;     // per token and round
-    const bf16_t *cent = a.cent + (int64_t)h * a.K * kHeadDim;
+    const bf16_t *cent = a.cent + (int64_t)h * a.cent_stride;
     const uint32_t kmax = (uint32_t)a.K - 1u;
 
     for (int ps = 0; ps < passes; ++ps) {
