@@ -150,67 +150,105 @@ void slab_decode_kernel(AttnArgs a, SlabArgs sl, int run) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// S^T = K Q^T, online soft-max (base 2), O^T += V^T P on one tile held in LDS (layouts of the
-// fused kernels: K [64][136] bf16, V [128][72] f16 transposed, 16-byte groups of a row XOR-ed with
-// 2 * (row / 32)).  ntile: tokens the tile holds (scores of the others are masked).
+// The tile loop.  Per wavefront and tile there are 32 contractions (32 cycles of the matrix pipe
+// each) and about 120 vector instructions, the 32 exponentials among them costing four times the
+// others.  One kind after the other, the two add up: the matrix pipe works beside the vector ALU
+// only on contractions issued before, so the kinds have to alternate.  The scores of tile i + 1 and
+// the probabilities of tile i do not depend on each other, nor do PV of a tile's first tokens and
+// the probabilities of its last:
+//   slots  0..15   scores of tile i + 1        beside   probabilities 0 .. kP1 - 1 of tile i
+//   slots 16..31   PV of tile i, token order   beside   the other probabilities, then the maxima of tile i + 1
+// A slot is one contraction, one operand read (kAhead slots ahead of its use) and its share of the
+// vector work; no instruction moves across a slot's end.
+// What bounds it is the power cap: 4680 queries x 12 heads x 748800 tokens take 22.5 ms (tile decode 1.75
+// of it) against 23.2 ms with the kinds one after the other, but 17.3 against 19.2 ms when all queries are
+// zero, and the clock stands at 1.7-1.9 GHz instead of 2.4.  (A large bf16 product on this card:
+// 1.58 PFLOP/s, 2.13 on zeros.)  At equal clocks the parks cost most: 2.3 ms when they stand
+// together at the end of the tile, half of that spread over slots 9..15.
 // ---------------------------------------------------------------------------------------------
-// left: tokens of this tile the lane's query sees (only looked at when ql_mask is set: some query of
-// the wavefront ends in or before this tile).
-__device__ __forceinline__ void slab_tile_attend(const uint16_t *kt, const uint16_t *vt, const uint4 (&qa)[8], int col,
-                                                 int half, int ntile, bool ql_mask, int left, float scale2,
-                                                 floatx16_t (&O)[4], float &m, float &l) {
-    floatx16_t S[2];
+constexpr int kAhead = 4;          // operand fragments in flight
+constexpr int kP1 = 16;            // probabilities taken beside the scores (12, 20 and 24: 0-2 % slower)
+constexpr int kP2Slots = 10;       // slots of PV that carry the others (PV wants them by slots 24 and 28)
+constexpr int kSlabKBufs = 3;      // K tiles in LDS: read, next (its first fragments are read before the barrier), being written
+constexpr size_t kSlabSmem = ((size_t)kSlabKBufs * kKtElems + 2 * kVtElems) * sizeof(uint16_t);
+
+// probabilities whose exponential is issued by the end of slot k
+constexpr int probs_done(int k) {
+    return k < 0 ? 0 : k < 16 ? (k + 1) * kP1 / 16 : k >= 15 + kP2Slots ? 32 : kP1 + (k - 15) * (32 - kP1) / kP2Slots;
+}
+static_assert(probs_done(16 - 3) >= 8 && probs_done(20 - 3) >= 16 && probs_done(24 - 3) >= 24 && probs_done(28 - 3) >= 32,
+              "PV would read probabilities that are not there");
+
+// scores of the next tile that have gone into its maximum by the end of slot k: the first block's
+// contractions are slots 0..7, the second's 8..15, and a result is there two slots later
+constexpr int maxima_done(int k) { return k < 9 ? 0 : k <= 16 ? 2 * (k - 8) : k < 18 ? 16 : k < 26 ? 16 + 2 * (k - 17) : 32; }
+constexpr int kMaxSlot = 27;       // the maximum over both lane halves
+constexpr int kParkSlot = 9;       // the four pieces of the copy: slots 9, 11, 13, 15
+
+template <int A, int B_, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+    if constexpr (A < B_) { f(std::integral_constant<int, A>{}); static_for<A + 1, B_>(f); }
+}
+
+// No instruction: the value is computed no later than here (it would otherwise move to its first use,
+// behind the contractions it is meant to run beside).
+template <class T> __device__ __forceinline__ void keep_here(T &v) { asm volatile("" : "+v"(v)); }
+
+// Slot k's share of the probabilities exp2(S scale2 - m): argument, exponential, pair rounded to f16
+// and sum each one slot behind the one before, so that nothing waits for a result just issued.
+// Probability e belongs to score register e of the lane (two blocks of 16).  The normaliser is the
+// sum of the f16 values that the PV contraction uses.
+template <int k>
+__device__ __forceinline__ void slab_probs(const floatx16_t (&S)[2], float scale2, float m, float (&x)[32],
+                                           uint32_t (&p)[16], float &l) {
+    constexpr int e0 = probs_done(k - 3), e1 = probs_done(k - 2), e2 = probs_done(k - 1), e3 = probs_done(k), e4 = probs_done(k + 1);
+    const halfx2_t ones = {(_Float16)1.0f, (_Float16)1.0f};
+#pragma unroll
+    for (int e = k == 0 ? 0 : e3; e < e4; ++e) x[e] = __builtin_fmaf(S[e >> 4][e & 15], scale2, -m);
+#pragma unroll
+    for (int e = e2; e < e3; ++e) { x[e] = __builtin_amdgcn_exp2f(x[e]); keep_here(x[e]); }
+#pragma unroll
+    for (int j = e1 / 2; j < e2 / 2; ++j) { p[j] = pack_f16x2_rne(x[2 * j], x[2 * j + 1]); keep_here(p[j]); }
+#pragma unroll
+    for (int j = e0 / 2; j < e1 / 2; ++j) { l = __builtin_amdgcn_fdot2(__builtin_bit_cast(halfx2_t, p[j]), ones, l, false); keep_here(l); }
+}
+
+template <int k>
+__device__ __forceinline__ void slab_maxima(const floatx16_t (&N)[2], float &nmax) {
+#pragma unroll
+    for (int e = maxima_done(k - 1); e < maxima_done(k); ++e) nmax = fmaxf(nmax, N[e >> 4][e & 15]);
+    if (maxima_done(k - 1) < maxima_done(k)) keep_here(nmax);
+}
+
+__device__ __forceinline__ bf16x8_t slab_kfrag(const uint16_t *krow, int i) {          // krow: tile + col * pitch + half * 8
+    return *reinterpret_cast<const bf16x8_t *>(krow + (i >> 3) * 32 * kKtPitch + (i & 7) * 16);
+}
+// i: 16-token step i / 4, channel block i % 4
+__device__ __forceinline__ halfx8_t slab_vfrag(const uint16_t *vt, int col, int half, int i) {
+    const int mb = i & 3, st = i >> 2;
+    return *reinterpret_cast<const halfx8_t *>(vt + (mb * 32 + col) * kVtPitch + (((2 * st + half) ^ (mb * 2)) * 8));
+}
+
+// Scores the lane's query must not see: tokens at or beyond `limit` of the tile.
+__device__ __forceinline__ void slab_mask(floatx16_t (&S)[2], int half, int limit) {
+    limit -= half * 4;
+    keep_here(limit);                                                    // the comparisons, and what they need, stay in the rare branch
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) S[nb][r] = 0.0f;
-    {
-        constexpr int kKAhead = 4;                                       // operand fragments in flight
-        const uint16_t *arow = kt + col * kKtPitch + half * 8;
-        auto kfrag = [&](int i) {
-            return *reinterpret_cast<const bf16x8_t *>(arow + (i >> 3) * 32 * kKtPitch + (i & 7) * 16);
-        };
-        bf16x8_t kf[16];
-#pragma unroll
-        for (int i = 0; i < kKAhead; ++i) kf[i] = kfrag(i);
-        __builtin_amdgcn_sched_group_barrier(0x100, kKAhead, 0);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            S[i >> 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                kf[i], __builtin_bit_cast(bf16x8_t, qa[i & 7]), S[i >> 3], 0, 0, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (i + kKAhead < 16) {
-                kf[i + kKAhead] = kfrag(i + kKAhead);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            }
-        }
-    }
-    if (ntile < kAtKv) {                                                 // uniform: last tile of a chunk
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int kv = nb * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
-                if (kv >= ntile) S[nb][r] = -INFINITY;
-            }
-    }
-    if (ql_mask) {                                                       // uniform
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int kv = nb * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
-                if (kv >= left) S[nb][r] = -INFINITY;
-            }
-    }
-    float tmax = -INFINITY;
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, S[nb][r]);
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64)) * scale2;               // the scale is positive: order kept
-    const float m_new = fmaxf(m, tmax);
-    if (__ballot(m_new > m)) {                                           // uniform: skip when no maximum moved
+        for (int r = 0; r < 16; ++r)
+            if (nb * 32 + (r >> 2) * 8 + (r & 3) >= limit) S[nb][r] = -INFINITY;
+}
+
+// The running maximum of the lane's query with the lane halves' maxima of a tile (the scale is
+// positive: order kept).
+__device__ __forceinline__ float slab_new_max(float tmax, float scale2, float m) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(tmax), __float_as_uint(tmax), false, false);
+    return fmaxf(m, fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale2);
+}
+// What was summed under the old maximum, brought to the new one (skipped when no maximum moved).
+__device__ __forceinline__ void slab_rescale(float m_new, float &m, float &l, floatx16_t (&O)[4]) {
+    if (__ballot(m_new > m)) {                                           // uniform
         const float alpha = __builtin_amdgcn_exp2f(m - m_new);
         l *= alpha;
 #pragma unroll
@@ -219,40 +257,6 @@ __device__ __forceinline__ void slab_tile_attend(const uint16_t *kt, const uint1
             for (int r = 0; r < 16; ++r) O[mb][r] *= alpha;
     }
     m = m_new;
-    uint4 pb[4];
-#pragma unroll
-    for (int st = 0; st < 4; ++st) {
-        float p[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(S[st >> 1][(st & 1) * 8 + e], scale2, -m));
-        pb[st] = make_uint4(pack_f16x2_rne(p[0], p[1]), pack_f16x2_rne(p[2], p[3]),
-                            pack_f16x2_rne(p[4], p[5]), pack_f16x2_rne(p[6], p[7]));
-        // the normaliser is the sum of the f16 probabilities the PV contraction uses
-        l = sum_f16_pairs(pb[st], l);
-    }
-    {
-        constexpr int kVAhead = 4;
-        auto vfrag = [&](int i) {
-            const int mb = i >> 2, st = i & 3;
-            const int key = mb * 2;
-            return *reinterpret_cast<const halfx8_t *>(vt + (mb * 32 + col) * kVtPitch + (((2 * st + half) ^ key) * 8));
-        };
-        halfx8_t vf[16];
-#pragma unroll
-        for (int i = 0; i < kVAhead; ++i) vf[i] = vfrag(i);
-        __builtin_amdgcn_sched_group_barrier(0x100, kVAhead, 1);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            O[i >> 2] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                vf[i], __builtin_bit_cast(halfx8_t, pb[i & 3]), O[i >> 2], 0, 0, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
-            if (i + kVAhead < 16) {
-                vf[i + kVAhead] = vfrag(i + kVAhead);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 1);
-            }
-        }
-    }
 }
 
 // One workgroup = 8 wavefronts = 256 queries of one unit, over the tiles of one slab.
@@ -263,8 +267,8 @@ template <bool QL>
 __global__ __launch_bounds__(kAtThreads, 2)
 void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int blocks_per_xcd) {
     extern __shared__ __align__(16) unsigned char smem[];
-    uint16_t *Kt = reinterpret_cast<uint16_t *>(smem);                  // [2][64][136] bf16
-    uint16_t *Vt = Kt + 2 * kKtElems;                                   // [2][128][72] f16, transposed
+    uint16_t *Kt = reinterpret_cast<uint16_t *>(smem);                  // [3][64][136] bf16
+    uint16_t *Vt = Kt + kSlabKBufs * kKtElems;                          // [2][128][72] f16, transposed
 
     // the query blocks of one unit run on one XCD, whose L2 then serves the unit's images to all of them
     const int w = (int)(blockIdx.x % 8u) * blocks_per_xcd + (int)(blockIdx.x / 8u);
@@ -330,59 +334,160 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
     auto v_off = [&](int p) { const int row = p >> 3; return row * kVtPitch + (((p & 7) ^ ((row >> 5) * 2)) * 8); };
     const int koff[2] = {k_off(tid), k_off(tid + kAtThreads)};
     const int voff[2] = {v_off(tid), v_off(tid + kAtThreads)};
-    // The pieces of a tile are requested two iterations before they go to LDS: two register sets,
-    // used in turn, so that the park does not wait for them (requested one iteration ahead: 22.8
-    // against 22.1 ms per cfg5 call).
     const int n = sl.n_tiles;                                           // >= 1
+    // tiles this workgroup attends to: those that start before its longest prefix
+    int ne = n;
+    if (QL) {
+        const int64_t rel = (int64_t)wgmax - (int64_t)sl.c0 * a.chunk_len;
+        const int64_t full = rel <= 0 ? 0 : rel / a.chunk_len;
+        const int64_t e = rel <= 0 ? 0 : full * sl.tpc + (rel - full * a.chunk_len + kAtKv - 1) / kAtKv;
+        ne = e < n ? (int)e : n;
+    }
     auto clampt = [&](int i) { return i < n ? i : n - 1; };            // past the end: the last tile once more (never used)
-    uint4 pa0, pa1, pa2, pa3, pb0, pb1, pb2, pb3;
-#define QVG_SLAB_FETCH(s_, i_)                                                                    \
-    {                                                                                             \
-        const int ti_ = clampt(i_);                                                               \
-        const uint16_t *kp_ = kimg + (int64_t)ti_ * kImgElems, *vp_ = vimg + (int64_t)ti_ * kImgElems; \
-        s_##0 = *reinterpret_cast<const uint4 *>(kp_);                                            \
-        s_##1 = *reinterpret_cast<const uint4 *>(kp_ + kAtThreads * 8);                           \
-        s_##2 = *reinterpret_cast<const uint4 *>(vp_);                                            \
-        s_##3 = *reinterpret_cast<const uint4 *>(vp_ + kAtThreads * 8);                           \
-    }
-#define QVG_SLAB_PARK(s_, buf_)                                                                   \
-    {                                                                                             \
-        uint16_t *kt_ = Kt + (buf_) * kKtElems, *vt_ = Vt + (buf_) * kVtElems;                    \
-        *reinterpret_cast<uint4 *>(kt_ + koff[0]) = s_##0;                                        \
-        *reinterpret_cast<uint4 *>(kt_ + koff[1]) = s_##1;                                        \
-        *reinterpret_cast<uint4 *>(vt_ + voff[0]) = s_##2;                                        \
-        *reinterpret_cast<uint4 *>(vt_ + voff[1]) = s_##3;                                        \
-    }
-    // one iteration's work on tile i in buffer buf; false when the loop ends here
-    auto attend = [&](int i, int buf) -> bool {
-        const Tile t = slab_tile(a, sl, i);
-        if (QL && t.t0 >= wgmax) return false;                          // uniform: no query of the workgroup sees this tile or a later one
-        const int ntile = (t.cend - t.t0 < kAtKv) ? t.cend - t.t0 : kAtKv;
-        slab_tile_attend(Kt + buf * kKtElems, Vt + buf * kVtElems, qa, col, half, ntile, QL && t.t0 + kAtKv > wmin,
-                         qlen - t.t0, scale2, O, m, l);
-        return i + 1 < n;
+    uint4 gk0, gk1, gv0, gv1;                                           // the pieces on their way to LDS
+    auto fetch_k = [&](int i) {
+        const uint16_t *kp = kimg + (int64_t)clampt(i) * kImgElems;
+        gk0 = *reinterpret_cast<const uint4 *>(kp);
+        gk1 = *reinterpret_cast<const uint4 *>(kp + kAtThreads * 8);
     };
-    // tile 0 parked; set a holds tile 1, set b tile 2.  After the work on tile i, tile i + 1 goes from
-    // its set into the other buffer (nobody reads it in this iteration) and the set is refilled
-    // with tile i + 3.  (Parking in the middle of the iteration, between the score contractions
-    // and the soft-max, was slower: 22.5 against 22.1 ms per cfg5 call.)
-    QVG_SLAB_FETCH(pa, 0);
-    QVG_SLAB_PARK(pa, 0);
-    QVG_SLAB_FETCH(pa, 1);
-    QVG_SLAB_FETCH(pb, 2);
-    __syncthreads();
-    for (int i = 0; i < n; i += 2) {
-        if (!attend(i, 0)) break;                                       // uniform
-        QVG_SLAB_PARK(pa, 1);
-        QVG_SLAB_FETCH(pa, i + 3);
+    auto fetch_v = [&](int i) {
+        const uint16_t *vp = vimg + (int64_t)clampt(i) * kImgElems;
+        gv0 = *reinterpret_cast<const uint4 *>(vp);
+        gv1 = *reinterpret_cast<const uint4 *>(vp + kAtThreads * 8);
+    };
+    auto park_k = [&](uint16_t *kt) {
+        *reinterpret_cast<uint4 *>(kt + koff[0]) = gk0;
+        *reinterpret_cast<uint4 *>(kt + koff[1]) = gk1;
+    };
+    auto park_v = [&](uint16_t *vt) {
+        *reinterpret_cast<uint4 *>(vt + voff[0]) = gv0;
+        *reinterpret_cast<uint4 *>(vt + voff[1]) = gv1;
+    };
+    // one piece to its place in `tile`, and the same piece (0 or 1) of tile `next` requested
+    auto park = [&](uint16_t *tile, int off, const uint16_t *img, uint4 &piece, int next, int half_) {
+        *reinterpret_cast<uint4 *>(tile + off) = piece;
+        piece = *reinterpret_cast<const uint4 *>(img + (int64_t)clampt(next) * kImgElems + half_ * kAtThreads * 8);
+    };
+    // the tile whose scores are taken: its first token and the end of its chunk
+    const int nkv = (int)a.n_kv, clen = a.chunk_len < a.n_kv ? (int)a.chunk_len : nkv;
+    int t0 = sl.c0 * clen, cend = nkv - t0 < clen ? nkv : t0 + clen;
+    // scores of the tokens that the tile does not hold or that the lane's query does not see
+    auto mask = [&](floatx16_t (&S)[2]) {                               // true: some were
+        const bool tail = cend - t0 < kAtKv;                            // uniform: last tile of a chunk
+        const bool ends = QL && t0 + kAtKv > wmin;                      // uniform: some query of the wavefront ends here
+        if (tail) slab_mask(S, half, cend - t0);
+        if (ends) slab_mask(S, half, qlen - t0);
+        return tail || ends;
+    };
+    auto next_scores = [&]() {                                          // only while a next tile exists
+        t0 = cend - t0 > kAtKv ? t0 + kAtKv : cend;
+        if (t0 == cend) cend = nkv - t0 < clen ? nkv : t0 + clen;
+    };
+    const uint16_t *krow = Kt + col * kKtPitch + half * 8;
+    const floatx16_t zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    if (ne > 0) {                                                       // uniform
+        fetch_k(0); park_k(Kt);
+        fetch_k(1); park_k(Kt + kKtElems);
+        fetch_k(2); park_k(Kt + 2 * kKtElems);
+        fetch_v(0); park_v(Vt);
         __syncthreads();
-        if (!attend(i + 1, 1)) break;
-        QVG_SLAB_PARK(pb, 0);
-        QVG_SLAB_FETCH(pb, i + 4);
-        __syncthreads();
+        floatx16_t Sa[2], Sb[2];
+        bf16x8_t kf[kAhead];                                            // first fragments of the next tile's scores
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            Sa[i >> 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(slab_kfrag(krow, i), __builtin_bit_cast(bf16x8_t, qa[i & 7]),
+                                                                (i & 7) ? Sa[i >> 3] : zero, 0, 0, 0);
+        mask(Sa);
+        float tmax = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 32; ++e) tmax = fmaxf(tmax, Sa[e >> 4][e & 15]);
+        slab_rescale(slab_new_max(tmax, scale2, m), m, l, O);
+        fetch_v(1);
+        fetch_k(3);
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) kf[i] = slab_kfrag(krow + kKtElems, i);
+        __syncthreads();                                                // tile 3 overwrites K tile 0
+        // offsets of the K buffers: tile i + 1, i + 2, and the one that takes i + 3
+        int kb1 = kKtElems, kb2 = 2 * kKtElems, kb3 = 0;
+        // scores of tile i + 1 into N, probabilities (scores S) and PV of tile i
+        auto step = [&](int i, floatx16_t (&S)[2], floatx16_t (&N)[2], int vb) {
+            next_scores();
+            const uint16_t *kr = krow + kb1, *vt = Vt + vb * kVtElems;
+            float x[32];
+            uint32_t p[16];
+            bf16x8_t kq[16];
+            halfx8_t vq[16];
+            float nmax = -INFINITY, m_new = 0.0f;
+#pragma unroll
+            for (int j = 0; j < kAhead; ++j) kq[j] = kf[j];
+            static_for<0, 16>([&](auto kc) {
+                constexpr int k = decltype(kc)::value;
+                N[k >> 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kq[k], __builtin_bit_cast(bf16x8_t, qa[k & 7]),
+                                                                   (k & 7) ? N[k >> 3] : zero, 0, 0, 0);
+                if constexpr (k + kAhead < 16) kq[k + kAhead] = slab_kfrag(kr, k + kAhead);
+                else vq[k + kAhead - 16] = slab_vfrag(vt, col, half, k + kAhead - 16);
+                slab_probs<k>(S, scale2, m, x, p, l);
+                slab_maxima<k>(N, nmax);
+                // V tile i - 1 and K tile i were last read an iteration ago: i + 1 and i + 3 take their places,
+                // and i + 2 and i + 4 are requested into the registers that become free
+                if constexpr (k == kParkSlot) park(Vt + (vb ^ 1) * kVtElems, voff[0], vimg, gv0, i + 2, 0);
+                if constexpr (k == kParkSlot + 2) park(Vt + (vb ^ 1) * kVtElems, voff[1], vimg, gv1, i + 2, 1);
+                if constexpr (k == kParkSlot + 4) park(Kt + kb3, koff[0], kimg, gk0, i + 4, 0);
+                if constexpr (k == kParkSlot + 6) park(Kt + kb3, koff[1], kimg, gk1, i + 4, 1);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            if (mask(N)) {                                              // uniform
+                nmax = -INFINITY;
+#pragma unroll
+                for (int e = 0; e < maxima_done(15); ++e) nmax = fmaxf(nmax, N[e >> 4][e & 15]);
+            }
+            static_for<16, 32>([&](auto kc) {
+                constexpr int k = decltype(kc)::value;
+                constexpr int st = (k - 16) >> 2, mb = (k - 16) & 3;
+                const uint4 pb = make_uint4(p[4 * st], p[4 * st + 1], p[4 * st + 2], p[4 * st + 3]);
+                O[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vq[k - 16], __builtin_bit_cast(halfx8_t, pb), O[mb], 0, 0, 0);
+                if constexpr (k + kAhead < 32) vq[k + kAhead - 16] = slab_vfrag(vt, col, half, k + kAhead - 16);
+                else kf[k + kAhead - 32] = slab_kfrag(krow + kb2, k + kAhead - 32);
+                slab_probs<k>(S, scale2, m, x, p, l);
+                slab_maxima<k>(N, nmax);
+                if constexpr (k == kMaxSlot) m_new = slab_new_max(nmax, scale2, m);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            slab_rescale(m_new, m, l, O);
+            __syncthreads();
+            const int kt = kb1;
+            kb1 = kb2; kb2 = kb3; kb3 = kt;
+        };
+        // the last tile: probabilities and PV
+        auto finish = [&](floatx16_t (&S)[2], int vb) {
+            const uint16_t *vt = Vt + vb * kVtElems;
+            uint4 pb[4];
+#pragma unroll
+            for (int st = 0; st < 4; ++st) {
+                float x[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(S[st >> 1][(st & 1) * 8 + e], scale2, -m));
+                pb[st] = make_uint4(pack_f16x2_rne(x[0], x[1]), pack_f16x2_rne(x[2], x[3]),
+                                    pack_f16x2_rne(x[4], x[5]), pack_f16x2_rne(x[6], x[7]));
+                l = sum_f16_pairs(pb[st], l);
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                O[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(slab_vfrag(vt, col, half, i),
+                                                                 __builtin_bit_cast(halfx8_t, pb[i >> 2]), O[i & 3], 0, 0, 0);
+        };
+        int i = 0;
+        for (; i + 2 < ne; i += 2) {
+            step(i, Sa, Sb, 0);
+            step(i + 1, Sb, Sa, 1);
+        }
+        if (i + 1 < ne) {
+            step(i, Sa, Sb, 0);
+            finish(Sb, 1);
+        } else {
+            finish(Sa, 0);
+        }
     }
-#undef QVG_SLAB_FETCH
-#undef QVG_SLAB_PARK
     if (sl.last) {
         store_result(a, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
     } else {
@@ -469,8 +574,8 @@ hipError_t launch_attn_slab(const AttnArgs &a, void *ws, size_t ws_bytes, hipStr
 
     static LdsHighWater lds_limit = {};
     static LdsHighWater lds_limit_ql = {};
-    hipError_t e = a.q_len ? ensure_dynamic_lds(reinterpret_cast<const void *>(&attn_slab_kernel<true>), kAtSmem, lds_limit_ql)
-                           : ensure_dynamic_lds(reinterpret_cast<const void *>(&attn_slab_kernel<false>), kAtSmem, lds_limit);
+    hipError_t e = a.q_len ? ensure_dynamic_lds(reinterpret_cast<const void *>(&attn_slab_kernel<true>), kSlabSmem, lds_limit_ql)
+                           : ensure_dynamic_lds(reinterpret_cast<const void *>(&attn_slab_kernel<false>), kSlabSmem, lds_limit);
     if (e != hipSuccess) return e;
     const int64_t nqb = (a.n_q + kAtQPerBlock - 1) / kAtQPerBlock;
     const int64_t nb = nqb * a.H;
@@ -494,8 +599,8 @@ hipError_t launch_attn_slab(const AttnArgs &a, void *ws, size_t ws_bytes, hipStr
         sl.first = c0 == 0;
         sl.last = c1 == a.n_chunks;
         if ((e = launch_slab_decode(a, sl, s)) != hipSuccess) return e;
-        if (a.q_len) hipLaunchKernelGGL(attn_slab_kernel<true>, dim3((unsigned)(bpx * 8)), dim3(kAtThreads), kAtSmem, s, a, sl, (int)nqb, (int)nb, bpx);
-        else hipLaunchKernelGGL(attn_slab_kernel<false>, dim3((unsigned)(bpx * 8)), dim3(kAtThreads), kAtSmem, s, a, sl, (int)nqb, (int)nb, bpx);
+        if (a.q_len) hipLaunchKernelGGL(attn_slab_kernel<true>, dim3((unsigned)(bpx * 8)), dim3(kAtThreads), kSlabSmem, s, a, sl, (int)nqb, (int)nb, bpx);
+        else hipLaunchKernelGGL(attn_slab_kernel<false>, dim3((unsigned)(bpx * 8)), dim3(kAtThreads), kSlabSmem, s, a, sl, (int)nqb, (int)nb, bpx);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
