@@ -300,6 +300,30 @@ int qvg_attn_decode_f32(const qvg_params *p, int64_t n_q, const void *q_bf16,
                         float softmax_scale, float *out_f32, float *lse_out, void *stream);
 
 /*
+ * qvg_attn_decode_causal (out_bf16) or qvg_attn_decode_f32 (out_f32; exactly one of the two is given)
+ * with scratch memory for calls of few query blocks.  Such a call fills a fraction of the chip while
+ * every workgroup walks the whole cache; with scratch of at least qvg_attn_scratch_bytes bytes
+ * (16-byte aligned) the cache's tiles are dealt to several workgroups per query block, and one
+ * more launch joins their partial results (fp32).  How many depends on n_heads, n_q, n_kv_tokens and chunk_len
+ * only, so equal calls give equal bits, with and without `workspace`.  They differ from the undivided
+ * result by the order of fp32 sums and by the maxima that the binary16 probabilities are taken
+ * against.  Without scratch (NULL, 0) or with less, this is the undivided call.
+ */
+int qvg_attn_decode_parts(const qvg_params *p, int64_t n_q, const void *q_bf16,
+                          int64_t n_kv_tokens, int64_t chunk_len, int64_t kv_capacity_tokens,
+                          const void *k_centroids, const uint8_t *k_ids, const uint8_t *k_codes,
+                          const void *k_scales,
+                          const void *v_centroids, const uint8_t *v_ids, const uint8_t *v_codes,
+                          const void *v_scales,
+                          const void *k_rope_f16, const int32_t *q_kv_len,
+                          float softmax_scale, void *out_bf16, float *out_f32, float *lse_out,
+                          void *workspace, size_t workspace_bytes,
+                          void *scratch, size_t scratch_bytes, void *stream);
+
+/* Bytes of scratch that let qvg_attn_decode_parts divide this call; 0 when it would not be divided. */
+int qvg_attn_scratch_bytes(const qvg_params *p, int64_t n_q, int64_t n_kv_tokens, int64_t chunk_len, size_t *out);
+
+/*
  * Merge two attention results over DISJOINT key sets (the compressed cache, from
  * qvg_attn_decode with lse_out, and the current chunk's own bf16 keys, from the model's
  * attention kernel) into the attention over their union (Sec. 3.1):

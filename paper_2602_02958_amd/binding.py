@@ -21,7 +21,7 @@ ENTRY_ENCODE, ENTRY_DECODE, ENTRY_ATTN, ENTRY_KMEANS_UPDATE, ENTRY_KMEANS_ASSIGN
 SCALE_F16, SCALE_E4M3 = 0, 1
 
 EXPORTS = ["qvg_encode_chunk", "qvg_encode_chunk_static", "qvg_decode", "qvg_decode_ex", "qvg_attn_decode", "qvg_attn_decode_ex",
-           "qvg_attn_decode_causal", "qvg_attn_decode_f32", "qvg_attn_merge",
+           "qvg_attn_decode_causal", "qvg_attn_decode_f32", "qvg_attn_decode_parts", "qvg_attn_scratch_bytes", "qvg_attn_merge",
            "qvg_kmeans_assign",
            "qvg_kmeans_update", "qvg_workspace_bytes", "qvg_compressed_bytes",
            "qvg_status_string", "qvg_version"]
@@ -71,6 +71,11 @@ def lib():
         L.qvg_attn_decode_f32.restype = C.c_int
         L.qvg_attn_decode_f32.argtypes = [pp, i64, vp, i64, i64, i64, vp, u8p, u8p, vp, vp, u8p, u8p, vp, vp, vp,
                                           C.c_float, vp, vp, vp]
+        L.qvg_attn_decode_parts.restype = C.c_int
+        L.qvg_attn_decode_parts.argtypes = [pp, i64, vp, i64, i64, i64, vp, u8p, u8p, vp, vp, u8p, u8p, vp, vp, vp,
+                                            C.c_float, vp, vp, vp, vp, C.c_size_t, vp, C.c_size_t, vp]
+        L.qvg_attn_scratch_bytes.restype = C.c_int
+        L.qvg_attn_scratch_bytes.argtypes = [pp, i64, i64, i64, C.POINTER(C.c_size_t)]
         L.qvg_attn_merge.restype = C.c_int
         L.qvg_attn_merge.argtypes = [i64, C.c_int32, vp, vp, vp, vp, vp, vp, vp]
         L.qvg_kmeans_assign.restype = C.c_int
@@ -262,15 +267,46 @@ def attn_workspace(heads: int, n_q: int, chunk_len: int, n_chunks: int, device) 
     return torch.empty(workspace_bytes(p, ENTRY_ATTN, padded, n_q), dtype=torch.uint8, device=device)
 
 
+def _scratch(nbytes: int, device):
+    """Scratch of one call, from torch's allocator on the current stream; None when there is none to be
+    had (the library then takes the form that needs none)."""
+    if nbytes == 0:
+        return None
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
+
+
+# An attn_decode that is lent no workspace takes one for itself when a unit has three query blocks or more:
+# 40 heads over 31997 tokens, 900 queries 2.90 -> 1.10 ms, 12 heads x 600 queries over 20000 195 -> 170 us; with two
+# blocks the one-kernel form is as fast or faster (40 heads x 300 queries over 20000 305 against 418 us).
+TILE_SCRATCH_MIN_QUERIES = 512
+TILE_SCRATCH_BYTES = 256 << 20
+
+
+def _tile_scratch(heads, n_q, chunk_len, n_chunks, device):
+    """The workspace of an attn_decode that was lent none: as many chunks as fit TILE_SCRATCH_BYTES,
+    none when not even one does."""
+    one = heads * -(-chunk_len // 64) * 64 * 512
+    chunks = min(n_chunks, TILE_SCRATCH_BYTES // one)
+    if chunks < 1:
+        return None
+    p = make_params(heads, 2, 128, 1)
+    return _scratch(workspace_bytes(p, ENTRY_ATTN, -(-chunk_len // 64) * 64 * chunks, n_q), device)
+
+
 def attn_decode(q, k: Encoded, v: Encoded, softmax_scale=None, want_lse=False, out=None, n_kv=None,
                 k_rope=None, q_kv_len=None, f32_out=False, workspace=None):
-    """qvg_attn_decode_ex.  q [H, Nq, d] bf16 contiguous -> out bf16 [H, Nq, d] (and lse fp32 [H, Nq]).
+    """qvg_attn_decode_parts.  q [H, Nq, d] bf16 contiguous -> out bf16 [H, Nq, d] (and lse fp32 [H, Nq]).
     n_kv: read only the first n_kv tokens of the caches (they are allocated for more);
     k_rope: [n_kv, d/2, 2] float16 (cos, sin), the rotary embedding of the decoded keys;
-    q_kv_len: [Nq] int32, query i sees the first q_kv_len[i] tokens only (qvg_attn_decode_causal);
-    f32_out: the result as float32, before the rounding to bf16 (qvg_attn_decode_f32);
+    q_kv_len: [Nq] int32, query i sees the first q_kv_len[i] tokens only;
+    f32_out: the result as float32, before the rounding to bf16;
     workspace: uint8 tensor (attn_workspace): every tile is then decoded once per unit into it and
-    shared by all query blocks, a slab of chunks at a time, instead of once per 256 queries."""
+    shared by all query blocks, a slab of chunks at a time, instead of once per 256 queries.  Without
+    one, calls of more than 512 queries take up to 256 MiB for the call from torch's allocator; one
+    that is too small for a chunk (an empty tensor) is ignored."""
     _check(q, torch.bfloat16, "q")
     q = q.contiguous()
     H, Nq, d = q.shape
@@ -304,31 +340,23 @@ def attn_decode(q, k: Encoded, v: Encoded, softmax_scale=None, want_lse=False, o
         _check(out, torch.float32, "out")
         if not out.is_contiguous():
             raise ValueError("out must be contiguous")
-        st = lib().qvg_attn_decode_f32(C.byref(p), Nq, _ptr(q), Nk, k.chunk_len, cap,
-                                       _ptr(k.centroids), _ptr(k.ids), _ptr(k.codes), _ptr(k.scales),
-                                       _ptr(v.centroids), _ptr(v.ids), _ptr(v.codes), _ptr(v.scales),
-                                       _ptr(k_rope), _ptr(q_kv_len), C.c_float(softmax_scale), _ptr(out),
-                                       _ptr(lse), _stream())
-        if st != 0:
-            raise QvgError(st, "qvg_attn_decode_f32")
-        return (out, lse) if want_lse else out
-    if q_kv_len is not None:
-        st = lib().qvg_attn_decode_causal(C.byref(p), Nq, _ptr(q), Nk, k.chunk_len, cap,
-                                          _ptr(k.centroids), _ptr(k.ids), _ptr(k.codes), _ptr(k.scales),
-                                          _ptr(v.centroids), _ptr(v.ids), _ptr(v.codes), _ptr(v.scales),
-                                          _ptr(k_rope), _ptr(q_kv_len), C.c_float(softmax_scale), _ptr(out),
-                                          _ptr(lse), _ptr(workspace), 0 if workspace is None else workspace.numel(),
-                                          _stream())
-        if st != 0:
-            raise QvgError(st, "qvg_attn_decode_causal")
-        return (out, lse) if want_lse else out
-    st = lib().qvg_attn_decode_ex(C.byref(p), Nq, _ptr(q), Nk, k.chunk_len, cap,
-                                  _ptr(k.centroids), _ptr(k.ids), _ptr(k.codes), _ptr(k.scales),
-                                  _ptr(v.centroids), _ptr(v.ids), _ptr(v.codes), _ptr(v.scales),
-                                  _ptr(k_rope), C.c_float(softmax_scale), _ptr(out), _ptr(lse),
-                                  _ptr(workspace), 0 if workspace is None else workspace.numel(), _stream())
+        workspace = None
+    need = C.c_size_t()
+    st = lib().qvg_attn_scratch_bytes(C.byref(p), Nq, Nk, k.chunk_len, C.byref(need))
     if st != 0:
-        raise QvgError(st, "qvg_attn_decode_ex")
+        raise QvgError(st, "qvg_attn_scratch_bytes")
+    scratch = _scratch(need.value, q.device)
+    if workspace is None and Nq > TILE_SCRATCH_MIN_QUERIES:
+        workspace = _tile_scratch(H, Nq, k.chunk_len, -(-Nk // k.chunk_len), q.device)
+    st = lib().qvg_attn_decode_parts(C.byref(p), Nq, _ptr(q), Nk, k.chunk_len, cap,
+                                     _ptr(k.centroids), _ptr(k.ids), _ptr(k.codes), _ptr(k.scales),
+                                     _ptr(v.centroids), _ptr(v.ids), _ptr(v.codes), _ptr(v.scales),
+                                     _ptr(k_rope), _ptr(q_kv_len), C.c_float(softmax_scale),
+                                     None if f32_out else _ptr(out), _ptr(out) if f32_out else None, _ptr(lse),
+                                     _ptr(workspace), 0 if workspace is None else workspace.numel(),
+                                     _ptr(scratch), 0 if scratch is None else scratch.numel(), _stream())
+    if st != 0:
+        raise QvgError(st, "qvg_attn_decode_parts")
     return (out, lse) if want_lse else out
 
 

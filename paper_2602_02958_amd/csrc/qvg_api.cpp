@@ -441,7 +441,7 @@ int attn_call(const qvg_params *p, int64_t n_q, const void *q, int64_t n_kv_toke
               const void *v_centroids, const uint8_t *v_ids, const uint8_t *v_codes,
               const void *v_scales, const void *k_rope, const int32_t *q_kv_len,
               float softmax_scale, void *out, float *out_f32, float *lse_out, void *workspace,
-              size_t workspace_bytes, void *stream) {
+              size_t workspace_bytes, void *scratch, size_t scratch_bytes, void *stream) {
     int st = check_params(p);
     if (st != QVG_OK) return st;
     if (n_q < 0 || n_kv_tokens < 1 || n_kv_tokens > 0x7fffffff || chunk_len < 1) return QVG_ERR_BAD_PARAM;
@@ -477,13 +477,24 @@ int attn_call(const qvg_params *p, int64_t n_q, const void *q, int64_t n_kv_toke
     if (!ids_aligned(p, k_ids) || !ids_aligned(p, v_ids)) return QVG_ERR_ALIGN;
     if (q_kv_len && (reinterpret_cast<uintptr_t>(q_kv_len) & 3u)) return QVG_ERR_ALIGN;
     a.q_len = q_kv_len;
+    a.parts = attn_parts(a.H, n_q, n_kv_tokens, chunk_len);
+    const size_t part_bytes = attn_parts_bytes(a.H, n_q, a.parts);
+    if (a.parts > 1 && scratch && scratch_bytes >= part_bytes) {
+        if (!aligned16(scratch)) return QVG_ERR_ALIGN;
+        a.part_state = static_cast<float *>(scratch);
+    } else {
+        a.parts = 1;                                   // no room for the parts' states: every workgroup walks the whole cache
+    }
+    hipStream_t s = static_cast<hipStream_t>(stream);
     // a workspace that holds at least one chunk's decoded tiles switches to the shared-tile path
     if (workspace && attn_slab_applicable(a, workspace, workspace_bytes)) {
         if (!aligned16(workspace)) return QVG_ERR_ALIGN;
-        return launch_attn_slab(a, workspace, workspace_bytes, static_cast<hipStream_t>(stream)) == hipSuccess
-                   ? QVG_OK : QVG_ERR_LAUNCH;
+        if (launch_attn_slab(a, workspace, workspace_bytes, s) != hipSuccess) return QVG_ERR_LAUNCH;
+    } else if (launch_attn(a, s) != hipSuccess) {
+        return QVG_ERR_LAUNCH;
     }
-    return launch_attn(a, static_cast<hipStream_t>(stream)) == hipSuccess ? QVG_OK : QVG_ERR_LAUNCH;
+    if (a.parts > 1 && launch_attn_join(a, s) != hipSuccess) return QVG_ERR_LAUNCH;
+    return QVG_OK;
 }
 }  // namespace
 
@@ -498,7 +509,29 @@ int qvg_attn_decode_causal(const qvg_params *p, int64_t n_q, const void *q, int6
                            size_t workspace_bytes, void *stream) {
     return attn_call(p, n_q, q, n_kv_tokens, chunk_len, kv_capacity_tokens, k_centroids, k_ids, k_codes, k_scales,
                      v_centroids, v_ids, v_codes, v_scales, k_rope, q_kv_len, softmax_scale, out, nullptr, lse_out,
-                     workspace, workspace_bytes, stream);
+                     workspace, workspace_bytes, nullptr, 0, stream);
+}
+
+int qvg_attn_scratch_bytes(const qvg_params *p, int64_t n_q, int64_t n_kv_tokens, int64_t chunk_len, size_t *out) {
+    int st = check_params(p);
+    if (st != QVG_OK) return st;
+    if (!out) return QVG_ERR_NULL;
+    if (n_q < 0 || n_kv_tokens < 1 || n_kv_tokens > 0x7fffffff || chunk_len < 1) return QVG_ERR_BAD_PARAM;
+    *out = attn_parts_bytes(p->n_heads, n_q, attn_parts(p->n_heads, n_q, n_kv_tokens, chunk_len));
+    return QVG_OK;
+}
+
+int qvg_attn_decode_parts(const qvg_params *p, int64_t n_q, const void *q, int64_t n_kv_tokens,
+                          int64_t chunk_len, int64_t kv_capacity_tokens, const void *k_centroids,
+                          const uint8_t *k_ids, const uint8_t *k_codes, const void *k_scales,
+                          const void *v_centroids, const uint8_t *v_ids, const uint8_t *v_codes,
+                          const void *v_scales, const void *k_rope, const int32_t *q_kv_len,
+                          float softmax_scale, void *out_bf16, float *out_f32, float *lse_out, void *workspace,
+                          size_t workspace_bytes, void *scratch, size_t scratch_bytes, void *stream) {
+    if (out_bf16 && out_f32) return QVG_ERR_BAD_PARAM;
+    return attn_call(p, n_q, q, n_kv_tokens, chunk_len, kv_capacity_tokens, k_centroids, k_ids, k_codes, k_scales,
+                     v_centroids, v_ids, v_codes, v_scales, k_rope, q_kv_len, softmax_scale, out_bf16, out_f32, lse_out,
+                     workspace, workspace_bytes, scratch, scratch_bytes, stream);
 }
 
 int qvg_attn_decode_f32(const qvg_params *p, int64_t n_q, const void *q, int64_t n_kv_tokens,
@@ -509,7 +542,7 @@ int qvg_attn_decode_f32(const qvg_params *p, int64_t n_q, const void *q, int64_t
                         float softmax_scale, float *out_f32, float *lse_out, void *stream) {
     return attn_call(p, n_q, q, n_kv_tokens, chunk_len, kv_capacity_tokens, k_centroids, k_ids, k_codes, k_scales,
                      v_centroids, v_ids, v_codes, v_scales, k_rope, q_kv_len, softmax_scale, nullptr, out_f32, lse_out,
-                     nullptr, 0, stream);
+                     nullptr, 0, nullptr, 0, stream);
 }
 
 }  // extern "C"

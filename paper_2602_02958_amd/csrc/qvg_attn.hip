@@ -51,8 +51,9 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     // (as in the staged kernel below; the grid is padded to a multiple of 8)
     const int w = (int)(blockIdx.x % 8u) * blocks_per_xcd + (int)(blockIdx.x / 8u);
     if (w >= n_blocks) return;                                          // uniform, before any barrier
-    const int h = w / n_qblocks;
-    const int qblock = w - h * n_qblocks;
+    const int h = w / (n_qblocks * a.parts);
+    const int qblock = (w - h * n_qblocks * a.parts) / a.parts;
+    const int part = w % a.parts;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
@@ -62,7 +63,7 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     // query sees tokens 0 .. qlen-1; wmin = the shortest prefix in the wavefront (tiles below it
     // need no mask); the workgroup walks the cache only up to its longest prefix.
     int qlen = 0x7fffffff, wmin = 0x7fffffff;
-    Span sp = span_of(a);
+    Span sp = span_of(a, part);
     if (QL) {
         __shared__ int bmax;
         if (tid == 0) bmax = 1;
@@ -149,6 +150,10 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
 
     // ---- prologue: tile 0 into buffer 0, raw data of tile 1 in flight -------------------
     Tile cur = first_tile(sp);
+    if (!cur.valid) {                // uniform: a part that lies behind the longest prefix
+        if (qvalid) store_state(part_state_of(a, n_qblocks, h, qblock, part), O, m, l);
+        return;
+    }
     Tile nxt = next_tile(sp, cur);
     Tile nn = nxt.valid ? next_tile(sp, nxt) : nxt;
     uint32_t idk[2], idv[2];
@@ -288,7 +293,8 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
         nn = nn.valid ? next_tile(sp, nn) : nn;
     }
     // ---- normalise and store: lane holds channels 32*mb + 8*g + 4*half + 0..3 of its query ----
-    store_result(a, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
+    if (a.parts > 1) { if (qvalid) store_state(part_state_of(a, n_qblocks, h, qblock, part), O, m, l); }
+    else store_result(a, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
 }
 
 
@@ -331,8 +337,9 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     // cache is fetched into that XCD's L2 only, not into all eight.
     const int w = (int)(blockIdx.x % 8u) * blocks_per_xcd + (int)(blockIdx.x / 8u);
     if (w >= n_blocks) return;                                          // uniform, before any barrier
-    const int h = w / n_qblocks;
-    const int qblock = w - h * n_qblocks;
+    const int h = w / (n_qblocks * a.parts);
+    const int qblock = (w - h * n_qblocks * a.parts) / a.parts;
+    const int part = w % a.parts;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);          // uniform: lets whole waves branch
@@ -530,7 +537,7 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     // QL: the lane's query sees tokens 0 .. qlen-1; wmin = the shortest prefix in the wavefront
     // (tiles below it need no mask); the workgroup walks the cache up to its longest prefix only
     int qlen = 0x7fffffff, wmin = 0x7fffffff;
-    Span sp = span_of(a);
+    Span sp = span_of(a, part);
     if (QL) {
         __shared__ int bmax;
         if (tid == 0) bmax = 1;
@@ -551,6 +558,10 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
         wmin = __builtin_amdgcn_readfirstlane(wmin);
     }
     Tile cur = first_tile(sp);
+    if (!cur.valid) {                // uniform: a part that lies behind the longest prefix
+        if (qvalid) store_state(part_state_of(a, n_qblocks, h, qblock, part), O, m, l);
+        return;
+    }
     Tile nxt = next_tile(sp, cur);
     Tile nn = nxt.valid ? next_tile(sp, nxt) : nxt;
     Tile n3 = nn.valid ? next_tile(sp, nn) : nn;
@@ -718,7 +729,8 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
         while (is_full(cur) && is_full(nxt) && is_full(nn)) tile_step(BoolC<true>{}, decode_first);
         if (!tile_step(BoolC<false>{}, false)) break;
     }
-    store_result(a, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
+    if (a.parts > 1) { if (qvalid) store_state(part_state_of(a, n_qblocks, h, qblock, part), O, m, l); }
+    else store_result(a, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
 }
 
 template <int T_, bool ROPE, bool FP8, bool I4, bool WIDE, bool QL = false>
@@ -728,7 +740,7 @@ static hipError_t launch_attn_staged_r(const AttnArgs &a, hipStream_t s) {
     hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&attn_kernel_staged<T_, ROPE, FP8, I4, WIDE, QL>), kSmem, lds_limit);
     if (e != hipSuccess) return e;
     const int64_t nqb = (a.n_q + kAtQPerBlock - 1) / kAtQPerBlock;
-    const int64_t nb = nqb * a.H;
+    const int64_t nb = nqb * a.H * a.parts;
     if (nb > 0x7fffffff - 8) return hipErrorInvalidValue;
     const int bpx = (int)((nb + 7) / 8);
     // the grid is padded to a multiple of 8 (one share per XCD): at most 7 surplus workgroups, whose
@@ -749,7 +761,7 @@ static hipError_t launch_attn_tr(const AttnArgs &a, hipStream_t s) {
     hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&attn_kernel_direct<T_, SM, FMT, ROPE, QL>), kAtSmem, lds_limit);
     if (e != hipSuccess) return e;
     const int64_t nqb = (a.n_q + kAtQPerBlock - 1) / kAtQPerBlock;
-    const int64_t nb = nqb * a.H;
+    const int64_t nb = nqb * a.H * a.parts;
     if (nb > 0x7fffffff - 8) return hipErrorInvalidValue;
     const int bpx = (int)((nb + 7) / 8);
     if ((int64_t)bpx * 8 > nb + 7) return hipErrorInvalidValue;        // at most 7 surplus workgroups, which return at once
@@ -867,6 +879,85 @@ hipError_t launch_attn(const AttnArgs &a, hipStream_t s) {
         case 3: return launch_attn_staged<3>(a, s);
         default: return launch_attn_staged<4>(a, s);
     }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Parts.  A call of few query blocks leaves most of the 256 CUs idle while each workgroup walks the
+// whole cache, 1.5-2.5 us a tile.  Its tiles are dealt out (tile g to part g % parts, so that every slab
+// of the shared-tile form and every prefix is spread evenly) until the chip is full once, with at
+// least four tiles to a part: fewer do not repay the part's start and its 132 KB of state.  64 queries
+// of one head over 4096 tokens 160 -> 33 us (34, 36, 44, 72 us with 4, 8, 2, 1 tiles at least); 12 heads x
+// 1560 queries over 31997 tokens 795 -> 440 us; twice the chip's worth of parts is 5 % slower there.
+// From 129 query blocks on nothing is dealt: 160 blocks in three parts gain nothing (1.09 against 1.08 ms).
+// ---------------------------------------------------------------------------------------------
+constexpr int kCus = 256;
+constexpr int kPartMinTiles = 4;
+int attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len) {
+    if (n_q < 1 || n_kv < 1) return 1;
+    const int64_t nb = (n_q + kAtQPerBlock - 1) / kAtQPerBlock * H;
+    const int64_t full = n_kv / chunk_len, rest = n_kv - full * chunk_len;
+    const int64_t tiles = full * ((chunk_len + kAtKv - 1) / kAtKv) + (rest + kAtKv - 1) / kAtKv;
+    const int64_t parts = kCus / nb < tiles / kPartMinTiles ? kCus / nb : tiles / kPartMinTiles;
+    return parts > 1 ? (int)parts : 1;
+}
+size_t attn_parts_bytes(int H, int64_t n_q, int parts) {
+    const int64_t nqb = (n_q + kAtQPerBlock - 1) / kAtQPerBlock;
+    return parts > 1 ? (size_t)parts * nqb * H * kStateFloats * kAtThreads * sizeof(float) : 0;
+}
+
+// The result of a query from the states of its parts: one workgroup per query block and 32 channels,
+// threads as in the kernels that left the states.  A part whose first tile lies behind the query's
+// prefix saw none of its tokens and is left out (its sums may be anything).
+__global__ __launch_bounds__(kAtThreads)
+void attn_join_kernel(AttnArgs a, int n_qblocks) {
+    const int h = (int)(blockIdx.x / (unsigned)n_qblocks), qblock = (int)(blockIdx.x - (unsigned)h * n_qblocks), mb = blockIdx.y;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, half = lane >> 5;
+    const int64_t qrow = (int64_t)qblock * kAtQPerBlock + wave * 32 + col;
+    const bool qvalid = qrow < a.n_q;
+    int seen = 0;                                                        // parts that saw a token: the first ones
+    if (qvalid) {
+        int64_t qlen = a.n_kv;
+        if (a.q_len) { const int64_t v = a.q_len[qrow]; qlen = v < 0 ? 0 : (v > a.n_kv ? a.n_kv : v); }
+        for (Span sp = span_of(a, 0); seen < a.parts; ++seen) {
+            sp.part = seen;
+            const Tile t = first_tile(sp);
+            if (!t.valid || t.t0 >= qlen) break;
+        }
+    }
+    float m = -INFINITY, l = 0.0f, o[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[r] = 0.0f;
+    for (int part = 0; part < seen; ++part) m = fmaxf(m, part_state_of(a, n_qblocks, h, qblock, part)[64 * kAtThreads]);
+    for (int part = 0; part < seen; ++part) {
+        const float *st = part_state_of(a, n_qblocks, h, qblock, part);
+        const float wgt = __builtin_amdgcn_exp2f(st[64 * kAtThreads] - m);
+        l = __builtin_fmaf(wgt, st[65 * kAtThreads], l);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[r] = __builtin_fmaf(wgt, st[(mb * 16 + r) * kAtThreads], o[r]);
+    }
+    const float ltot = l + __shfl_xor(l, 32, 64);
+    if (!qvalid) return;
+    const bool any = seen > 0;
+    const float inv = any ? 1.0f / ltot : 0.0f;
+    const int64_t at = ((int64_t)h * a.n_q + qrow) * kHeadDim + half * 4 + mb * 32;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        if (a.out_f32)
+            *reinterpret_cast<float4 *>(a.out_f32 + at + g * 8) =
+                make_float4(o[4 * g] * inv, o[4 * g + 1] * inv, o[4 * g + 2] * inv, o[4 * g + 3] * inv);
+        else
+            *reinterpret_cast<uint2 *>(a.out + at + g * 8) = make_uint2(pack_bf16x2(o[4 * g] * inv, o[4 * g + 1] * inv),
+                                                                        pack_bf16x2(o[4 * g + 2] * inv, o[4 * g + 3] * inv));
+    }
+    if (a.lse && half == 0 && mb == 0)
+        a.lse[(int64_t)h * a.n_q + qrow] = any ? (m + __builtin_log2f(ltot)) * 0.6931471805599453f : -INFINITY;
+}
+
+hipError_t launch_attn_join(const AttnArgs &a, hipStream_t s) {
+    const int64_t nqb = (a.n_q + kAtQPerBlock - 1) / kAtQPerBlock;
+    if (nqb * a.H > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(attn_join_kernel, dim3((unsigned)(nqb * a.H), 4), dim3(kAtThreads), 0, s, a, (int)nqb);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------------

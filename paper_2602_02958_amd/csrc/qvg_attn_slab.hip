@@ -20,7 +20,6 @@
 namespace qvg {
 
 constexpr int kImgElems = kAtKv * kHeadDim;             // 16-bit elements of one operand image (16 KB)
-constexpr int kStateFloats = 66;                        // per thread: 64 output values, maximum, normaliser
 
 struct SlabArgs {
     uint16_t *kimg, *vimg;     // [H][tiles_cap][kImgElems]
@@ -28,7 +27,7 @@ struct SlabArgs {
     int c0;                    // first chunk of the slab
     int n_tiles;               // tiles of the slab (every one holds at least one token)
     int tpc;                   // tiles per chunk = ceil(chunk_len / 64)
-    float *state;              // [workgroup][kStateFloats][512] running state, or nullptr (single slab)
+    float *state;              // [workgroup][kStateFloats][512] running state, or nullptr (single slab, or several parts: AttnArgs)
     int first, last;           // first / last slab of the call
 };
 
@@ -263,7 +262,8 @@ __device__ __forceinline__ void slab_rescale(float m_new, float &m, float &l, fl
 // QL: a prefix length per query (a.q_len): scores beyond the lane's prefix are masked in the tiles
 // at or past the shortest prefix of the wavefront, and the workgroup stops at the longest prefix
 // among its 256 queries.
-template <bool QL>
+// PARTS: the tiles are dealt to several workgroups per query block (a.parts).
+template <bool QL, bool PARTS>
 __global__ __launch_bounds__(kAtThreads, 2)
 void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int blocks_per_xcd) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -273,8 +273,10 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
     // the query blocks of one unit run on one XCD, whose L2 then serves the unit's images to all of them
     const int w = (int)(blockIdx.x % 8u) * blocks_per_xcd + (int)(blockIdx.x / 8u);
     if (w >= n_blocks) return;                                          // uniform, before any barrier
-    const int h = w / n_qblocks;
-    const int qblock = w - h * n_qblocks;
+    const int parts = PARTS ? a.parts : 1;
+    const int h = w / (n_qblocks * parts);
+    const int qblock = (w - h * n_qblocks * parts) / parts;
+    const int part = PARTS ? w % parts : 0;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
@@ -290,7 +292,8 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
     }
     floatx16_t O[4];
     float m = -INFINITY, l = 0.0f;
-    float *st = sl.state ? sl.state + (int64_t)w * kStateFloats * kAtThreads + tid : nullptr;
+    float *st = PARTS ? part_state_of(a, n_qblocks, h, qblock, part)
+                            : sl.state ? sl.state + (int64_t)w * kStateFloats * kAtThreads + tid : nullptr;
     if (sl.first) {
 #pragma unroll
         for (int mb = 0; mb < 4; ++mb)
@@ -343,7 +346,11 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
         const int64_t e = rel <= 0 ? 0 : full * sl.tpc + (rel - full * a.chunk_len + kAtKv - 1) / kAtKv;
         ne = e < n ? (int)e : n;
     }
-    auto clampt = [&](int i) { return i < n ? i : n - 1; };            // past the end: the last tile once more (never used)
+    // this part's share of them: tiles i0, i0 + parts, ... of the slab (part g % parts has tile g of the cache)
+    const int i0 = !PARTS ? 0 : (int)(((int64_t)part + parts - (int64_t)sl.c0 * sl.tpc % parts) % parts);
+    const int count = i0 < ne ? (ne - i0 + parts - 1) / parts : 0;
+    // the slab's index of the part's j-th tile; past the end: the last tile (never used)
+    auto clampt = [&](int j) { return j < count ? i0 + j * parts : n - 1; };
     uint4 gk0, gk1, gv0, gv1;                                           // the pieces on their way to LDS
     auto fetch_k = [&](int i) {
         const uint16_t *kp = kimg + (int64_t)clampt(i) * kImgElems;
@@ -370,7 +377,13 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
     };
     // the tile whose scores are taken: its first token and the end of its chunk
     const int nkv = (int)a.n_kv, clen = a.chunk_len < a.n_kv ? (int)a.chunk_len : nkv;
-    int t0 = sl.c0 * clen, cend = nkv - t0 < clen ? nkv : t0 + clen;
+    int tb = sl.c0 * clen, ti = i0;                                     // its chunk's first token, its place in the chunk
+    int t0, cend;
+    auto place = [&]() {
+        if (ti >= sl.tpc) { const int c = ti / sl.tpc; tb += c * clen; ti -= c * sl.tpc; }
+        t0 = tb + ti * kAtKv;
+        cend = nkv - tb < clen ? nkv : tb + clen;
+    };
     // scores of the tokens that the tile does not hold or that the lane's query does not see
     auto mask = [&](floatx16_t (&S)[2]) {                               // true: some were
         const bool tail = cend - t0 < kAtKv;                            // uniform: last tile of a chunk
@@ -379,13 +392,10 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
         if (ends) slab_mask(S, half, qlen - t0);
         return tail || ends;
     };
-    auto next_scores = [&]() {                                          // only while a next tile exists
-        t0 = cend - t0 > kAtKv ? t0 + kAtKv : cend;
-        if (t0 == cend) cend = nkv - t0 < clen ? nkv : t0 + clen;
-    };
     const uint16_t *krow = Kt + col * kKtPitch + half * 8;
     const floatx16_t zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    if (ne > 0) {                                                       // uniform
+    if (count > 0) {                                                    // uniform
+        place();
         fetch_k(0); park_k(Kt);
         fetch_k(1); park_k(Kt + kKtElems);
         fetch_k(2); park_k(Kt + 2 * kKtElems);
@@ -411,7 +421,8 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
         int kb1 = kKtElems, kb2 = 2 * kKtElems, kb3 = 0;
         // scores of tile i + 1 into N, probabilities (scores S) and PV of tile i
         auto step = [&](int i, floatx16_t (&S)[2], floatx16_t (&N)[2], int vb) {
-            next_scores();
+            ti += parts;
+            place();
             const uint16_t *kr = krow + kb1, *vt = Vt + vb * kVtElems;
             float x[32];
             uint32_t p[16];
@@ -477,27 +488,19 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
                                                                  __builtin_bit_cast(halfx8_t, pb[i >> 2]), O[i & 3], 0, 0, 0);
         };
         int i = 0;
-        for (; i + 2 < ne; i += 2) {
+        for (; i + 2 < count; i += 2) {
             step(i, Sa, Sb, 0);
             step(i + 1, Sb, Sa, 1);
         }
-        if (i + 1 < ne) {
+        if (i + 1 < count) {
             step(i, Sa, Sb, 0);
             finish(Sb, 1);
         } else {
             finish(Sa, 0);
         }
     }
-    if (sl.last) {
-        store_result(a, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
-    } else {
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) st[(mb * 16 + r) * kAtThreads] = O[mb][r];
-        st[64 * kAtThreads] = m;
-        st[65 * kAtThreads] = l;
-    }
+    if (sl.last && !PARTS) store_result(a, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
+    else store_state(st, O, m, l);
 }
 
 // ---- host side ---------------------------------------------------------------------------------
@@ -572,20 +575,22 @@ hipError_t launch_attn_slab(const AttnArgs &a, void *ws, size_t ws_bytes, hipStr
     if (slab_chunks < 1 || tpc * slab_chunks > 0x7fffffff) return hipErrorInvalidValue;
     if (slab_chunks > a.n_chunks) slab_chunks = a.n_chunks;
 
-    static LdsHighWater lds_limit = {};
-    static LdsHighWater lds_limit_ql = {};
-    hipError_t e = a.q_len ? ensure_dynamic_lds(reinterpret_cast<const void *>(&attn_slab_kernel<true>), kSlabSmem, lds_limit_ql)
-                           : ensure_dynamic_lds(reinterpret_cast<const void *>(&attn_slab_kernel<false>), kSlabSmem, lds_limit);
+    const int form = (a.q_len ? 1 : 0) + (a.parts > 1 ? 2 : 0);
+    typedef void (*slab_kernel_t)(AttnArgs, SlabArgs, int, int, int);
+    static const slab_kernel_t kernels[4] = {attn_slab_kernel<false, false>, attn_slab_kernel<true, false>,
+                                             attn_slab_kernel<false, true>, attn_slab_kernel<true, true>};
+    static LdsHighWater lds_limit[4] = {};
+    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kernels[form]), kSlabSmem, lds_limit[form]);
     if (e != hipSuccess) return e;
     const int64_t nqb = (a.n_q + kAtQPerBlock - 1) / kAtQPerBlock;
-    const int64_t nb = nqb * a.H;
+    const int64_t nb = nqb * a.H * a.parts;
     if (nb > 0x7fffffff - 8) return hipErrorInvalidValue;
     const int bpx = (int)((nb + 7) / 8);
     if ((int64_t)bpx * 8 > nb + 7) return hipErrorInvalidValue;        // at most 7 surplus workgroups, which return at once
 
     SlabArgs sl{};
     unsigned char *base = static_cast<unsigned char *>(ws);
-    sl.state = single ? nullptr : reinterpret_cast<float *>(base);
+    sl.state = single ? nullptr : reinterpret_cast<float *>(base);      // not used by several parts
     sl.tiles_cap = tpc * slab_chunks;
     sl.kimg = reinterpret_cast<uint16_t *>(base + state);
     sl.vimg = sl.kimg + (size_t)a.H * sl.tiles_cap * kImgElems;
@@ -599,8 +604,7 @@ hipError_t launch_attn_slab(const AttnArgs &a, void *ws, size_t ws_bytes, hipStr
         sl.first = c0 == 0;
         sl.last = c1 == a.n_chunks;
         if ((e = launch_slab_decode(a, sl, s)) != hipSuccess) return e;
-        if (a.q_len) hipLaunchKernelGGL(attn_slab_kernel<true>, dim3((unsigned)(bpx * 8)), dim3(kAtThreads), kSlabSmem, s, a, sl, (int)nqb, (int)nb, bpx);
-        else hipLaunchKernelGGL(attn_slab_kernel<false>, dim3((unsigned)(bpx * 8)), dim3(kAtThreads), kSlabSmem, s, a, sl, (int)nqb, (int)nb, bpx);
+        hipLaunchKernelGGL(kernels[form], dim3((unsigned)(bpx * 8)), dim3(kAtThreads), kSlabSmem, s, a, sl, (int)nqb, (int)nb, bpx);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;

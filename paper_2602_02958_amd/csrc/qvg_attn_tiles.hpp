@@ -36,33 +36,56 @@ struct CacheSide {                 // one of K / V, already offset to this unit
 };
 
 struct Tile {                      // one 64-token tile; tiles never straddle a chunk
-    int chunk; int t0, cend; bool valid;     // token indices fit 31 bits (checked by the caller)
+    int chunk, ti; int t0, cend; bool valid; // ti-th tile of its chunk; token indices fit 31 bits (checked by the caller)
 };
 
-struct Span {                      // the part of the cache a workgroup walks
+struct Span {                      // the part of the cache a workgroup walks: tiles part, part + parts, ...
     int64_t chunk_len, n_kv; int n_chunks;
+    int tpc, part, parts;          // tpc: tiles per chunk = ceil(chunk_len / 64)
 };
-__device__ __forceinline__ Span span_of(const AttnArgs &a) {
+__device__ __forceinline__ Span span_of(const AttnArgs &a, int part) {
     Span s; s.chunk_len = a.chunk_len; s.n_kv = a.n_kv; s.n_chunks = a.n_chunks;
+    const int64_t l = a.chunk_len < a.n_kv ? a.chunk_len : a.n_kv;
+    s.tpc = (int)((l + kAtKv - 1) / kAtKv); s.part = part; s.parts = a.parts;
     return s;
+}
+// Where (t.chunk, t.ti) is once t.ti may have run past its chunk
+__device__ __forceinline__ Tile place_tile(const Span &a, Tile t) {
+    if (t.ti >= a.tpc) { const int c = t.ti / a.tpc; t.chunk += c; t.ti -= c * a.tpc; }
+    t.valid = t.chunk < a.n_chunks;
+    if (t.valid) {
+        const int64_t b = (int64_t)t.chunk * a.chunk_len;
+        t.t0 = (int)(b + (int64_t)t.ti * kAtKv);
+        t.cend = (int)((b + a.chunk_len < a.n_kv) ? b + a.chunk_len : a.n_kv);
+        t.valid = t.t0 < t.cend;
+    }
+    if (!t.valid) { t.chunk = a.n_chunks - 1; t.t0 = 0; t.cend = 0; }
+    return t;
 }
 __device__ __forceinline__ Tile first_tile(const Span &a) {
     Tile t;
-    t.chunk = 0; t.t0 = 0; t.cend = (int)(a.chunk_len < a.n_kv ? a.chunk_len : a.n_kv); t.valid = true;
-    return t;
+    t.chunk = 0; t.ti = a.part; t.t0 = 0; t.cend = 0;
+    return place_tile(a, t);
 }
 __device__ __forceinline__ Tile next_tile(const Span &a, Tile t) {
-    t.t0 += kAtKv;
-    if (t.t0 >= t.cend) {
-        t.chunk += 1;
-        if (t.chunk >= a.n_chunks) { t.valid = false; t.chunk = a.n_chunks - 1; }
-        else {
-            const int64_t b = (int64_t)t.chunk * a.chunk_len;
-            t.t0 = (int)b;
-            t.cend = (int)((b + a.chunk_len < a.n_kv) ? b + a.chunk_len : a.n_kv);
-        }
-    }
-    return t;
+    t.ti += a.parts;
+    return place_tile(a, t);
+}
+
+// Running state of a workgroup's 256 queries, [kStateFloats][512] floats: per thread its 64 output
+// values (unnormalised), the maximum and the lane's share of the normaliser.
+constexpr int kStateFloats = 66;
+__device__ __forceinline__ void store_state(float *st, const floatx16_t (&O)[4], float m, float l) {
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) st[(mb * 16 + r) * kAtThreads] = O[mb][r];
+    st[64 * kAtThreads] = m;
+    st[65 * kAtThreads] = l;
+}
+// the state of query block `qblock` of unit h as part `part` leaves it
+__device__ __forceinline__ float *part_state_of(const AttnArgs &a, int n_qblocks, int h, int qblock, int part) {
+    return a.part_state + (((int64_t)part * a.H + h) * n_qblocks + qblock) * kStateFloats * kAtThreads + threadIdx.x;
 }
 
 // Normalise and store one query's result: the lane holds channels 32*mb + 8*g + 4*half + 0..3 of its

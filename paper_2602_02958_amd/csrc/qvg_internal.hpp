@@ -250,8 +250,14 @@ struct AttnArgs {
     int id_wide;           // ids are 16-bit words (K > 256)
     const int32_t *q_len;  // [n_q] prefix length per query (clamped to 0 .. n_kv), or nullptr: all n_kv tokens
     float *out_f32;        // when set, the result goes here as fp32 [H][n_q][d] (not rounded to bf16) and `out` is not written
+    int parts;             // the cache's tiles are dealt to this many workgroups per query block (tile g to part g % parts);
+    float *part_state;     // with more than one, each leaves its running state here and launch_attn_join makes the result
 };
 hipError_t launch_attn(const AttnArgs &a, hipStream_t s);
+// parts for a call of these sizes, and the bytes of their state (0 for a single part)
+int attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len);
+size_t attn_parts_bytes(int H, int64_t n_q, int parts);
+hipError_t launch_attn_join(const AttnArgs &a, hipStream_t s);
 // The same attention with every tile decoded once per unit into a caller-lent workspace and shared
 // by all query blocks (qvg_attn_slab.hip).  Workspace = running state of the queries (only when the
 // cache needs more than one slab) + the operand images of a slab of whole chunks.

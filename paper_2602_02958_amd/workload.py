@@ -109,7 +109,7 @@ def step_decode(s: Streaming):
 
 
 def step_attn(s: Streaming, shared_tiles=True):
-    B.attn_decode(s.q, s.k, s.v, out=s.attn_out, workspace=s.attn_ws if shared_tiles else None)
+    B.attn_decode(s.q, s.k, s.v, out=s.attn_out, workspace=s.attn_ws if shared_tiles else torch.empty(0, dtype=torch.uint8, device=s.q.device))
 
 
 def step(s: Streaming):

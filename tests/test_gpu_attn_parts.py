@@ -1,0 +1,89 @@
+"""Attention of few query blocks: the cache's tiles are dealt to several workgroups per query block and
+their partial results joined.  Against the oracle at the existing bound, at sizes where the deal is
+ragged (a last part with fewer tiles, chunks of one tile, parts that lie behind every prefix);
+equal bits with a tile workspace, without one and in the fp32 result; NaN stays in its row."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import qvg_oracle as O
+from paper_2602_02958_amd import binding as B
+from paper_2602_02958_amd import synth
+from paper_2602_02958_amd.configs import CONFIGS
+from conftest import bf16_bits
+import parity_util as P
+from test_gpu_attn_integration import _filled_caches, _rope_table, _check_against_oracle
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _scratch_bytes(H, Nq, n_kv, L):
+    need = B.C.c_size_t()
+    p = B.make_params(H, 16, 64, 1)
+    assert B.lib().qvg_attn_scratch_bytes(B.C.byref(p), Nq, n_kv, L, B.C.byref(need)) == 0
+    return need.value
+
+
+@pytest.mark.parametrize("H,Nq,L,chunks,n_kv,T,Bg,S,bits,fmt,K", [
+    (1, 1, 520, 1, 511, 2, 64, 1, 2, B.SCALE_F16, 16),       # eight tiles, two parts, the last tile one short
+    (1, 64, 520, 3, 1173, 3, 32, 1, 2, B.SCALE_F16, 64),     # staged kernel, chunks of 8 tiles + 8 tokens
+    (2, 33, 516, 2, 1000, 2, 64, 1, 2, B.SCALE_F16, 16),     # general kernel
+    (3, 256, 40, 20, 793, 2, 64, 1, 2, B.SCALE_F16, 16),     # chunks of one short tile
+    (2, 70, 520, 2, 1040, 1, 16, 4, 2, B.SCALE_E4M3, 64),    # four smoothing stages
+    (1, 300, 520, 2, 1033, 1, 64, 1, 4, B.SCALE_E4M3, 64),   # two query blocks
+    (1, 520, 200, 5, 933, 5, 128, 1, 2, B.SCALE_F16, 16),    # three query blocks: a tile workspace by default
+    (2, 300, 136, 6, 816, 1, 64, 1, 2, B.SCALE_E4M3, 300),   # 16-bit ids
+])
+def test_parts_against_the_oracle(H, Nq, L, chunks, n_kv, T, Bg, S, bits, fmt, K):
+    assert _scratch_bytes(H, Nq, n_kv, L) > 0
+    kc, vc = _filled_caches(H, L, chunks, min(n_kv + 5, L * chunks), K, Bg, T, S=S, bits=bits, fmt=fmt)
+    q = synth.queries(CONFIGS["cfg2_window21"], H, Nq, DEV)
+    khat, vhat = B.decode(kc), B.decode(vc)
+    g = torch.Generator().manual_seed(3)
+    lens = torch.randint(-2, n_kv + 3, (Nq,), generator=g)
+    lens[:min(Nq, 34)] = 65                          # a wavefront (and a query block of 33) that ends in the second tile
+    lens[0] = 0
+    none = torch.empty(0, dtype=torch.uint8, device=DEV)             # lent, too small: one kernel
+    rope = _rope_table(n_kv).to(DEV)
+    for ql, table in ((None, None), (lens.to(torch.int32).to(DEV), None), (None, rope)):
+        kw = dict(n_kv=n_kv, q_kv_len=ql, k_rope=table)
+        out, lse = B.attn_decode(q, kc, vc, want_lse=True, **kw)
+        one, lse1 = B.attn_decode(q, kc, vc, want_lse=True, workspace=none, **kw)
+        ws = B.attn_workspace(H, Nq, L, 1, DEV)
+        slab, lses = B.attn_decode(q, kc, vc, want_lse=True, workspace=ws, **kw)
+        f32 = B.attn_decode(q, kc, vc, f32_out=True, **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(out, one) and torch.equal(lse, lse1)
+        assert torch.equal(out, slab) and torch.equal(lse, lses)
+        assert torch.equal(f32.to(torch.bfloat16), out)
+        eff = (lens.clamp(0, n_kv) if ql is not None else torch.full((Nq,), n_kv)).numpy()
+        for h in range(H):
+            kb, vb = P.to_np_u16(khat[h, :n_kv]), P.to_np_u16(vhat[h, :n_kv])
+            if table is not None:
+                kb = O.rope_keys(kb, rope.cpu().view(torch.int16).numpy().view(np.uint16))
+            if ql is None:
+                _check_against_oracle(q, out, lse, kb, vb, h)
+                continue
+            for i in sorted({0, 1 % Nq, 33 % Nq, Nq // 2, Nq - 1, int(eff.argmax()), int(eff.argmin())}):
+                n = int(eff[i])
+                if n == 0:
+                    assert not out[h, i].any() and lse[h, i] == -float("inf")
+                    continue
+                want, lse_w = O.attention(bf16_bits(q[h, i:i + 1]), kb[:n], vb[:n], want_lse=True)
+                ok, max_abs, worst = P.attn_tolerance_ok(P.to_np_u16(out[h, i:i + 1]), want)
+                assert ok, (h, i, n, max_abs, worst)
+                assert abs(float(lse[h, i]) - lse_w[0]) < 2e-3
+
+
+def test_parts_keep_a_nan_query_in_its_row():
+    H, Nq, L, n_kv = 2, 70, 520, 1000
+    kc, vc = _filled_caches(H, L, 2, n_kv, 16, 64, 2)
+    q = synth.queries(CONFIGS["cfg2_window21"], H, Nq, DEV)
+    clean = B.attn_decode(q, kc, vc, n_kv=n_kv)
+    q[1, 5, 17] = float("nan")
+    out = B.attn_decode(q, kc, vc, n_kv=n_kv)
+    torch.cuda.synchronize()
+    assert out[1, 5].isnan().all()
+    out[1, 5] = clean[1, 5]
+    assert torch.equal(out, clean)
