@@ -886,8 +886,8 @@ hipError_t launch_attn(const AttnArgs &a, hipStream_t s) {
 // whole cache, 1.5-2.5 us a tile.  Its tiles are dealt out (tile g to part g % parts, so that every slab
 // of the shared-tile form and every prefix is spread evenly) until the chip is full once, with at
 // least four tiles to a part: fewer do not repay the part's start and its 132 KB of state.  64 queries
-// of one head over 4096 tokens 160 -> 33 us (34, 36, 44, 72 us with 4, 8, 2, 1 tiles at least); 12 heads x
-// 1560 queries over 31997 tokens 795 -> 440 us; twice the chip's worth of parts is 5 % slower there.
+// of one head over 4096 tokens 160 -> 28 us (2, 3 and 6 tiles at least: 28, 29, 30); 12 heads x
+// 1560 queries over 31997 tokens 795 -> 430 us; twice the chip's worth of parts is 5 % slower there.
 // From 129 query blocks on nothing is dealt: 160 blocks in three parts gain nothing (1.09 against 1.08 ms).
 // ---------------------------------------------------------------------------------------------
 constexpr int kCus = 256;
@@ -905,43 +905,65 @@ size_t attn_parts_bytes(int H, int64_t n_q, int parts) {
     return parts > 1 ? (size_t)parts * nqb * H * kStateFloats * kAtThreads * sizeof(float) : 0;
 }
 
-// The result of a query from the states of its parts: one workgroup per query block and 32 channels,
-// threads as in the kernels that left the states.  A part whose first tile lies behind the query's
-// prefix saw none of its tokens and is left out (its sums may be anything).
+// The result of a query from the states of its parts: one workgroup per query block and 8 of a lane's
+// 64 values, threads as in the kernels that left the states.  A part whose first tile lies behind
+// the query's prefix saw none of its tokens and is left out (its sums may be anything).  A chain of
+// loads: several parts are requested before the first is used (one at a time, 16 parts took 17 us).
+constexpr int kJoinAhead = 8;
 __global__ __launch_bounds__(kAtThreads)
 void attn_join_kernel(AttnArgs a, int n_qblocks) {
-    const int h = (int)(blockIdx.x / (unsigned)n_qblocks), qblock = (int)(blockIdx.x - (unsigned)h * n_qblocks), mb = blockIdx.y;
+    const int h = (int)(blockIdx.x / (unsigned)n_qblocks), qblock = (int)(blockIdx.x - (unsigned)h * n_qblocks);
+    const int v0 = blockIdx.y * 8;                                       // channels 32 * (v0 / 16) + 8 * (v / 4 % 4) + 4 * half + v % 4
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, half = lane >> 5;
     const int64_t qrow = (int64_t)qblock * kAtQPerBlock + wave * 32 + col;
-    const bool qvalid = qrow < a.n_q;
-    int seen = 0;                                                        // parts that saw a token: the first ones
-    if (qvalid) {
-        int64_t qlen = a.n_kv;
-        if (a.q_len) { const int64_t v = a.q_len[qrow]; qlen = v < 0 ? 0 : (v > a.n_kv ? a.n_kv : v); }
-        for (Span sp = span_of(a, 0); seen < a.parts; ++seen) {
-            sp.part = seen;
-            const Tile t = first_tile(sp);
-            if (!t.valid || t.t0 >= qlen) break;
+    if (qrow >= a.n_q) return;                                           // both lane halves of a query
+    const float *st = part_state_of(a, n_qblocks, h, qblock, 0);
+    const int64_t pitch = (int64_t)a.H * n_qblocks * kStateFloats * kAtThreads;
+    int seen = a.parts;                                                  // the parts that saw a token are the first ones
+    if (a.q_len) {
+        const int nk = (int)a.n_kv, clen = a.chunk_len < a.n_kv ? (int)a.chunk_len : nk;
+        int qlen = a.q_len[qrow];
+        qlen = qlen < 0 ? 0 : (qlen > nk ? nk : qlen);
+        const int full = qlen / clen, rest = qlen - full * clen;
+        const int64_t tiles = (int64_t)full * ((clen + kAtKv - 1) / kAtKv) + (rest + kAtKv - 1) / kAtKv;
+        if (tiles < seen) seen = (int)tiles;
+    }
+    float m = -INFINITY, l = 0.0f, o[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) o[i] = 0.0f;
+    for (int p0 = 0; p0 < a.parts; p0 += kJoinAhead) {
+        float mp[kJoinAhead];
+#pragma unroll
+        for (int u = 0; u < kJoinAhead; ++u) mp[u] = st[(p0 + u < a.parts ? p0 + u : 0) * pitch + 64 * kAtThreads];
+#pragma unroll
+        for (int u = 0; u < kJoinAhead; ++u) m = p0 + u < seen ? fmaxf(m, mp[u]) : m;
+    }
+    constexpr int kRows = 4;
+    for (int p0 = 0; p0 < a.parts; p0 += kRows) {
+        float x[kRows][10];
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            const float *sp = st + (p0 + u < a.parts ? p0 + u : 0) * pitch;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[u][i] = sp[(v0 + i) * kAtThreads];
+            x[u][8] = sp[64 * kAtThreads]; x[u][9] = sp[65 * kAtThreads];
+        }
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            if (p0 + u < seen) {
+                const float wgt = __builtin_amdgcn_exp2f(x[u][8] - m);
+                l = __builtin_fmaf(wgt, x[u][9], l);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) o[i] = __builtin_fmaf(wgt, x[u][i], o[i]);
+            }
         }
     }
-    float m = -INFINITY, l = 0.0f, o[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[r] = 0.0f;
-    for (int part = 0; part < seen; ++part) m = fmaxf(m, part_state_of(a, n_qblocks, h, qblock, part)[64 * kAtThreads]);
-    for (int part = 0; part < seen; ++part) {
-        const float *st = part_state_of(a, n_qblocks, h, qblock, part);
-        const float wgt = __builtin_amdgcn_exp2f(st[64 * kAtThreads] - m);
-        l = __builtin_fmaf(wgt, st[65 * kAtThreads], l);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[r] = __builtin_fmaf(wgt, st[(mb * 16 + r) * kAtThreads], o[r]);
-    }
     const float ltot = l + __shfl_xor(l, 32, 64);
-    if (!qvalid) return;
     const bool any = seen > 0;
     const float inv = any ? 1.0f / ltot : 0.0f;
-    const int64_t at = ((int64_t)h * a.n_q + qrow) * kHeadDim + half * 4 + mb * 32;
+    const int64_t at = ((int64_t)h * a.n_q + qrow) * kHeadDim + half * 4 + (v0 >> 4) * 32 + ((v0 >> 2) & 3) * 8;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < 2; ++g) {
         if (a.out_f32)
             *reinterpret_cast<float4 *>(a.out_f32 + at + g * 8) =
                 make_float4(o[4 * g] * inv, o[4 * g + 1] * inv, o[4 * g + 2] * inv, o[4 * g + 3] * inv);
@@ -949,14 +971,14 @@ void attn_join_kernel(AttnArgs a, int n_qblocks) {
             *reinterpret_cast<uint2 *>(a.out + at + g * 8) = make_uint2(pack_bf16x2(o[4 * g] * inv, o[4 * g + 1] * inv),
                                                                         pack_bf16x2(o[4 * g + 2] * inv, o[4 * g + 3] * inv));
     }
-    if (a.lse && half == 0 && mb == 0)
+    if (a.lse && half == 0 && v0 == 0)
         a.lse[(int64_t)h * a.n_q + qrow] = any ? (m + __builtin_log2f(ltot)) * 0.6931471805599453f : -INFINITY;
 }
 
 hipError_t launch_attn_join(const AttnArgs &a, hipStream_t s) {
     const int64_t nqb = (a.n_q + kAtQPerBlock - 1) / kAtQPerBlock;
     if (nqb * a.H > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(attn_join_kernel, dim3((unsigned)(nqb * a.H), 4), dim3(kAtThreads), 0, s, a, (int)nqb);
+    hipLaunchKernelGGL(attn_join_kernel, dim3((unsigned)(nqb * a.H), 8), dim3(kAtThreads), 0, s, a, (int)nqb);
     return hipGetLastError();
 }
 

@@ -506,10 +506,14 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
 // ---- host side ---------------------------------------------------------------------------------
 template <int T_, int SM, int FMT>
 static hipError_t launch_slab_decode_t(const AttnArgs &a, const SlabArgs &sl, hipStream_t s) {
-    constexpr int kRun = 8;                                             // tiles per workgroup
-    dim3 grid((unsigned)((sl.n_tiles + kRun - 1) / kRun), (unsigned)a.H);
-    if (a.rope) hipLaunchKernelGGL((slab_decode_kernel<T_, SM, FMT, true>), grid, dim3(kAtThreads), 0, s, a, sl, kRun);
-    else hipLaunchKernelGGL((slab_decode_kernel<T_, SM, FMT, false>), grid, dim3(kAtThreads), 0, s, a, sl, kRun);
+    // Tiles per workgroup: eight (a workgroup starts with a chain of dependent loads; 16, or as many as
+    // fill the chip a whole number of times, make no difference), fewer while the chip is not full once:
+    // 600 queries of one head over 4096 tokens 39 -> 34 us
+    const int64_t tiles = (int64_t)sl.n_tiles * a.H;
+    const int run = tiles >= 8 * 512 ? 8 : (int)((tiles + 511) / 512);
+    dim3 grid((unsigned)((sl.n_tiles + run - 1) / run), (unsigned)a.H);
+    if (a.rope) hipLaunchKernelGGL((slab_decode_kernel<T_, SM, FMT, true>), grid, dim3(kAtThreads), 0, s, a, sl, run);
+    else hipLaunchKernelGGL((slab_decode_kernel<T_, SM, FMT, false>), grid, dim3(kAtThreads), 0, s, a, sl, run);
     return hipGetLastError();
 }
 
