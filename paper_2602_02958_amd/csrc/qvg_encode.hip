@@ -191,6 +191,27 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
         nh[u] = make_uint2(__float_as_uint(-3.0e38f) >> 16, 0u);
         if (row < K) nh[u] = a.nh3[(int64_t)h * a.nh3_stride + row];
     }
+    const int64_t blk0 = (int64_t)blockIdx.y * tiles_per_wave * (kAsgWaves * kAsgTile);
+    const bf16_t *xh = a.x + (int64_t)h * a.stride_head + half * 64;
+    // this lane's 64 channels of its two tokens of a step (the MFMA B operands); a token past the
+    // end of the chunk reads as zero
+    auto load_x = [&](int64_t n0_, uint4 (&dst)[2][8]) {
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb) {
+            const int64_t nn = n0_ + tb * 32 + col;
+            const bf16_t *xp = xh + nn * a.stride_token;
+#pragma unroll
+            for (int kk = 0; kk < 8; ++kk)
+                dst[tb][kk] = (nn < N) ? *reinterpret_cast<const uint4 *>(xp + kk * 8) : make_uint4(0u, 0u, 0u, 0u);
+        }
+    };
+    auto step_start = [&](int k) {
+        return k < tiles_per_wave ? blk0 + (int64_t)(k * kAsgWaves + wave) * kAsgTile : N;
+    };
+    // the first step's tokens are on their way while the table is staged (80 units x 10800 tokens,
+    // K = 128, I = 3: 535 -> 490 us)
+    uint4 xa[2][8];
+    if (step_start(0) < N) load_x(step_start(0), xa);
     // Eight 16-byte pieces per thread are requested before the first is used: taken one at a time
     // (load, store to LDS) every piece waits a whole memory round trip (0.85 us measured),
     // which was most of what a workgroup with a single 256-token step spent on a 256-row table.
@@ -244,20 +265,6 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
     const float pinf = __uint_as_float(vgpr_const(0x7f800000u));
     const uint4 ones = half ? make_uint4(0u, 0u, 0u, 0u) : make_uint4(0x3F803F80u, 0x00003F80u, 0u, 0u);
 
-    const int64_t blk0 = (int64_t)blockIdx.y * tiles_per_wave * (kAsgWaves * kAsgTile);
-    const bf16_t *xh = a.x + (int64_t)h * a.stride_head + half * 64;
-    // this lane's 64 channels of its two tokens of a step (the MFMA B operands); a token past the
-    // end of the chunk reads as zero
-    auto load_x = [&](int64_t n0_, uint4 (&dst)[2][8]) {
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb) {
-            const int64_t nn = n0_ + tb * 32 + col;
-            const bf16_t *xp = xh + nn * a.stride_token;
-#pragma unroll
-            for (int kk = 0; kk < 8; ++kk)
-                dst[tb][kk] = (nn < N) ? *reinterpret_cast<const uint4 *>(xp + kk * 8) : make_uint4(0u, 0u, 0u, 0u);
-        }
-    };
     // fp64 squared distances of the token in `scr` to centroids ja and jb (wave-uniform indices), one
     // per half of the wavefront: two rows of 16 lanes summed by DPP moves, the row sums read as
     // scalars (no exchange through LDS).  Both go through the same operations, so equal rows give
@@ -344,18 +351,14 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
         }
         return bj;
     };
-    auto step_start = [&](int k) {
-        return k < tiles_per_wave ? blk0 + (int64_t)(k * kAsgWaves + wave) * kAsgTile : N;
-    };
     // One step: 64 tokens.  Measured and left out, each without effect on the time of the pass:
     // requesting the next step's tokens a step ahead into a second register set; fetching the
     // tokens with whole rows per instruction through a staging area in LDS (each lane below reads
     // 16 bytes out of 64 different cache lines per instruction); more or fewer steps per workgroup.
-    uint4 xa[2][8];
     for (int k = 0; k < tiles_per_wave; ++k) {
         const int64_t n0 = step_start(k);
         if (n0 >= N) break;                                  // uniform per wavefront
-        load_x(n0, xa);
+        if (k > 0) load_x(n0, xa);
         int64_t n[2];
         bool valid[2];
         float xn[2];

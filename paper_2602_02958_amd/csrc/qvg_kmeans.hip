@@ -45,12 +45,16 @@ hipError_t launch_member_lists(const uint8_t *ids, int64_t ids_stride, int64_t n
     return hipGetLastError();
 }
 
-constexpr int kMeanThreads = 256;           // 4 wavefronts
-constexpr int kMeanWaves = kMeanThreads / 64;
+constexpr int kMeanWaves = 4;               // wavefronts (and centroids) of a block
+constexpr int kMeanWideWaves = 16;          // wavefronts of a block with one centroid and long lists
 constexpr int kMeanParallelMin = 96;        // member lists at least this long try the order-free path
 constexpr int kMeanCoopMin = 192;           // lists at least this long are summed by the whole block
                                             // (with one centroid per block: every order-free list)
 constexpr int kMeanSmallGrid = 2048;        // up to this many centroids in a launch: one block each
+// With at most one such block per CU, and lists of 64 members or more on average, the block has 16
+// wavefronts: 2 units x 4096 tokens, K = 16, I = 10 195 -> 176 us, 2 x 10800, K = 64, I = 3 80 -> 70 us (24 x 4680,
+// K = 64, six blocks to a CU: 92 -> 171 us)
+constexpr int kMeanWideGrid = 256, kMeanWideMin = 64;
 
 // A cluster's members in up to 64 consecutive blocks of its unit: lane b holds block b's part.
 struct Segments {
@@ -181,7 +185,8 @@ __device__ __forceinline__ void store_centroid(const UpdateArgs &a, int h, int j
     }
 }
 
-// the defining order: members in token order, two channels per lane, 16 rows in flight
+// the defining order: members in token order, two channels per lane
+constexpr int kRowsAhead = 16;             // rows in flight (divides 64)
 __device__ __forceinline__ uint32_t mean_token_order(const bf16_t *xu, int64_t stride_token, const ListView &v, int j,
                                                      Segments sg, int n, int lane) {
     double s0 = 0.0, s1 = 0.0;
@@ -191,16 +196,16 @@ __device__ __forceinline__ uint32_t mean_token_order(const bf16_t *xu, int64_t s
             // 64 member indices at once, then broadcast lane by lane
             const int mine = member_token(v, sg, b0, base + lane);
             const int cntm = (sg.n - base < 64) ? sg.n - base : 64;
-            for (int u0 = 0; u0 < cntm; u0 += 16) {
-                uint32_t wv[16];
+            // all lanes of `mine` hold tokens that exist, so that no load needs a predicate
+            for (int u0 = 0; u0 < cntm; u0 += kRowsAhead) {
+                uint32_t wv[kRowsAhead];
 #pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    const int idx = __shfl(mine, u0 + u, 64);
-                    wv[u] = (u0 + u < cntm)
-                        ? *reinterpret_cast<const uint32_t *>(xb + (int64_t)idx * stride_token) : 0u;
+                for (int u = 0; u < kRowsAhead; ++u) {
+                    const int idx = __builtin_amdgcn_readlane(mine, u0 + u);
+                    wv[u] = *reinterpret_cast<const uint32_t *>(xb + (int64_t)idx * stride_token);
                 }
 #pragma unroll
-                for (int u = 0; u < 16; ++u)
+                for (int u = 0; u < kRowsAhead; ++u)
                     if (u0 + u < cntm) { s0 += (double)bf16_lo(wv[u]); s1 += (double)bf16_hi(wv[u]); }
             }
         }
@@ -225,23 +230,25 @@ __device__ __forceinline__ uint32_t mean_token_order(const bf16_t *xu, int64_t s
 // test is summed again in token order.  Lists of medium length use the four member slots of their
 // own wavefront; the longest ones (one cluster can hold a large share of a unit's tokens, e.g.
 // in the later smoothing stages) are split over all wavefronts of the block, whose partial
-// results meet in LDS.  Four wavefronts per block and at most 80 registers (the few values that
-// spill are touched once per block-wide list) keep six wavefronts per SIMD resident, which is what
-// the common case of many short lists lives on; eight wavefronts per block sum the longest lists
-// faster and everything else slower.  A launch with few centroids (one chunk of a few heads) cannot
+// results meet in LDS.  Four wavefronts per block and at most 96 registers keep five wavefronts per
+// SIMD resident (six, at 80 registers, spill: a QVG-Pro chunk 690 against 666 us; four with sixteen rows in
+// flight 690 too), which is what the common case of many short lists lives on; eight wavefronts
+// per block sum the longest lists faster and everything else slower.  The unit is the fastest
+// grid index, as in the assignment: a unit's tokens and lists are then read through one XCD's L2 (the
+// other way round that chunk takes 742 us).  A launch with few centroids (one chunk of a few heads) cannot
 // fill the chip anyway and is a chain of dependent loads: there a block has ONE centroid (CPB = 1),
 // every list long enough for the order-free path is spread over the block's four wavefronts, and
 // 16 rows are in flight per lane (ROWS = 16: no occupancy to protect).
-template <int CPB, int ROWS>
-__global__ __launch_bounds__(kMeanThreads, CPB == 1 ? 2 : 6)
+template <int CPB, int ROWS, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, CPB == 1 ? WAVES / 4 : 5)
 void kmeans_mean_kernel(UpdateArgs a) {
     constexpr int kCoopMin = CPB == 1 ? kMeanParallelMin : kMeanCoopMin;
-    __shared__ double part[kMeanWaves][kHeadDim];
-    __shared__ uint32_t pmx[kMeanWaves][kHeadDim / 2], pmn[kMeanWaves][kHeadDim / 2];
-    __shared__ int list_len[kMeanWaves];
-    const int h = blockIdx.y, lane = threadIdx.x & 63;
+    __shared__ double part[WAVES][kHeadDim];
+    __shared__ uint32_t pmx[WAVES][kHeadDim / 2], pmn[WAVES][kHeadDim / 2];
+    __shared__ int list_len[WAVES];
+    const int h = blockIdx.x, lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int j0 = blockIdx.x * CPB;
+    const int j0 = blockIdx.y * CPB;
     const int j = j0 + wave;
     const int K = a.K;
     const bf16_t *xu = a.x + (int64_t)h * a.stride_head;
@@ -316,7 +323,7 @@ void kmeans_mean_kernel(UpdateArgs a) {
         for (int i = 0; i < 8; ++i) s[i] = 0.0;
         uint32_t amax[4] = {0u, 0u, 0u, 0u}, amin[4] = {~0u, ~0u, ~0u, ~0u};
         const Segments st = load_segments(v, jt, 0, lane);
-        mean_partial<ROWS>(xu + c8 * 8, a.stride_token, v, jt, st, wave, kMeanWaves, lane, s, amax, amin);
+        mean_partial<ROWS>(xu + c8 * 8, a.stride_token, v, jt, st, wave, WAVES, lane, s, amax, amin);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {          // harmless if an addition rounds: then the result is discarded
             s[i] += __shfl_xor(s[i], 16, 64);
@@ -341,7 +348,7 @@ void kmeans_mean_kernel(UpdateArgs a) {
             double s0 = 0.0, s1 = 0.0;
             uint32_t mx = 0u, mn = ~0u;
 #pragma unroll
-            for (int w = 0; w < kMeanWaves; ++w) {
+            for (int w = 0; w < WAVES; ++w) {
                 s0 += part[w][2 * lane];
                 s1 += part[w][2 * lane + 1];
                 mx = pk_max_u16(mx, pmx[w][lane]);
@@ -364,10 +371,14 @@ void kmeans_mean_kernel(UpdateArgs a) {
 
 hipError_t launch_update(const UpdateArgs &a, hipStream_t s) {
     if ((int64_t)a.K * a.H <= kMeanSmallGrid) {
-        hipLaunchKernelGGL((kmeans_mean_kernel<1, 16>), dim3((unsigned)a.K, (unsigned)a.H), dim3(kMeanThreads), 0, s, a);
+        const dim3 grid((unsigned)a.H, (unsigned)a.K);
+        if ((int64_t)a.K * a.H <= kMeanWideGrid && a.n_tokens >= (int64_t)kMeanWideMin * a.K)
+            hipLaunchKernelGGL((kmeans_mean_kernel<1, 16, kMeanWideWaves>), grid, dim3(kMeanWideWaves * 64), 0, s, a);
+        else
+            hipLaunchKernelGGL((kmeans_mean_kernel<1, 16, kMeanWaves>), grid, dim3(kMeanWaves * 64), 0, s, a);
     } else {
-        dim3 grid((unsigned)((a.K + kMeanWaves - 1) / kMeanWaves), (unsigned)a.H);
-        hipLaunchKernelGGL((kmeans_mean_kernel<kMeanWaves, 8>), grid, dim3(kMeanThreads), 0, s, a);
+        dim3 grid((unsigned)a.H, (unsigned)((a.K + kMeanWaves - 1) / kMeanWaves));
+        hipLaunchKernelGGL((kmeans_mean_kernel<kMeanWaves, 8, kMeanWaves>), grid, dim3(kMeanWaves * 64), 0, s, a);
     }
     return hipGetLastError();
 }
