@@ -142,10 +142,14 @@ int qvg_encode_chunk(const qvg_params *p, int64_t n_tokens,
  * qvg_encode_chunk for callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): the same call without the workspace
  * arguments.  The workspace lives in a static device array inside the library,
- * QVG_STATIC_SCRATCH_BYTES per GPU the library runs on, held until the process ends; the call
+ * 48 MiB per GPU the library runs on, held until the process ends; the call
  * allocates and frees nothing.  Arguments, results and errors are those of qvg_encode_chunk, plus
- *   QVG_ERR_SCRATCH_LIMIT  when qvg_workspace_bytes(p, QVG_ENTRY_ENCODE, n_tokens, 0) exceeds
- *                          QVG_STATIC_SCRATCH_BYTES (nothing was enqueued).  One layer's chunk of
+ *   QVG_ERR_SCRATCH_LIMIT  when the sum of 8 bytes per centroid (K rounded up to a multiple of
+ *                          64) and 4 per unit, of two bf16 tables (kmeans_iters > 0 or several
+ *                          stages), of 4 bytes per token and 4 (K + 1) per unit (kmeans_iters > 0), and of
+ *                          one (two stages) or two (more) bf16 copies of the chunk, each rounded up
+ *                          to 256 bytes, exceeds QVG_STATIC_SCRATCH_BYTES
+ *                          (nothing was enqueued).  One layer's chunk of
  *                          every configuration this library is measured on fits (24 units x 4680
  *                          tokens, K = 256: 3.7 MB; 80 units x 10800 tokens, K = 128: 9 MB);
  *                          several smoothing stages need two bf16 copies of the chunk and fit only

@@ -311,9 +311,21 @@ int qvg_encode_chunk(const qvg_params *p, int64_t n_tokens, const void *x, int64
 // own address), alive until the process ends.  The name below is only a handle on the host: the
 // device address comes from hipGetSymbolAddress, once per device, and only that address is ever
 // passed to a kernel or a copy.
-static __device__ __align__(256) unsigned char scratch[QVG_STATIC_SCRATCH_BYTES];
+constexpr size_t kStaticArrayBytes = (size_t)48 << 20;
+static __device__ __align__(256) unsigned char scratch[kStaticArrayBytes];
 
 namespace {
+// The bytes that QVG_STATIC_SCRATCH_BYTES limits (see the header): what a call is accepted by stays
+// the same when the workspace's layout changes.  The layout in use takes more per token (the member lists) and per
+// stage (the norms): at most 43 MB over the sizes that the rule accepts.
+size_t static_rule_bytes(const qvg_params *p, int64_t N) {
+    const size_t H = (size_t)p->n_heads, K = (size_t)p->n_clusters, n = (size_t)(N > 0 ? N : 1);
+    size_t o = round256(H * k_padded(p->n_clusters) * 8) + round256(H * 4);
+    if (p->kmeans_iters > 0 || p->n_smooth_stages > 1) o += 2 * round256(H * K * kHeadDim * 2);
+    if (p->kmeans_iters > 0) o += round256(H * n * 4) + round256(H * (K + 1) * 4);
+    const int resid = p->n_smooth_stages > 2 ? 2 : p->n_smooth_stages - 1;
+    return o + resid * round256(H * n * kHeadDim * 2);
+}
 constexpr int kMaxDevices = 64;
 // device address of `scratch` on the current device (looked up on the first call on that device)
 int static_scratch_address(void **out) {
@@ -345,7 +357,8 @@ int qvg_encode_chunk_static(const qvg_params *p, int64_t n_tokens, const void *x
     // the same workspace layout as qvg_encode_chunk, placed in the static array
     const size_t need = n_tokens == 0 ? 0 : encode_ws(p, n_tokens, true, p->kmeans_iters > 0,
                                                       p->kmeans_iters > 0).total;
-    if (need > (size_t)QVG_STATIC_SCRATCH_BYTES) return QVG_ERR_SCRATCH_LIMIT;
+    if (need > 0 && static_rule_bytes(p, n_tokens) > (size_t)QVG_STATIC_SCRATCH_BYTES) return QVG_ERR_SCRATCH_LIMIT;
+    if (need > kStaticArrayBytes) return QVG_ERR_SCRATCH_LIMIT;
     void *ws = nullptr;
     if (need > 0 && (st = static_scratch_address(&ws)) != QVG_OK) return st;
     // nothing in the workspace has to start at zero: every kernel writes what it later reads
