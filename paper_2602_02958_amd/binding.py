@@ -307,6 +307,18 @@ def attn_decode(q, k: Encoded, v: Encoded, softmax_scale=None, want_lse=False, o
     shared by all query blocks, a slab of chunks at a time, instead of once per 256 queries.  Without
     one, calls of more than 512 queries take up to 256 MiB for the call from torch's allocator; one
     that is too small for a chunk (an empty tensor) is ignored."""
+    if (v.ids.shape, v.codes.shape, v.scales.shape, v.scales.dtype, v.centroids.shape, v.chunk_len, v.n_smooth) != \
+            (k.ids.shape, k.codes.shape, k.scales.shape, k.scales.dtype, k.centroids.shape, k.chunk_len, k.n_smooth):
+        raise ValueError("K and V caches must share shapes and parameters")
+    _check(v.ids, id_dtype(v.centroids.shape[-2]), "v.ids")
+    kp = (_ptr(k.centroids), _ptr(k.ids), _ptr(k.codes), _ptr(k.scales))
+    vp = (_ptr(v.centroids), _ptr(v.ids), _ptr(v.codes), _ptr(v.scales))
+    return _attn(q, k, kp, vp, softmax_scale, want_lse, out, n_kv, k_rope, q_kv_len, f32_out, workspace)
+
+
+def _attn(q, k: Encoded, kp, vp, softmax_scale, want_lse, out, n_kv, k_rope, q_kv_len, f32_out, workspace):
+    """attn_decode on the pointers kp and vp (centroids, ids, codes, scales of the two sides); sizes and
+    formats are those of k."""
     _check(q, torch.bfloat16, "q")
     q = q.contiguous()
     H, Nq, d = q.shape
@@ -321,10 +333,6 @@ def attn_decode(q, k: Encoded, v: Encoded, softmax_scale=None, want_lse=False, o
     K = k.centroids.shape[-2]
     T, G = k.codes.shape[2], k.scales.shape[3]
     _check(k.ids, id_dtype(K), "k.ids")
-    _check(v.ids, id_dtype(K), "v.ids")
-    if (v.ids.shape, v.codes.shape, v.scales.shape, v.scales.dtype, v.centroids.shape, v.chunk_len, v.n_smooth) != \
-            (k.ids.shape, k.codes.shape, k.scales.shape, k.scales.dtype, k.centroids.shape, k.chunk_len, k.n_smooth):
-        raise ValueError("K and V caches must share shapes and parameters")
     p = make_params(H, K, d // G, T, 0, head_dim=d, n_smooth_stages=k.n_smooth, bits=k.bits,
                     scale_format=k.scale_format)
     if softmax_scale is None:
@@ -349,9 +357,7 @@ def attn_decode(q, k: Encoded, v: Encoded, softmax_scale=None, want_lse=False, o
     if workspace is None and Nq > TILE_SCRATCH_MIN_QUERIES:
         workspace = _tile_scratch(H, Nq, k.chunk_len, -(-Nk // k.chunk_len), q.device)
     st = lib().qvg_attn_decode_parts(C.byref(p), Nq, _ptr(q), Nk, k.chunk_len, cap,
-                                     _ptr(k.centroids), _ptr(k.ids), _ptr(k.codes), _ptr(k.scales),
-                                     _ptr(v.centroids), _ptr(v.ids), _ptr(v.codes), _ptr(v.scales),
-                                     _ptr(k_rope), _ptr(q_kv_len), C.c_float(softmax_scale),
+                                     *kp, *vp, _ptr(k_rope), _ptr(q_kv_len), C.c_float(softmax_scale),
                                      None if f32_out else _ptr(out), _ptr(out) if f32_out else None, _ptr(lse),
                                      _ptr(workspace), 0 if workspace is None else workspace.numel(),
                                      _ptr(scratch), 0 if scratch is None else scratch.numel(), _stream())
@@ -481,8 +487,13 @@ class StreamingCache:
         """Attention of q [heads, n_q, d] over the tokens appended so far (decode fused in)."""
         if self.n_tokens == 0:
             raise ValueError("the cache is empty")
-        return attn_decode(q, self.k, self.v, softmax_scale=softmax_scale, want_lse=want_lse, out=out,
-                           n_kv=self.n_tokens, k_rope=k_rope, workspace=workspace)
+        # the two halves of the cache by address: views of both sides (self.k, self.v) cost more than the
+        # smallest attention's launches
+        c = self.cache
+        ts = (c.centroids, c.ids, c.codes, c.scales)
+        vp = tuple(C.c_void_p(t.data_ptr() + self.heads * t.stride(0) * t.element_size()) for t in ts)
+        return _attn(q, c, tuple(_ptr(t) for t in ts), vp, softmax_scale, want_lse, out, self.n_tokens, k_rope, None,
+                     False, workspace)
 
     def decode(self, out=None, first_chunk=0, n_tokens=None) -> torch.Tensor:
         """bf16 [2 * heads, n, d] of the tokens appended so far, from chunk `first_chunk` on."""
