@@ -45,18 +45,18 @@ __device__ __forceinline__ Tile slab_tile(const AttnArgs &a, const SlabArgs &sl,
 }
 
 // ---------------------------------------------------------------------------------------------
-// Decode a run of tiles of one unit's K and V into the operand images.  512 threads: thread
-// (tp, c8) has tokens 2 tp, 2 tp + 1 and channels 8 c8 .. 8 c8 + 7 of both sides, as in the fused
+// Decode a run of tiles of one unit's K or V into the operand images.  512 threads: thread
+// (tp, c8) has tokens 2 tp, 2 tp + 1 and channels 8 c8 .. 8 c8 + 7, as in the fused
 // kernels.  K rows go straight to memory (16 lanes cover a 256-byte row); V is transposed through
 // LDS.  Tokens past the end of a chunk decode to zero.
 // ---------------------------------------------------------------------------------------------
-template <int TM, int SM>
-struct TileRaw { Raw<TM, SM> k, v; uint4 rp[2]; };
-
-// Two workgroups per CU (at most 128 registers) for the instances with one smoothing stage and a
-// compile-time round count: the kernel is a chain of small dependent loads and lives on occupancy.
+// A workgroup decodes ONE side (blockIdx.z: 0 K, 1 V): the kernel is a chain of small dependent loads and lives
+// on occupancy, and one side's raw data takes half the registers (three workgroups per CU up to two smoothing
+// stages, else two).  32 chunks of 12 heads x 4680 tokens, T = 4: 353 us with both sides in one workgroup, 320 so (364
+// and 694 with two and four workgroups per CU); 37440 tokens, S = 4 147 -> 120 us (150 with three), T = 3 86 -> 90.
+// 0.92 GB written and 0.57 read in 320 us are 4.7 TB/s, nine tenths of a copy's rate.
 template <int T_, int SM, int FMT, bool ROPE>
-__global__ __launch_bounds__(kAtThreads, (T_ > 0 && SM == 1) ? 4 : 2)
+__global__ __launch_bounds__(kAtThreads, (T_ > 0 && SM <= 2) ? 6 : 4)
 void slab_decode_kernel(AttnArgs a, SlabArgs sl, int run) {
     constexpr int TM = T_ > 0 ? T_ : kMaxStages;
     __shared__ __align__(16) uint16_t Vt[kVtElems];                     // [128][72] f16, transposed, swizzled (below)
@@ -68,15 +68,14 @@ void slab_decode_kernel(AttnArgs a, SlabArgs sl, int run) {
     const int S = SM > 0 ? SM : a.S;
     const int G = kHeadDim / B;
 
-    CacheSide ks, vs;
+    const bool vside = blockIdx.z != 0;                                  // uniform
+    CacheSide cs;
     constexpr int kCodeBytes = (FMT & kFmtInt4) ? 64 : 32, kScaleBytes = (FMT & kFmtE4M3) ? 1 : 2;
-    ks.ids = a.k_ids + (int64_t)h * a.kv_stride * S * (a.id_wide ? 2 : 1);  ks.codes = a.k_codes + (int64_t)h * a.kv_stride * T * kCodeBytes;
-    ks.scales = reinterpret_cast<const uint8_t *>(a.k_scales) + (int64_t)h * a.kv_stride * T * G * kScaleBytes;
-    ks.cent = a.k_cent + (int64_t)h * a.chunk_stride * S * K * kHeadDim;
-    ks.wide = vs.wide = a.id_wide;
-    vs.ids = a.v_ids + (int64_t)h * a.kv_stride * S * (a.id_wide ? 2 : 1);  vs.codes = a.v_codes + (int64_t)h * a.kv_stride * T * kCodeBytes;
-    vs.scales = reinterpret_cast<const uint8_t *>(a.v_scales) + (int64_t)h * a.kv_stride * T * G * kScaleBytes;
-    vs.cent = a.v_cent + (int64_t)h * a.chunk_stride * S * K * kHeadDim;
+    cs.ids = (vside ? a.v_ids : a.k_ids) + (int64_t)h * a.kv_stride * S * (a.id_wide ? 2 : 1);
+    cs.codes = (vside ? a.v_codes : a.k_codes) + (int64_t)h * a.kv_stride * T * kCodeBytes;
+    cs.scales = reinterpret_cast<const uint8_t *>(vside ? a.v_scales : a.k_scales) + (int64_t)h * a.kv_stride * T * G * kScaleBytes;
+    cs.cent = (vside ? a.v_cent : a.k_cent) + (int64_t)h * a.chunk_stride * S * K * kHeadDim;
+    cs.wide = a.id_wide;
 
     const int c8 = tid & 15, tp = tid >> 4;
     const int g = (c8 * 8) / B;
@@ -84,28 +83,35 @@ void slab_decode_kernel(AttnArgs a, SlabArgs sl, int run) {
     // position of the token pair in a transposed V row (the order in which a lane's soft-max
     // values feed the PV contraction): token 16 s + 8 a + 4 hh + e sits at 16 s + 8 hh + 4 a + e
     const int v_pos = 16 * (tok >> 4) + 8 * ((tok >> 2) & 1) + 4 * ((tok >> 3) & 1) + (tok & 3);
-    uint16_t *kimg = sl.kimg + (int64_t)h * sl.tiles_cap * kImgElems;
-    uint16_t *vimg = sl.vimg + (int64_t)h * sl.tiles_cap * kImgElems;
+    uint16_t *img = (vside ? sl.vimg : sl.kimg) + (int64_t)h * sl.tiles_cap * kImgElems;
 
-    uint32_t idk[2], idv[2];
-    auto fetch = [&](const Tile &t, TileRaw<TM, SM> &r) {            // ids of `t` are in idk / idv
-        load_raw<T_, TM, SM, FMT>(ks, t, tp, c8, T, G, g, K, S, idk, r.k);
-        load_raw<T_, TM, SM, FMT>(vs, t, tp, c8, T, G, g, K, S, idv, r.v);
-        if (ROPE) load_rope(a.rope, t, tp, c8, r.rp);
+    uint32_t id[2];
+    Raw<TM, SM> r;
+    uint4 rp[2];
+    auto fetch = [&](const Tile &t) {                                    // ids of `t` are in id
+        load_raw<T_, TM, SM, FMT>(cs, t, tp, c8, T, G, g, K, S, id, r);
+        if (ROPE && !vside) load_rope(a.rope, t, tp, c8, rp);
     };
-    // decode the tile held in r (both sides) and write its two images; `next` is called as soon as
-    // r has been consumed: it requests the following tile into the same registers, so that its
-    // loads are in flight during the transposition (with two workgroups per CU the other one's
-    // work hides the rest of their latency)
-    auto emit = [&](int i, TileRaw<TM, SM> &r, auto next) {
+    if (i0 >= i1) return;                                                // uniform
+    // raw data one tile ahead (requested as soon as the registers are free), ids two tiles ahead
+    Tile t = slab_tile(a, sl, i0);
+    load_ids(cs, t, tp, S, a.id_wide, id);
+    fetch(t);
+    Tile tn = slab_tile(a, sl, i0 + 1 < i1 ? i0 + 1 : sl.n_tiles);
+    load_ids(cs, tn, tp, S, a.id_wide, id);
+    for (int i = i0; i < i1; ++i) {
         float accA[8], accB[8];
-        dequant2x8<T_, TM, SM, FMT>(r.k, T, accA, accB);
-        if (ROPE) { rope_rotate8(accA, r.rp[0]); rope_rotate8(accB, r.rp[1]); }
-        uint16_t *kt = kimg + (int64_t)i * kImgElems;
-        *reinterpret_cast<uint4 *>(kt + (tok + 0) * kHeadDim + c8 * 8) = pack_bf16x8(accA);
-        *reinterpret_cast<uint4 *>(kt + (tok + 1) * kHeadDim + c8 * 8) = pack_bf16x8(accB);
-        dequant2x8<T_, TM, SM, FMT>(r.v, T, accA, accB);
-        next();
+        dequant2x8<T_, TM, SM, FMT>(r, T, accA, accB);
+        if (ROPE && !vside) { rope_rotate8(accA, rp[0]); rope_rotate8(accB, rp[1]); }
+        fetch(tn);                                                       // tile i + 1 (its ids arrived an iteration ago)
+        tn = slab_tile(a, sl, i + 2 < i1 ? i + 2 : sl.n_tiles);
+        load_ids(cs, tn, tp, S, a.id_wide, id);
+        uint16_t *it = img + (int64_t)i * kImgElems;
+        if (!vside) {
+            *reinterpret_cast<uint4 *>(it + (tok + 0) * kHeadDim + c8 * 8) = pack_bf16x8(accA);
+            *reinterpret_cast<uint4 *>(it + (tok + 1) * kHeadDim + c8 * 8) = pack_bf16x8(accB);
+            continue;
+        }
         // rows 8 c8 .. 8 c8 + 7; the 16-byte group of a row is XOR-ed with (row / 8) & 7 so that the 16
         // lanes that write the same column of 16 different row groups spread over the banks
         uint16_t *vt = Vt + (((v_pos >> 3) ^ (c8 & 7)) * 8 + (v_pos & 7));
@@ -118,33 +124,13 @@ void slab_decode_kernel(AttnArgs a, SlabArgs sl, int run) {
             *reinterpret_cast<uint32_t *>(vt + (c8 * 8 + e + 1) * kVtPitch) = pack_f16x2_rtz(bf16_hi(pa), bf16_hi(pb));
         }
         __syncthreads();
-        uint16_t *vo = vimg + (int64_t)i * kImgElems;
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int p = tid + k * kAtThreads;                          // 16-byte piece: row p / 8, group p % 8
-            *reinterpret_cast<uint4 *>(vo + p * 8) =
+            *reinterpret_cast<uint4 *>(it + p * 8) =
                 *reinterpret_cast<const uint4 *>(Vt + (p >> 3) * kVtPitch + (((p & 7) ^ ((p >> 6) & 7)) * 8));
         }
         __syncthreads();                                                 // Vt is rewritten by the next tile
-    };
-
-    if (i0 >= i1) return;                                                // uniform
-    // raw data one tile ahead (requested as soon as the registers are free), ids two tiles ahead
-    TileRaw<TM, SM> r;
-    Tile t = slab_tile(a, sl, i0);
-    load_ids(ks, t, tp, S, a.id_wide, idk);
-    load_ids(vs, t, tp, S, a.id_wide, idv);
-    fetch(t, r);
-    Tile tn = slab_tile(a, sl, i0 + 1 < i1 ? i0 + 1 : sl.n_tiles);
-    load_ids(ks, tn, tp, S, a.id_wide, idk);
-    load_ids(vs, tn, tp, S, a.id_wide, idv);
-    for (int i = i0; i < i1; ++i) {
-        emit(i, r, [&]() {
-            fetch(tn, r);                                                // tile i + 1 (its ids arrived an iteration ago)
-            tn = slab_tile(a, sl, i + 2 < i1 ? i + 2 : sl.n_tiles);
-            load_ids(ks, tn, tp, S, a.id_wide, idk);
-            load_ids(vs, tn, tp, S, a.id_wide, idv);
-        });
     }
 }
 
@@ -511,7 +497,7 @@ static hipError_t launch_slab_decode_t(const AttnArgs &a, const SlabArgs &sl, hi
     // 600 queries of one head over 4096 tokens 39 -> 34 us
     const int64_t tiles = (int64_t)sl.n_tiles * a.H;
     const int run = tiles >= 8 * 512 ? 8 : (int)((tiles + 511) / 512);
-    dim3 grid((unsigned)((sl.n_tiles + run - 1) / run), (unsigned)a.H);
+    dim3 grid((unsigned)((sl.n_tiles + run - 1) / run), (unsigned)a.H, 2);
     if (a.rope) hipLaunchKernelGGL((slab_decode_kernel<T_, SM, FMT, true>), grid, dim3(kAtThreads), 0, s, a, sl, run);
     else hipLaunchKernelGGL((slab_decode_kernel<T_, SM, FMT, false>), grid, dim3(kAtThreads), 0, s, a, sl, run);
     return hipGetLastError();
