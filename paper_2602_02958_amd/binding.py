@@ -119,11 +119,11 @@ def compressed_bytes(p: QvgParams, n_tokens: int) -> int:
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t):
-    return C.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _check(t, dtype, name):
@@ -214,10 +214,10 @@ def encode_chunk(x, init_centroids, group_size, n_stages, kmeans_iters, cache: E
     p = make_params(H, K, group_size, n_stages, kmeans_iters, head_dim=d, n_smooth_stages=S, bits=bits,
                     scale_format=scale_format)
     T, G = n_stages, d // group_size
-    outs = (C.c_void_p(cache.centroids.data_ptr() + chunk_index * S * K * d * 2), n_chunks * S * K * d,
-            C.c_void_p(cache.ids.data_ptr() + off * S * cache.ids.element_size()),
-            C.c_void_p(cache.codes.data_ptr() + off * T * (d * bits // 8)),
-            C.c_void_p(cache.scales.data_ptr() + off * T * G * cache.scales.element_size()), n_total)
+    outs = (cache.centroids.data_ptr() + chunk_index * S * K * d * 2, n_chunks * S * K * d,
+            cache.ids.data_ptr() + off * S * cache.ids.element_size(),
+            cache.codes.data_ptr() + off * T * (d * bits // 8),
+            cache.scales.data_ptr() + off * T * G * cache.scales.element_size(), n_total)
     if static_scratch:
         st = lib().qvg_encode_chunk_static(C.byref(p), N, _ptr(x), sh, st_, _ptr(init_centroids), *outs, _stream())
         if st != 0:
@@ -357,7 +357,7 @@ def _attn(q, k: Encoded, kp, vp, softmax_scale, want_lse, out, n_kv, k_rope, q_k
     if workspace is None and Nq > TILE_SCRATCH_MIN_QUERIES:
         workspace = _tile_scratch(H, Nq, k.chunk_len, -(-Nk // k.chunk_len), q.device)
     st = lib().qvg_attn_decode_parts(C.byref(p), Nq, _ptr(q), Nk, k.chunk_len, cap,
-                                     *kp, *vp, _ptr(k_rope), _ptr(q_kv_len), C.c_float(softmax_scale),
+                                     *kp, *vp, _ptr(k_rope), _ptr(q_kv_len), softmax_scale,
                                      None if f32_out else _ptr(out), _ptr(out) if f32_out else None, _ptr(lse),
                                      _ptr(workspace), 0 if workspace is None else workspace.numel(),
                                      _ptr(scratch), 0 if scratch is None else scratch.numel(), _stream())
@@ -491,7 +491,7 @@ class StreamingCache:
         # smallest attention's launches
         c = self.cache
         ts = (c.centroids, c.ids, c.codes, c.scales)
-        vp = tuple(C.c_void_p(t.data_ptr() + self.heads * t.stride(0) * t.element_size()) for t in ts)
+        vp = tuple(t.data_ptr() + self.heads * t.stride(0) * t.element_size() for t in ts)
         return _attn(q, c, tuple(_ptr(t) for t in ts), vp, softmax_scale, want_lse, out, self.n_tokens, k_rope, None,
                      False, workspace)
 

@@ -165,9 +165,10 @@ int qvg_kmeans_assign(const qvg_params *p, int64_t n_tokens, const void *x, int6
     if (!aligned16(workspace)) return QVG_ERR_ALIGN;
     AssignArgs a{};
     const int64_t table = (int64_t)p->n_clusters * kHeadDim;
-    uint2 *nh3 = reinterpret_cast<uint2 *>(static_cast<unsigned char *>(workspace) + w.init_norms);
+    uint2 *nh3 = assign_takes_norms(p->n_heads, p->n_clusters, n_tokens) ? nullptr
+                     : reinterpret_cast<uint2 *>(static_cast<unsigned char *>(workspace) + w.init_norms);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (launch_half_norms(static_cast<const bf16_t *>(centroids), table, p->n_heads, 1, p->n_clusters, nh3, s) != hipSuccess)
+    if (nh3 && launch_half_norms(static_cast<const bf16_t *>(centroids), table, p->n_heads, 1, p->n_clusters, nh3, s) != hipSuccess)
         return QVG_ERR_LAUNCH;
     a.nh3 = nh3; a.nh3_stride = k_padded(p->n_clusters);
     a.x = static_cast<const bf16_t *>(x); a.stride_head = stride_head; a.stride_token = stride_token;
@@ -242,9 +243,9 @@ int qvg_encode_chunk(const qvg_params *p, int64_t n_tokens, const void *x, int64
     if (!aligned16(workspace)) return QVG_ERR_ALIGN;
     unsigned char *ws = static_cast<unsigned char *>(workspace);
     const int64_t table = (int64_t)p->n_clusters * kHeadDim, kpad = k_padded(p->n_clusters);
-    // every stage's start table is known: one launch takes all their norms
-    uint2 *init_norms = reinterpret_cast<uint2 *>(ws + w.init_norms);
-    if (launch_half_norms(static_cast<const bf16_t *>(init_centroids), S * table, p->n_heads, S, p->n_clusters, init_norms, s) != hipSuccess)
+    // every stage's start table is known: one launch takes all their norms (none for a small call)
+    uint2 *init_norms = assign_takes_norms(p->n_heads, p->n_clusters, n_tokens) ? nullptr : reinterpret_cast<uint2 *>(ws + w.init_norms);
+    if (init_norms && launch_half_norms(static_cast<const bf16_t *>(init_centroids), S * table, p->n_heads, S, p->n_clusters, init_norms, s) != hipSuccess)
         return QVG_ERR_LAUNCH;
     // input of the current smoothing stage: the caller's view first, then dense residual tensors
     const bf16_t *xin = static_cast<const bf16_t *>(x);
@@ -257,7 +258,7 @@ int qvg_encode_chunk(const qvg_params *p, int64_t n_tokens, const void *x, int64
         a.ids_step = S; a.ids_off = stage; a.id_wide = id_wide(p);
         // the caller's start tables are [H][S][K][d], the Lloyd loop's are dense
         a.cent = static_cast<const bf16_t *>(init_centroids) + stage * table; a.cent_stride = S * table;
-        a.nh3 = init_norms + stage * kpad; a.nh3_stride = S * kpad;
+        if (init_norms) { a.nh3 = init_norms + stage * kpad; a.nh3_stride = S * kpad; }
         bf16_t *buf[2] = {reinterpret_cast<bf16_t *>(ws + w.cent[0]), reinterpret_cast<bf16_t *>(ws + w.cent[1])};
         if (I > 0) {
             UpdateArgs u{};

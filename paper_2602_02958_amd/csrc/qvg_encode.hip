@@ -57,6 +57,18 @@ __device__ __forceinline__ uint32_t vgpr_const(uint32_t c) {
     return v;
 }
 
+// ||c||^2 of a row spread over 16 lanes, 8 channels each
+__device__ __forceinline__ double row_sumsq(const uint4 &v) {
+    double s = 0.0;
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const double lo = (double)bf16_lo(w[e]), hi = (double)bf16_hi(w[e]);
+        s += lo * lo; s += hi * hi;
+    }
+    return sum16_f64(s);
+}
+
 // The split norms of start tables (see split_half_norm); the tables of later Lloyd iterations get
 // theirs from the update kernel that makes them.  16 lanes per centroid, grid: x = rows, y = table of
 // the unit, z = unit.
@@ -67,14 +79,7 @@ void half_norm_kernel(const bf16_t *cent, int64_t cent_stride, int K, int Kpad, 
     if (row < K)
         v = *reinterpret_cast<const uint4 *>(cent + (int64_t)blockIdx.z * cent_stride +
                                              ((int64_t)blockIdx.y * K + row) * kHeadDim + c16 * 8);
-    double s = 0.0;
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const double lo = (double)bf16_lo(w[e]), hi = (double)bf16_hi(w[e]);
-        s += lo * lo; s += hi * hi;
-    }
-    s = sum16_f64(s);
+    const double s = row_sumsq(v);
     if (row < K && c16 == 0)
         nh3[((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * Kpad + row] = split_half_norm(s);
 }
@@ -189,7 +194,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
     for (int u = 0; u < kMaxClusters / kAsgThreads; ++u) {
         const int row = tid + u * kAsgThreads;
         nh[u] = make_uint2(__float_as_uint(-3.0e38f) >> 16, 0u);
-        if (row < K) nh[u] = a.nh3[(int64_t)h * a.nh3_stride + row];
+        if (row < K && a.nh3) nh[u] = a.nh3[(int64_t)h * a.nh3_stride + row];
     }
     const int64_t blk0 = (int64_t)blockIdx.y * tiles_per_wave * (kAsgWaves * kAsgTile);
     const bf16_t *xh = a.x + (int64_t)h * a.stride_head + half * 64;
@@ -236,17 +241,32 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
             *reinterpret_cast<uint4 *>(lc + row * kCPitch + c16 * 8) = v;
         }
     }
-    __syncthreads();                                                    // smax is zero
+    __syncthreads();                                                    // smax is zero, the rows are in place
+    auto place_norm = [&](int row, uint2 n) -> float {                  // returns an upper bound of ||c||^2 in fp32
+        *reinterpret_cast<uint4 *>(lc + row * kCPitch + kHeadDim) = make_uint4(n.x, n.y, 0u, 0u);
+        return row < K ? -2.0f * ((bf16_lo(n.x) + bf16_hi(n.x)) + bf16_lo(n.y)) * (1.0f + 0x1p-22f) : 0.0f;
+    };
+    if (!a.nh3) {                                                       // uniform: a start table of a small launch
+        float up = 0.0f;
+        const int c16 = tid & 15;
+        for (int row = tid >> 4; row < Kpad; row += kAsgThreads / 16) {  // 16 lanes per row, sums as in half_norm_kernel
+            const double sq = row_sumsq(*reinterpret_cast<const uint4 *>(lc + row * kCPitch + c16 * 8));
+            if (c16 == 0) up = fmaxf(up, place_norm(row, row < K ? split_half_norm(sq) : make_uint2(__float_as_uint(-3.0e38f) >> 16, 0u)));
+        }
 #pragma unroll
-    for (int u = 0; u < kMaxClusters / kAsgThreads; ++u) {
-        const int row = tid + u * kAsgThreads;
-        if (row < Kpad) *reinterpret_cast<uint4 *>(lc + row * kCPitch + kHeadDim) = make_uint4(nh[u].x, nh[u].y, 0u, 0u);
-        float up = 0.0f;                                                // upper bound of ||c||^2 in fp32
-        if (row < K) up = -2.0f * ((bf16_lo(nh[u].x) + bf16_hi(nh[u].x)) + bf16_lo(nh[u].y)) * (1.0f + 0x1p-22f);
-        if (u * kAsgThreads < Kpad) {                                   // uniform
+        for (int off = 32; off >= 16; off >>= 1) up = fmaxf(up, __shfl_xor(up, off, 64));
+        if (lane == 0) atomicMax(&smax, __float_as_uint(up));
+    } else {
 #pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) up = fmaxf(up, __shfl_xor(up, off, 64));
-            if (lane == 0) atomicMax(&smax, __float_as_uint(up));
+        for (int u = 0; u < kMaxClusters / kAsgThreads; ++u) {
+            const int row = tid + u * kAsgThreads;
+            float up = 0.0f;
+            if (row < Kpad) up = place_norm(row, nh[u]);
+            if (u * kAsgThreads < Kpad) {                               // uniform
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) up = fmaxf(up, __shfl_xor(up, off, 64));
+                if (lane == 0) atomicMax(&smax, __float_as_uint(up));
+            }
         }
     }
     __syncthreads();
@@ -614,6 +634,15 @@ int assign_tiles_per_wave(int H, int64_t n_tokens) {
     int tpw = 1;
     while (tpw < kMaxTilesPerWave && (steps / (2 * tpw)) * H >= 2048) tpw *= 2;
     return tpw;
+}
+
+// Start tables of up to 64 centroids: the workgroups of a small launch take the norms themselves from the staged rows,
+// which saves a launch (24 units x 4680 tokens, K = 64, I = 3 91 -> 89 us; 6 units x 4053 tokens, no iteration 22.7 -> 19.8).
+// With more centroids half_norm_kernel's once per unit is faster, however few the workgroups (K = 256: 36 against
+// 39 us at 456 of them, 22.8 against 24.1 at 24; four stages of 6 units x 2000 tokens 124 against 136).
+bool assign_takes_norms(int H, int K, int64_t n_tokens) {
+    const int64_t block = member_block(H, n_tokens), wgs = (n_tokens + block - 1) / block * H;
+    return K <= 64 && wgs <= 1024;
 }
 
 template <int B_, bool FUSED, int T_>

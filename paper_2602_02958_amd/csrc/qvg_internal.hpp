@@ -189,6 +189,7 @@ struct MemberLists {
 // tokens per assignment workgroup = 256 x this
 int assign_tiles_per_wave(int H, int64_t n_tokens);
 inline int member_block(int H, int64_t n_tokens) { return 256 * assign_tiles_per_wave(H, n_tokens); }
+bool assign_takes_norms(int H, int K, int64_t n_tokens);    // AssignArgs.nh3 may then be nullptr
 
 struct AssignArgs {
     const bf16_t *x; int64_t stride_head, stride_token; int64_t n_tokens;
@@ -199,7 +200,7 @@ struct AssignArgs {
     int64_t out_stride;      // tokens between consecutive units in ids / codes / scales
     int ids_step, ids_off;   // a token has ids_step id bytes; this pass writes byte ids_off (smoothing stage)
     int fused;
-    const uint2 *nh3; int64_t nh3_stride;      // split -||c||^2/2 per row, unit h at nh3 + h * nh3_stride
+    const uint2 *nh3; int64_t nh3_stride;      // split -||c||^2/2 per row, unit h at nh3 + h * nh3_stride; nullptr: taken here
     bf16_t *cent_copy; int64_t cent_copy_stride;   // optional: the table also goes here, unit h at h * stride elements
                                                    // (written by the unit's first workgroup while it stages the table)
     MemberLists lists;       // lists.perm: optional, the member lists of this assignment (not with fused)
