@@ -125,7 +125,7 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) O[mb][r] = 0.0f;
-    float m = -INFINITY, l = 0.0f;
+    float m = kNoScore, l = 0.0f;
     const float scale2 = a.scale * 1.4426950408889634f;
 
     uint4 rp[2];                      // (cos, sin) of the tile held in rk (ROPE only)
@@ -377,7 +377,7 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) O[mb][r] = 0.0f;
-    float m = -INFINITY, l = 0.0f;
+    float m = kNoScore, l = 0.0f;
     const float scale2 = a.scale * 1.4426950408889634f;
 
     // ---- staging: what a thread fetches for a tile ------------------------------------------

@@ -277,7 +277,7 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
             qa[kk] = qvalid ? *reinterpret_cast<const uint4 *>(qp + kk * 16) : make_uint4(0u, 0u, 0u, 0u);
     }
     floatx16_t O[4];
-    float m = -INFINITY, l = 0.0f;
+    float m = kNoScore, l = 0.0f;
     float *st = PARTS ? part_state_of(a, n_qblocks, h, qblock, part)
                             : sl.state ? sl.state + (int64_t)w * kStateFloats * kAtThreads + tid : nullptr;
     if (sl.first) {

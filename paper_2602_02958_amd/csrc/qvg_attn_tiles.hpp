@@ -75,6 +75,10 @@ __device__ __forceinline__ Tile next_tile(const Span &a, Tile t) {
 // Running state of a workgroup's 256 queries, [kStateFloats][512] floats: per thread its 64 output
 // values (unnormalised), the maximum and the lane's share of the normaliser.
 constexpr int kStateFloats = 66;
+// The running maximum before any score.  Finite: finite queries and keys can have a product below fp32's
+// range, and where all scores of a tile, or of a part, are -inf, exp2(-inf - (-inf)) would be NaN.
+// From here their weights are exp2(-inf) = 0, and a part that holds nothing else joins with weight 0.
+constexpr float kNoScore = -3.402823466e38f;
 __device__ __forceinline__ void store_state(float *st, const floatx16_t (&O)[4], float m, float l) {
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb)

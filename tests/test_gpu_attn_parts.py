@@ -87,3 +87,35 @@ def test_parts_keep_a_nan_query_in_its_row():
     assert out[1, 5].isnan().all()
     out[1, 5] = clean[1, 5]
     assert torch.equal(out, clean)
+
+
+def _constant_cache(H, n, L, ids, table):
+    """A cache whose tokens decode to the constant rows `table[id]` (all scales zero)."""
+    e = B.alloc_cache(H, n, L, len(table), 64, 1, 128, DEV)
+    e.centroids.copy_(torch.tensor(table, device=DEV).to(torch.bfloat16)[None, None, :, None].expand_as(e.centroids))
+    e.ids.copy_(ids.to(DEV, torch.uint8)[None].expand_as(e.ids))
+    e.codes.zero_()
+    e.scales.zero_()
+    return e
+
+
+@pytest.mark.parametrize("Nq,L,lend", [(64, 520, False), (33, 516, False), (300, 520, True), (300, 520, False)])
+@pytest.mark.parametrize("seen", [0, 100, 999])
+def test_scores_that_overflow_weigh_nothing(Nq, L, lend, seen):
+    """Finite queries and keys whose product is below fp32's range: those tokens have weight zero, also
+    where every token of a part (or of the first tile) is one of them.  Token `seen` is the only other."""
+    H, n = 2, 1000
+    ids = torch.zeros(n, dtype=torch.int64)
+    ids[seen] = 1
+    k = _constant_cache(H, n, L, ids, [-2e19, 0.0])
+    v = _constant_cache(H, n, L, ids, [-3.0, 1.5])
+    assert _scratch_bytes(H, Nq, n, L) > 0
+    q = torch.full((H, Nq, 128), 2e19, dtype=torch.bfloat16, device=DEV)
+    ws = B.attn_workspace(H, Nq, L, 1, DEV) if lend else torch.empty(0, dtype=torch.uint8, device=DEV)
+    lens = torch.full((Nq,), n, dtype=torch.int32, device=DEV)
+    lens[::2] = seen + 1
+    for ql in (None, lens):
+        out, lse = B.attn_decode(q, k, v, want_lse=True, workspace=ws, q_kv_len=ql)
+        torch.cuda.synchronize()
+        assert (out == 1.5).all(), (ql is None, out.flatten()[:4])
+        assert (lse == 0.0).all()                                  # one token of score 0
