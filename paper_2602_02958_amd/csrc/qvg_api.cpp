@@ -14,6 +14,11 @@ namespace {
 
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t round256(size_t v) { return (v + 255u) & ~(size_t)255u; }
+// Chunk counts and lengths: any chunk_len >= 1 is accepted (one that is not shorter than the cache, up to
+// INT64_MAX, means one chunk), so no sum with it may overflow.  The kernels and the size rules
+// get a length of at most 2^36, beyond every token count, which leaves them room for theirs.
+inline int64_t chunk_count(int64_t n_tokens, int64_t chunk_len) { return n_tokens / chunk_len + (n_tokens % chunk_len != 0); }
+inline int64_t bounded_chunk_len(int64_t chunk_len) { return chunk_len < ((int64_t)1 << 36) ? chunk_len : (int64_t)1 << 36; }
 
 int check_params(const qvg_params *p) {
     if (!p) return QVG_ERR_NULL;
@@ -385,13 +390,13 @@ int qvg_decode_ex(const qvg_params *p, int64_t n_tokens, int64_t chunk_len, int6
     if (first_token < 0 || first_token % chunk_len != 0) return QVG_ERR_BAD_PARAM;
     if (kv_capacity_tokens == 0) kv_capacity_tokens = first_token + n_tokens;
     if (kv_capacity_tokens < first_token + n_tokens) return QVG_ERR_BAD_PARAM;
-    const int64_t cap_chunks = (kv_capacity_tokens + chunk_len - 1) / chunk_len;
+    const int64_t cap_chunks = chunk_count(kv_capacity_tokens, chunk_len);
     if (cap_chunks > 0x7fffffff) return QVG_ERR_BAD_PARAM;
     if (n_tokens == 0) return QVG_OK;
     if (!centroids || !ids || !codes || !scales || !x_out) return QVG_ERR_NULL;
     if ((st = check_view(x_out, stride_head, stride_token, n_tokens)) != QVG_OK) return st;
     if (!aligned16(centroids) || !aligned16(codes) || !scales_aligned(p, scales) || !ids_aligned(p, ids)) return QVG_ERR_ALIGN;
-    const int64_t n_chunks = (n_tokens + chunk_len - 1) / chunk_len;
+    const int64_t n_chunks = chunk_count(n_tokens, chunk_len);
     if (n_chunks > 0x7fffffff) return QVG_ERR_BAD_PARAM;
     DecodeArgs a{};
     // the range starts on a chunk boundary: move the unit-0 pointers to it, keep the unit strides
@@ -404,7 +409,7 @@ int qvg_decode_ex(const qvg_params *p, int64_t n_tokens, int64_t chunk_len, int6
                                                first_token * T_ * G_ * (p->scale_format == QVG_SCALE_E4M3 ? 1 : 2));
     a.out = static_cast<bf16_t *>(x_out);
     a.kv_stride = kv_capacity_tokens; a.chunk_stride = (int)cap_chunks;
-    a.n_tokens = n_tokens; a.chunk_len = chunk_len; a.n_chunks = (int)n_chunks;
+    a.n_tokens = n_tokens; a.chunk_len = bounded_chunk_len(chunk_len); a.n_chunks = (int)n_chunks;
     a.H = p->n_heads; a.K = p->n_clusters; a.B = p->group_size; a.T = p->n_stages;
     a.stride_head = stride_head; a.stride_token = stride_token; a.S = p->n_smooth_stages; a.fmt = format_of(p);
     return launch_decode(a, static_cast<hipStream_t>(stream)) == hipSuccess ? QVG_OK : QVG_ERR_LAUNCH;
@@ -467,17 +472,17 @@ int attn_call(const qvg_params *p, int64_t n_q, const void *q, int64_t n_kv_toke
     if (!aligned16(q) || !aligned16(out) || !aligned16(out_f32) || !aligned16(k_centroids) || !aligned16(v_centroids) ||
         !aligned16(k_codes) || !aligned16(v_codes) || !scales_aligned(p, k_scales) || !scales_aligned(p, v_scales))
         return QVG_ERR_ALIGN;
-    const int64_t n_chunks = (n_kv_tokens + chunk_len - 1) / chunk_len;
+    const int64_t n_chunks = chunk_count(n_kv_tokens, chunk_len);
     if (n_chunks > 0x7fffffff) return QVG_ERR_BAD_PARAM;
     if ((n_q + 127) / 128 > 0x7fffffff) return QVG_ERR_BAD_PARAM;
     if (kv_capacity_tokens == 0) kv_capacity_tokens = n_kv_tokens;
     if (kv_capacity_tokens < n_kv_tokens) return QVG_ERR_BAD_PARAM;
-    const int64_t cap_chunks = (kv_capacity_tokens + chunk_len - 1) / chunk_len;
+    const int64_t cap_chunks = chunk_count(kv_capacity_tokens, chunk_len);
     if (cap_chunks > 0x7fffffff) return QVG_ERR_BAD_PARAM;
     if (k_rope && !aligned16(k_rope)) return QVG_ERR_ALIGN;
     AttnArgs a{};
     a.q = static_cast<const bf16_t *>(q); a.out = static_cast<bf16_t *>(out); a.out_f32 = out_f32; a.lse = lse_out;
-    a.n_q = n_q; a.n_kv = n_kv_tokens; a.chunk_len = chunk_len; a.n_chunks = (int)n_chunks;
+    a.n_q = n_q; a.n_kv = n_kv_tokens; a.chunk_len = bounded_chunk_len(chunk_len); a.n_chunks = (int)n_chunks;
     a.H = p->n_heads; a.K = p->n_clusters; a.B = p->group_size; a.T = p->n_stages;
     a.scale = softmax_scale;
     a.k_cent = static_cast<const bf16_t *>(k_centroids); a.k_ids = k_ids; a.k_codes = k_codes;
@@ -491,7 +496,7 @@ int attn_call(const qvg_params *p, int64_t n_q, const void *q, int64_t n_kv_toke
     if (!ids_aligned(p, k_ids) || !ids_aligned(p, v_ids)) return QVG_ERR_ALIGN;
     if (q_kv_len && (reinterpret_cast<uintptr_t>(q_kv_len) & 3u)) return QVG_ERR_ALIGN;
     a.q_len = q_kv_len;
-    a.parts = attn_parts(a.H, n_q, n_kv_tokens, chunk_len);
+    a.parts = attn_parts(a.H, n_q, n_kv_tokens, a.chunk_len);
     const size_t part_bytes = attn_parts_bytes(a.H, n_q, a.parts);
     if (a.parts > 1 && scratch && scratch_bytes >= part_bytes) {
         if (!aligned16(scratch)) return QVG_ERR_ALIGN;
@@ -531,7 +536,7 @@ int qvg_attn_scratch_bytes(const qvg_params *p, int64_t n_q, int64_t n_kv_tokens
     if (st != QVG_OK) return st;
     if (!out) return QVG_ERR_NULL;
     if (n_q < 0 || n_kv_tokens < 1 || n_kv_tokens > 0x7fffffff || chunk_len < 1) return QVG_ERR_BAD_PARAM;
-    *out = attn_parts_bytes(p->n_heads, n_q, attn_parts(p->n_heads, n_q, n_kv_tokens, chunk_len));
+    *out = attn_parts_bytes(p->n_heads, n_q, attn_parts(p->n_heads, n_q, n_kv_tokens, bounded_chunk_len(chunk_len)));
     return QVG_OK;
 }
 
