@@ -43,31 +43,32 @@ struct Span {                      // the part of the cache a workgroup walks: t
     int64_t chunk_len, n_kv; int n_chunks;
     int tpc, part, parts;          // tpc: tiles per chunk = ceil(chunk_len / 64)
 };
-__device__ __forceinline__ Span span_of(const AttnArgs &a, int part) {
+__host__ __device__ __forceinline__ Span span_of(const AttnArgs &a, int part) {
     Span s; s.chunk_len = a.chunk_len; s.n_kv = a.n_kv; s.n_chunks = a.n_chunks;
     const int64_t l = a.chunk_len < a.n_kv ? a.chunk_len : a.n_kv;
     s.tpc = (int)((l + kAtKv - 1) / kAtKv); s.part = part; s.parts = a.parts;
     return s;
 }
-// Where (t.chunk, t.ti) is once t.ti may have run past its chunk
-__device__ __forceinline__ Tile place_tile(const Span &a, Tile t) {
+// Where (t.chunk, t.ti) is once t.ti may have run past its chunk.  (The position is compared in 64 bits: a
+// step of `parts` tiles past the end of a cache of nearly 2^31 tokens does not fit 31.)
+__host__ __device__ __forceinline__ Tile place_tile(const Span &a, Tile t) {
     if (t.ti >= a.tpc) { const int c = t.ti / a.tpc; t.chunk += c; t.ti -= c * a.tpc; }
     t.valid = t.chunk < a.n_chunks;
     if (t.valid) {
-        const int64_t b = (int64_t)t.chunk * a.chunk_len;
-        t.t0 = (int)(b + (int64_t)t.ti * kAtKv);
-        t.cend = (int)((b + a.chunk_len < a.n_kv) ? b + a.chunk_len : a.n_kv);
-        t.valid = t.t0 < t.cend;
+        const int64_t b = (int64_t)t.chunk * a.chunk_len, t0 = b + (int64_t)t.ti * kAtKv;
+        const int64_t cend = (b + a.chunk_len < a.n_kv) ? b + a.chunk_len : a.n_kv;
+        t.valid = t0 < cend;
+        t.t0 = (int)t0; t.cend = (int)cend;
     }
     if (!t.valid) { t.chunk = a.n_chunks - 1; t.t0 = 0; t.cend = 0; }
     return t;
 }
-__device__ __forceinline__ Tile first_tile(const Span &a) {
+__host__ __device__ __forceinline__ Tile first_tile(const Span &a) {
     Tile t;
     t.chunk = 0; t.ti = a.part; t.t0 = 0; t.cend = 0;
     return place_tile(a, t);
 }
-__device__ __forceinline__ Tile next_tile(const Span &a, Tile t) {
+__host__ __device__ __forceinline__ Tile next_tile(const Span &a, Tile t) {
     t.ti += a.parts;
     return place_tile(a, t);
 }

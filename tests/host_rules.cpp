@@ -1,0 +1,42 @@
+// Device rules that are plain arithmetic, run on the CPU (test_host_rules.py compiles this file for the
+// host only).  Prints one line per rule: its name, then "ok" or what is wrong.
+#include <cstdio>
+
+#include "qvg_attn_tiles.hpp"
+
+using namespace qvg;
+
+// every tile of the cache belongs to exactly one part, in order, and none lies past the end
+static const char *tiles_of(int64_t n_kv, int64_t chunk_len, int parts, bool ends_only) {
+    AttnArgs a{};
+    a.n_kv = n_kv; a.chunk_len = chunk_len; a.n_chunks = (int)((n_kv - 1) / chunk_len + 1); a.parts = parts;
+    const int64_t tpc = span_of(a, 0).tpc;
+    for (int p = 0; p < parts; ++p) {
+        const Span s = span_of(a, p);
+        Tile t = first_tile(s);
+        int64_t g = p;                                     // the tile's number in the cache
+        if (ends_only && t.valid) {                        // start near the end instead
+            const int64_t last = (int64_t)(a.n_chunks - 1) * tpc + (n_kv - (int64_t)(a.n_chunks - 1) * chunk_len + kAtKv - 1) / kAtKv - 1;
+            g = last - (last - p) % parts;
+            t.chunk = (int)(g / tpc); t.ti = (int)(g % tpc);
+            t = place_tile(s, t);
+        }
+        for (; t.valid; t = next_tile(s, t), g += parts) {
+            if (t.chunk != g / tpc || t.ti != g % tpc) return "order";
+            if (t.t0 < 0 || t.t0 >= n_kv || t.cend > n_kv || t.t0 >= t.cend) return "range";
+            if (t.t0 != t.chunk * chunk_len + t.ti * kAtKv) return "position";
+        }
+        if (g % tpc == 0 && g / tpc < a.n_chunks) return "end";
+    }
+    return "ok";
+}
+
+int main() {
+    std::printf("tiles_small %s\n", tiles_of(1000, 130, 3, false));
+    std::printf("tiles_one_chunk %s\n", tiles_of(8191, (int64_t)1 << 36, 16, false));
+    const int64_t top = 0x7fffffff;
+    std::printf("tiles_top %s\n", tiles_of(top, 4680, 256, true));
+    std::printf("tiles_top_one_chunk %s\n", tiles_of(top, (int64_t)1 << 36, 256, true));
+    std::printf("tiles_top_undivided %s\n", tiles_of(top, (int64_t)1 << 36, 1, true));
+    return 0;
+}
