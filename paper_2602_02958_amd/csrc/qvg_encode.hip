@@ -244,7 +244,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
     __syncthreads();                                                    // smax is zero, the rows are in place
     auto place_norm = [&](int row, uint2 n) -> float {                  // returns an upper bound of ||c||^2 in fp32
         *reinterpret_cast<uint4 *>(lc + row * kCPitch + kHeadDim) = make_uint4(n.x, n.y, 0u, 0u);
-        return row < K ? -2.0f * ((bf16_lo(n.x) + bf16_hi(n.x)) + bf16_lo(n.y)) * (1.0f + 0x1p-22f) : 0.0f;
+        return row < K ? norm_bound(n) : 0.0f;
     };
     if (!a.nh3) {                                                       // uniform: a start table of a small launch
         float up = 0.0f;

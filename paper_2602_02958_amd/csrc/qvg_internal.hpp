@@ -168,13 +168,12 @@ hipError_t launch_decode(const DecodeArgs &a, hipStream_t s);
 // bf16 pieces (truncated, 8 significant bits each: hi + mid + lo == nh exactly), .x = hi | mid << 16,
 // .y = lo; one row of Kpad entries per unit.
 __host__ __device__ inline int k_padded(int K) { return (K + 63) & ~63; }
-__device__ __forceinline__ uint2 split_half_norm(double sumsq) {
+__host__ __device__ __forceinline__ uint2 split_half_norm(double sumsq) {
+    auto bits = [](float v) { return __builtin_bit_cast(uint32_t, v); };
+    auto head = [&](float v) { return __builtin_bit_cast(float, bits(v) & 0xffff0000u); };
     const float nh = (float)(-0.5 * sumsq);
-    const float hi = __uint_as_float(__float_as_uint(nh) & 0xffff0000u);
-    const float r1 = nh - hi;
-    const float mid = __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
-    const float lo = __uint_as_float(__float_as_uint(r1 - mid) & 0xffff0000u);
-    return make_uint2((__float_as_uint(hi) >> 16) | (__float_as_uint(mid) & 0xffff0000u), __float_as_uint(lo) >> 16);
+    const float hi = head(nh), r1 = nh - hi, mid = head(r1), lo = head(r1 - mid);
+    return make_uint2((bits(hi) >> 16) | (bits(mid) & 0xffff0000u), bits(lo) >> 16);
 }
 
 // Member lists.  The tokens of a unit are split into blocks of `block` (the tokens of one workgroup of

@@ -51,6 +51,16 @@ __device__ __forceinline__ int scan64(int v) {
     return v;
 }
 
+// Upper bound (one ulp up) of ||c||^2 from the split of -||c||^2 / 2.  Never -0: the largest bound of a
+// table is found by comparing bit patterns as unsigned numbers, where 0x80000000 would be above every norm
+// (a zero row's split is +0, and -2 times it -0: 64 zero rows of one wavefront then hid the table's
+// largest norm from the certification).
+__host__ __device__ __forceinline__ float norm_bound(uint2 split) {
+    const float hi = __builtin_bit_cast(float, split.x << 16), mid = __builtin_bit_cast(float, split.x & 0xffff0000u);
+    const float lo = __builtin_bit_cast(float, split.y << 16);
+    return 2.0f * __builtin_fabsf((hi + mid) + lo) * (1.0f + 0x1p-22f);
+}
+
 // LDS of block_member_sort: counters per wavefront and cluster, wavefront totals of the scan
 __host__ __device__ inline size_t member_sort_bytes(int K) { return (size_t)(kAsgWaves * k_padded(K) + 8) * sizeof(int); }
 

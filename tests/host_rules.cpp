@@ -3,6 +3,7 @@
 #include <cstdio>
 
 #include "qvg_attn_tiles.hpp"
+#include "qvg_kmeans.hpp"
 
 using namespace qvg;
 
@@ -31,7 +32,24 @@ static const char *tiles_of(int64_t n_kv, int64_t chunk_len, int parts, bool end
     return "ok";
 }
 
+// bounds of squared norms: not below the norm, at most 2^-21 above it, and ordered as bit patterns
+static const char *norm_bounds() {
+    uint32_t prev = 0;
+    double v = 0.0;
+    for (int i = 0; i < 4000; ++i) {
+        const float b = norm_bound(split_half_norm(v));
+        const uint32_t u = __builtin_bit_cast(uint32_t, b);
+        if (u & 0x80000000u) return "sign";
+        if ((double)b < v || (double)b > v * (1.0 + 0x1p-21)) return "bound";
+        if (u < prev) return "order";
+        prev = u;
+        v = v == 0.0 ? 0x1p-100 : v * 1.0353;              // to about 2^100
+    }
+    return "ok";
+}
+
 int main() {
+    std::printf("norm_bounds %s\n", norm_bounds());
     std::printf("tiles_small %s\n", tiles_of(1000, 130, 3, false));
     std::printf("tiles_one_chunk %s\n", tiles_of(8191, (int64_t)1 << 36, 16, false));
     const int64_t top = 0x7fffffff;

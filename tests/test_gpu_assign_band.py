@@ -45,3 +45,24 @@ def test_ids_equal_the_oracle(K, kind):
     for h in range(H):
         want = O.assign(bits_to_f32(bf16_bits(xb)[h]), bf16_bits(cb)[h])
         assert np.array_equal(got[h].astype(np.int64), want.astype(np.int64)), (h, np.flatnonzero(got[h] != want)[:5])
+
+
+@pytest.mark.parametrize("K,first", [(128, 0), (128, 64), (256, 64), (256, 192), (512, 128), (512, 448)])
+def test_a_block_of_zero_rows_beside_near_ties(K, first):
+    """64 zero rows that one wavefront places (the table's largest norm must survive them), the others in
+    pairs one unit of the last place apart."""
+    H, N, d = 2, 333, 128
+    g = torch.Generator().manual_seed(K + first)
+    c = torch.randn(H, K, d, generator=g) * torch.exp(torch.randn(H, K, 1, generator=g))
+    c[:, 1::2] = c[:, ::2] * (1.0 + 2.0 ** -8)
+    c[:, first:first + 64] = 0.0
+    pick = torch.randint(0, K, (H, N), generator=g)
+    x = torch.gather(c, 1, pick[:, :, None].expand(-1, -1, d))
+    x = 1.5 * x + 0.05 * x.abs().mean(-1, keepdim=True) * torch.randn(H, N, d, generator=g)
+    x[:, ::7] = 0.0
+    xb, cb = x.to(torch.bfloat16), c.to(torch.bfloat16)
+    ids = B.kmeans_assign(xb.to(DEV), cb.to(DEV))
+    got = P.to_np_u8(ids) if K <= 256 else P.to_np_u16(ids)
+    for h in range(H):
+        want = O.assign(bits_to_f32(bf16_bits(xb)[h]), bf16_bits(cb)[h])
+        assert np.array_equal(got[h].astype(np.int64), want.astype(np.int64)), (h, np.flatnonzero(got[h] != want)[:5])
