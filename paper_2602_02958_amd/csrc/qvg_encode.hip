@@ -543,7 +543,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
             // tokens, K = 128, I = 3: 0.88 to 1.68 ms, by the draw, against 0.56 to 0.58).
             // d^2 = ||x||^2 - 2 score, with 2^-10 of slack on both terms for the rounding of the score.
             const float d2 = fmaxf(xn[tb] - 2.0f * c1, 0.0f) * (1.0f + 0x1p-10f) + xn[tb] * 0x1p-10f;
-            const float reach = (xn[tb] + d2 + 2.0f * __builtin_amdgcn_sqrtf(xn[tb] * d2)) * (1.0f + 0x1p-10f);
+            const float reach = norm_reach(xn[tb], d2, [](float v) { return __builtin_amdgcn_sqrtf(v); });
             // (the last term: the tag of a score that is zero, where all norms are)
             const float thr = (K > 256 ? 0x1.8p-14f : 0x1p-14f) * (0.5f * xn[tb] + fminf(cmax, reach)) + 0x1p-126f;
             int id = i1;

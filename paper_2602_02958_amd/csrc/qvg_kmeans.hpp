@@ -61,6 +61,15 @@ __host__ __device__ __forceinline__ float norm_bound(uint2 split) {
     return 2.0f * __builtin_fabsf((hi + mid) + lo) * (1.0f + 0x1p-22f);
 }
 
+// Largest ||c||^2 that can matter to a token of squared norm xn at squared distance d2 from its leader:
+// (||x|| + d)^2.  fast_sqrt: a square root good to a few ulp that may flush subnormals.  2^-120 stands
+// in for a product below fp32's range (its root, 2^-60, is above the true one's 2^-63), which would
+// otherwise halve the result for tokens of norm 2^-32 and less.
+template <class F>
+__host__ __device__ __forceinline__ float norm_reach(float xn, float d2, F fast_sqrt) {
+    return (xn + d2 + 2.0f * fast_sqrt(__builtin_fmaf(xn, d2, 0x1p-120f))) * (1.0f + 0x1p-10f);
+}
+
 // LDS of block_member_sort: counters per wavefront and cluster, wavefront totals of the scan
 __host__ __device__ inline size_t member_sort_bytes(int K) { return (size_t)(kAsgWaves * k_padded(K) + 8) * sizeof(int); }
 

@@ -1,5 +1,6 @@
 // Device rules that are plain arithmetic, run on the CPU (test_host_rules.py compiles this file for the
 // host only).  Prints one line per rule: its name, then "ok" or what is wrong.
+#include <cmath>
 #include <cstdio>
 
 #include "qvg_attn_tiles.hpp"
@@ -48,7 +49,24 @@ static const char *norm_bounds() {
     return "ok";
 }
 
+// the reach is not below (||x|| + d)^2, from the smallest normal numbers to where the sum overflows; the
+// device's square root flushes subnormals
+static const char *norm_reaches() {
+    auto flushing = [](float v) { return v < 0x1p-126f ? 0.0f : sqrtf(v); };
+    for (int i = -126; i < 127; ++i)
+        for (int j = -126; j < 127; ++j) {
+            const float xn = ldexpf(1.37f, i), d2 = ldexpf(1.61f, j);
+            const double want = pow(sqrt((double)xn) + sqrt((double)d2), 2.0);
+            const double got = norm_reach(xn, d2, flushing);
+            if (got < want) return "below";
+            if ((double)xn * d2 > 3.4e38) continue;          // the product overflows: the reach is infinite, the table's own norms limit the band
+            if (got > want * (1.0 + 0x1p-8) + 0x1p-58) return "above";
+        }
+    return "ok";
+}
+
 int main() {
+    std::printf("norm_reaches %s\n", norm_reaches());
     std::printf("norm_bounds %s\n", norm_bounds());
     std::printf("tiles_small %s\n", tiles_of(1000, 130, 3, false));
     std::printf("tiles_one_chunk %s\n", tiles_of(8191, (int64_t)1 << 36, 16, false));
