@@ -66,7 +66,8 @@ EncodeWs encode_ws(const qvg_params *p, int64_t N, bool with_assign, bool with_t
     if (with_update) {
         const int64_t block = member_block(p->n_heads, N), n_blocks = N > 0 ? (N + block - 1) / block : 1;
         w.perm = o; o += round256((size_t)p->n_heads * (size_t)(n_blocks * block) * sizeof(uint16_t));
-        w.seg = o; o += round256((size_t)p->n_heads * (size_t)n_blocks * (size_t)p->n_clusters * sizeof(uint32_t));
+        // (a workspace must serve every call of fewer tokens or units)
+        w.seg = o; o += round256((size_t)member_blocks_bound(p->n_heads, N) * (size_t)p->n_clusters * sizeof(uint32_t));
     }
     // bf16 residual tensors that carry the data from one smoothing stage to the next
     if (with_assign && p->n_smooth_stages > 1) {

@@ -629,11 +629,22 @@ static size_t assign_smem_bytes(int Kpad) {
 
 // 256-token steps per workgroup: more of them amortise the table staging once there are enough
 // workgroups to fill the chip several times over
+constexpr int64_t kAsgManyGroups = 2048;
 int assign_tiles_per_wave(int H, int64_t n_tokens) {
     const int64_t steps = (n_tokens + kAsgWaves * kAsgTile - 1) / (kAsgWaves * kAsgTile);
     int tpw = 1;
-    while (tpw < kMaxTilesPerWave && (steps / (2 * tpw)) * H >= 2048) tpw *= 2;
+    while (tpw < kMaxTilesPerWave && (steps / (2 * tpw)) * H >= kAsgManyGroups) tpw *= 2;
     return tpw;
+}
+
+// The blocks themselves get fewer where the steps per workgroup double, and a workspace sized by them would not
+// serve a shorter call.  With one step per workgroup there are at most 2 (kAsgManyGroups - 1) + H blocks, with
+// two 2 (kAsgManyGroups - 1) + 2 H, with four the number itself.
+int64_t member_blocks_bound(int H, int64_t n_tokens) {
+    const int64_t steps = (n_tokens + kAsgWaves * kAsgTile - 1) / (kAsgWaves * kAsgTile), h = H;
+    const int64_t fewest = h * ((steps + kMaxTilesPerWave - 1) / kMaxTilesPerWave), most = 2 * (kAsgManyGroups - 1) + 2 * h;
+    const int64_t bound = most > fewest ? most : fewest;
+    return h * steps < bound ? h * steps : bound;
 }
 
 // Start tables of up to 64 centroids: the workgroups of a small launch take the norms themselves from the staged rows,
