@@ -281,6 +281,9 @@ def _scratch(nbytes: int, device):
 # An attn_decode that is lent no workspace takes one for itself when a unit has three query blocks or more:
 # 40 heads over 31997 tokens, 900 queries 2.90 -> 1.10 ms, 12 heads x 600 queries over 20000 195 -> 170 us; with two
 # blocks the one-kernel form is as fast or faster (40 heads x 300 queries over 20000 305 against 418 us).
+# Not with a prefix length per query: the workspace decodes every tile of the cache, however short the prefixes
+# (which only the device knows), the one-kernel form those below the longest (12 heads x 600 queries that see
+# 300 of 74880 tokens: 235 us with one, 26 without).
 TILE_SCRATCH_MIN_QUERIES = 512
 TILE_SCRATCH_BYTES = 256 << 20
 
@@ -305,8 +308,9 @@ def attn_decode(q, k: Encoded, v: Encoded, softmax_scale=None, want_lse=False, o
     f32_out: the result as float32, before the rounding to bf16;
     workspace: uint8 tensor (attn_workspace): every tile is then decoded once per unit into it and
     shared by all query blocks, a slab of chunks at a time, instead of once per 256 queries.  Without
-    one, calls of more than 512 queries take up to 256 MiB for the call from torch's allocator; one
-    that is too small for a chunk (an empty tensor) is ignored."""
+    one, calls of more than 512 queries and no q_kv_len take up to 256 MiB for the call from torch's
+    allocator; one that is too small for a chunk (an empty tensor) is ignored.  Worth lending with
+    q_kv_len too, unless the prefixes are short: every tile of the cache is decoded."""
     if (v.ids.shape, v.codes.shape, v.scales.shape, v.scales.dtype, v.centroids.shape, v.chunk_len, v.n_smooth) != \
             (k.ids.shape, k.codes.shape, k.scales.shape, k.scales.dtype, k.centroids.shape, k.chunk_len, k.n_smooth):
         raise ValueError("K and V caches must share shapes and parameters")
@@ -354,7 +358,7 @@ def _attn(q, k: Encoded, kp, vp, softmax_scale, want_lse, out, n_kv, k_rope, q_k
     if st != 0:
         raise QvgError(st, "qvg_attn_scratch_bytes")
     scratch = _scratch(need.value, q.device)
-    if workspace is None and Nq > TILE_SCRATCH_MIN_QUERIES:
+    if workspace is None and q_kv_len is None and Nq > TILE_SCRATCH_MIN_QUERIES:
         workspace = _tile_scratch(H, Nq, k.chunk_len, -(-Nk // k.chunk_len), q.device)
     st = lib().qvg_attn_decode_parts(C.byref(p), Nq, _ptr(q), Nk, k.chunk_len, cap,
                                      *kp, *vp, _ptr(k_rope), _ptr(q_kv_len), softmax_scale,
