@@ -150,10 +150,7 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
 
     // ---- prologue: tile 0 into buffer 0, raw data of tile 1 in flight -------------------
     Tile cur = first_tile(sp);
-    if (!cur.valid) {                // uniform: a part that lies behind the longest prefix
-        if (qvalid) store_state(part_state_of(a, n_qblocks, h, qblock, part), O, m, l);
-        return;
-    }
+    if (!cur.valid) return;          // uniform: a part behind the longest prefix, which the join does not read
     Tile nxt = next_tile(sp, cur);
     Tile nn = nxt.valid ? next_tile(sp, nxt) : nxt;
     uint32_t idk[2], idv[2];
@@ -558,10 +555,7 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
         wmin = __builtin_amdgcn_readfirstlane(wmin);
     }
     Tile cur = first_tile(sp);
-    if (!cur.valid) {                // uniform: a part that lies behind the longest prefix
-        if (qvalid) store_state(part_state_of(a, n_qblocks, h, qblock, part), O, m, l);
-        return;
-    }
+    if (!cur.valid) return;          // uniform: a part behind the longest prefix, which the join does not read
     Tile nxt = next_tile(sp, cur);
     Tile nn = nxt.valid ? next_tile(sp, nxt) : nxt;
     Tile n3 = nn.valid ? next_tile(sp, nn) : nn;
@@ -907,8 +901,9 @@ size_t attn_parts_bytes(int H, int64_t n_q, int parts) {
 
 // The result of a query from the states of its parts: one workgroup per query block and 8 of a lane's
 // 64 values, threads as in the kernels that left the states.  A part whose first tile lies behind
-// the query's prefix saw none of its tokens and is left out (its sums may be anything).  A chain of
-// loads: several parts are requested before the first is used (one at a time, 16 parts took 17 us).
+// the query's prefix saw none of its tokens and is left out (its sums may be anything; behind all prefixes of the
+// block it leaves none: 64 queries of one head that see one of 74880 tokens, 256 parts, 54 us when all of them were
+// written and read).  A chain of loads: several parts are requested before the first is used (one at a time, 16 parts took 17 us).
 constexpr int kJoinAhead = 8;
 __global__ __launch_bounds__(kAtThreads)
 void attn_join_kernel(AttnArgs a, int n_qblocks) {
@@ -916,34 +911,44 @@ void attn_join_kernel(AttnArgs a, int n_qblocks) {
     const int v0 = blockIdx.y * 8;                                       // channels 32 * (v0 / 16) + 8 * (v / 4 % 4) + 4 * half + v % 4
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, half = lane >> 5;
     const int64_t qrow = (int64_t)qblock * kAtQPerBlock + wave * 32 + col;
-    if (qrow >= a.n_q) return;                                           // both lane halves of a query
+    const bool qvalid = qrow < a.n_q;                                    // the same for both lane halves of a query
     const float *st = part_state_of(a, n_qblocks, h, qblock, 0);
     const int64_t pitch = (int64_t)a.H * n_qblocks * kStateFloats * kAtThreads;
-    int seen = a.parts;                                                  // the parts that saw a token are the first ones
-    if (a.q_len) {
-        const int nk = (int)a.n_kv, clen = a.chunk_len < a.n_kv ? (int)a.chunk_len : nk;
-        int qlen = a.q_len[qrow];
-        qlen = qlen < 0 ? 0 : (qlen > nk ? nk : qlen);
-        const int full = qlen / clen, rest = qlen - full * clen;
-        const int64_t tiles = (int64_t)full * ((clen + kAtKv - 1) / kAtKv) + (rest + kAtKv - 1) / kAtKv;
-        if (tiles < seen) seen = (int)tiles;
+    // the parts that saw a token of the query are the first ones; the wavefront reads those of its longest prefix (the
+    // block's workgroups that lay behind all of its prefixes left nothing)
+    int seen = a.parts, read = a.parts;
+    if (a.q_len) {                                                       // uniform
+        seen = 0;
+        if (qvalid) {
+            const int nk = (int)a.n_kv, clen = a.chunk_len < a.n_kv ? (int)a.chunk_len : nk;
+            int qlen = a.q_len[qrow];
+            qlen = qlen < 0 ? 0 : (qlen > nk ? nk : qlen);
+            const int full = qlen / clen, rest = qlen - full * clen;
+            const int64_t tiles = (int64_t)full * ((clen + kAtKv - 1) / kAtKv) + (rest + kAtKv - 1) / kAtKv;
+            seen = tiles < a.parts ? (int)tiles : a.parts;
+        }
+        read = seen;
+#pragma unroll
+        for (int off = 16; off >= 1; off >>= 1) { const int o = __shfl_xor(read, off, 64); read = o > read ? o : read; }
+        read = __builtin_amdgcn_readfirstlane(read);
     }
+    if (!qvalid) return;
     float m = -INFINITY, l = 0.0f, o[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] = 0.0f;
-    for (int p0 = 0; p0 < a.parts; p0 += kJoinAhead) {
+    for (int p0 = 0; p0 < read; p0 += kJoinAhead) {
         float mp[kJoinAhead];
 #pragma unroll
-        for (int u = 0; u < kJoinAhead; ++u) mp[u] = st[(p0 + u < a.parts ? p0 + u : 0) * pitch + 64 * kAtThreads];
+        for (int u = 0; u < kJoinAhead; ++u) mp[u] = st[(p0 + u < read ? p0 + u : 0) * pitch + 64 * kAtThreads];
 #pragma unroll
         for (int u = 0; u < kJoinAhead; ++u) m = p0 + u < seen ? fmaxf(m, mp[u]) : m;
     }
     constexpr int kRows = 4;
-    for (int p0 = 0; p0 < a.parts; p0 += kRows) {
+    for (int p0 = 0; p0 < read; p0 += kRows) {
         float x[kRows][10];
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
-            const float *sp = st + (p0 + u < a.parts ? p0 + u : 0) * pitch;
+            const float *sp = st + (p0 + u < read ? p0 + u : 0) * pitch;
 #pragma unroll
             for (int i = 0; i < 8; ++i) x[u][i] = sp[(v0 + i) * kAtThreads];
             x[u][8] = sp[64 * kAtThreads]; x[u][9] = sp[65 * kAtThreads];

@@ -313,6 +313,10 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
         __syncthreads();
         wgmax = bmax;
         wmin = __builtin_amdgcn_readfirstlane(wmin);
+        if (PARTS) {                 // a part behind the longest prefix (its first tile is tile `part`): the join does not read it
+            const int64_t full = wgmax / a.chunk_len, rest = wgmax - full * a.chunk_len;
+            if (part >= full * sl.tpc + (rest + kAtKv - 1) / kAtKv) return;                              // uniform
+        }
     }
 
     // a thread's four 16-byte pieces of a tile: K pieces tid, tid + 512 (row p / 16, group p % 16),

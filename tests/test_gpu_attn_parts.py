@@ -119,3 +119,51 @@ def test_scores_that_overflow_weigh_nothing(Nq, L, lend, seen):
         torch.cuda.synchronize()
         assert (out == 1.5).all(), (ql is None, out.flatten()[:4])
         assert (lse == 0.0).all()                                  # one token of score 0
+
+
+def _decode_parts(q, k, v, lens, scratch, ws=None):
+    """qvg_attn_decode_parts (or, without scratch, the undivided call) on caches of one format."""
+    H, Nq, d = q.shape
+    out = torch.empty_like(q)
+    T, G = k.codes.shape[2], k.scales.shape[3]
+    p = B.make_params(H, k.centroids.shape[-2], d // G, T, n_smooth_stages=k.n_smooth, bits=k.bits, scale_format=k.scale_format)
+    ptr = lambda t: None if t is None else t.data_ptr()
+    st = B.lib().qvg_attn_decode_parts(
+        B.C.byref(p), Nq, ptr(q), k.ids.shape[1], k.chunk_len, 0, ptr(k.centroids), ptr(k.ids), ptr(k.codes), ptr(k.scales),
+        ptr(v.centroids), ptr(v.ids), ptr(v.codes), ptr(v.scales), None, ptr(lens), d ** -0.5, ptr(out), None, None,
+        ptr(ws), 0 if ws is None else ws.numel(), ptr(scratch), 0 if scratch is None else scratch.numel(),
+        torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    return out
+
+
+@pytest.mark.parametrize("Nq,L,lend", [(64, 520, False), (33, 516, False), (300, 520, True)])
+@pytest.mark.parametrize("longest", [0, 1, 65, 700])
+def test_parts_behind_every_prefix_leave_no_state(Nq, L, lend, longest):
+    """A call of short prefixes over a long cache costs what its prefixes cost: the parts that lie behind
+    the longest one write no state, and the join does not read it."""
+    H, n = 2, 4160
+    kc, vc = _filled_caches(H, L, -(-n // L), n, 16, 64, 2)
+    kc, vc = (B.Encoded(c.centroids, c.ids[:, :n].contiguous(), c.codes[:, :n].contiguous(), c.scales[:, :n].contiguous(),
+                        c.chunk_len) for c in (kc, vc))
+    q = synth.queries(CONFIGS["cfg2_window21"], H, Nq, DEV)
+    need = _scratch_bytes(H, Nq, n, L)
+    state = 66 * 512 * 4                                   # of a query block (256 queries)
+    blocks = H * -(-Nq // 256)
+    parts = need // (blocks * state)
+    assert parts > 12
+    scratch = torch.full((need,), 0x7F, dtype=torch.uint8, device=DEV)      # as floats: 3.4e38
+    lens = torch.full((Nq,), longest, dtype=torch.int32, device=DEV)
+    lens[::3] = min(longest, 2)
+    ws = B.attn_workspace(H, Nq, L, 2, DEV) if lend else None
+    out = _decode_parts(q, kc, vc, lens, scratch, ws)
+    one = _decode_parts(q, kc, vc, lens, None, ws)
+    torch.cuda.synchronize()
+    full, rest = divmod(longest, L)
+    tiles = full * -(-L // 64) + -(-rest // 64)
+    touched = (scratch.view(parts, blocks * state) != 0x7F).any(1)
+    assert touched[:tiles].all() and not touched[max(tiles, 1):].any()
+    if longest == 0:
+        assert not out.any()
+    # one output's rounding and the order of the sums apart
+    assert (out.float() - one.float()).abs().max() <= 2 ** -8 * one.float().abs().max() + 2e-3
