@@ -53,7 +53,6 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     if (w >= n_blocks) return;                                          // uniform, before any barrier
     const int h = w / (n_qblocks * a.parts);
     const int qblock = (w - h * n_qblocks * a.parts) / a.parts;
-    const int part = w % a.parts;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
@@ -63,7 +62,7 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     // query sees tokens 0 .. qlen-1; wmin = the shortest prefix in the wavefront (tiles below it
     // need no mask); the workgroup walks the cache only up to its longest prefix.
     int qlen = 0x7fffffff, wmin = 0x7fffffff;
-    Span sp = span_of(a, part);
+    Span sp = span_of(a, w % a.parts);
     if (QL) {
         __shared__ int bmax;
         if (tid == 0) bmax = 1;
@@ -79,7 +78,7 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
         }
         if (lane == 0) atomicMax(&bmax, mx);
         __syncthreads();
-        sp.n_kv = bmax;
+        sp.n_kv = __builtin_amdgcn_readfirstlane(bmax);
         sp.n_chunks = (int)((sp.n_kv + sp.chunk_len - 1) / sp.chunk_len);
         wmin = __builtin_amdgcn_readfirstlane(wmin);
     }
@@ -290,8 +289,9 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
         nn = nn.valid ? next_tile(sp, nn) : nn;
     }
     // ---- normalise and store: lane holds channels 32*mb + 8*g + 4*half + 0..3 of its query ----
-    if (a.parts > 1) { if (qvalid) store_state(part_state_of(a, n_qblocks, h, qblock, part), O, m, l); }
-    else store_result(a, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
+    const AttnArgs &e = late_args();
+    if (e.parts > 1) { if (qvalid) store_state(part_state_of_block(e, n_qblocks, blocks_per_xcd), O, m, l); }
+    else store_result(e, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
 }
 
 
@@ -336,7 +336,6 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     if (w >= n_blocks) return;                                          // uniform, before any barrier
     const int h = w / (n_qblocks * a.parts);
     const int qblock = (w - h * n_qblocks * a.parts) / a.parts;
-    const int part = w % a.parts;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);          // uniform: lets whole waves branch
@@ -534,7 +533,7 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     // QL: the lane's query sees tokens 0 .. qlen-1; wmin = the shortest prefix in the wavefront
     // (tiles below it need no mask); the workgroup walks the cache up to its longest prefix only
     int qlen = 0x7fffffff, wmin = 0x7fffffff;
-    Span sp = span_of(a, part);
+    Span sp = span_of(a, w % a.parts);
     if (QL) {
         __shared__ int bmax;
         if (tid == 0) bmax = 1;
@@ -550,7 +549,7 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
         }
         if (lane == 0) atomicMax(&bmax, mx);
         __syncthreads();
-        sp.n_kv = bmax;
+        sp.n_kv = __builtin_amdgcn_readfirstlane(bmax);
         sp.n_chunks = (int)((sp.n_kv + sp.chunk_len - 1) / sp.chunk_len);
         wmin = __builtin_amdgcn_readfirstlane(wmin);
     }
@@ -723,8 +722,9 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
         while (is_full(cur) && is_full(nxt) && is_full(nn)) tile_step(BoolC<true>{}, decode_first);
         if (!tile_step(BoolC<false>{}, false)) break;
     }
-    if (a.parts > 1) { if (qvalid) store_state(part_state_of(a, n_qblocks, h, qblock, part), O, m, l); }
-    else store_result(a, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
+    const AttnArgs &e = late_args();
+    if (e.parts > 1) { if (qvalid) store_state(part_state_of_block(e, n_qblocks, blocks_per_xcd), O, m, l); }
+    else store_result(e, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
 }
 
 template <int T_, bool ROPE, bool FP8, bool I4, bool WIDE, bool QL = false>

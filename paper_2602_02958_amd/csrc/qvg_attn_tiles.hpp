@@ -36,41 +36,47 @@ struct CacheSide {                 // one of K / V, already offset to this unit
 };
 
 struct Tile {                      // one 64-token tile; tiles never straddle a chunk
-    int chunk, ti; int t0, cend; bool valid; // ti-th tile of its chunk; token indices fit 31 bits (checked by the caller)
+    int chunk; int t0, cend; bool valid;     // token indices fit 31 bits (checked by the caller)
 };
 
 struct Span {                      // the part of the cache a workgroup walks: tiles part, part + parts, ...
     int64_t chunk_len, n_kv; int n_chunks;
-    int tpc, part, parts;          // tpc: tiles per chunk = ceil(chunk_len / 64)
+    int part, parts;
 };
 __host__ __device__ __forceinline__ Span span_of(const AttnArgs &a, int part) {
     Span s; s.chunk_len = a.chunk_len; s.n_kv = a.n_kv; s.n_chunks = a.n_chunks;
-    const int64_t l = a.chunk_len < a.n_kv ? a.chunk_len : a.n_kv;
-    s.tpc = (int)((l + kAtKv - 1) / kAtKv); s.part = part; s.parts = a.parts;
+    s.part = part; s.parts = a.parts;
     return s;
 }
-// Where (t.chunk, t.ti) is once t.ti may have run past its chunk.  (The position is compared in 64 bits: a
-// step of `parts` tiles past the end of a cache of nearly 2^31 tokens does not fit 31.)
-__host__ __device__ __forceinline__ Tile place_tile(const Span &a, Tile t) {
-    if (t.ti >= a.tpc) { const int c = t.ti / a.tpc; t.chunk += c; t.ti -= c * a.tpc; }
-    t.valid = t.chunk < a.n_chunks;
+__host__ __device__ __forceinline__ int tiles_per_chunk(const Span &a) {
+    const int64_t l = a.chunk_len < a.n_kv ? a.chunk_len : a.n_kv;
+    return (int)((l + kAtKv - 1) / kAtKv);
+}
+// Tile `ti` of a chunk, counted on into the following ones.  (Its position is compared in 64 bits: a step past
+// the end of a cache of nearly 2^31 tokens does not fit 31.)
+__host__ __device__ __forceinline__ Tile place_tile(const Span &a, int chunk, int ti) {
+    Tile t;
+    const int tpc = tiles_per_chunk(a);
+    while (ti >= tpc) { ti -= tpc; ++chunk; }            // a division would take vector registers from the tile loops
+    t.valid = chunk < a.n_chunks;
     if (t.valid) {
-        const int64_t b = (int64_t)t.chunk * a.chunk_len, t0 = b + (int64_t)t.ti * kAtKv;
+        const int64_t b = (int64_t)chunk * a.chunk_len, t0 = b + (int64_t)ti * kAtKv;
         const int64_t cend = (b + a.chunk_len < a.n_kv) ? b + a.chunk_len : a.n_kv;
         t.valid = t0 < cend;
-        t.t0 = (int)t0; t.cend = (int)cend;
+        t.chunk = chunk; t.t0 = (int)t0; t.cend = (int)cend;
     }
     if (!t.valid) { t.chunk = a.n_chunks - 1; t.t0 = 0; t.cend = 0; }
     return t;
 }
-__host__ __device__ __forceinline__ Tile first_tile(const Span &a) {
-    Tile t;
-    t.chunk = 0; t.ti = a.part; t.t0 = 0; t.cend = 0;
-    return place_tile(a, t);
-}
+static_assert(kAtKv == 64, "next_tile counts tiles by shifts");
+__host__ __device__ __forceinline__ Tile first_tile(const Span &a) { return place_tile(a, 0, a.part); }
+// Inside a chunk a step is one comparison and one addition: every tile of the one-kernel forms takes it (placed
+// anew by chunk and tile number, 40 heads x 1560 queries took 1.48 instead of 1.44 ms over 16384 tokens, 1.34 instead
+// of 1.26 over 8192 in the general kernel)
 __host__ __device__ __forceinline__ Tile next_tile(const Span &a, Tile t) {
-    t.ti += a.parts;
-    return place_tile(a, t);
+    const int step = a.parts * kAtKv;
+    if (t.cend - t.t0 > step) { t.t0 += step; return t; }
+    return place_tile(a, t.chunk, (int)(((int64_t)t.t0 - (int64_t)t.chunk * a.chunk_len) >> 6) + a.parts);
 }
 
 // Running state of a workgroup's 256 queries, [kStateFloats][512] floats: per thread its 64 output
@@ -91,6 +97,22 @@ __device__ __forceinline__ void store_state(float *st, const floatx16_t (&O)[4],
 // the state of query block `qblock` of unit h as part `part` leaves it
 __device__ __forceinline__ float *part_state_of(const AttnArgs &a, int n_qblocks, int h, int qblock, int part) {
     return a.part_state + (((int64_t)part * a.H + h) * n_qblocks + qblock) * kStateFloats * kAtThreads + threadIdx.x;
+}
+
+// The one-kernel forms' arguments (their kernels' first), read anew where they are called for, and the state's
+// place worked out anew from the workgroup's number: what only the end of the kernel needs would otherwise
+// be loaded at its start and carried through the tile loop, and scalar registers spill there (general
+// kernel, 40 heads x 1560 queries over 8192 tokens with prefix lengths, 1.30 ms instead of 1.20).
+__device__ __forceinline__ const AttnArgs &late_args() {
+    auto p = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const AttnArgs *)p;
+}
+__device__ __forceinline__ float *part_state_of_block(const AttnArgs &a, int n_qblocks, int blocks_per_xcd) {
+    unsigned b = blockIdx.x;
+    asm volatile("" : "+s"(b));
+    const int w = (int)(b % 8u) * blocks_per_xcd + (int)(b / 8u), wq = w / a.parts;
+    return part_state_of(a, n_qblocks, wq / n_qblocks, wq % n_qblocks, w - wq * a.parts);
 }
 
 // Normalise and store one query's result: the lane holds channels 32*mb + 8*g + 4*half + 0..3 of its

@@ -12,7 +12,7 @@ using namespace qvg;
 static const char *tiles_of(int64_t n_kv, int64_t chunk_len, int parts, bool ends_only) {
     AttnArgs a{};
     a.n_kv = n_kv; a.chunk_len = chunk_len; a.n_chunks = (int)((n_kv - 1) / chunk_len + 1); a.parts = parts;
-    const int64_t tpc = span_of(a, 0).tpc;
+    const int64_t tpc = tiles_per_chunk(span_of(a, 0));
     for (int p = 0; p < parts; ++p) {
         const Span s = span_of(a, p);
         Tile t = first_tile(s);
@@ -20,13 +20,12 @@ static const char *tiles_of(int64_t n_kv, int64_t chunk_len, int parts, bool end
         if (ends_only && t.valid) {                        // start near the end instead
             const int64_t last = (int64_t)(a.n_chunks - 1) * tpc + (n_kv - (int64_t)(a.n_chunks - 1) * chunk_len + kAtKv - 1) / kAtKv - 1;
             g = last - (last - p) % parts;
-            t.chunk = (int)(g / tpc); t.ti = (int)(g % tpc);
-            t = place_tile(s, t);
+            t = place_tile(s, (int)(g / tpc), (int)(g % tpc));
         }
         for (; t.valid; t = next_tile(s, t), g += parts) {
-            if (t.chunk != g / tpc || t.ti != g % tpc) return "order";
+            if (t.chunk != g / tpc) return "order";
             if (t.t0 < 0 || t.t0 >= n_kv || t.cend > n_kv || t.t0 >= t.cend) return "range";
-            if (t.t0 != t.chunk * chunk_len + t.ti * kAtKv) return "position";
+            if (t.t0 != t.chunk * chunk_len + g % tpc * kAtKv) return "position";
         }
         if (g % tpc == 0 && g / tpc < a.n_chunks) return "end";
     }
