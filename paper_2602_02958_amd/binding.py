@@ -352,7 +352,6 @@ def _attn(q, k: Encoded, kp, vp, softmax_scale, want_lse, out, n_kv, k_rope, q_k
         _check(out, torch.float32, "out")
         if not out.is_contiguous():
             raise ValueError("out must be contiguous")
-        workspace = None
     need = C.c_size_t()
     st = lib().qvg_attn_scratch_bytes(C.byref(p), Nq, Nk, k.chunk_len, C.byref(need))
     if st != 0:

@@ -1,6 +1,6 @@
 """The memory that an attention takes for itself, and the workspace it is lent: a call with a prefix
 length per query takes no tile workspace (every tile of the cache would be decoded, however short the
-prefixes)."""
+prefixes); the fp32 result uses the lent workspace like the bf16 one."""
 import pytest
 import torch
 
@@ -37,3 +37,20 @@ def test_a_prefix_length_per_query_takes_no_tile_workspace():
     lent = B.attn_decode(q, kc, vc, q_kv_len=lens, workspace=B.attn_workspace(H, Nq, L, 1, DEV))
     torch.cuda.synchronize()
     assert torch.equal(out, lent)
+
+
+def test_the_fp32_result_uses_the_lent_workspace():
+    H, Nq, L, n = 12, 600, 4680, 14040
+    kc, vc = _filled_caches(H, L, 3, n, 16, 64, 2)
+    q = synth.queries(CONFIGS["cfg2_window21"], H, Nq, DEV)
+    out = B.attn_decode(q, kc, vc)
+    states = 256 * 66 * 512 * 4
+    ws = B.attn_workspace(H, Nq, L, 1, DEV).fill_(0xA5)
+    f32, taken = _taken(lambda: B.attn_decode(q, kc, vc, f32_out=True, workspace=ws))
+    assert taken <= states + (1 << 20)
+    assert (ws != 0xA5).any()
+    assert torch.equal(f32.to(torch.bfloat16), out)
+    none = torch.empty(0, dtype=torch.uint8, device=DEV)     # lent, too small: the one-kernel form
+    f32, taken = _taken(lambda: B.attn_decode(q, kc, vc, f32_out=True, workspace=none))
+    assert taken <= states + (1 << 20)
+    assert torch.equal(f32.to(torch.bfloat16), out)
