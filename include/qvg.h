@@ -209,7 +209,7 @@ int qvg_decode_ex(const qvg_params *p, int64_t n_tokens, int64_t chunk_len,
  *              is decoded ONCE per unit into the workspace (K_hat as bf16, V_hat as binary16, 512
  *              bytes per token and unit) and read from there by all query blocks: a slab of as many
  *              whole chunks as fit at a time, two launches per slab, the queries' running soft-max
- *              state (264 bytes per query and unit) carried in the workspace from slab to slab.
+ *              state (528 bytes per query and unit) carried in the workspace from slab to slab.
  *              The full-precision cache is never held beyond one slab.  Useful from 512 queries
  *              per unit upward (the dequantization is what bounds the one-kernel form).
  *              qvg_workspace_bytes(p, QVG_ENTRY_ATTN, tokens, n_q) gives the bytes that hold

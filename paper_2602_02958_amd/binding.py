@@ -285,18 +285,20 @@ def _scratch(nbytes: int, device):
 # (which only the device knows), the one-kernel form those below the longest (12 heads x 600 queries that see
 # 300 of 74880 tokens: 235 us with one, 26 without).
 TILE_SCRATCH_MIN_QUERIES = 512
-TILE_SCRATCH_BYTES = 256 << 20
+TILE_SCRATCH_TILES = 256 << 20       # bytes of decoded tiles: a slab
+TILE_SCRATCH_STATE = 256 << 20       # bytes of running state (528 per query and head), where one slab is not the whole cache
 
 
-def _tile_scratch(heads, n_q, chunk_len, n_chunks, device):
-    """The workspace of an attn_decode that was lent none: as many chunks as fit TILE_SCRATCH_BYTES,
-    none when not even one does."""
+def _tile_scratch_bytes(heads, n_q, chunk_len, n_chunks):
+    """Bytes of the workspace of an attn_decode that was lent none: the whole cache where it fits
+    TILE_SCRATCH_TILES, else the running state and as many chunks as fit; 0 (none) when not even one does,
+    or when the state alone is larger than TILE_SCRATCH_STATE."""
     one = heads * -(-chunk_len // 64) * 64 * 512
-    chunks = min(n_chunks, TILE_SCRATCH_BYTES // one)
-    if chunks < 1:
-        return None
-    p = make_params(heads, 2, 128, 1)
-    return _scratch(workspace_bytes(p, ENTRY_ATTN, -(-chunk_len // 64) * 64 * chunks, n_q), device)
+    chunks = min(n_chunks, TILE_SCRATCH_TILES // one)
+    if chunks == n_chunks:
+        return one * chunks
+    state = workspace_bytes(make_params(heads, 2, 128, 1), ENTRY_ATTN, 0, n_q)
+    return one * chunks + state if chunks > 0 and state <= TILE_SCRATCH_STATE else 0
 
 
 def attn_decode(q, k: Encoded, v: Encoded, softmax_scale=None, want_lse=False, out=None, n_kv=None,
@@ -308,9 +310,12 @@ def attn_decode(q, k: Encoded, v: Encoded, softmax_scale=None, want_lse=False, o
     f32_out: the result as float32, before the rounding to bf16;
     workspace: uint8 tensor (attn_workspace): every tile is then decoded once per unit into it and
     shared by all query blocks, a slab of chunks at a time, instead of once per 256 queries.  Without
-    one, calls of more than 512 queries and no q_kv_len take up to 256 MiB for the call from torch's
-    allocator; one that is too small for a chunk (an empty tensor) is ignored.  Worth lending with
-    q_kv_len too, unless the prefixes are short: every tile of the cache is decoded."""
+    one, calls of more than 512 queries and no q_kv_len take it from torch's allocator for the call: up to
+    256 MiB of tiles, and up to 256 MiB of running state when the cache needs more.  One that is too
+    small for a chunk (an empty tensor) is ignored.  Worth lending with q_kv_len too, unless the prefixes
+    are short: every tile of the cache is decoded.  Calls of few query blocks take up to 34 MiB for the
+    partial results of their divided cache; where torch has no memory left they run undivided, which
+    differs by the order of fp32 sums."""
     if (v.ids.shape, v.codes.shape, v.scales.shape, v.scales.dtype, v.centroids.shape, v.chunk_len, v.n_smooth) != \
             (k.ids.shape, k.codes.shape, k.scales.shape, k.scales.dtype, k.centroids.shape, k.chunk_len, k.n_smooth):
         raise ValueError("K and V caches must share shapes and parameters")
@@ -358,7 +363,7 @@ def _attn(q, k: Encoded, kp, vp, softmax_scale, want_lse, out, n_kv, k_rope, q_k
         raise QvgError(st, "qvg_attn_scratch_bytes")
     scratch = _scratch(need.value, q.device)
     if workspace is None and q_kv_len is None and Nq > TILE_SCRATCH_MIN_QUERIES:
-        workspace = _tile_scratch(H, Nq, k.chunk_len, -(-Nk // k.chunk_len), q.device)
+        workspace = _scratch(_tile_scratch_bytes(H, Nq, k.chunk_len, -(-Nk // k.chunk_len)), q.device)
     st = lib().qvg_attn_decode_parts(C.byref(p), Nq, _ptr(q), Nk, k.chunk_len, cap,
                                      *kp, *vp, _ptr(k_rope), _ptr(q_kv_len), softmax_scale,
                                      None if f32_out else _ptr(out), _ptr(out) if f32_out else None, _ptr(lse),

@@ -20,3 +20,23 @@ def test_a_workspace_serves_every_smaller_call(entry, K, S):
     for n in (1, 300, 4680, 13312, 26624, 131072, 1 << 20):
         sizes = [need(H, n) for H in range(1, 500)]
         assert all(a <= b for a, b in zip(sizes, sizes[1:])), n
+
+
+@pytest.mark.parametrize("heads", [1, 12, 40, 128])
+@pytest.mark.parametrize("n_q", [513, 1560, 4680, 10800, 100000])
+def test_the_attention_s_own_workspace_stays_within_its_bounds(heads, n_q):
+    """What attn_decode takes when it is lent none: at most 256 MiB of tiles and 256 MiB of state, no state
+    where one slab holds the cache, and never less than one chunk with the state."""
+    state = heads * -(-n_q // 256) * 66 * 512 * 4
+    taken = 0
+    for chunk_len in (1, 64, 200, 1560, 4680, 10800, 1 << 20, (1 << 63) - 1):
+        one = heads * -(-chunk_len // 64) * 64 * 512
+        for n_chunks in (1, 2, 3, 8, 160):
+            b = B._tile_scratch_bytes(heads, n_q, chunk_len, n_chunks)
+            taken += b > 0
+            if one * n_chunks <= 256 << 20:
+                assert b == one * n_chunks
+            elif b:
+                assert state <= 256 << 20 and (b - state) % one == 0 and one <= b - state <= 256 << 20
+                assert B.workspace_bytes(B.make_params(heads, 16, 64, 1), B.ENTRY_ATTN, 0, n_q) == state
+    assert taken > 0
