@@ -284,7 +284,10 @@ def _scratch(nbytes: int, device):
 # Not with a prefix length per query: the workspace decodes every tile of the cache, however short the prefixes
 # (which only the device knows), the one-kernel form those below the longest (12 heads x 600 queries that see
 # 300 of 74880 tokens: 235 us with one, 26 without).
+# Nor over fewer than four tiles: 700 queries of 1, 12 or 40 heads over 64 tokens 17 us with one, 12.5 without; over 256
+# 19 against 21 (40 heads: 22.8 against 21.9).
 TILE_SCRATCH_MIN_QUERIES = 512
+TILE_SCRATCH_MIN_TOKENS = 256
 TILE_SCRATCH_TILES = 256 << 20       # bytes of decoded tiles: a slab
 TILE_SCRATCH_STATE = 256 << 20       # bytes of running state (528 per query and head), where one slab is not the whole cache
 
@@ -310,7 +313,7 @@ def attn_decode(q, k: Encoded, v: Encoded, softmax_scale=None, want_lse=False, o
     f32_out: the result as float32, before the rounding to bf16;
     workspace: uint8 tensor (attn_workspace): every tile is then decoded once per unit into it and
     shared by all query blocks, a slab of chunks at a time, instead of once per 256 queries.  Without
-    one, calls of more than 512 queries and no q_kv_len take it from torch's allocator for the call: up to
+    one, calls of more than 512 queries over 256 tokens or more, without q_kv_len, take it from torch's allocator for the call: up to
     256 MiB of tiles, and up to 256 MiB of running state when the cache needs more.  One that is too
     small for a chunk (an empty tensor) is ignored.  Worth lending with q_kv_len too, unless the prefixes
     are short: every tile of the cache is decoded.  Calls of few query blocks take up to 34 MiB for the
@@ -362,7 +365,7 @@ def _attn(q, k: Encoded, kp, vp, softmax_scale, want_lse, out, n_kv, k_rope, q_k
     if st != 0:
         raise QvgError(st, "qvg_attn_scratch_bytes")
     scratch = _scratch(need.value, q.device)
-    if workspace is None and q_kv_len is None and Nq > TILE_SCRATCH_MIN_QUERIES:
+    if workspace is None and q_kv_len is None and Nq > TILE_SCRATCH_MIN_QUERIES and Nk >= TILE_SCRATCH_MIN_TOKENS:
         workspace = _scratch(_tile_scratch_bytes(H, Nq, k.chunk_len, -(-Nk // k.chunk_len)), q.device)
     st = lib().qvg_attn_decode_parts(C.byref(p), Nq, _ptr(q), Nk, k.chunk_len, cap,
                                      *kp, *vp, _ptr(k_rope), _ptr(q_kv_len), softmax_scale,

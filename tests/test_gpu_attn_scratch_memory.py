@@ -1,6 +1,6 @@
 """The memory that an attention takes for itself, and the workspace it is lent: a call with a prefix
 length per query takes no tile workspace (every tile of the cache would be decoded, however short the
-prefixes); the fp32 result uses the lent workspace like the bf16 one."""
+prefixes), nor does one over a few tiles; the fp32 result uses the lent workspace like the bf16 one."""
 import pytest
 import torch
 
@@ -35,6 +35,17 @@ def test_a_prefix_length_per_query_takes_no_tile_workspace():
     states = 256 * 66 * 512 * 4                              # of at most 256 parts
     assert taken <= states + (1 << 20) < tiles + states
     lent = B.attn_decode(q, kc, vc, q_kv_len=lens, workspace=B.attn_workspace(H, Nq, L, 1, DEV))
+    torch.cuda.synchronize()
+    assert torch.equal(out, lent)
+
+
+def test_a_cache_of_a_few_tiles_takes_no_tile_workspace():
+    H, Nq, L = 12, 600, 4680
+    kc, vc = _filled_caches(H, L, 1, 300, 16, 64, 2)
+    q = synth.queries(CONFIGS["cfg2_window21"], H, Nq, DEV)
+    out, taken = _taken(lambda: B.attn_decode(q, kc, vc, n_kv=255))
+    assert taken <= 1 << 20
+    lent = B.attn_decode(q, kc, vc, n_kv=255, workspace=B.attn_workspace(H, Nq, L, 1, DEV))
     torch.cuda.synchronize()
     assert torch.equal(out, lent)
 
