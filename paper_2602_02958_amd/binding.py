@@ -278,6 +278,12 @@ def _scratch(nbytes: int, device):
         return None
 
 
+def _may_divide(n_kv, chunk_len):
+    """False for caches of fewer than eight tiles, which are never divided: a call over them is host time (11.7 us,
+    12.5 with the question asked)."""
+    return n_kv // 64 + n_kv // chunk_len >= 6
+
+
 # An attn_decode that is lent no workspace takes one for itself when a unit has three query blocks or more:
 # 40 heads over 31997 tokens, 900 queries 2.90 -> 1.10 ms, 12 heads x 600 queries over 20000 195 -> 170 us; with two
 # blocks the one-kernel form is as fast or faster (40 heads x 300 queries over 20000 305 against 418 us).
@@ -360,11 +366,13 @@ def _attn(q, k: Encoded, kp, vp, softmax_scale, want_lse, out, n_kv, k_rope, q_k
         _check(out, torch.float32, "out")
         if not out.is_contiguous():
             raise ValueError("out must be contiguous")
-    need = C.c_size_t()
-    st = lib().qvg_attn_scratch_bytes(C.byref(p), Nq, Nk, k.chunk_len, C.byref(need))
-    if st != 0:
-        raise QvgError(st, "qvg_attn_scratch_bytes")
-    scratch = _scratch(need.value, q.device)
+    scratch = None
+    if _may_divide(Nk, k.chunk_len):
+        need = C.c_size_t()
+        st = lib().qvg_attn_scratch_bytes(C.byref(p), Nq, Nk, k.chunk_len, C.byref(need))
+        if st != 0:
+            raise QvgError(st, "qvg_attn_scratch_bytes")
+        scratch = _scratch(need.value, q.device)
     if workspace is None and q_kv_len is None and Nq > TILE_SCRATCH_MIN_QUERIES and Nk >= TILE_SCRATCH_MIN_TOKENS:
         workspace = _scratch(_tile_scratch_bytes(H, Nq, k.chunk_len, -(-Nk // k.chunk_len)), q.device)
     st = lib().qvg_attn_decode_parts(C.byref(p), Nq, _ptr(q), Nk, k.chunk_len, cap,

@@ -40,3 +40,14 @@ def test_the_attention_s_own_workspace_stays_within_its_bounds(heads, n_q):
                 assert state <= 256 << 20 and (b - state) % one == 0 and one <= b - state <= 256 << 20
                 assert B.workspace_bytes(B.make_params(heads, 16, 64, 1), B.ENTRY_ATTN, 0, n_q) == state
     assert taken > 0
+
+
+def test_a_cache_that_is_not_asked_about_is_not_divided():
+    need = B.C.c_size_t()
+    asked = 0
+    for chunk_len in (1, 8, 40, 64, 65, 100, 520, 4680, 1 << 40):
+        for n_kv in range(1, 600):
+            assert B.lib().qvg_attn_scratch_bytes(B.C.byref(B.make_params(1, 16, 64, 1)), 1, n_kv, chunk_len, B.C.byref(need)) == 0
+            asked += B._may_divide(n_kv, chunk_len)
+            assert need.value == 0 or B._may_divide(n_kv, chunk_len)
+    assert asked > 0
