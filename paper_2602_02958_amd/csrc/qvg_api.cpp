@@ -270,7 +270,7 @@ int qvg_encode_chunk(const qvg_params *p, int64_t n_tokens, const void *x, int64
             UpdateArgs u{};
             u.x = a.x; u.stride_head = sh; u.stride_token = stt; u.n_tokens = n_tokens;
             u.counts_out = nullptr; u.H = p->n_heads; u.K = p->n_clusters;
-            u.lists = member_lists(p, n_tokens, ws, w);
+            u.lists = member_lists(p, n_tokens, ws, w); u.stage = stage;
             u.nh3 = reinterpret_cast<uint2 *>(ws + w.norms);
             for (int it = 0; it < I; ++it) {
                 a.lists = u.lists;

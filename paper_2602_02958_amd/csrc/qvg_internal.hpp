@@ -221,6 +221,7 @@ struct UpdateArgs {
     int32_t *counts_out;
     MemberLists lists;
     int H; int K;
+    int stage;                                       // smoothing stage, from 0
 };
 hipError_t launch_update(const UpdateArgs &a, hipStream_t s);
 

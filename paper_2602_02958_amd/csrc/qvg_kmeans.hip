@@ -14,6 +14,8 @@
 // single workgroup (1024 threads), took 6.5 to 8 us of every iteration at 2 to 24 units of 4096 to
 // 4680 tokens and 15 us at 80 units of 10800; sorting where the ids are made costs the assignment
 // about 1 us.
+#include <type_traits>
+
 #include "qvg_kmeans.hpp"
 
 namespace qvg {
@@ -196,18 +198,28 @@ __device__ __forceinline__ uint32_t mean_token_order(const bf16_t *xu, int64_t s
             // 64 member indices at once, then broadcast lane by lane
             const int mine = member_token(v, sg, b0, base + lane);
             const int cntm = (sg.n - base < 64) ? sg.n - base : 64;
-            // all lanes of `mine` hold tokens that exist, so that no load needs a predicate
-            for (int u0 = 0; u0 < cntm; u0 += kRowsAhead) {
-                uint32_t wv[kRowsAhead];
+            // all lanes of `mine` hold tokens that exist, so that no load needs a predicate; as many rows at a
+            // time as there are members, to the next power of two (always sixteen: 400 units x 1024 tokens,
+            // K = 512, lists of two, 142 instead of 70 us)
+            auto rows = [&](auto count, int u0) {
+                constexpr int R = decltype(count)::value;
+                uint32_t wv[R];
 #pragma unroll
-                for (int u = 0; u < kRowsAhead; ++u) {
+                for (int u = 0; u < R; ++u) {
                     const int idx = __builtin_amdgcn_readlane(mine, u0 + u);
                     wv[u] = *reinterpret_cast<const uint32_t *>(xb + (int64_t)idx * stride_token);
                 }
 #pragma unroll
-                for (int u = 0; u < kRowsAhead; ++u)
+                for (int u = 0; u < R; ++u)
                     if (u0 + u < cntm) { s0 += (double)bf16_lo(wv[u]); s1 += (double)bf16_hi(wv[u]); }
-            }
+            };
+            int u0 = 0;
+            for (; u0 + kRowsAhead <= cntm; u0 += kRowsAhead) rows(std::integral_constant<int, kRowsAhead>{}, u0);
+            const int left = cntm - u0;
+            if (left > 8) rows(std::integral_constant<int, 16>{}, u0);
+            else if (left > 4) rows(std::integral_constant<int, 8>{}, u0);
+            else if (left > 2) rows(std::integral_constant<int, 4>{}, u0);
+            else if (left > 0) rows(std::integral_constant<int, 2>{}, u0);
         }
         b0 += 64;
         if (b0 >= v.n_blocks) break;                                     // uniform
@@ -231,16 +243,19 @@ __device__ __forceinline__ uint32_t mean_token_order(const bf16_t *xu, int64_t s
 // own wavefront; the longest ones (one cluster can hold a large share of a unit's tokens, e.g.
 // in the later smoothing stages) are split over all wavefronts of the block, whose partial
 // results meet in LDS.  Four wavefronts per block and at most 96 registers keep five wavefronts per
-// SIMD resident (six, at 80 registers, spill: a QVG-Pro chunk 690 against 666 us; four with sixteen rows in
-// flight 690 too), which is what the common case of many short lists lives on; eight wavefronts
+// SIMD resident, which is what the common case of many short lists lives on (four with sixteen rows in flight:
+// a QVG-Pro chunk 690 against 666 us).  Six, at 80 registers, spill in the order-free sums, which a call
+// of short lists hardly takes: there six are better (400 units x 4096 tokens, K = 256 147 -> 135 us, K = 512 202 ->
+// 182; 24 x 4680 with K = 256 encoded in 134 instead of 138), but not where a few clusters hold most of a unit
+// (that QVG-Pro chunk 848 -> 868, its later stages); eight wavefronts
 // per block sum the longest lists faster and everything else slower.  The unit is the fastest
 // grid index, as in the assignment: a unit's tokens and lists are then read through one XCD's L2 (the
 // other way round that chunk takes 742 us).  A launch with few centroids (one chunk of a few heads) cannot
 // fill the chip anyway and is a chain of dependent loads: there a block has ONE centroid (CPB = 1),
 // every list long enough for the order-free path is spread over the block's four wavefronts, and
 // 16 rows are in flight per lane (ROWS = 16: no occupancy to protect).
-template <int CPB, int ROWS, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, CPB == 1 ? WAVES / 4 : 5)
+template <int CPB, int ROWS, int WAVES, int PER_SIMD>
+__global__ __launch_bounds__(WAVES * 64, PER_SIMD)
 void kmeans_mean_kernel(UpdateArgs a) {
     constexpr int kCoopMin = CPB == 1 ? kMeanParallelMin : kMeanCoopMin;
     __shared__ double part[WAVES][kHeadDim];
@@ -264,8 +279,15 @@ void kmeans_mean_kernel(UpdateArgs a) {
         for (int b0 = 64; b0 < v.n_blocks; b0 += 64) n += load_segments(v, j, b0, lane).n;
         if (a.counts_out && lane == 0) a.counts_out[(int64_t)h * K + j] = n;
     }
-    if (lane == 0) list_len[wave] = n;
-    __syncthreads();
+    // the block's long lists, the same mask in every wavefront; a unit this short has none
+    uint32_t coop = 0u;
+    int len = 0;
+    if (a.n_tokens >= kCoopMin) {                                        // uniform
+        if (lane == 0) list_len[wave] = n;
+        __syncthreads();
+        len = list_len[lane < CPB ? lane : 0];
+        coop = (uint32_t)__ballot(lane < CPB && len >= kCoopMin);
+    }
 
     // ---- the wavefront's own centroid, unless its list is left to the whole block ----
     if (own && n < kCoopMin) {
@@ -314,9 +336,9 @@ void kmeans_mean_kernel(UpdateArgs a) {
 
     // ---- the block's longest lists, one after the other, by all wavefronts (every wavefront of
     // the block takes the same branches: the list lengths are read by all of them) ----
-    for (int t = 0; t < CPB; ++t) {
-        const int nt = __builtin_amdgcn_readfirstlane(list_len[t]);
-        if (nt < kCoopMin) continue;                                     // uniform over the block
+    if (coop) for (int t = 0; t < CPB; ++t) {
+        if (!(coop >> t & 1)) continue;
+        const int nt = __builtin_amdgcn_readlane(len, t);
         const int jt = j0 + t;
         double s[8];
 #pragma unroll
@@ -369,17 +391,21 @@ void kmeans_mean_kernel(UpdateArgs a) {
     }
 }
 
+// Short lists: fewer members than this on average, in a first smoothing stage (what it leaves is centred, and one
+// cluster of a later stage can hold most of it)
+constexpr int64_t kMeanShort = 32;
+
 hipError_t launch_update(const UpdateArgs &a, hipStream_t s) {
-    if ((int64_t)a.K * a.H <= kMeanSmallGrid) {
-        const dim3 grid((unsigned)a.H, (unsigned)a.K);
-        if ((int64_t)a.K * a.H <= kMeanWideGrid && a.n_tokens >= (int64_t)kMeanWideMin * a.K)
-            hipLaunchKernelGGL((kmeans_mean_kernel<1, 16, kMeanWideWaves>), grid, dim3(kMeanWideWaves * 64), 0, s, a);
-        else
-            hipLaunchKernelGGL((kmeans_mean_kernel<1, 16, kMeanWaves>), grid, dim3(kMeanWaves * 64), 0, s, a);
-    } else {
-        dim3 grid((unsigned)a.H, (unsigned)((a.K + kMeanWaves - 1) / kMeanWaves));
-        hipLaunchKernelGGL((kmeans_mean_kernel<kMeanWaves, 8, kMeanWaves>), grid, dim3(kMeanWaves * 64), 0, s, a);
-    }
+    const int64_t lists = (int64_t)a.K * a.H;
+    const dim3 one((unsigned)a.H, (unsigned)a.K), four((unsigned)a.H, (unsigned)((a.K + kMeanWaves - 1) / kMeanWaves));
+    if (lists <= kMeanWideGrid && a.n_tokens >= (int64_t)kMeanWideMin * a.K)
+        hipLaunchKernelGGL((kmeans_mean_kernel<1, 16, kMeanWideWaves, kMeanWideWaves / 4>), one, dim3(kMeanWideWaves * 64), 0, s, a);
+    else if (lists <= kMeanSmallGrid)
+        hipLaunchKernelGGL((kmeans_mean_kernel<1, 16, kMeanWaves, kMeanWaves / 4>), one, dim3(kMeanWaves * 64), 0, s, a);
+    else if (a.stage == 0 && a.n_tokens < kMeanShort * a.K)
+        hipLaunchKernelGGL((kmeans_mean_kernel<kMeanWaves, 8, kMeanWaves, 6>), four, dim3(kMeanWaves * 64), 0, s, a);
+    else
+        hipLaunchKernelGGL((kmeans_mean_kernel<kMeanWaves, 8, kMeanWaves, 5>), four, dim3(kMeanWaves * 64), 0, s, a);
     return hipGetLastError();
 }
 
