@@ -171,7 +171,7 @@ int qvg_kmeans_assign(const qvg_params *p, int64_t n_tokens, const void *x, int6
     if (!aligned16(workspace)) return QVG_ERR_ALIGN;
     AssignArgs a{};
     const int64_t table = (int64_t)p->n_clusters * kHeadDim;
-    uint2 *nh3 = assign_takes_norms(p->n_heads, p->n_clusters, n_tokens) ? nullptr
+    uint2 *nh3 = assign_takes_norms(p->n_heads, p->n_clusters, n_tokens, false) ? nullptr
                      : reinterpret_cast<uint2 *>(static_cast<unsigned char *>(workspace) + w.init_norms);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (nh3 && launch_half_norms(static_cast<const bf16_t *>(centroids), table, p->n_heads, 1, p->n_clusters, nh3, s) != hipSuccess)
@@ -250,7 +250,7 @@ int qvg_encode_chunk(const qvg_params *p, int64_t n_tokens, const void *x, int64
     unsigned char *ws = static_cast<unsigned char *>(workspace);
     const int64_t table = (int64_t)p->n_clusters * kHeadDim, kpad = k_padded(p->n_clusters);
     // every stage's start table is known: one launch takes all their norms (none for a small call)
-    uint2 *init_norms = assign_takes_norms(p->n_heads, p->n_clusters, n_tokens) ? nullptr : reinterpret_cast<uint2 *>(ws + w.init_norms);
+    uint2 *init_norms = assign_takes_norms(p->n_heads, p->n_clusters, n_tokens, I == 0 && S == 1 && fmt == 0) ? nullptr : reinterpret_cast<uint2 *>(ws + w.init_norms);
     if (init_norms && launch_half_norms(static_cast<const bf16_t *>(init_centroids), S * table, p->n_heads, S, p->n_clusters, init_norms, s) != hipSuccess)
         return QVG_ERR_LAUNCH;
     // input of the current smoothing stage: the caller's view first, then dense residual tensors

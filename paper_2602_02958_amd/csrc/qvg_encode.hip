@@ -647,13 +647,18 @@ int64_t member_blocks_bound(int H, int64_t n_tokens) {
     return h * steps < bound ? h * steps : bound;
 }
 
-// Start tables of up to 64 centroids: the workgroups of a small launch take the norms themselves from the staged rows,
-// which saves a launch (24 units x 4680 tokens, K = 64, I = 3 91 -> 89 us; 6 units x 4053 tokens, no iteration 22.7 -> 19.8).
-// With more centroids half_norm_kernel's once per unit is faster, however few the workgroups (K = 256: 36 against
-// 39 us at 456 of them, 22.8 against 24.1 at 24; four stages of 6 units x 2000 tokens 124 against 136).
-bool assign_takes_norms(int H, int K, int64_t n_tokens) {
-    const int64_t block = member_block(H, n_tokens), wgs = (n_tokens + block - 1) / block * H;
-    return K <= 64 && wgs <= 1024;
+// Start tables of up to 128 centroids: the workgroups of a small launch take the norms themselves from the staged rows,
+// which saves a launch (2.5 us of a call that is short enough to be host time).  Each workgroup repeats the sums of its
+// unit's rows, in a time that grows with their number, so the limit falls with its square: K = 64 up to 2048 workgroups
+// (one unit of 2^20 tokens, no iteration 114.1 -> 112.3 us; 400 x 300 27.2 -> 25.1; at 3200 168.6 -> 172.3), K = 128 up to
+// 512 (24 units x 64 tokens 15.3 -> 12.0; 24 x 4680 21.5 -> 21.1; at 1024 37.3 -> 39.4).  With more centroids half_norm_kernel's once per
+// unit is faster, however few the workgroups (K = 256, no iteration: 20.4 against 21.4 us at 64 of them, 29.7 against 30.9 at
+// 456), unless a unit has one workgroup anyway and the assignment is not the fused pass (one unit of 64 tokens 15.5 ->
+// 12.6, 400 18.2 -> 16.9; fused 15.6 -> 16.4).
+bool assign_takes_norms(int H, int K, int64_t n_tokens, bool fused) {
+    const int64_t block = member_block(H, n_tokens), wgs = (n_tokens + block - 1) / block * H, kp = k_padded(K);
+    if (!fused && wgs == H && kp <= 256) return true;
+    return kp <= 128 && wgs * kp * kp <= ((int64_t)1 << 23);
 }
 
 template <int B_, bool FUSED, int T_>

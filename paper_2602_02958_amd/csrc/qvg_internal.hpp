@@ -190,7 +190,7 @@ int assign_tiles_per_wave(int H, int64_t n_tokens);
 inline int member_block(int H, int64_t n_tokens) { return 256 * assign_tiles_per_wave(H, n_tokens); }
 // at least the blocks of H units of n_tokens tokens (H * n_blocks), and never less for more units or tokens
 int64_t member_blocks_bound(int H, int64_t n_tokens);
-bool assign_takes_norms(int H, int K, int64_t n_tokens);    // AssignArgs.nh3 may then be nullptr
+bool assign_takes_norms(int H, int K, int64_t n_tokens, bool fused);    // AssignArgs.nh3 may then be nullptr
 
 struct AssignArgs {
     const bf16_t *x; int64_t stride_head, stride_token; int64_t n_tokens;
