@@ -22,6 +22,12 @@ def _ws(H, Nq, L, n_chunks):
     return B.attn_workspace(H, Nq, L, n_chunks, DEV)
 
 
+def _one_kernel():
+    """Lent, but too small for a chunk: the form in which every query block decodes the cache for itself (without a
+    workspace a call of this many queries takes one of its own, and would be compared with itself)."""
+    return torch.empty(0, dtype=torch.uint8, device=DEV)
+
+
 @pytest.mark.parametrize("L,T,Bg,S,bits,fmt,K", [
     (200, 3, 64, 1, 2, B.SCALE_F16, 32),      # chunks of 3 tiles + 8 tokens
     (520, 4, 64, 1, 2, B.SCALE_F16, 256),
@@ -41,7 +47,7 @@ def test_shared_tiles_equal_the_fused_kernels(L, T, Bg, S, bits, fmt, K):
     q = synth.queries(CONFIGS["cfg2_window21"], H, Nq, DEV)
     khat, vhat = B.decode(kc), B.decode(vc)
     for n_kv in (filled, 2 * L, L + 7, 64, 1):
-        fused, lse_f = B.attn_decode(q, kc, vc, want_lse=True, n_kv=n_kv)
+        fused, lse_f = B.attn_decode(q, kc, vc, want_lse=True, n_kv=n_kv, workspace=_one_kernel())
         n_chunks = -(-n_kv // L)
         # one slab; one chunk per slab (state carried n_chunks - 1 times); slabs of two and of three chunks
         for slab_chunks in sorted({n_chunks, 1, min(2, n_chunks), min(3, n_chunks)}):
@@ -62,7 +68,7 @@ def test_shared_tiles_with_rotary_embedding():
     kc, vc = _filled_caches(H, L, 3, filled, K, Bg, T)
     q = synth.queries(CONFIGS["cfg2_window21"], H, Nq, DEV)
     rope = _rope_table(filled, offset=3).to(DEV)
-    fused = B.attn_decode(q, kc, vc, n_kv=filled, k_rope=rope)
+    fused = B.attn_decode(q, kc, vc, n_kv=filled, k_rope=rope, workspace=_one_kernel())
     out, lse = B.attn_decode(q, kc, vc, want_lse=True, n_kv=filled, k_rope=rope, workspace=_ws(H, Nq, L, 2))
     torch.cuda.synchronize()
     assert torch.equal(out, fused)
@@ -77,7 +83,7 @@ def test_a_workspace_too_small_for_one_chunk_is_ignored():
     H, L, K, Bg, T, Nq = 2, 520, 64, 64, 2, 600
     kc, vc = _filled_caches(H, L, 2, 2 * L, K, Bg, T)
     q = synth.queries(CONFIGS["cfg2_window21"], H, Nq, DEV)
-    fused = B.attn_decode(q, kc, vc)
+    fused = B.attn_decode(q, kc, vc, workspace=_ws(H, Nq, L, 2))
     small = torch.empty(4096, dtype=torch.uint8, device=DEV)
     out = B.attn_decode(q, kc, vc, workspace=small)
     torch.cuda.synchronize()
@@ -101,7 +107,7 @@ def test_shared_tiles_16_bit_ids():
     filled = L + 77
     kc, vc = _filled_caches(H, L, 2, filled, K, Bg, T, fmt=B.SCALE_E4M3)
     q = synth.queries(CONFIGS["cfg2_window21"], H, Nq, DEV)
-    fused = B.attn_decode(q, kc, vc, n_kv=filled)
+    fused = B.attn_decode(q, kc, vc, n_kv=filled, workspace=_one_kernel())
     out = B.attn_decode(q, kc, vc, n_kv=filled, workspace=_ws(H, Nq, L, 1))
     torch.cuda.synchronize()
     assert torch.equal(out, fused)
@@ -130,7 +136,7 @@ def test_shared_tiles_with_a_prefix_length_per_query(L, T, Bg, S, bits, fmt, rop
         if order == "shuffled":
             lens = lens[torch.randperm(Nq, generator=g)]
         ql = lens.to(torch.int32).to(DEV)
-        one, lse_one = B.attn_decode(q, kc, vc, want_lse=True, n_kv=filled, k_rope=table, q_kv_len=ql)
+        one, lse_one = B.attn_decode(q, kc, vc, want_lse=True, n_kv=filled, k_rope=table, q_kv_len=ql, workspace=_one_kernel())
         for slab_chunks in (n_chunks, 1):
             out, lse = B.attn_decode(q, kc, vc, want_lse=True, n_kv=filled, k_rope=table, q_kv_len=ql,
                                      workspace=_ws(H, Nq, L, slab_chunks))
@@ -170,7 +176,7 @@ def test_calls_back_to_back_on_two_streams_share_one_workspace():
             for filled in (8 * L + 100, 7 * L + 1, 9 * L):             # 3, 2 and 3 slabs; the caches differ in length
                 kc, vc = _filled_caches(H, L, 9, filled, K, Bg, T)
                 out, lse = B.attn_decode(q, kc, vc, want_lse=True, n_kv=filled, workspace=ws)
-                fused, lse_f = B.attn_decode(q, kc, vc, want_lse=True, n_kv=filled)
+                fused, lse_f = B.attn_decode(q, kc, vc, want_lse=True, n_kv=filled, workspace=_one_kernel())
                 results.append((out, lse, fused, lse_f))
     torch.cuda.synchronize()
     for out, lse, fused, lse_f in results:

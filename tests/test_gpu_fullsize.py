@@ -257,7 +257,7 @@ def test_paper_presets_on_the_cfg2_window_sampled(S, Bg, bits, with_rope):
     rope = bench_rope(n) if with_rope else None
     k = B.Encoded(cache.centroids[:heads], cache.ids[:heads], cache.codes[:heads], cache.scales[:heads], L, S)
     v = B.Encoded(cache.centroids[heads:], cache.ids[heads:], cache.codes[heads:], cache.scales[heads:], L, S)
-    out = B.attn_decode(q, k, v, k_rope=rope)
+    out = B.attn_decode(q, k, v, k_rope=rope, workspace=torch.empty(0, dtype=torch.uint8, device="cuda"))   # one kernel, as bench.py
     torch.cuda.synchronize()
     c = wl.n_chunks - 1
     lo = c * L
