@@ -192,7 +192,8 @@ constexpr int kRowsAhead = 16;             // rows in flight (divides 64)
 __device__ __forceinline__ uint32_t mean_token_order(const bf16_t *xu, int64_t stride_token, const ListView &v, int j,
                                                      Segments sg, int n, int lane) {
     double s0 = 0.0, s1 = 0.0;
-    const bf16_t *xb = xu + lane * 2;
+    // bytes between tokens, or 0 where an offset inside the unit may not fit 32 bits
+    const uint32_t row_bytes = stride_token * 2 * ((int64_t)v.n_blocks * v.block) < ((int64_t)1 << 31) ? (uint32_t)(stride_token * 2) : 0u;
     for (int b0 = 0;;) {
         for (int base = 0; base < sg.n; base += 64) {
             // 64 member indices at once, then broadcast lane by lane
@@ -201,25 +202,34 @@ __device__ __forceinline__ uint32_t mean_token_order(const bf16_t *xu, int64_t s
             // all lanes of `mine` hold tokens that exist, so that no load needs a predicate; as many rows at a
             // time as there are members, to the next power of two (always sixteen: 400 units x 1024 tokens,
             // K = 512, lists of two, 142 instead of 70 us)
-            auto rows = [&](auto count, int u0) {
+            // (32-bit offsets where the unit's tokens allow them: a 64-bit product per row is eight scalar
+            // instructions, and the scalar unit was busier than the vector one)
+            auto rows = [&](auto count, auto narrow, int u0) {
                 constexpr int R = decltype(count)::value;
                 uint32_t wv[R];
 #pragma unroll
                 for (int u = 0; u < R; ++u) {
                     const int idx = __builtin_amdgcn_readlane(mine, u0 + u);
-                    wv[u] = *reinterpret_cast<const uint32_t *>(xb + (int64_t)idx * stride_token);
+                    if (decltype(narrow)::value)
+                        wv[u] = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(xu) +
+                                                                    (uint32_t)(idx * row_bytes + lane * 4));
+                    else
+                        wv[u] = *reinterpret_cast<const uint32_t *>(xu + (int64_t)idx * stride_token + lane * 2);
                 }
 #pragma unroll
                 for (int u = 0; u < R; ++u)
                     if (u0 + u < cntm) { s0 += (double)bf16_lo(wv[u]); s1 += (double)bf16_hi(wv[u]); }
             };
-            int u0 = 0;
-            for (; u0 + kRowsAhead <= cntm; u0 += kRowsAhead) rows(std::integral_constant<int, kRowsAhead>{}, u0);
-            const int left = cntm - u0;
-            if (left > 8) rows(std::integral_constant<int, 16>{}, u0);
-            else if (left > 4) rows(std::integral_constant<int, 8>{}, u0);
-            else if (left > 2) rows(std::integral_constant<int, 4>{}, u0);
-            else if (left > 0) rows(std::integral_constant<int, 2>{}, u0);
+            auto group = [&](auto narrow) {
+                int u0 = 0;
+                for (; u0 + kRowsAhead <= cntm; u0 += kRowsAhead) rows(std::integral_constant<int, kRowsAhead>{}, narrow, u0);
+                const int left = cntm - u0;
+                if (left > 8) rows(std::integral_constant<int, 16>{}, narrow, u0);
+                else if (left > 4) rows(std::integral_constant<int, 8>{}, narrow, u0);
+                else if (left > 2) rows(std::integral_constant<int, 4>{}, narrow, u0);
+                else if (left > 0) rows(std::integral_constant<int, 2>{}, narrow, u0);
+            };
+            if (row_bytes) group(std::true_type{}); else group(std::false_type{});
         }
         b0 += 64;
         if (b0 >= v.n_blocks) break;                                     // uniform

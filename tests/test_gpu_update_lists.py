@@ -57,3 +57,25 @@ def test_lists_of_every_short_length(H, K, stride):
         flat = torch.cat([flat, torch.full((N - flat.numel(),), K - 1)])
         ids[h] = flat[torch.randperm(N, generator=g)]
     _check(torch.randn(H, N, 128, generator=g), ids, torch.randn(H, K, 128, generator=g), K, sorted({0, H // 2, H - 1}))
+
+
+@pytest.mark.parametrize("stride", [136, 10240, 16384, 32768])
+def test_tokens_far_apart(stride):
+    """Views whose unit spans less and more than 2^31 bytes (65793 tokens: 1.35 and 2.16, 4.3 * 10^9): the rows of
+    short and of long lists are found in both, as in a dense copy."""
+    N, K = 65793, 1000 // 2
+    g = torch.Generator(device=DEV).manual_seed(stride)
+    base = torch.empty(1, N, stride, dtype=torch.bfloat16, device=DEV)
+    x = base[:, :, 8:136]
+    x.copy_(torch.randn(1, N, 128, generator=g, device=DEV))
+    ids = torch.randint(0, 400, (1, N), generator=g, device=DEV)
+    ids[:, :N // 2] = torch.arange(N // 2, device=DEV) % 300 + 100
+    ids[:, -900:] = 400 + torch.arange(900, device=DEV) % 100      # lists of nine
+    ids = ids.to(torch.int16)
+    prev = torch.randn(1, K, 128, generator=g, device=DEV).to(torch.bfloat16)
+    far, dense = B.kmeans_update(x, ids, prev), B.kmeans_update(x.contiguous(), ids, prev)
+    torch.cuda.synchronize()
+    assert torch.equal(far[1], dense[1]) and torch.equal(far[0].view(torch.int16), dense[0].view(torch.int16))
+    want, count = O.update(bits_to_f32(bf16_bits(x[0])), ids[0].cpu().numpy().astype(np.int32), bf16_bits(prev[0]))
+    assert np.array_equal(dense[1][0].cpu().numpy(), count)
+    assert np.array_equal(P.to_np_u16(dense[0][0]), want)
