@@ -56,7 +56,7 @@ def test_static_scratch_encode_equals_workspace_encode_twice_in_a_row():
 
 def test_static_scratch_encode_refuses_sizes_beyond_its_array():
     dev = "cuda"
-    H, N, K = 720, 4680, 256                                       # two 47 MB tables: beyond the 16 MiB array
+    H, N, K = 720, 4680, 256                                       # two 47 MB tables: beyond the 16 MiB limit
     p = B.make_params(H, K, 64, 2, kmeans_iters=3)
     assert B.workspace_bytes(p, B.ENTRY_ENCODE, N) > (16 << 20)
     x = torch.zeros(1, 8, 128, dtype=torch.bfloat16, device=dev)   # never read: the call fails first
