@@ -882,19 +882,19 @@ hipError_t launch_attn(const AttnArgs &a, hipStream_t s) {
 // least four tiles to a part: fewer do not repay the part's start and its 132 KB of state.  64 queries
 // of one head over 4096 tokens 160 -> 28 us (2, 3 and 6 tiles at least: 28, 29, 30); 12 heads x
 // 1560 queries over 31997 tokens 795 -> 430 us; twice the chip's worth of parts is 5 % slower there.
-// With more than 64 query blocks a part has at least five tiles: their states are 132 KB each to write and to read, and two
+// More than 64 query blocks are not divided below ten tiles: the states are 132 KB each to write and to read, and two
 // parts of four tiles do not repay them (12 heads x 1560 queries over 512 tokens 30 us undivided, 34 divided; 40 x 700
-// 30.5 and 35; with 36 blocks 30 and 27).
+// 30.5 and 35; with 36 blocks 30 and 27; 40 x 300 over twelve tiles 32 in three parts, 36 in two).
 // From 129 query blocks on nothing is dealt: 160 blocks in three parts gain nothing (1.09 against 1.08 ms).
 // ---------------------------------------------------------------------------------------------
 constexpr int kCus = 256;
-constexpr int kPartMinTiles = 4, kPartMinTilesMany = 5, kPartManyBlocks = 64;
+constexpr int kPartMinTiles = 4, kPartManyBlocks = 64, kPartManyMinTiles = 10;
 int attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len) {
     if (n_q < 1 || n_kv < 1) return 1;
     const int64_t nb = (n_q + kAtQPerBlock - 1) / kAtQPerBlock * H;
     const int64_t full = n_kv / chunk_len, rest = n_kv - full * chunk_len;
     const int64_t tiles = full * ((chunk_len + kAtKv - 1) / kAtKv) + (rest + kAtKv - 1) / kAtKv;
-    const int64_t most = tiles / (nb > kPartManyBlocks ? kPartMinTilesMany : kPartMinTiles);
+    const int64_t most = nb > kPartManyBlocks && tiles < kPartManyMinTiles ? 1 : tiles / kPartMinTiles;
     const int64_t parts = kCus / nb < most ? kCus / nb : most;
     return parts > 1 ? (int)parts : 1;
 }
