@@ -255,7 +255,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
         }
 #pragma unroll
         for (int off = 32; off >= 16; off >>= 1) up = fmaxf(up, __shfl_xor(up, off, 64));
-        if (lane == 0) atomicMax(&smax, __float_as_uint(up));
+        if (lane == 0) atomicMax(&smax, norm_order(up));
     } else {
 #pragma unroll
         for (int u = 0; u < kMaxClusters / kAsgThreads; ++u) {
@@ -265,7 +265,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
             if (u * kAsgThreads < Kpad) {                               // uniform
 #pragma unroll
                 for (int off = 32; off >= 1; off >>= 1) up = fmaxf(up, __shfl_xor(up, off, 64));
-                if (lane == 0) atomicMax(&smax, __float_as_uint(up));
+                if (lane == 0) atomicMax(&smax, norm_order(up));
             }
         }
     }

@@ -51,15 +51,16 @@ __device__ __forceinline__ int scan64(int v) {
     return v;
 }
 
-// Upper bound (one ulp up) of ||c||^2 from the split of -||c||^2 / 2.  Never -0: the largest bound of a
-// table is found by comparing bit patterns as unsigned numbers, where 0x80000000 would be above every norm
-// (a zero row's split is +0, and -2 times it -0: 64 zero rows of one wavefront then hid the table's
-// largest norm from the certification).
+// Upper bound (one ulp up) of ||c||^2 from the split of -||c||^2 / 2; -0 for a zero row.
 __host__ __device__ __forceinline__ float norm_bound(uint2 split) {
     const float hi = __builtin_bit_cast(float, split.x << 16), mid = __builtin_bit_cast(float, split.x & 0xffff0000u);
     const float lo = __builtin_bit_cast(float, split.y << 16);
-    return 2.0f * __builtin_fabsf((hi + mid) + lo) * (1.0f + 0x1p-22f);
+    return -2.0f * ((hi + mid) + lo) * (1.0f + 0x1p-22f);
 }
+// A bound as a number that orders like it.  Without the sign: a -0 would be above every norm (64 zero rows of one
+// wavefront then hid the table's largest norm from the certification).  Taken off here and not in norm_bound, where
+// the assignment with 512 centroids comes out 4 % slower (400 units x 4096 tokens 568 against 589 us).
+__host__ __device__ __forceinline__ uint32_t norm_order(float bound) { return __builtin_bit_cast(uint32_t, bound) & 0x7fffffffu; }
 
 // Largest ||c||^2 that can matter to a token of squared norm xn at squared distance d2 from its leader:
 // (||x|| + d)^2.  fast_sqrt: a square root good to a few ulp that may flush subnormals.  2^-120 stands

@@ -38,7 +38,7 @@ static const char *norm_bounds() {
     double v = 0.0;
     for (int i = 0; i < 4000; ++i) {
         const float b = norm_bound(split_half_norm(v));
-        const uint32_t u = __builtin_bit_cast(uint32_t, b);
+        const uint32_t u = norm_order(b);
         if (u & 0x80000000u) return "sign";
         if ((double)b < v || (double)b > v * (1.0 + 0x1p-21)) return "bound";
         if (u < prev) return "order";
