@@ -14,8 +14,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqvg.so")
-SOURCES = ["qvg_api.cpp", "qvg_decode.hip", "qvg_encode.hip", "qvg_kmeans.hip", "qvg_quant.hip", "qvg_attn.hip", "qvg_attn_slab.hip"]
-HEADERS = [os.path.join(CSRC, "qvg_internal.hpp"), os.path.join(CSRC, "qvg_attn_tiles.hpp"), os.path.join(CSRC, "qvg_kmeans.hpp"),
+SOURCES = ["qvg_api.cpp", "qvg_decode.hip", "qvg_encode.hip", "qvg_lloyd.hip", "qvg_kmeans.hip", "qvg_quant.hip", "qvg_attn.hip", "qvg_attn_slab.hip"]
+HEADERS = [os.path.join(CSRC, "qvg_internal.hpp"), os.path.join(CSRC, "qvg_attn_tiles.hpp"), os.path.join(CSRC, "qvg_kmeans.hpp"), os.path.join(CSRC, "qvg_assign.hpp"),
            os.path.join(ROOT, "include", "qvg.h")]
 
 FLAGS = [

@@ -95,6 +95,143 @@ int check_view(const void *base, int64_t stride_head, int64_t stride_token, int6
     return QVG_OK;
 }
 
+// Whether the start tables and the tables' place in the output share memory.
+bool tables_overlap(const qvg_params *p, const void *init, const void *out, int64_t out_stride) {
+    const uintptr_t unit = (uintptr_t)p->n_smooth_stages * p->n_clusters * kHeadDim * sizeof(bf16_t);
+    const uintptr_t a = reinterpret_cast<uintptr_t>(init), b = reinterpret_cast<uintptr_t>(out);
+    return a < b + (uintptr_t)(p->n_heads - 1) * out_stride * sizeof(bf16_t) + unit && b < a + (uintptr_t)p->n_heads * unit;
+}
+
+// wait_ticks: the longest wait of a workgroup in the one-launch form, of 10 ns
+int encode_call(const qvg_params *p, int64_t n_tokens, const void *x, int64_t stride_head,
+                int64_t stride_token, const void *init_centroids, void *centroids_out,
+                int64_t cent_out_stride_head, uint8_t *ids_out, uint8_t *codes_out,
+                void *scales_out, int64_t out_stride_head_tokens, void *workspace,
+                size_t workspace_bytes, uint32_t wait_ticks, void *stream) {
+    int st = check_params(p);
+    if (st != QVG_OK) return st;
+    if (n_tokens < 0 || n_tokens > kMaxTokensPerChunk) return QVG_ERR_BAD_PARAM;
+    if (!init_centroids || !centroids_out) return QVG_ERR_NULL;
+    if (!aligned16(init_centroids) || !aligned16(centroids_out)) return QVG_ERR_ALIGN;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const size_t row = (size_t)p->n_clusters * kHeadDim * sizeof(bf16_t);    // one unit's table
+    if (cent_out_stride_head == 0) cent_out_stride_head = (int64_t)p->n_smooth_stages * p->n_clusters * kHeadDim;
+    if (out_stride_head_tokens == 0) out_stride_head_tokens = n_tokens;
+    if (cent_out_stride_head < (int64_t)p->n_smooth_stages * p->n_clusters * kHeadDim || (cent_out_stride_head & 7))
+        return QVG_ERR_ALIGN;
+    if (out_stride_head_tokens < n_tokens) return QVG_ERR_BAD_PARAM;
+    // n_tokens == 0: the start tables go out unchanged, H rows of S*K*d bf16 with the caller's pitch
+    auto copy_out = [&](const void *src) -> int {
+        const size_t all = row * (size_t)p->n_smooth_stages;
+        if (src == centroids_out && cent_out_stride_head == (int64_t)p->n_smooth_stages * p->n_clusters * kHeadDim) return QVG_OK;
+        return hipMemcpy2DAsync(centroids_out, (size_t)cent_out_stride_head * sizeof(bf16_t), src, all, all,
+                                (size_t)p->n_heads, hipMemcpyDeviceToDevice, s) == hipSuccess
+                   ? QVG_OK : QVG_ERR_LAUNCH;
+    };
+    if (n_tokens == 0) return copy_out(init_centroids);
+    if (!x || !ids_out || !codes_out || !scales_out) return QVG_ERR_NULL;
+    if ((st = check_view(x, stride_head, stride_token, n_tokens)) != QVG_OK) return st;
+    if (!aligned16(codes_out) || !scales_aligned(p, scales_out) || !ids_aligned(p, ids_out)) return QVG_ERR_ALIGN;
+    const int I = p->kmeans_iters;
+    const int fmt = format_of(p);
+    const int S = p->n_smooth_stages;
+    const EncodeWs w = encode_ws(p, n_tokens, true, I > 0, I > 0);
+    if (!workspace || workspace_bytes < w.total) return QVG_ERR_WORKSPACE;
+    if (!aligned16(workspace)) return QVG_ERR_ALIGN;
+    unsigned char *ws = static_cast<unsigned char *>(workspace);
+    const int64_t table = (int64_t)p->n_clusters * kHeadDim, kpad = k_padded(p->n_clusters);
+    // small enough that all its workgroups run at the same time: one launch for all iterations and stages (its start
+    // tables must outlast the first results)
+    const int groups = tables_overlap(p, init_centroids, centroids_out, cent_out_stride_head) ? 0
+                           : lloyd_groups(p->n_heads, p->n_clusters, n_tokens, stride_token, I);
+    if (groups > 0) {
+        LloydArgs l{};
+        l.x = static_cast<const bf16_t *>(x); l.stride_head = stride_head; l.stride_token = stride_token;
+        l.n_tokens = (int)n_tokens; l.init = static_cast<const bf16_t *>(init_centroids);
+        l.H = p->n_heads; l.K = p->n_clusters; l.B = p->group_size; l.T = p->n_stages; l.S = S; l.iters = I;
+        l.cent_out = static_cast<bf16_t *>(centroids_out); l.cent_out_stride = cent_out_stride_head;
+        l.ids = ids_out; l.codes = codes_out; l.scales = static_cast<f16_t *>(scales_out);
+        l.out_stride = out_stride_head_tokens; l.id_wide = id_wide(p); l.fused = fmt == 0;
+        l.init_norms = reinterpret_cast<const uint2 *>(ws + w.init_norms);
+        l.meet = reinterpret_cast<uint32_t *>(ws + w.cent[1]);           // 256 bytes per unit; a table has at least one row
+        l.ids_x = reinterpret_cast<uint16_t *>(ws + w.perm);
+        l.table = reinterpret_cast<bf16_t *>(ws + w.cent[0]); l.norms = reinterpret_cast<uint2 *>(ws + w.norms);
+        for (int i = 0; i < 2; ++i) l.resid[i] = reinterpret_cast<bf16_t *>(ws + w.resid[i]);
+        l.n_blocks = (int)((n_tokens + 255) / 256); l.groups = groups;
+        l.wait_ticks = wait_ticks;
+        if (launch_lloyd(l, s) != hipSuccess) return QVG_ERR_LAUNCH;
+        if (fmt == 0) return QVG_OK;
+        QuantArgs q{};
+        q.x = l.x; q.stride_head = stride_head; q.stride_token = stride_token;
+        if (S > 1) { q.x = l.resid[S & 1]; q.stride_head = n_tokens * kHeadDim; q.stride_token = kHeadDim; }   // stage S - 2 left it
+        q.n_tokens = n_tokens; q.cent = static_cast<const bf16_t *>(centroids_out) + (S - 1) * table; q.cent_stride = cent_out_stride_head;
+        q.ids = ids_out; q.ids_step = S; q.ids_off = S - 1; q.codes = codes_out; q.scales = scales_out;
+        q.out_stride = out_stride_head_tokens; q.H = p->n_heads; q.K = p->n_clusters; q.B = p->group_size;
+        q.T = p->n_stages; q.fmt = fmt; q.id_wide = id_wide(p);
+        return launch_quantize(q, s) == hipSuccess ? QVG_OK : QVG_ERR_LAUNCH;
+    }
+    // every stage's start table is known: one launch takes all their norms (none for a small call)
+    uint2 *init_norms = assign_takes_norms(p->n_heads, p->n_clusters, n_tokens, I == 0 && S == 1 && fmt == 0) ? nullptr : reinterpret_cast<uint2 *>(ws + w.init_norms);
+    if (init_norms && launch_half_norms(static_cast<const bf16_t *>(init_centroids), S * table, p->n_heads, S, p->n_clusters, init_norms, s) != hipSuccess)
+        return QVG_ERR_LAUNCH;
+    // input of the current smoothing stage: the caller's view first, then dense residual tensors
+    const bf16_t *xin = static_cast<const bf16_t *>(x);
+    int64_t sh = stride_head, stt = stride_token;
+    for (int stage = 0; stage < S; ++stage) {
+        AssignArgs a{};
+        a.x = xin; a.stride_head = sh; a.stride_token = stt;
+        a.n_tokens = n_tokens; a.H = p->n_heads; a.K = p->n_clusters; a.B = p->group_size;
+        a.T = p->n_stages; a.ids = ids_out; a.out_stride = out_stride_head_tokens; a.fused = 0;
+        a.ids_step = S; a.ids_off = stage; a.id_wide = id_wide(p);
+        // the caller's start tables are [H][S][K][d], the Lloyd loop's are dense
+        a.cent = static_cast<const bf16_t *>(init_centroids) + stage * table; a.cent_stride = S * table;
+        if (init_norms) { a.nh3 = init_norms + stage * kpad; a.nh3_stride = S * kpad; }
+        bf16_t *buf[2] = {reinterpret_cast<bf16_t *>(ws + w.cent[0]), reinterpret_cast<bf16_t *>(ws + w.cent[1])};
+        if (I > 0) {
+            UpdateArgs u{};
+            u.x = a.x; u.stride_head = sh; u.stride_token = stt; u.n_tokens = n_tokens;
+            u.counts_out = nullptr; u.H = p->n_heads; u.K = p->n_clusters;
+            u.lists = member_lists(p, n_tokens, ws, w); u.stage = stage;
+            u.nh3 = reinterpret_cast<uint2 *>(ws + w.norms);
+            for (int it = 0; it < I; ++it) {
+                a.lists = u.lists;
+                if (launch_assign(a, s) != hipSuccess) return QVG_ERR_LAUNCH;
+                u.cent_prev = a.cent; u.prev_stride = a.cent_stride; u.cent_out = buf[it & 1];
+                if (launch_update(u, s) != hipSuccess) return QVG_ERR_LAUNCH;
+                a.cent = u.cent_out; a.cent_stride = table;
+                a.nh3 = u.nh3; a.nh3_stride = kpad;
+            }
+            a.lists = MemberLists{};
+        }
+        // this stage's table goes out as H rows of K*d bf16 with the caller's pitch: the stage's
+        // last assignment writes them while it stages the table (no copy of its own)
+        bf16_t *cdst = static_cast<bf16_t *>(centroids_out) + stage * table;
+        if (!(a.cent == cdst && a.cent_stride == cent_out_stride_head)) {
+            a.cent_copy = cdst; a.cent_copy_stride = cent_out_stride_head;
+        }
+        if (stage + 1 < S) {
+            // final assignment of this stage; the bf16 residual it leaves is the next stage's input
+            a.resid = reinterpret_cast<bf16_t *>(ws + w.resid[stage & 1]);
+            if (launch_assign(a, s) != hipSuccess) return QVG_ERR_LAUNCH;
+            xin = a.resid; sh = n_tokens * kHeadDim; stt = kHeadDim;
+        } else if (fmt == 0) {
+            a.codes = codes_out; a.scales = static_cast<f16_t *>(scales_out); a.fused = 1;
+            if (launch_assign(a, s) != hipSuccess) return QVG_ERR_LAUNCH;
+        } else {
+            // the other stored formats: assignment, then the quantization kernel
+            if (launch_assign(a, s) != hipSuccess) return QVG_ERR_LAUNCH;
+            QuantArgs q{};
+            q.x = xin; q.stride_head = sh; q.stride_token = stt; q.n_tokens = n_tokens;
+            q.cent = a.cent; q.cent_stride = a.cent_stride;
+            q.ids = ids_out; q.ids_step = S; q.ids_off = stage; q.codes = codes_out; q.scales = scales_out;
+            q.out_stride = out_stride_head_tokens; q.H = p->n_heads; q.K = p->n_clusters; q.B = p->group_size;
+            q.T = p->n_stages; q.fmt = fmt; q.id_wide = id_wide(p);
+            if (launch_quantize(q, s) != hipSuccess) return QVG_ERR_LAUNCH;
+        }
+    }
+    return QVG_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -217,98 +354,19 @@ int qvg_encode_chunk(const qvg_params *p, int64_t n_tokens, const void *x, int64
                      int64_t cent_out_stride_head, uint8_t *ids_out, uint8_t *codes_out,
                      void *scales_out, int64_t out_stride_head_tokens, void *workspace,
                      size_t workspace_bytes, void *stream) {
-    int st = check_params(p);
-    if (st != QVG_OK) return st;
-    if (n_tokens < 0 || n_tokens > kMaxTokensPerChunk) return QVG_ERR_BAD_PARAM;
-    if (!init_centroids || !centroids_out) return QVG_ERR_NULL;
-    if (!aligned16(init_centroids) || !aligned16(centroids_out)) return QVG_ERR_ALIGN;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    const size_t row = (size_t)p->n_clusters * kHeadDim * sizeof(bf16_t);    // one unit's table
-    if (cent_out_stride_head == 0) cent_out_stride_head = (int64_t)p->n_smooth_stages * p->n_clusters * kHeadDim;
-    if (out_stride_head_tokens == 0) out_stride_head_tokens = n_tokens;
-    if (cent_out_stride_head < (int64_t)p->n_smooth_stages * p->n_clusters * kHeadDim || (cent_out_stride_head & 7))
-        return QVG_ERR_ALIGN;
-    if (out_stride_head_tokens < n_tokens) return QVG_ERR_BAD_PARAM;
-    // n_tokens == 0: the start tables go out unchanged, H rows of S*K*d bf16 with the caller's pitch
-    auto copy_out = [&](const void *src) -> int {
-        const size_t all = row * (size_t)p->n_smooth_stages;
-        if (src == centroids_out && cent_out_stride_head == (int64_t)p->n_smooth_stages * p->n_clusters * kHeadDim) return QVG_OK;
-        return hipMemcpy2DAsync(centroids_out, (size_t)cent_out_stride_head * sizeof(bf16_t), src, all, all,
-                                (size_t)p->n_heads, hipMemcpyDeviceToDevice, s) == hipSuccess
-                   ? QVG_OK : QVG_ERR_LAUNCH;
-    };
-    if (n_tokens == 0) return copy_out(init_centroids);
-    if (!x || !ids_out || !codes_out || !scales_out) return QVG_ERR_NULL;
-    if ((st = check_view(x, stride_head, stride_token, n_tokens)) != QVG_OK) return st;
-    if (!aligned16(codes_out) || !scales_aligned(p, scales_out) || !ids_aligned(p, ids_out)) return QVG_ERR_ALIGN;
-    const int I = p->kmeans_iters;
-    const int fmt = format_of(p);
-    const int S = p->n_smooth_stages;
-    const EncodeWs w = encode_ws(p, n_tokens, true, I > 0, I > 0);
-    if (!workspace || workspace_bytes < w.total) return QVG_ERR_WORKSPACE;
-    if (!aligned16(workspace)) return QVG_ERR_ALIGN;
-    unsigned char *ws = static_cast<unsigned char *>(workspace);
-    const int64_t table = (int64_t)p->n_clusters * kHeadDim, kpad = k_padded(p->n_clusters);
-    // every stage's start table is known: one launch takes all their norms (none for a small call)
-    uint2 *init_norms = assign_takes_norms(p->n_heads, p->n_clusters, n_tokens, I == 0 && S == 1 && fmt == 0) ? nullptr : reinterpret_cast<uint2 *>(ws + w.init_norms);
-    if (init_norms && launch_half_norms(static_cast<const bf16_t *>(init_centroids), S * table, p->n_heads, S, p->n_clusters, init_norms, s) != hipSuccess)
-        return QVG_ERR_LAUNCH;
-    // input of the current smoothing stage: the caller's view first, then dense residual tensors
-    const bf16_t *xin = static_cast<const bf16_t *>(x);
-    int64_t sh = stride_head, stt = stride_token;
-    for (int stage = 0; stage < S; ++stage) {
-        AssignArgs a{};
-        a.x = xin; a.stride_head = sh; a.stride_token = stt;
-        a.n_tokens = n_tokens; a.H = p->n_heads; a.K = p->n_clusters; a.B = p->group_size;
-        a.T = p->n_stages; a.ids = ids_out; a.out_stride = out_stride_head_tokens; a.fused = 0;
-        a.ids_step = S; a.ids_off = stage; a.id_wide = id_wide(p);
-        // the caller's start tables are [H][S][K][d], the Lloyd loop's are dense
-        a.cent = static_cast<const bf16_t *>(init_centroids) + stage * table; a.cent_stride = S * table;
-        if (init_norms) { a.nh3 = init_norms + stage * kpad; a.nh3_stride = S * kpad; }
-        bf16_t *buf[2] = {reinterpret_cast<bf16_t *>(ws + w.cent[0]), reinterpret_cast<bf16_t *>(ws + w.cent[1])};
-        if (I > 0) {
-            UpdateArgs u{};
-            u.x = a.x; u.stride_head = sh; u.stride_token = stt; u.n_tokens = n_tokens;
-            u.counts_out = nullptr; u.H = p->n_heads; u.K = p->n_clusters;
-            u.lists = member_lists(p, n_tokens, ws, w); u.stage = stage;
-            u.nh3 = reinterpret_cast<uint2 *>(ws + w.norms);
-            for (int it = 0; it < I; ++it) {
-                a.lists = u.lists;
-                if (launch_assign(a, s) != hipSuccess) return QVG_ERR_LAUNCH;
-                u.cent_prev = a.cent; u.prev_stride = a.cent_stride; u.cent_out = buf[it & 1];
-                if (launch_update(u, s) != hipSuccess) return QVG_ERR_LAUNCH;
-                a.cent = u.cent_out; a.cent_stride = table;
-                a.nh3 = u.nh3; a.nh3_stride = kpad;
-            }
-            a.lists = MemberLists{};
-        }
-        // this stage's table goes out as H rows of K*d bf16 with the caller's pitch: the stage's
-        // last assignment writes them while it stages the table (no copy of its own)
-        bf16_t *cdst = static_cast<bf16_t *>(centroids_out) + stage * table;
-        if (!(a.cent == cdst && a.cent_stride == cent_out_stride_head)) {
-            a.cent_copy = cdst; a.cent_copy_stride = cent_out_stride_head;
-        }
-        if (stage + 1 < S) {
-            // final assignment of this stage; the bf16 residual it leaves is the next stage's input
-            a.resid = reinterpret_cast<bf16_t *>(ws + w.resid[stage & 1]);
-            if (launch_assign(a, s) != hipSuccess) return QVG_ERR_LAUNCH;
-            xin = a.resid; sh = n_tokens * kHeadDim; stt = kHeadDim;
-        } else if (fmt == 0) {
-            a.codes = codes_out; a.scales = static_cast<f16_t *>(scales_out); a.fused = 1;
-            if (launch_assign(a, s) != hipSuccess) return QVG_ERR_LAUNCH;
-        } else {
-            // the other stored formats: assignment, then the quantization kernel
-            if (launch_assign(a, s) != hipSuccess) return QVG_ERR_LAUNCH;
-            QuantArgs q{};
-            q.x = xin; q.stride_head = sh; q.stride_token = stt; q.n_tokens = n_tokens;
-            q.cent = a.cent; q.cent_stride = a.cent_stride;
-            q.ids = ids_out; q.ids_step = S; q.ids_off = stage; q.codes = codes_out; q.scales = scales_out;
-            q.out_stride = out_stride_head_tokens; q.H = p->n_heads; q.K = p->n_clusters; q.B = p->group_size;
-            q.T = p->n_stages; q.fmt = fmt; q.id_wide = id_wide(p);
-            if (launch_quantize(q, s) != hipSuccess) return QVG_ERR_LAUNCH;
-        }
-    }
-    return QVG_OK;
+    return encode_call(p, n_tokens, x, stride_head, stride_token, init_centroids, centroids_out, cent_out_stride_head, ids_out,
+                       codes_out, scales_out, out_stride_head_tokens, workspace, workspace_bytes, kLloydWaitTicks, stream);
+}
+
+// qvg_encode_chunk with another bound on the one-launch encoder's waits (0: every workgroup but the last to arrive gives up
+// at once), so that a test reaches what follows a wait that lasts too long.  Not part of the interface.
+int qvg_encode_chunk_wait(const qvg_params *p, int64_t n_tokens, const void *x, int64_t stride_head,
+                          int64_t stride_token, const void *init_centroids, void *centroids_out,
+                          int64_t cent_out_stride_head, uint8_t *ids_out, uint8_t *codes_out,
+                          void *scales_out, int64_t out_stride_head_tokens, void *workspace,
+                          size_t workspace_bytes, void *stream, uint32_t wait_ticks) {
+    return encode_call(p, n_tokens, x, stride_head, stride_token, init_centroids, centroids_out, cent_out_stride_head, ids_out,
+                       codes_out, scales_out, out_stride_head_tokens, workspace, workspace_bytes, wait_ticks, stream);
 }
 
 }  // extern "C"

@@ -225,6 +225,28 @@ struct UpdateArgs {
 };
 hipError_t launch_update(const UpdateArgs &a, hipStream_t s);
 
+// A chunk's encode in one launch (qvg_lloyd.hip): all stages' Lloyd iterations and final assignments.
+struct LloydArgs {
+    const bf16_t *x; int64_t stride_head, stride_token; int n_tokens;
+    const bf16_t *init;                      // [H][S][K][d]; not written, and disjoint from cent_out
+    int H, K, B, T, S, iters;
+    bf16_t *cent_out; int64_t cent_out_stride;     // unit h's tables at cent_out + h * stride elements
+    uint8_t *ids; uint8_t *codes; f16_t *scales; int64_t out_stride; int id_wide;
+    int fused;                               // codes and scales are written (2-bit levels, binary16 scales)
+    // scratch
+    const uint2 *init_norms;                 // [H][S][Kpad]
+    uint32_t *meet;                          // [H][64]
+    uint16_t *ids_x;                         // [H][n_blocks * 256]
+    bf16_t *table; uint2 *norms;             // [H][K][d], [H][Kpad]
+    bf16_t *resid[2];                        // stage s leaves the next one's input [H][N][d] in resid[s & 1]
+    int n_blocks, groups;                    // blocks of 256 tokens per unit; workgroups per unit
+    uint32_t wait_ticks;                     // of 10 ns: the longest wait of a workgroup
+    int redo, by_xcd;                        // set by launch_lloyd
+};
+constexpr uint32_t kLloydWaitTicks = 200000;
+int lloyd_groups(int H, int K, int64_t n_tokens, int64_t stride_token, int iters);      // workgroups per unit, 0: not for this call
+hipError_t launch_lloyd(const LloydArgs &a, hipStream_t s);
+
 // member lists of a given assignment, ids [H][ids_stride]; ids at or above K are left out
 hipError_t launch_member_lists(const uint8_t *ids, int64_t ids_stride, int64_t n_tokens, int H, int K, int id_wide,
                                const MemberLists &lists, hipStream_t s);

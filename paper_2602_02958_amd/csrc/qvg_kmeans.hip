@@ -99,15 +99,6 @@ __device__ __forceinline__ int member_token(const ListView &v, const Segments &s
     return (b0 + b) * v.block + (int)v.perm[(int64_t)__shfl(s.delta, b, 64) + m];
 }
 
-typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, a), __builtin_bit_cast(ushort2_t, b)));
-}
-__device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(ushort2_t, a), __builtin_bit_cast(ushort2_t, b)));
-}
-
 // Order-free partial sums of a member list: the wavefront takes the groups of 64 members
 // first, first + step, .. of the list; lane = member slot (4) x 8 channels, 8 rows in
 // flight per lane (ROWS = 16 where registers do not matter).  s: the lane's partial sums of its 8 channels; amax / amin: per 16-bit half the
@@ -142,39 +133,13 @@ __device__ __forceinline__ void mean_partial(const bf16_t *xb, int64_t stride_to
                                         : make_uint4(0u, 0u, 0u, 0u);
                 }
 #pragma unroll
-                for (int i = 0; i < ROWS; ++i) {
-                    const uint32_t w[4] = {row[i].x, row[i].y, row[i].z, row[i].w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        s[2 * e] += (double)bf16_lo(w[e]);
-                        s[2 * e + 1] += (double)bf16_hi(w[e]);
-                        const uint32_t mag = w[e] & 0x7fff7fffu;
-                        const ushort2_t one = {1, 1};
-                        amax[e] = pk_max_u16(amax[e], mag);
-                        amin[e] = pk_min_u16(amin[e], __builtin_bit_cast(uint32_t, (ushort2_t)(__builtin_bit_cast(ushort2_t, mag) - one)));   // zero -> 0xffff
-                    }
-                }
+                for (int i = 0; i < ROWS; ++i) add_row(row[i], s, amax, amin);
             }
         }
         b0 += 64;
         if (b0 >= v.n_blocks) break;                                     // uniform: more than 64 blocks per unit
         sg = load_segments(v, j, b0, lane);
     }
-}
-
-// no partial sum of n members can round in fp64 when ceil(log2 n) + 8 + emax - emin <= 53; mx /
-// mn: the packed largest / smallest-non-zero-minus-one magnitude bits of two channels
-__device__ __forceinline__ bool mean_exact(uint32_t mx, uint32_t mn, int lg) {
-    bool ok = true;
-#pragma unroll
-    for (int hf = 0; hf < 2; ++hf) {
-        const uint32_t big = (mx >> (16 * hf)) & 0xffffu, small1 = (mn >> (16 * hf)) & 0xffffu;
-        if (small1 == 0xffffu) continue;                     // no non-zero member in this channel: the sum is zero
-        const int eb = (int)(big >> 7) > 1 ? (int)(big >> 7) : 1;
-        const int es = (int)((small1 + 1u) >> 7) > 1 ? (int)((small1 + 1u) >> 7) : 1;
-        if (lg + 8 + eb - es > 53) ok = false;
-    }
-    return ok;
 }
 
 // a new centroid's two channels of this lane: rounded to bf16, stored, and the split of its norm

@@ -51,6 +51,47 @@ __device__ __forceinline__ int scan64(int v) {
     return v;
 }
 
+typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, a), __builtin_bit_cast(ushort2_t, b)));
+}
+__device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(ushort2_t, a), __builtin_bit_cast(ushort2_t, b)));
+}
+
+// Two channels of a member into the lane's partial sums; mx / mn as amax / amin below.
+__device__ __forceinline__ void add_pair(uint32_t w, double &s0, double &s1, uint32_t &mx, uint32_t &mn) {
+    s0 += (double)bf16_lo(w);
+    s1 += (double)bf16_hi(w);
+    const uint32_t mag = w & 0x7fff7fffu;
+    const ushort2_t one = {1, 1};
+    mx = pk_max_u16(mx, mag);
+    mn = pk_min_u16(mn, __builtin_bit_cast(uint32_t, (ushort2_t)(__builtin_bit_cast(ushort2_t, mag) - one)));   // zero -> 0xffff
+}
+// A member's 8 channels into the lane's partial sums s; amax / amin: per 16-bit half the largest magnitude bits and
+// the smallest non-zero magnitude bits minus one (0xffff: none).
+__device__ __forceinline__ void add_row(const uint4 &row, double s[8], uint32_t amax[4], uint32_t amin[4]) {
+    const uint32_t w[4] = {row.x, row.y, row.z, row.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) add_pair(w[e], s[2 * e], s[2 * e + 1], amax[e], amin[e]);
+}
+
+// no partial sum of n members can round in fp64 when ceil(log2 n) + 8 + emax - emin <= 53; mx /
+// mn: the packed largest / smallest-non-zero-minus-one magnitude bits of two channels
+__device__ __forceinline__ bool mean_exact(uint32_t mx, uint32_t mn, int lg) {
+    bool ok = true;
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+        const uint32_t big = (mx >> (16 * hf)) & 0xffffu, small1 = (mn >> (16 * hf)) & 0xffffu;
+        if (small1 == 0xffffu) continue;                     // no non-zero member in this channel: the sum is zero
+        const int eb = (int)(big >> 7) > 1 ? (int)(big >> 7) : 1;
+        const int es = (int)((small1 + 1u) >> 7) > 1 ? (int)((small1 + 1u) >> 7) : 1;
+        if (lg + 8 + eb - es > 53) ok = false;
+    }
+    return ok;
+}
+
 // Upper bound (one ulp up) of ||c||^2 from the split of -||c||^2 / 2; -0 for a zero row.
 __host__ __device__ __forceinline__ float norm_bound(uint2 split) {
     const float hi = __builtin_bit_cast(float, split.x << 16), mid = __builtin_bit_cast(float, split.x & 0xffff0000u);
