@@ -21,7 +21,8 @@ ENTRY_ENCODE, ENTRY_DECODE, ENTRY_ATTN, ENTRY_KMEANS_UPDATE, ENTRY_KMEANS_ASSIGN
 SCALE_F16, SCALE_E4M3 = 0, 1
 
 EXPORTS = ["qvg_encode_chunk", "qvg_encode_chunk_static", "qvg_decode", "qvg_decode_ex", "qvg_attn_decode", "qvg_attn_decode_ex",
-           "qvg_attn_decode_causal", "qvg_attn_decode_f32", "qvg_attn_decode_parts", "qvg_attn_scratch_bytes", "qvg_attn_merge",
+           "qvg_attn_decode_causal", "qvg_attn_decode_f32", "qvg_attn_decode_parts", "qvg_attn_scratch_bytes", "qvg_attn_scratch_bytes_causal",
+           "qvg_attn_merge",
            "qvg_kmeans_assign",
            "qvg_kmeans_update", "qvg_workspace_bytes", "qvg_compressed_bytes",
            "qvg_status_string", "qvg_version"]
@@ -76,6 +77,8 @@ def lib():
                                             C.c_float, vp, vp, vp, vp, C.c_size_t, vp, C.c_size_t, vp]
         L.qvg_attn_scratch_bytes.restype = C.c_int
         L.qvg_attn_scratch_bytes.argtypes = [pp, i64, i64, i64, C.POINTER(C.c_size_t)]
+        L.qvg_attn_scratch_bytes_causal.restype = C.c_int
+        L.qvg_attn_scratch_bytes_causal.argtypes = L.qvg_attn_scratch_bytes.argtypes
         L.qvg_attn_merge.restype = C.c_int
         L.qvg_attn_merge.argtypes = [i64, C.c_int32, vp, vp, vp, vp, vp, vp, vp]
         L.qvg_kmeans_assign.restype = C.c_int
@@ -323,7 +326,7 @@ def attn_decode(q, k: Encoded, v: Encoded, softmax_scale=None, want_lse=False, o
     256 MiB of tiles, and up to 256 MiB of running state when the cache needs more.  One that is too
     small for a chunk (an empty tensor) is ignored.  Worth lending with q_kv_len too, unless the prefixes
     are short: every tile of the cache is decoded.  Calls of few query blocks take up to 34 MiB for the
-    partial results of their divided cache; where torch has no memory left they run undivided, which
+    partial results of their divided cache, with q_kv_len calls of up to 256 blocks of 256 queries up to 99 MiB; where torch has no memory left they run undivided, which
     differs by the order of fp32 sums."""
     if (v.ids.shape, v.codes.shape, v.scales.shape, v.scales.dtype, v.centroids.shape, v.chunk_len, v.n_smooth) != \
             (k.ids.shape, k.codes.shape, k.scales.shape, k.scales.dtype, k.centroids.shape, k.chunk_len, k.n_smooth):
@@ -369,7 +372,8 @@ def _attn(q, k: Encoded, kp, vp, softmax_scale, want_lse, out, n_kv, k_rope, q_k
     scratch = None
     if _may_divide(Nk, k.chunk_len):
         need = C.c_size_t()
-        st = lib().qvg_attn_scratch_bytes(C.byref(p), Nq, Nk, k.chunk_len, C.byref(need))
+        ask = lib().qvg_attn_scratch_bytes if q_kv_len is None else lib().qvg_attn_scratch_bytes_causal
+        st = ask(C.byref(p), Nq, Nk, k.chunk_len, C.byref(need))
         if st != 0:
             raise QvgError(st, "qvg_attn_scratch_bytes")
         scratch = _scratch(need.value, q.device)

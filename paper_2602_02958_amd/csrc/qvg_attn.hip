@@ -46,13 +46,8 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     uint16_t *Kt = reinterpret_cast<uint16_t *>(smem);                  // [2][64][136] bf16
     uint16_t *Vt = Kt + 2 * kKtElems;                                   // [2][128][72] f16, transposed
 
-    // Workgroups are dealt to the 8 XCDs round-robin by their linear id; they are re-numbered so
-    // that the query blocks of one unit run on one XCD and its cache is fetched into one L2 only
-    // (as in the staged kernel below; the grid is padded to a multiple of 8)
-    const int w = (int)(blockIdx.x % 8u) * blocks_per_xcd + (int)(blockIdx.x / 8u);
-    if (w >= n_blocks) return;                                          // uniform, before any barrier
-    const int h = w / (n_qblocks * a.parts);
-    const int qblock = (w - h * n_qblocks * a.parts) / a.parts;
+    int h, qblock, part;
+    if (!block_of<QL>(a, a.parts, n_qblocks, n_blocks, blocks_per_xcd, blockIdx.x, h, qblock, part)) return;    // uniform, before any barrier
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
@@ -62,7 +57,7 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     // query sees tokens 0 .. qlen-1; wmin = the shortest prefix in the wavefront (tiles below it
     // need no mask); the workgroup walks the cache only up to its longest prefix.
     int qlen = 0x7fffffff, wmin = 0x7fffffff;
-    Span sp = span_of(a, w % a.parts);
+    Span sp = span_of(a, part);
     if (QL) {
         __shared__ int bmax;
         if (tid == 0) bmax = 1;
@@ -80,6 +75,10 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
         __syncthreads();
         sp.n_kv = __builtin_amdgcn_readfirstlane(bmax);
         sp.n_chunks = (int)((sp.n_kv + sp.chunk_len - 1) / sp.chunk_len);
+        if (a.part_tiles) {                                              // uniform
+            sp.parts = block_parts(a, (int)sp.n_kv);
+            if (part >= sp.parts) return;                                // uniform
+        }
         wmin = __builtin_amdgcn_readfirstlane(wmin);
     }
     const int T = T_ > 0 ? T_ : a.T, B = a.B, K = a.K;
@@ -290,7 +289,7 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     }
     // ---- normalise and store: lane holds channels 32*mb + 8*g + 4*half + 0..3 of its query ----
     const AttnArgs &e = late_args();
-    if (e.parts > 1) { if (qvalid) store_state(part_state_of_block(e, n_qblocks, blocks_per_xcd), O, m, l); }
+    if ((QL ? sp.parts : e.parts) > 1) { if (qvalid) store_state(part_state_of_block<QL>(e, n_qblocks, blocks_per_xcd), O, m, l); }
     else store_result(e, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
 }
 
@@ -329,13 +328,8 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     typedef typename std::conditional<WIDE, uint16_t, unsigned char>::type id_t;
     id_t *idring = reinterpret_cast<id_t *>(stage + 2 * kStBytes);      // [4][2][64]: ids run one tile further ahead
 
-    // Workgroups are dealt to the 8 XCDs round-robin by their linear id; re-number them so that
-    // the query blocks of one unit run on one XCD (two at a boundary) and the unit's compressed
-    // cache is fetched into that XCD's L2 only, not into all eight.
-    const int w = (int)(blockIdx.x % 8u) * blocks_per_xcd + (int)(blockIdx.x / 8u);
-    if (w >= n_blocks) return;                                          // uniform, before any barrier
-    const int h = w / (n_qblocks * a.parts);
-    const int qblock = (w - h * n_qblocks * a.parts) / a.parts;
+    int h, qblock, part;
+    if (!block_of<QL>(a, a.parts, n_qblocks, n_blocks, blocks_per_xcd, blockIdx.x, h, qblock, part)) return;    // uniform, before any barrier
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);          // uniform: lets whole waves branch
@@ -533,7 +527,7 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     // QL: the lane's query sees tokens 0 .. qlen-1; wmin = the shortest prefix in the wavefront
     // (tiles below it need no mask); the workgroup walks the cache up to its longest prefix only
     int qlen = 0x7fffffff, wmin = 0x7fffffff;
-    Span sp = span_of(a, w % a.parts);
+    Span sp = span_of(a, part);
     if (QL) {
         __shared__ int bmax;
         if (tid == 0) bmax = 1;
@@ -551,6 +545,10 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
         __syncthreads();
         sp.n_kv = __builtin_amdgcn_readfirstlane(bmax);
         sp.n_chunks = (int)((sp.n_kv + sp.chunk_len - 1) / sp.chunk_len);
+        if (a.part_tiles) {                                              // uniform
+            sp.parts = block_parts(a, (int)sp.n_kv);
+            if (part >= sp.parts) return;                                // uniform
+        }
         wmin = __builtin_amdgcn_readfirstlane(wmin);
     }
     Tile cur = first_tile(sp);
@@ -723,7 +721,7 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
         if (!tile_step(BoolC<false>{}, false)) break;
     }
     const AttnArgs &e = late_args();
-    if (e.parts > 1) { if (qvalid) store_state(part_state_of_block(e, n_qblocks, blocks_per_xcd), O, m, l); }
+    if ((QL ? sp.parts : e.parts) > 1) { if (qvalid) store_state(part_state_of_block<QL>(e, n_qblocks, blocks_per_xcd), O, m, l); }
     else store_result(e, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
 }
 
@@ -886,14 +884,25 @@ hipError_t launch_attn(const AttnArgs &a, hipStream_t s) {
 // parts of four tiles do not repay them (12 heads x 1560 queries over 512 tokens 30 us undivided, 34 divided; 40 x 700
 // 30.5 and 35; with 36 blocks 30 and 27; 40 x 300 over twelve tiles 32 in three parts, 36 in two).
 // From 129 query blocks on nothing is dealt: 160 blocks in three parts gain nothing (1.09 against 1.08 ms).
+// A prefix length per query makes the blocks' work differ, and a call ends with its longest block: there up to 256
+// blocks are divided too, those of 96 tiles or more in up to three parts, the longest first.  37440 tokens, four groups of
+// queries that see a quarter of them more each, 12 heads x 4680 queries 1010 -> 850 us, with queries that are new to the caches 1010 ->
+// 921 (two parts 887, four 847; parts of at least 96 tiles 920), 7 heads 938 -> 524 (two parts 577), without a tile workspace 1720 -> 1330.  More blocks are taken whole, the
+// longest first: 20 heads x 4680 over 14040 tokens 762 -> 614 us (in two parts 704).
 // ---------------------------------------------------------------------------------------------
 constexpr int kCus = 256;
+constexpr int kLenMinBlocks = 129, kLenMinTiles = 192, kLenParts = 3, kLenPartTiles = 48;
 constexpr int kPartMinTiles = 4, kPartManyBlocks = 64, kPartManyMinTiles = 10;
-int attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len) {
+int attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool with_len, int *part_tiles) {
+    if (part_tiles) *part_tiles = 0;
     if (n_q < 1 || n_kv < 1) return 1;
     const int64_t nb = (n_q + kAtQPerBlock - 1) / kAtQPerBlock * H;
     const int64_t full = n_kv / chunk_len, rest = n_kv - full * chunk_len;
     const int64_t tiles = full * ((chunk_len + kAtKv - 1) / kAtKv) + (rest + kAtKv - 1) / kAtKv;
+    if (with_len && nb >= kLenMinBlocks && tiles >= kLenMinTiles) {
+        if (part_tiles) *part_tiles = kLenPartTiles;
+        return nb <= kCus ? kLenParts : 1;
+    }
     const int64_t most = nb > kPartManyBlocks && tiles < kPartManyMinTiles ? 1 : tiles / kPartMinTiles;
     const int64_t parts = kCus / nb < most ? kCus / nb : most;
     return parts > 1 ? (int)parts : 1;
@@ -903,16 +912,21 @@ size_t attn_parts_bytes(int H, int64_t n_q, int parts) {
     return parts > 1 ? (size_t)parts * nqb * H * kStateFloats * kAtThreads * sizeof(float) : 0;
 }
 
-// The result of a query from the states of its parts: one workgroup per query block and 8 of a lane's
+// The result of a query from the states of its parts: one workgroup per query block and NV of a lane's
 // 64 values, threads as in the kernels that left the states.  A part whose first tile lies behind
 // the query's prefix saw none of its tokens and is left out (its sums may be anything; behind all prefixes of the
 // block it leaves none: 64 queries of one head that see one of 74880 tokens, 256 parts, 54 us when all of them were
-// written and read).  A chain of loads: several parts are requested before the first is used (one at a time, 16 parts took 17 us).
-constexpr int kJoinAhead = 8;
+// written and read).  A chain of loads: many parts are requested before the first is used, and the requests are kept from
+// moving into the branches that use them; few blocks (the ones with many parts) take four values to a workgroup, which
+// doubles the workgroups.  (64 queries of one head over 4096 tokens, 16 parts, the call 21.5 -> 20.3 us; 204 over 103473, 256
+// parts 102 -> 81; 168 over 223961 126 -> 106.)
+constexpr int kJoinAhead = 16;
+constexpr int kJoinFewBlocks = 32;      // up to this many take NV = 4
+template <bool QL, int NV>         // QL: with a.q_len; NV: 4 or 8
 __global__ __launch_bounds__(kAtThreads)
 void attn_join_kernel(AttnArgs a, int n_qblocks) {
     const int h = (int)(blockIdx.x / (unsigned)n_qblocks), qblock = (int)(blockIdx.x - (unsigned)h * n_qblocks);
-    const int v0 = blockIdx.y * 8;                                       // channels 32 * (v0 / 16) + 8 * (v / 4 % 4) + 4 * half + v % 4
+    const int v0 = blockIdx.y * NV;                                      // channels 32 * (v0 / 16) + 8 * (v / 4 % 4) + 4 * half + v % 4
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, half = lane >> 5;
     const int64_t qrow = (int64_t)qblock * kAtQPerBlock + wave * 32 + col;
     const bool qvalid = qrow < a.n_q;                                    // the same for both lane halves of a query
@@ -921,49 +935,63 @@ void attn_join_kernel(AttnArgs a, int n_qblocks) {
     // the parts that saw a token of the query are the first ones; the wavefront reads those of its longest prefix (the
     // block's workgroups that lay behind all of its prefixes left nothing)
     int seen = a.parts, read = a.parts;
-    if (a.q_len) {                                                       // uniform
-        seen = 0;
-        if (qvalid) {
-            const int nk = (int)a.n_kv, clen = a.chunk_len < a.n_kv ? (int)a.chunk_len : nk;
-            int qlen = a.q_len[qrow];
-            qlen = qlen < 0 ? 0 : (qlen > nk ? nk : qlen);
-            const int full = qlen / clen, rest = qlen - full * clen;
-            const int64_t tiles = (int64_t)full * ((clen + kAtKv - 1) / kAtKv) + (rest + kAtKv - 1) / kAtKv;
-            seen = tiles < a.parts ? (int)tiles : a.parts;
-        }
-        read = seen;
+    if (QL) {
+        const int nk = (int)a.n_kv;
+        int qlen = 0;
+        if (qvalid) { const int v = a.q_len[qrow]; qlen = v < 0 ? 0 : (v > nk ? nk : v); }
+        int longest = qlen;
 #pragma unroll
-        for (int off = 16; off >= 1; off >>= 1) { const int o = __shfl_xor(read, off, 64); read = o > read ? o : read; }
-        read = __builtin_amdgcn_readfirstlane(read);
+        for (int off = 16; off >= 1; off >>= 1) { const int o = __shfl_xor(longest, off, 64); longest = o > longest ? o : longest; }
+        longest = __builtin_amdgcn_readfirstlane(longest);
+        int parts = a.parts;
+        if (a.part_tiles) {                                              // uniform: the block's parts
+            __shared__ int wave_longest[kAtWaves];
+            if (lane == 0) wave_longest[wave] = longest;
+            __syncthreads();
+            int all = 0;
+#pragma unroll
+            for (int i = 0; i < kAtWaves; ++i) all = wave_longest[i] > all ? wave_longest[i] : all;
+            parts = block_parts(a, __builtin_amdgcn_readfirstlane(all));
+            if (parts == 1) return;                                      // uniform: its workgroup stored the result
+        }
+        const int64_t tiles = tiles_of(a, qlen), most = tiles_of(a, longest);
+        seen = tiles < parts ? (int)tiles : parts;
+        read = most < parts ? (int)most : parts;
     }
     if (!qvalid) return;
-    float m = -INFINITY, l = 0.0f, o[8];
+    float m = -INFINITY, l = 0.0f, o[NV];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) o[i] = 0.0f;
+    for (int i = 0; i < NV; ++i) o[i] = 0.0f;
     for (int p0 = 0; p0 < read; p0 += kJoinAhead) {
         float mp[kJoinAhead];
 #pragma unroll
         for (int u = 0; u < kJoinAhead; ++u) mp[u] = st[(p0 + u < read ? p0 + u : 0) * pitch + 64 * kAtThreads];
 #pragma unroll
+        for (int u = 0; u < kJoinAhead; ++u) asm volatile("" : "+v"(mp[u]));
+#pragma unroll
         for (int u = 0; u < kJoinAhead; ++u) m = p0 + u < seen ? fmaxf(m, mp[u]) : m;
     }
-    constexpr int kRows = 4;
+    constexpr int kRows = 32 / NV;
     for (int p0 = 0; p0 < read; p0 += kRows) {
-        float x[kRows][10];
+        float x[kRows][NV + 2];
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
             const float *sp = st + (p0 + u < read ? p0 + u : 0) * pitch;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) x[u][i] = sp[(v0 + i) * kAtThreads];
-            x[u][8] = sp[64 * kAtThreads]; x[u][9] = sp[65 * kAtThreads];
+            for (int i = 0; i < NV; ++i) x[u][i] = sp[(v0 + i) * kAtThreads];
+            x[u][NV] = sp[64 * kAtThreads]; x[u][NV + 1] = sp[65 * kAtThreads];
         }
+#pragma unroll
+        for (int u = 0; u < kRows; ++u)
+#pragma unroll
+            for (int i = 0; i < NV + 2; ++i) asm volatile("" : "+v"(x[u][i]));
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
             if (p0 + u < seen) {
-                const float wgt = __builtin_amdgcn_exp2f(x[u][8] - m);
-                l = __builtin_fmaf(wgt, x[u][9], l);
+                const float wgt = __builtin_amdgcn_exp2f(x[u][NV] - m);
+                l = __builtin_fmaf(wgt, x[u][NV + 1], l);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) o[i] = __builtin_fmaf(wgt, x[u][i], o[i]);
+                for (int i = 0; i < NV; ++i) o[i] = __builtin_fmaf(wgt, x[u][i], o[i]);
             }
         }
     }
@@ -972,7 +1000,7 @@ void attn_join_kernel(AttnArgs a, int n_qblocks) {
     const float inv = any ? 1.0f / ltot : 0.0f;
     const int64_t at = ((int64_t)h * a.n_q + qrow) * kHeadDim + half * 4 + (v0 >> 4) * 32 + ((v0 >> 2) & 3) * 8;
 #pragma unroll
-    for (int g = 0; g < 2; ++g) {
+    for (int g = 0; g < NV / 4; ++g) {
         if (a.out_f32)
             *reinterpret_cast<float4 *>(a.out_f32 + at + g * 8) =
                 make_float4(o[4 * g] * inv, o[4 * g + 1] * inv, o[4 * g + 2] * inv, o[4 * g + 3] * inv);
@@ -987,7 +1015,12 @@ void attn_join_kernel(AttnArgs a, int n_qblocks) {
 hipError_t launch_attn_join(const AttnArgs &a, hipStream_t s) {
     const int64_t nqb = (a.n_q + kAtQPerBlock - 1) / kAtQPerBlock;
     if (nqb * a.H > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(attn_join_kernel, dim3((unsigned)(nqb * a.H), 8), dim3(kAtThreads), 0, s, a, (int)nqb);
+    const int64_t blocks = nqb * a.H;
+    const bool few = blocks <= kJoinFewBlocks;
+    const dim3 grid((unsigned)blocks, few ? 16 : 8);
+    typedef void (*join_kernel_t)(AttnArgs, int);
+    static const join_kernel_t kernels[4] = {attn_join_kernel<false, 8>, attn_join_kernel<true, 8>, attn_join_kernel<false, 4>, attn_join_kernel<true, 4>};
+    hipLaunchKernelGGL(kernels[(a.q_len ? 1 : 0) + (few ? 2 : 0)], grid, dim3(kAtThreads), 0, s, a, (int)nqb);
     return hipGetLastError();
 }
 

@@ -256,18 +256,16 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
     uint16_t *Kt = reinterpret_cast<uint16_t *>(smem);                  // [3][64][136] bf16
     uint16_t *Vt = Kt + kSlabKBufs * kKtElems;                          // [2][128][72] f16, transposed
 
-    // the query blocks of one unit run on one XCD, whose L2 then serves the unit's images to all of them
-    const int w = (int)(blockIdx.x % 8u) * blocks_per_xcd + (int)(blockIdx.x / 8u);
-    if (w >= n_blocks) return;                                          // uniform, before any barrier
-    const int parts = PARTS ? a.parts : 1;
-    const int h = w / (n_qblocks * parts);
-    const int qblock = (w - h * n_qblocks * parts) / parts;
-    const int part = PARTS ? w % parts : 0;
+    int parts = PARTS ? a.parts : 1, h, qblock, part;
+    if (!block_of<QL>(a, parts, n_qblocks, n_blocks, blocks_per_xcd, blockIdx.x, h, qblock, part)) return;      // uniform, before any barrier
+    const int w = h * n_qblocks + qblock;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
     const int64_t qrow = (int64_t)qblock * kAtQPerBlock + wave * 32 + col;
     const bool qvalid = qrow < a.n_q;
+    // no query: helps with the copy only
+    const bool idle = PARTS && (int64_t)qblock * kAtQPerBlock + __builtin_amdgcn_readfirstlane(wave) * 32 >= a.n_q;
 
     uint4 qa[8];
     {
@@ -314,8 +312,8 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
         wgmax = bmax;
         wmin = __builtin_amdgcn_readfirstlane(wmin);
         if (PARTS) {                 // a part behind the longest prefix (its first tile is tile `part`): the join does not read it
-            const int64_t full = wgmax / a.chunk_len, rest = wgmax - full * a.chunk_len;
-            if (part >= full * sl.tpc + (rest + kAtKv - 1) / kAtKv) return;                              // uniform
+            parts = block_parts(a, wgmax);
+            if (part >= parts || (parts > 1 && part >= tiles_of(a, wgmax))) return;                             // uniform
         }
     }
 
@@ -391,6 +389,26 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
         fetch_k(2); park_k(Kt + 2 * kKtElems);
         fetch_v(0); park_v(Vt);
         __syncthreads();
+        // A wavefront without queries (the last block of a unit) does the copy and the barriers of the steps below only:
+        // its SIMD is the other one's, and the energy that it saves is the clock of all (1560 queries, six blocks and 24
+        // rows, 12 heads x 31997 tokens 405 -> 392 us; undivided blocks, of which few are such, gain nothing: 4680
+        // queries over 748800 tokens 22.48 -> 22.88 ms).
+        if (idle) {                                                     // uniform per wavefront
+            fetch_v(1);
+            fetch_k(3);
+            __syncthreads();
+            int kb = 0;
+            for (int i = 0; i + 1 < count; ++i) {
+                uint16_t *vt = Vt + ((i & 1) ^ 1) * kVtElems, *kt = Kt + kb;
+                park(vt, voff[0], vimg, gv0, i + 2, 0);
+                park(vt, voff[1], vimg, gv1, i + 2, 1);
+                park(kt, koff[0], kimg, gk0, i + 4, 0);
+                park(kt, koff[1], kimg, gk1, i + 4, 1);
+                kb = kb == 2 * kKtElems ? 0 : kb + kKtElems;
+                __syncthreads();
+            }
+            return;
+        }
         floatx16_t Sa[2], Sb[2];
         bf16x8_t kf[kAhead];                                            // first fragments of the next tile's scores
 #pragma unroll
@@ -489,7 +507,8 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
             finish(Sa, 0);
         }
     }
-    if (sl.last && !PARTS) store_result(a, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
+    if (idle) return;
+    if (sl.last && parts == 1) store_result(a, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
     else store_state(st, O, m, l);
 }
 

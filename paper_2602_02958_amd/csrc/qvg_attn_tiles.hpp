@@ -79,6 +79,38 @@ __host__ __device__ __forceinline__ Tile next_tile(const Span &a, Tile t) {
     return place_tile(a, t.chunk, (int)(((int64_t)t.t0 - (int64_t)t.chunk * a.chunk_len) >> 6) + a.parts);
 }
 
+// Which query block and part a workgroup has, b: its number.  Workgroups are dealt to the 8 XCDs round-robin; they are
+// re-numbered so that the query blocks of one unit run on one XCD, whose L2 then serves the unit's cache to all of them.
+// Prefixes of different lengths (a.part_tiles) are dealt the other way, all units' last queries first: what is left
+// when the chip runs empty is short, and the XCDs have equal shares of every length.  False: none.
+template <bool QL>
+__device__ __forceinline__ bool block_of(const AttnArgs &a, int parts, int n_qblocks, int n_blocks, int blocks_per_xcd, unsigned b,
+                                         int &h, int &qblock, int &part) {
+    if (QL && a.part_tiles) {                                            // uniform
+        const int i = (int)(b / (unsigned)a.H), last = i / parts;
+        h = (int)(b % (unsigned)a.H); part = i - last * parts; qblock = n_qblocks - 1 - last;
+        return (int)b < n_blocks;
+    }
+    const int w = (int)(b % 8u) * blocks_per_xcd + (int)(b / 8u), wq = w / parts;
+    h = wq / n_qblocks; qblock = wq - h * n_qblocks; part = w - wq * parts;
+    return w < n_blocks;
+}
+// Tiles of the cache's first n tokens.
+__device__ __forceinline__ int64_t tiles_of(const AttnArgs &a, int n) {
+    const int nk = (int)a.n_kv, clen = a.chunk_len < a.n_kv ? (int)a.chunk_len : nk;
+    const int full = n / clen, rest = n - full * clen;
+    return (int64_t)full * (((int64_t)clen + kAtKv - 1) / kAtKv) + ((int64_t)rest + kAtKv - 1) / kAtKv;
+}
+
+// Parts of a block whose longest prefix is `longest` tokens.  Where the first query sees about as much, all blocks
+// are taken to, and dividing them only costs (228 blocks of 592 tiles each 1102 us, in two parts 1180, in three 1240).
+__device__ __forceinline__ int block_parts(const AttnArgs &a, int longest) {
+    if (!a.part_tiles || a.parts == 1) return a.parts;
+    const int64_t n = tiles_of(a, longest) / a.part_tiles;
+    if (n < 2 || (int64_t)a.q_len[0] * 8 >= (int64_t)longest * 7) return 1;
+    return n < a.parts ? (int)n : a.parts;
+}
+
 // Running state of a workgroup's 256 queries, [kStateFloats][512] floats: per thread its 64 output
 // values (unnormalised), the maximum and the lane's share of the normaliser.
 constexpr int kStateFloats = 66;
@@ -108,11 +140,13 @@ __device__ __forceinline__ const AttnArgs &late_args() {
     asm volatile("" : "+s"(p));
     return *(const AttnArgs *)p;
 }
+template <bool QL>
 __device__ __forceinline__ float *part_state_of_block(const AttnArgs &a, int n_qblocks, int blocks_per_xcd) {
     unsigned b = blockIdx.x;
     asm volatile("" : "+s"(b));
-    const int w = (int)(b % 8u) * blocks_per_xcd + (int)(b / 8u), wq = w / a.parts;
-    return part_state_of(a, n_qblocks, wq / n_qblocks, wq % n_qblocks, w - wq * a.parts);
+    int h, qblock, part;
+    block_of<QL>(a, a.parts, n_qblocks, 0, blocks_per_xcd, b, h, qblock, part);
+    return part_state_of(a, n_qblocks, h, qblock, part);
 }
 
 // Normalise and store one query's result: the lane holds channels 32*mb + 8*g + 4*half + 0..3 of its
