@@ -235,13 +235,13 @@ struct LloydArgs {
     int fused;                               // codes and scales are written (2-bit levels, binary16 scales)
     // scratch
     const uint2 *init_norms;                 // [H][S][Kpad]
-    uint32_t *meet;                          // [H][64]
+    uint32_t *meet;                          // [H][64]: arrivals, workgroups that gave the unit up
     uint16_t *ids_x;                         // [H][n_blocks * 256]
     bf16_t *table; uint2 *norms;             // [H][K][d], [H][Kpad]
     bf16_t *resid[2];                        // stage s leaves the next one's input [H][N][d] in resid[s & 1]
     int n_blocks, groups;                    // blocks of 256 tokens per unit; workgroups per unit
     uint32_t wait_ticks;                     // of 10 ns: the longest wait of a workgroup
-    int redo, by_xcd;                        // set by launch_lloyd
+    int by_xcd;                              // set by launch_lloyd
 };
 constexpr uint32_t kLloydWaitTicks = 200000;
 int lloyd_groups(int H, int K, int64_t n_tokens, int64_t stride_token, int iters);      // workgroups per unit, 0: not for this call

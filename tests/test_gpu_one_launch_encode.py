@@ -1,7 +1,7 @@
 """The encoder that runs all Lloyd iterations in one launch, at the sizes where its division of the work has edges:
 blocks of 256 tokens, more workgroups than blocks, more than 64 rows per workgroup, lists summed by a wavefront and by a
 workgroup (with sums that depend on the order), 16-bit ids, several stages; and the same calls with every wait between
-workgroups given up at once, which leaves the units to the second launch.  Stored arrays against the oracle, bit for bit."""
+workgroups given up at once, which leaves the units to the last of their workgroups to leave.  Stored arrays against the oracle, bit for bit."""
 import ctypes as C
 
 import numpy as np
