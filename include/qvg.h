@@ -305,7 +305,8 @@ int qvg_attn_decode_f32(const qvg_params *p, int64_t n_q, const void *q_bf16,
 
 /*
  * qvg_attn_decode_causal (out_bf16) or qvg_attn_decode_f32 (out_f32; exactly one of the two is given)
- * with scratch memory for calls of few query blocks, or of prefixes of different lengths.  Such a call fills a fraction of the chip while
+ * with scratch memory for calls of few query blocks, of prefixes of different lengths, or with a few blocks beyond a
+ * multiple of 256.  Such a call fills, or ends with, a fraction of the chip while
  * every workgroup walks the whole cache; with scratch of at least qvg_attn_scratch_bytes bytes
  * (16-byte aligned) the cache's tiles are dealt to several workgroups per query block, and one
  * more launch joins their partial results (fp32).  How many depends on n_heads, n_q, n_kv_tokens, chunk_len

@@ -325,7 +325,7 @@ def attn_decode(q, k: Encoded, v: Encoded, softmax_scale=None, want_lse=False, o
     one, calls of more than 512 queries over 256 tokens or more, without q_kv_len, take it from torch's allocator for the call: up to
     256 MiB of tiles, and up to 256 MiB of running state when the cache needs more.  One that is too
     small for a chunk (an empty tensor) is ignored.  Worth lending with q_kv_len too, unless the prefixes
-    are short: every tile of the cache is decoded.  Calls of few query blocks take up to 34 MiB for the
+    are short: every tile of the cache is decoded.  Calls of few query blocks, or with up to 128 beyond a multiple of 256, take up to 34 MiB for the
     partial results of their divided cache, with q_kv_len calls of up to 256 blocks of 256 queries up to 99 MiB; where torch has no memory left they run undivided, which
     differs by the order of fp32 sums."""
     if (v.ids.shape, v.codes.shape, v.scales.shape, v.scales.dtype, v.centroids.shape, v.chunk_len, v.n_smooth) != \

@@ -555,13 +555,14 @@ int attn_call(const qvg_params *p, int64_t n_q, const void *q, int64_t n_kv_toke
     if (!ids_aligned(p, k_ids) || !ids_aligned(p, v_ids)) return QVG_ERR_ALIGN;
     if (q_kv_len && (reinterpret_cast<uintptr_t>(q_kv_len) & 3u)) return QVG_ERR_ALIGN;
     a.q_len = q_kv_len;
-    a.parts = attn_parts(a.H, n_q, n_kv_tokens, a.chunk_len, q_kv_len != nullptr, &a.part_tiles);
-    const size_t part_bytes = attn_parts_bytes(a.H, n_q, a.parts);
+    const AttnParts parts = attn_parts(a.H, n_q, n_kv_tokens, a.chunk_len, q_kv_len != nullptr);
+    const size_t part_bytes = attn_parts_bytes(a.H, n_q, parts);
+    a.parts = parts.parts; a.part_tiles = parts.part_tiles; a.whole = parts.whole;
     if (a.parts > 1 && scratch && scratch_bytes >= part_bytes) {
         if (!aligned16(scratch)) return QVG_ERR_ALIGN;
         a.part_state = static_cast<float *>(scratch);
     } else {
-        a.parts = 1;                                   // no room for the parts' states: every workgroup walks the whole cache
+        a.parts = 1; a.whole = 0;                      // no room for the parts' states: every workgroup walks the whole cache
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     // a workspace that holds at least one chunk's decoded tiles switches to the shared-tile path
@@ -595,7 +596,7 @@ int qvg_attn_scratch_bytes(const qvg_params *p, int64_t n_q, int64_t n_kv_tokens
     if (st != QVG_OK) return st;
     if (!out) return QVG_ERR_NULL;
     if (n_q < 0 || n_kv_tokens < 1 || n_kv_tokens > 0x7fffffff || chunk_len < 1) return QVG_ERR_BAD_PARAM;
-    *out = attn_parts_bytes(p->n_heads, n_q, attn_parts(p->n_heads, n_q, n_kv_tokens, bounded_chunk_len(chunk_len), false, nullptr));
+    *out = attn_parts_bytes(p->n_heads, n_q, attn_parts(p->n_heads, n_q, n_kv_tokens, bounded_chunk_len(chunk_len), false));
     return QVG_OK;
 }
 
@@ -604,7 +605,7 @@ int qvg_attn_scratch_bytes_causal(const qvg_params *p, int64_t n_q, int64_t n_kv
     if (st != QVG_OK) return st;
     if (!out) return QVG_ERR_NULL;
     if (n_q < 0 || n_kv_tokens < 1 || n_kv_tokens > 0x7fffffff || chunk_len < 1) return QVG_ERR_BAD_PARAM;
-    *out = attn_parts_bytes(p->n_heads, n_q, attn_parts(p->n_heads, n_q, n_kv_tokens, bounded_chunk_len(chunk_len), true, nullptr));
+    *out = attn_parts_bytes(p->n_heads, n_q, attn_parts(p->n_heads, n_q, n_kv_tokens, bounded_chunk_len(chunk_len), true));
     return QVG_OK;
 }
 

@@ -46,8 +46,8 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     uint16_t *Kt = reinterpret_cast<uint16_t *>(smem);                  // [2][64][136] bf16
     uint16_t *Vt = Kt + 2 * kKtElems;                                   // [2][128][72] f16, transposed
 
-    int h, qblock, part;
-    if (!block_of<QL>(a, a.parts, n_qblocks, n_blocks, blocks_per_xcd, blockIdx.x, h, qblock, part)) return;    // uniform, before any barrier
+    int h, qblock, part, parts = a.parts;
+    if (!block_of<QL>(a, parts, n_qblocks, n_blocks, blocks_per_xcd, blockIdx.x, h, qblock, part)) return;    // uniform, before any barrier
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
@@ -57,7 +57,7 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     // query sees tokens 0 .. qlen-1; wmin = the shortest prefix in the wavefront (tiles below it
     // need no mask); the workgroup walks the cache only up to its longest prefix.
     int qlen = 0x7fffffff, wmin = 0x7fffffff;
-    Span sp = span_of(a, part);
+    Span sp = span_of(a, part, parts);
     if (QL) {
         __shared__ int bmax;
         if (tid == 0) bmax = 1;
@@ -289,7 +289,7 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     }
     // ---- normalise and store: lane holds channels 32*mb + 8*g + 4*half + 0..3 of its query ----
     const AttnArgs &e = late_args();
-    if ((QL ? sp.parts : e.parts) > 1) { if (qvalid) store_state(part_state_of_block<QL>(e, n_qblocks, blocks_per_xcd), O, m, l); }
+    if (sp.parts > 1) { if (qvalid) store_state(part_state_of_block<QL>(e, n_qblocks, blocks_per_xcd), O, m, l); }
     else store_result(e, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
 }
 
@@ -328,8 +328,8 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     typedef typename std::conditional<WIDE, uint16_t, unsigned char>::type id_t;
     id_t *idring = reinterpret_cast<id_t *>(stage + 2 * kStBytes);      // [4][2][64]: ids run one tile further ahead
 
-    int h, qblock, part;
-    if (!block_of<QL>(a, a.parts, n_qblocks, n_blocks, blocks_per_xcd, blockIdx.x, h, qblock, part)) return;    // uniform, before any barrier
+    int h, qblock, part, parts = a.parts;
+    if (!block_of<QL>(a, parts, n_qblocks, n_blocks, blocks_per_xcd, blockIdx.x, h, qblock, part)) return;    // uniform, before any barrier
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);          // uniform: lets whole waves branch
@@ -527,7 +527,7 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     // QL: the lane's query sees tokens 0 .. qlen-1; wmin = the shortest prefix in the wavefront
     // (tiles below it need no mask); the workgroup walks the cache up to its longest prefix only
     int qlen = 0x7fffffff, wmin = 0x7fffffff;
-    Span sp = span_of(a, part);
+    Span sp = span_of(a, part, parts);
     if (QL) {
         __shared__ int bmax;
         if (tid == 0) bmax = 1;
@@ -721,7 +721,7 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
         if (!tile_step(BoolC<false>{}, false)) break;
     }
     const AttnArgs &e = late_args();
-    if ((QL ? sp.parts : e.parts) > 1) { if (qvalid) store_state(part_state_of_block<QL>(e, n_qblocks, blocks_per_xcd), O, m, l); }
+    if (sp.parts > 1) { if (qvalid) store_state(part_state_of_block<QL>(e, n_qblocks, blocks_per_xcd), O, m, l); }
     else store_result(e, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
 }
 
@@ -732,13 +732,13 @@ static hipError_t launch_attn_staged_r(const AttnArgs &a, hipStream_t s) {
     hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&attn_kernel_staged<T_, ROPE, FP8, I4, WIDE, QL>), kSmem, lds_limit);
     if (e != hipSuccess) return e;
     const int64_t nqb = (a.n_q + kAtQPerBlock - 1) / kAtQPerBlock;
-    const int64_t nb = nqb * a.H * a.parts;
-    if (nb > 0x7fffffff - 8) return hipErrorInvalidValue;
+    const int64_t nb = (nqb * a.H - a.whole) * a.parts;                 // beside the whole blocks
+    if (nb + a.whole > 0x7fffffff - 8) return hipErrorInvalidValue;
     const int bpx = (int)((nb + 7) / 8);
     // the grid is padded to a multiple of 8 (one share per XCD): at most 7 surplus workgroups, whose
     // renumbered index is >= nb; each returns on its first statement, before it forms a unit index
     if ((int64_t)bpx * 8 > nb + 7) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((attn_kernel_staged<T_, ROPE, FP8, I4, WIDE, QL>), dim3((unsigned)(bpx * 8)), dim3(kAtThreads), kSmem, s, a,
+    hipLaunchKernelGGL((attn_kernel_staged<T_, ROPE, FP8, I4, WIDE, QL>), dim3((unsigned)(a.whole + bpx * 8)), dim3(kAtThreads), kSmem, s, a,
                        (int)nqb, (int)nb, bpx);
     return hipGetLastError();
 }
@@ -753,11 +753,11 @@ static hipError_t launch_attn_tr(const AttnArgs &a, hipStream_t s) {
     hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&attn_kernel_direct<T_, SM, FMT, ROPE, QL>), kAtSmem, lds_limit);
     if (e != hipSuccess) return e;
     const int64_t nqb = (a.n_q + kAtQPerBlock - 1) / kAtQPerBlock;
-    const int64_t nb = nqb * a.H * a.parts;
-    if (nb > 0x7fffffff - 8) return hipErrorInvalidValue;
+    const int64_t nb = (nqb * a.H - a.whole) * a.parts;                 // beside the whole blocks
+    if (nb + a.whole > 0x7fffffff - 8) return hipErrorInvalidValue;
     const int bpx = (int)((nb + 7) / 8);
     if ((int64_t)bpx * 8 > nb + 7) return hipErrorInvalidValue;        // at most 7 surplus workgroups, which return at once
-    hipLaunchKernelGGL((attn_kernel_direct<T_, SM, FMT, ROPE, QL>), dim3((unsigned)(bpx * 8)), dim3(kAtThreads), kAtSmem, s, a,
+    hipLaunchKernelGGL((attn_kernel_direct<T_, SM, FMT, ROPE, QL>), dim3((unsigned)(a.whole + bpx * 8)), dim3(kAtThreads), kAtSmem, s, a,
                        (int)nqb, (int)nb, bpx);
     return hipGetLastError();
 }
@@ -884,6 +884,10 @@ hipError_t launch_attn(const AttnArgs &a, hipStream_t s) {
 // parts of four tiles do not repay them (12 heads x 1560 queries over 512 tokens 30 us undivided, 34 divided; 40 x 700
 // 30.5 and 35; with 36 blocks 30 and 27; 40 x 300 over twelve tiles 32 in three parts, 36 in two).
 // From 129 query blocks on nothing is dealt: 160 blocks in three parts gain nothing (1.09 against 1.08 ms).
+// More than 256 are taken whole up to the last round of 256, and that one is dealt out if at most 128 are left for it: the
+// call would end with a few blocks on an idle chip.  266 blocks over 293 tiles 1025 -> 655 us (all blocks in four parts
+// 779), over 32 tiles 137 -> 100; 320 blocks 1048 -> 790, 384 1066 -> 945; 792 over 148 tiles 1108 -> 952; 16 x 6108 queries over 34483
+// tokens 1887 -> 1665; 570 over 18 tiles 135 -> 124.  Beyond 4096 blocks a round is a sixteenth of the call.
 // A prefix length per query makes the blocks' work differ, and a call ends with its longest block: there up to 256
 // blocks are divided too, those of 96 tiles or more in up to three parts, the longest first.  37440 tokens, four groups of
 // queries that see a quarter of them more each, 12 heads x 4680 queries 1010 -> 850 us, with queries that are new to the caches 1010 ->
@@ -892,24 +896,34 @@ hipError_t launch_attn(const AttnArgs &a, hipStream_t s) {
 // ---------------------------------------------------------------------------------------------
 constexpr int kCus = 256;
 constexpr int kLenMinBlocks = 129, kLenMinTiles = 192, kLenParts = 3, kLenPartTiles = 48;
+constexpr int kTailMaxBlocks = 4096, kTailMinTiles = 16;
 constexpr int kPartMinTiles = 4, kPartManyBlocks = 64, kPartManyMinTiles = 10;
-int attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool with_len, int *part_tiles) {
-    if (part_tiles) *part_tiles = 0;
-    if (n_q < 1 || n_kv < 1) return 1;
+AttnParts attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool with_len) {
+    AttnParts p{1, 0, 0};
+    if (n_q < 1 || n_kv < 1) return p;
     const int64_t nb = (n_q + kAtQPerBlock - 1) / kAtQPerBlock * H;
     const int64_t full = n_kv / chunk_len, rest = n_kv - full * chunk_len;
     const int64_t tiles = full * ((chunk_len + kAtKv - 1) / kAtKv) + (rest + kAtKv - 1) / kAtKv;
     if (with_len && nb >= kLenMinBlocks && tiles >= kLenMinTiles) {
-        if (part_tiles) *part_tiles = kLenPartTiles;
-        return nb <= kCus ? kLenParts : 1;
+        p.part_tiles = kLenPartTiles;
+        p.parts = nb <= kCus ? kLenParts : 1;
+        return p;
+    }
+    if (nb > kCus && nb <= kTailMaxBlocks) {
+        const int64_t rest = nb % kCus, most = tiles / kPartMinTiles;
+        if (with_len || rest == 0 || rest > kCus / 2 || tiles < kTailMinTiles) return p;
+        p.parts = (int)(kCus / rest < most ? kCus / rest : most);
+        p.whole = (int)(nb - rest);
+        return p;
     }
     const int64_t most = nb > kPartManyBlocks && tiles < kPartManyMinTiles ? 1 : tiles / kPartMinTiles;
     const int64_t parts = kCus / nb < most ? kCus / nb : most;
-    return parts > 1 ? (int)parts : 1;
+    if (parts > 1) p.parts = (int)parts;
+    return p;
 }
-size_t attn_parts_bytes(int H, int64_t n_q, int parts) {
+size_t attn_parts_bytes(int H, int64_t n_q, const AttnParts &p) {
     const int64_t nqb = (n_q + kAtQPerBlock - 1) / kAtQPerBlock;
-    return parts > 1 ? (size_t)parts * nqb * H * kStateFloats * kAtThreads * sizeof(float) : 0;
+    return p.parts > 1 ? (size_t)p.parts * (nqb * H - p.whole) * kStateFloats * kAtThreads * sizeof(float) : 0;
 }
 
 // The result of a query from the states of its parts: one workgroup per query block and NV of a lane's
@@ -925,13 +939,14 @@ constexpr int kJoinFewBlocks = 32;      // up to this many take NV = 4
 template <bool QL, int NV>         // QL: with a.q_len; NV: 4 or 8
 __global__ __launch_bounds__(kAtThreads)
 void attn_join_kernel(AttnArgs a, int n_qblocks) {
-    const int h = (int)(blockIdx.x / (unsigned)n_qblocks), qblock = (int)(blockIdx.x - (unsigned)h * n_qblocks);
+    const unsigned block = blockIdx.x + (unsigned)a.whole;
+    const int h = (int)(block / (unsigned)n_qblocks), qblock = (int)(block - (unsigned)h * n_qblocks);
     const int v0 = blockIdx.y * NV;                                      // channels 32 * (v0 / 16) + 8 * (v / 4 % 4) + 4 * half + v % 4
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, half = lane >> 5;
     const int64_t qrow = (int64_t)qblock * kAtQPerBlock + wave * 32 + col;
     const bool qvalid = qrow < a.n_q;                                    // the same for both lane halves of a query
     const float *st = part_state_of(a, n_qblocks, h, qblock, 0);
-    const int64_t pitch = (int64_t)a.H * n_qblocks * kStateFloats * kAtThreads;
+    const int64_t pitch = ((int64_t)a.H * n_qblocks - a.whole) * kStateFloats * kAtThreads;
     // the parts that saw a token of the query are the first ones; the wavefront reads those of its longest prefix (the
     // block's workgroups that lay behind all of its prefixes left nothing)
     int seen = a.parts, read = a.parts;
@@ -1015,7 +1030,7 @@ void attn_join_kernel(AttnArgs a, int n_qblocks) {
 hipError_t launch_attn_join(const AttnArgs &a, hipStream_t s) {
     const int64_t nqb = (a.n_q + kAtQPerBlock - 1) / kAtQPerBlock;
     if (nqb * a.H > 0x7fffffff) return hipErrorInvalidValue;
-    const int64_t blocks = nqb * a.H;
+    const int64_t blocks = nqb * a.H - a.whole;
     const bool few = blocks <= kJoinFewBlocks;
     const dim3 grid((unsigned)blocks, few ? 16 : 8);
     typedef void (*join_kernel_t)(AttnArgs, int);

@@ -265,7 +265,7 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
     const int64_t qrow = (int64_t)qblock * kAtQPerBlock + wave * 32 + col;
     const bool qvalid = qrow < a.n_q;
     // no query: helps with the copy only
-    const bool idle = PARTS && (int64_t)qblock * kAtQPerBlock + __builtin_amdgcn_readfirstlane(wave) * 32 >= a.n_q;
+    const bool idle = PARTS && !a.whole && (int64_t)qblock * kAtQPerBlock + __builtin_amdgcn_readfirstlane(wave) * 32 >= a.n_q;
 
     uint4 qa[8];
     {
@@ -276,7 +276,7 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
     }
     floatx16_t O[4];
     float m = kNoScore, l = 0.0f;
-    float *st = PARTS ? part_state_of(a, n_qblocks, h, qblock, part)
+    float *st = PARTS && !(a.whole && parts == 1) ? part_state_of(a, n_qblocks, h, qblock, part)
                             : sl.state ? sl.state + (int64_t)w * kStateFloats * kAtThreads + tid : nullptr;
     if (sl.first) {
 #pragma unroll
@@ -596,14 +596,14 @@ hipError_t launch_attn_slab(const AttnArgs &a, void *ws, size_t ws_bytes, hipStr
     hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kernels[form]), kSlabSmem, lds_limit[form]);
     if (e != hipSuccess) return e;
     const int64_t nqb = (a.n_q + kAtQPerBlock - 1) / kAtQPerBlock;
-    const int64_t nb = nqb * a.H * a.parts;
-    if (nb > 0x7fffffff - 8) return hipErrorInvalidValue;
+    const int64_t nb = (nqb * a.H - a.whole) * a.parts;                 // beside the whole blocks
+    if (nb + a.whole > 0x7fffffff - 8) return hipErrorInvalidValue;
     const int bpx = (int)((nb + 7) / 8);
     if ((int64_t)bpx * 8 > nb + 7) return hipErrorInvalidValue;        // at most 7 surplus workgroups, which return at once
 
     SlabArgs sl{};
     unsigned char *base = static_cast<unsigned char *>(ws);
-    sl.state = single ? nullptr : reinterpret_cast<float *>(base);      // not used by several parts
+    sl.state = single ? nullptr : reinterpret_cast<float *>(base);      // of the blocks that are not divided
     sl.tiles_cap = tpc * slab_chunks;
     sl.kimg = reinterpret_cast<uint16_t *>(base + state);
     sl.vimg = sl.kimg + (size_t)a.H * sl.tiles_cap * kImgElems;
@@ -617,7 +617,7 @@ hipError_t launch_attn_slab(const AttnArgs &a, void *ws, size_t ws_bytes, hipStr
         sl.first = c0 == 0;
         sl.last = c1 == a.n_chunks;
         if ((e = launch_slab_decode(a, sl, s)) != hipSuccess) return e;
-        hipLaunchKernelGGL(kernels[form], dim3((unsigned)(bpx * 8)), dim3(kAtThreads), kSlabSmem, s, a, sl, (int)nqb, (int)nb, bpx);
+        hipLaunchKernelGGL(kernels[form], dim3((unsigned)(a.whole + bpx * 8)), dim3(kAtThreads), kSlabSmem, s, a, sl, (int)nqb, (int)nb, bpx);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;

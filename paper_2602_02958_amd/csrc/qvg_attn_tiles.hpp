@@ -43,9 +43,9 @@ struct Span {                      // the part of the cache a workgroup walks: t
     int64_t chunk_len, n_kv; int n_chunks;
     int part, parts;
 };
-__host__ __device__ __forceinline__ Span span_of(const AttnArgs &a, int part) {
+__host__ __device__ __forceinline__ Span span_of(const AttnArgs &a, int part, int parts) {
     Span s; s.chunk_len = a.chunk_len; s.n_kv = a.n_kv; s.n_chunks = a.n_chunks;
-    s.part = part; s.parts = a.parts;
+    s.part = part; s.parts = parts;
     return s;
 }
 __host__ __device__ __forceinline__ int tiles_per_chunk(const Span &a) {
@@ -82,17 +82,23 @@ __host__ __device__ __forceinline__ Tile next_tile(const Span &a, Tile t) {
 // Which query block and part a workgroup has, b: its number.  Workgroups are dealt to the 8 XCDs round-robin; they are
 // re-numbered so that the query blocks of one unit run on one XCD, whose L2 then serves the unit's cache to all of them.
 // Prefixes of different lengths (a.part_tiles) are dealt the other way, all units' last queries first: what is left
-// when the chip runs empty is short, and the XCDs have equal shares of every length.  False: none.
+// when the chip runs empty is short, and the XCDs have equal shares of every length.  The first a.whole workgroups (a
+// multiple of 8) have a block each.  False: none.  parts: a.parts, 1 for a whole block.
 template <bool QL>
-__device__ __forceinline__ bool block_of(const AttnArgs &a, int parts, int n_qblocks, int n_blocks, int blocks_per_xcd, unsigned b,
+__device__ __forceinline__ bool block_of(const AttnArgs &a, int &parts, int n_qblocks, int n_blocks, int blocks_per_xcd, unsigned b,
                                          int &h, int &qblock, int &part) {
     if (QL && a.part_tiles) {                                            // uniform
         const int i = (int)(b / (unsigned)a.H), last = i / parts;
         h = (int)(b % (unsigned)a.H); part = i - last * parts; qblock = n_qblocks - 1 - last;
         return (int)b < n_blocks;
     }
-    const int w = (int)(b % 8u) * blocks_per_xcd + (int)(b / 8u), wq = w / parts;
-    h = wq / n_qblocks; qblock = wq - h * n_qblocks; part = w - wq * parts;
+    int first = 0;
+    if (!QL && a.whole) {                                                // uniform
+        if (b < (unsigned)a.whole) { parts = 1; blocks_per_xcd = a.whole / 8; n_blocks = a.whole; }
+        else { first = a.whole; b -= (unsigned)a.whole; }
+    }
+    const int w = (int)(b % 8u) * blocks_per_xcd + (int)(b / 8u), wq = w / parts, block = first + wq;
+    h = block / n_qblocks; qblock = block - h * n_qblocks; part = w - wq * parts;
     return w < n_blocks;
 }
 // Tiles of the cache's first n tokens.
@@ -128,7 +134,8 @@ __device__ __forceinline__ void store_state(float *st, const floatx16_t (&O)[4],
 }
 // the state of query block `qblock` of unit h as part `part` leaves it
 __device__ __forceinline__ float *part_state_of(const AttnArgs &a, int n_qblocks, int h, int qblock, int part) {
-    return a.part_state + (((int64_t)part * a.H + h) * n_qblocks + qblock) * kStateFloats * kAtThreads + threadIdx.x;
+    const int64_t block = (int64_t)h * n_qblocks + qblock - a.whole, blocks = (int64_t)a.H * n_qblocks - a.whole;
+    return a.part_state + (part * blocks + block) * kStateFloats * kAtThreads + threadIdx.x;
 }
 
 // The one-kernel forms' arguments (their kernels' first), read anew where they are called for, and the state's
@@ -144,8 +151,8 @@ template <bool QL>
 __device__ __forceinline__ float *part_state_of_block(const AttnArgs &a, int n_qblocks, int blocks_per_xcd) {
     unsigned b = blockIdx.x;
     asm volatile("" : "+s"(b));
-    int h, qblock, part;
-    block_of<QL>(a, a.parts, n_qblocks, 0, blocks_per_xcd, b, h, qblock, part);
+    int h, qblock, part, parts = a.parts;
+    block_of<QL>(a, parts, n_qblocks, 0, blocks_per_xcd, b, h, qblock, part);
     return part_state_of(a, n_qblocks, h, qblock, part);
 }
 

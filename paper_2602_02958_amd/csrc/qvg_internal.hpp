@@ -277,14 +277,15 @@ struct AttnArgs {
     float *out_f32;        // when set, the result goes here as fp32 [H][n_q][d] (not rounded to bf16) and `out` is not written
     int parts;             // the cache's tiles are dealt to this many workgroups per query block (tile g to part g % parts);
     float *part_state;     // with more than one, each leaves its running state here and launch_attn_join makes the result
+    int whole;             // the first blocks, in the order of unit and block, that are not divided (without q_len; a multiple of 8)
     int part_tiles;        // with q_len, not 0: a block has as many parts as its longest prefix has this many tiles (1 .. parts); a
                            // block of one part stores its result itself; the longest prefixes (the last queries') are taken first
 };
 hipError_t launch_attn(const AttnArgs &a, hipStream_t s);
-// parts for a call of these sizes (with_len: with a prefix length per query; part_tiles: AttnArgs', or nullptr), and the bytes
-// of their state (0 for a single part)
-int attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool with_len, int *part_tiles);
-size_t attn_parts_bytes(int H, int64_t n_q, int parts);
+// parts for a call of these sizes (with_len: with a prefix length per query), and the bytes of their state (0 for a single part)
+struct AttnParts { int parts, part_tiles, whole; };                      // as in AttnArgs
+AttnParts attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool with_len);
+size_t attn_parts_bytes(int H, int64_t n_q, const AttnParts &p);
 hipError_t launch_attn_join(const AttnArgs &a, hipStream_t s);
 // The same attention with every tile decoded once per unit into a caller-lent workspace and shared
 // by all query blocks (qvg_attn_slab.hip).  Workspace = running state of the queries (only when the
