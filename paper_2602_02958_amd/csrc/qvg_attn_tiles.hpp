@@ -48,6 +48,7 @@ __host__ __device__ __forceinline__ Span span_of(const AttnArgs &a, int part, in
     s.part = part; s.parts = parts;
     return s;
 }
+__host__ __device__ __forceinline__ Span span_of(const AttnArgs &a, int part) { return span_of(a, part, a.parts); }
 __host__ __device__ __forceinline__ int tiles_per_chunk(const Span &a) {
     const int64_t l = a.chunk_len < a.n_kv ? a.chunk_len : a.n_kv;
     return (int)((l + kAtKv - 1) / kAtKv);
