@@ -28,7 +28,7 @@ namespace qvg {
 
 constexpr uint32_t kUnitFailed = 0x80000000u;
 constexpr int kMeetWords = 64;                   // a 256-byte line per unit
-constexpr int kLloydMaxBlocks = 48;              // blocks of 256 tokens per unit (LDS of two workgroups to a CU; token numbers of 16 bits)
+constexpr int kLloydMaxBlocks = 24;              // blocks of 256 tokens per unit (lloyd_groups; token numbers have 16 bits)
 constexpr int kListLong = 128;                   // lists at least this long are summed by the whole workgroup,
 constexpr int kListShared = 32;                  // where it has one or two rows, at least this long
 constexpr int kRowsAhead = 16;                   // members in flight (a power of two)
@@ -621,6 +621,9 @@ static hipError_t launch_lloyd_t(LloydArgs a, hipStream_t s) {
 // - or a unit has up to eight blocks and its lists are short on average (up to 40 members: 6 units x 2000 tokens, K = 64
 //   61 -> 59 us, K = 16 62 -> 70).  Every workgroup looks through its whole unit's ids, and few units with long
 //   lists have too few wavefronts for the sums: 2 units x 10800, K = 64 65 -> 84 us.
+// For the same reason units of more than 24 blocks are left out (I = 10: 8 units x 10800, K = 16 274 -> 324 us, K = 64 257 -> 284, K = 256
+// 304 -> 316), and those of more than 21, which only calls of up to 16 units have, where lists are long (16 x 6000, K = 16
+// 282 -> 309, K = 64 242 -> 254, but K = 256 325 -> 285; 22 x 4500, K = 16 317 -> 233).
 // A workgroup with many rows and few blocks to share them is slower too (80 x 800, K = 256: 64 rows each, 111 -> 119 us; 80 x
 // 1536, 43 rows, 142 -> 122).
 int lloyd_groups(int H, int K, int64_t n_tokens, int64_t stride_token, int iters) {
@@ -636,6 +639,7 @@ int lloyd_groups(int H, int K, int64_t n_tokens, int64_t stride_token, int iters
     }
     const int64_t units = H >= 8 ? (H + 7) / 8 * 8 : H;                  // by_xcd: whole rounds of the eight XCDs
     if (units * nb > (int64_t)n * (K > 256 ? 1 : 2)) return 0;
+    if (nb > 21 && n_tokens > (int64_t)64 * K) return 0;
     if (H * nb < 300 && (nb > 8 || n_tokens > (int64_t)40 * K)) return 0;
     // A chip that is not full: more workgroups than blocks, which take rows of the update only, at least eight of them,
     // and at most one workgroup to a CU in all (10 units x 1571 tokens, K = 256: 78 -> 69 us)

@@ -63,8 +63,8 @@ SHAPES = [
     (2, 2047, 256, 1, 3, 1, 16, 2, True, True),
     (10, 300, 256, 1, 2, 1, 64, 4, True, False),        # more workgroups than blocks
     (40, 1536, 512, 1, 1, 1, 64, 2, False, False),      # 86 rows per workgroup, 16-bit ids
-    (8, 9729, 33, 1, 2, 2, 64, 2, False, True),         # 39 blocks; the longest lists
-    (8, 12288, 64, 1, 1, 5, 128, 2, False, False),      # the most blocks
+    (24, 5121, 16, 1, 2, 2, 64, 2, False, True),        # 21 blocks; the longest lists
+    (16, 6144, 96, 1, 1, 5, 128, 2, False, False),      # the most blocks
     (5, 700, 256, 4, 2, 1, 16, 2, True, False),         # four stages
     (3, 600, 300, 2, 2, 2, 64, 2, False, True),         # two, 16-bit ids
 ]
