@@ -34,9 +34,9 @@ namespace qvg {
 // not fit in LDS), for chunks whose scale records do not start on 16-byte boundaries, and for
 // several smoothing stages (the rows of all stages are added as they arrive).
 
-template <int T_, int SM, int FMT, bool ROPE, bool QL>   // T_ > 0: compile-time stage count; 0: run-time (up to kMaxStages).
+template <int T_, int SM, int FMT, bool ROPE, int FORM>   // T_ > 0: compile-time stage count; 0: run-time (up to kMaxStages).
                                 // SM: smoothing stages (a.S tables and id bytes): 1, 2..4, or 0 = a.S
-                                // QL: a prefix length per query (a.q_len)
+                                // FORM: a BlockForm; QL: with a prefix length per query (a.q_len)
                                 // FMT: stored format (kFmt* bits)
                                 // ROPE: rotate the decoded keys by a.rope
 __global__ __launch_bounds__(kAtThreads, 2)
@@ -46,8 +46,16 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     uint16_t *Kt = reinterpret_cast<uint16_t *>(smem);                  // [2][64][136] bf16
     uint16_t *Vt = Kt + 2 * kKtElems;                                   // [2][128][72] f16, transposed
 
-    int h, qblock, part, parts = a.parts;
-    if (!block_of<QL>(a, parts, n_qblocks, n_blocks, blocks_per_xcd, blockIdx.x, h, qblock, part)) return;    // uniform, before any barrier
+    constexpr bool QL = FORM != kPlain;
+    Place at;
+    if (!block_of<FORM>(a, n_qblocks, n_blocks, blocks_per_xcd, blockIdx.x, at)) return;            // uniform, before any barrier
+    // How the end of the kernel learns where its result goes: from LDS, or (kLengths; several stages) as in `e` below.  The
+    // compiler's allocation decides: 21 heads x 250 queries over 20000 tokens, five rounds 174 us without, 158 with;
+    // four stages of one round 128 and 139.
+    constexpr bool kKeep = FORM == kLengthsParted || (FORM == kPlain && SM == 1);
+    __shared__ Place kept;
+    if (kKeep && threadIdx.x == 0) kept = at;
+    const int h = at.h, qblock = at.qblock;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
@@ -57,7 +65,7 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     // query sees tokens 0 .. qlen-1; wmin = the shortest prefix in the wavefront (tiles below it
     // need no mask); the workgroup walks the cache only up to its longest prefix.
     int qlen = 0x7fffffff, wmin = 0x7fffffff;
-    Span sp = span_of(a, part, parts);
+    Span sp = span_of(a, at.part, at.parts);
     if (QL) {
         __shared__ int bmax;
         if (tid == 0) bmax = 1;
@@ -75,9 +83,10 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
         __syncthreads();
         sp.n_kv = __builtin_amdgcn_readfirstlane(bmax);
         sp.n_chunks = (int)((sp.n_kv + sp.chunk_len - 1) / sp.chunk_len);
-        if (a.part_tiles) {                                              // uniform
-            sp.parts = block_parts(a, (int)sp.n_kv);
-            if (part >= sp.parts) return;                                // uniform
+        if (FORM == kLengthsParted) {
+            sp.parts = __builtin_amdgcn_readfirstlane(block_parts(a, (int)sp.n_kv));
+            if (at.part >= sp.parts) return;                             // uniform
+            if (tid == 0) kept.parts = sp.parts;
         }
         wmin = __builtin_amdgcn_readfirstlane(wmin);
     }
@@ -289,8 +298,20 @@ void attn_kernel_direct(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     }
     // ---- normalise and store: lane holds channels 32*mb + 8*g + 4*half + 0..3 of its query ----
     const AttnArgs &e = late_args();
-    if (sp.parts > 1) { if (qvalid) store_state(part_state_of_block<QL>(e, n_qblocks, blocks_per_xcd), O, m, l); }
-    else store_result(e, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
+    if (!kKeep) {
+        if ((QL ? e.parts : sp.parts) > 1) {
+            const Place end = late_place<FORM>(e, n_qblocks, blocks_per_xcd);
+            if (qvalid) store_state(part_state_of(e, n_qblocks, end.h, end.qblock, end.part), O, m, l);
+        } else store_result(e, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
+    } else {
+        const Place end = kept.uniform();
+        const int te = late_thread();
+        const int64_t row = (int64_t)end.qblock * kAtQPerBlock + (te >> 6) * 32 + (te & 31);
+        const bool stored = row < e.n_q;
+        const int late_half = SM != 1 && (FMT & kFmtInt4) ? half : (te >> 5) & 1;   // (worked out anew there, 92 registers spill instead of 37)
+        if (end.parts > 1) { if (stored) store_state(part_state_of(e, n_qblocks, end.h, end.qblock, end.part), O, m, l); }
+        else store_result(e, end.h, row, stored && (!QL || qlen > 0), stored, late_half, O, m, l);
+    }
 }
 
 
@@ -312,10 +333,10 @@ constexpr size_t kAtSmemStagedWide = kAtSmemStaged + 4 * 2 * kAtKv;      // the 
 
 template <bool V> struct BoolC { static constexpr bool value = V; };
 
-template <int T_, bool ROPE, bool FP8, bool I4, bool WIDE, bool QL>   // ROPE: rotate the decoded keys by a.rope; FP8: E4M3 scale bytes;
+template <int T_, bool ROPE, bool FP8, bool I4, bool WIDE, int FORM>   // ROPE: rotate the decoded keys by a.rope; FP8: E4M3 scale bytes;
                                                   // I4: 4-bit levels (64 code bytes per token and round, T_ <= 2);
                                                   // WIDE: 16-bit ids (more than 256 centroids);
-                                                  // QL: a prefix length per query (a.q_len)
+                                                  // FORM: a BlockForm; QL: with a prefix length per query (a.q_len)
 __global__ __launch_bounds__(kAtThreads, 2)
 void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_xcd) {
     constexpr int T = T_;
@@ -328,8 +349,12 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     typedef typename std::conditional<WIDE, uint16_t, unsigned char>::type id_t;
     id_t *idring = reinterpret_cast<id_t *>(stage + 2 * kStBytes);      // [4][2][64]: ids run one tile further ahead
 
-    int h, qblock, part, parts = a.parts;
-    if (!block_of<QL>(a, parts, n_qblocks, n_blocks, blocks_per_xcd, blockIdx.x, h, qblock, part)) return;    // uniform, before any barrier
+    constexpr bool QL = FORM != kPlain;
+    Place at;
+    if (!block_of<FORM>(a, n_qblocks, n_blocks, blocks_per_xcd, blockIdx.x, at)) return;            // uniform, before any barrier
+    __shared__ Place kept;                                              // for the end of the kernel
+    if (FORM != kLengths && threadIdx.x == 0) kept = at;
+    const int h = at.h, qblock = at.qblock;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);          // uniform: lets whole waves branch
@@ -527,7 +552,7 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
     // QL: the lane's query sees tokens 0 .. qlen-1; wmin = the shortest prefix in the wavefront
     // (tiles below it need no mask); the workgroup walks the cache up to its longest prefix only
     int qlen = 0x7fffffff, wmin = 0x7fffffff;
-    Span sp = span_of(a, part, parts);
+    Span sp = span_of(a, at.part, at.parts);
     if (QL) {
         __shared__ int bmax;
         if (tid == 0) bmax = 1;
@@ -545,9 +570,10 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
         __syncthreads();
         sp.n_kv = __builtin_amdgcn_readfirstlane(bmax);
         sp.n_chunks = (int)((sp.n_kv + sp.chunk_len - 1) / sp.chunk_len);
-        if (a.part_tiles) {                                              // uniform
-            sp.parts = block_parts(a, (int)sp.n_kv);
-            if (part >= sp.parts) return;                                // uniform
+        if (FORM == kLengthsParted) {
+            sp.parts = __builtin_amdgcn_readfirstlane(block_parts(a, (int)sp.n_kv));
+            if (at.part >= sp.parts) return;                             // uniform
+            if (tid == 0) kept.parts = sp.parts;
         }
         wmin = __builtin_amdgcn_readfirstlane(wmin);
     }
@@ -721,15 +747,26 @@ void attn_kernel_staged(AttnArgs a, int n_qblocks, int n_blocks, int blocks_per_
         if (!tile_step(BoolC<false>{}, false)) break;
     }
     const AttnArgs &e = late_args();
-    if (sp.parts > 1) { if (qvalid) store_state(part_state_of_block<QL>(e, n_qblocks, blocks_per_xcd), O, m, l); }
-    else store_result(e, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
+    if (FORM == kLengths) {
+        if (e.parts > 1) {
+            const Place end = late_place<FORM>(e, n_qblocks, blocks_per_xcd);
+            if (qvalid) store_state(part_state_of(e, n_qblocks, end.h, end.qblock, end.part), O, m, l);
+        } else store_result(e, h, qrow, qvalid && qlen > 0, qvalid, half, O, m, l);
+    } else {
+        const Place end = kept.uniform();
+        const int te = late_thread();
+        const int64_t row = (int64_t)end.qblock * kAtQPerBlock + (te >> 6) * 32 + (te & 31);
+        const bool stored = row < e.n_q;
+        if (end.parts > 1) { if (stored) store_state(part_state_of(e, n_qblocks, end.h, end.qblock, end.part), O, m, l); }
+        else store_result(e, end.h, row, stored && (!QL || qlen > 0), stored, (te >> 5) & 1, O, m, l);
+    }
 }
 
-template <int T_, bool ROPE, bool FP8, bool I4, bool WIDE, bool QL = false>
+template <int T_, bool ROPE, bool FP8, bool I4, bool WIDE, int FORM = kPlain>
 static hipError_t launch_attn_staged_r(const AttnArgs &a, hipStream_t s) {
     constexpr size_t kSmem = WIDE ? kAtSmemStagedWide : kAtSmemStaged;
     static LdsHighWater lds_limit = {};
-    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&attn_kernel_staged<T_, ROPE, FP8, I4, WIDE, QL>), kSmem, lds_limit);
+    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&attn_kernel_staged<T_, ROPE, FP8, I4, WIDE, FORM>), kSmem, lds_limit);
     if (e != hipSuccess) return e;
     const int64_t nqb = (a.n_q + kAtQPerBlock - 1) / kAtQPerBlock;
     const int64_t nb = (nqb * a.H - a.whole) * a.parts;                 // beside the whole blocks
@@ -738,7 +775,7 @@ static hipError_t launch_attn_staged_r(const AttnArgs &a, hipStream_t s) {
     // the grid is padded to a multiple of 8 (one share per XCD): at most 7 surplus workgroups, whose
     // renumbered index is >= nb; each returns on its first statement, before it forms a unit index
     if ((int64_t)bpx * 8 > nb + 7) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((attn_kernel_staged<T_, ROPE, FP8, I4, WIDE, QL>), dim3((unsigned)(a.whole + bpx * 8)), dim3(kAtThreads), kSmem, s, a,
+    hipLaunchKernelGGL((attn_kernel_staged<T_, ROPE, FP8, I4, WIDE, FORM>), dim3((unsigned)(a.whole + bpx * 8)), dim3(kAtThreads), kSmem, s, a,
                        (int)nqb, (int)nb, bpx);
     return hipGetLastError();
 }
@@ -747,17 +784,17 @@ static hipError_t launch_attn_staged(const AttnArgs &a, hipStream_t s) {
     return a.rope ? launch_attn_staged_r<T_, true, FP8, I4, WIDE>(a, s) : launch_attn_staged_r<T_, false, FP8, I4, WIDE>(a, s);
 }
 
-template <int T_, int SM, int FMT, bool ROPE, bool QL = false>
+template <int T_, int SM, int FMT, bool ROPE, int FORM = kPlain>
 static hipError_t launch_attn_tr(const AttnArgs &a, hipStream_t s) {
     static LdsHighWater lds_limit = {};
-    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&attn_kernel_direct<T_, SM, FMT, ROPE, QL>), kAtSmem, lds_limit);
+    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&attn_kernel_direct<T_, SM, FMT, ROPE, FORM>), kAtSmem, lds_limit);
     if (e != hipSuccess) return e;
     const int64_t nqb = (a.n_q + kAtQPerBlock - 1) / kAtQPerBlock;
     const int64_t nb = (nqb * a.H - a.whole) * a.parts;                 // beside the whole blocks
     if (nb + a.whole > 0x7fffffff - 8) return hipErrorInvalidValue;
     const int bpx = (int)((nb + 7) / 8);
     if ((int64_t)bpx * 8 > nb + 7) return hipErrorInvalidValue;        // at most 7 surplus workgroups, which return at once
-    hipLaunchKernelGGL((attn_kernel_direct<T_, SM, FMT, ROPE, QL>), dim3((unsigned)(a.whole + bpx * 8)), dim3(kAtThreads), kAtSmem, s, a,
+    hipLaunchKernelGGL((attn_kernel_direct<T_, SM, FMT, ROPE, FORM>), dim3((unsigned)(a.whole + bpx * 8)), dim3(kAtThreads), kAtSmem, s, a,
                        (int)nqb, (int)nb, bpx);
     return hipGetLastError();
 }
@@ -783,42 +820,47 @@ static hipError_t launch_attn_fmt(const AttnArgs &a, hipStream_t s) {
     return launch_attn_t<0, 1, FMT>(a, s);
 }
 
-template <int FMT>
+template <int FMT, int FORM>
 static hipError_t launch_attn_qlen(const AttnArgs &a, hipStream_t s) {
-    if (a.S > 1) return a.rope ? launch_attn_tr<0, 0, FMT, true, true>(a, s) : launch_attn_tr<0, 0, FMT, false, true>(a, s);
-    return a.rope ? launch_attn_tr<0, 1, FMT, true, true>(a, s) : launch_attn_tr<0, 1, FMT, false, true>(a, s);
+    if (a.S > 1) return a.rope ? launch_attn_tr<0, 0, FMT, true, FORM>(a, s) : launch_attn_tr<0, 0, FMT, false, FORM>(a, s);
+    return a.rope ? launch_attn_tr<0, 1, FMT, true, FORM>(a, s) : launch_attn_tr<0, 1, FMT, false, FORM>(a, s);
 }
 
-template <int T_>
+template <int T_, int FORM>
 static hipError_t launch_attn_staged_qlen(const AttnArgs &a, hipStream_t s) {
-    return a.rope ? launch_attn_staged_r<T_, true, false, false, false, true>(a, s)
-                  : launch_attn_staged_r<T_, false, false, false, false, true>(a, s);
+    return a.rope ? launch_attn_staged_r<T_, true, false, false, false, FORM>(a, s)
+                  : launch_attn_staged_r<T_, false, false, false, false, FORM>(a, s);
+}
+
+// a prefix per query: the staged kernel for the plain format (2-bit levels, binary16 scales,
+// one smoothing stage, byte ids, up to 4 rounds, aligned chunks); else instances of the
+// general kernel with run-time counts
+template <int FORM>
+static hipError_t launch_attn_lengths(const AttnArgs &a, hipStream_t s) {
+    const bool al = ((a.chunk_len % 8 == 0) || a.n_chunks == 1) &&
+        (reinterpret_cast<uintptr_t>(a.k_scales) & 15u) == 0 && (reinterpret_cast<uintptr_t>(a.v_scales) & 15u) == 0 &&
+        (a.H == 1 || (a.kv_stride * a.T * (kHeadDim / a.B) * 2) % 16 == 0);
+    if (a.fmt == 0 && a.S == 1 && !a.id_wide && al && a.T <= kStMaxT) {
+        switch (a.T) {
+            case 1: return launch_attn_staged_qlen<1, FORM>(a, s);
+            case 2: return launch_attn_staged_qlen<2, FORM>(a, s);
+            case 3: return launch_attn_staged_qlen<3, FORM>(a, s);
+            default: return launch_attn_staged_qlen<4, FORM>(a, s);
+        }
+    }
+    switch (a.fmt) {
+        case 0: return launch_attn_qlen<0, FORM>(a, s);
+        case kFmtE4M3: return launch_attn_qlen<kFmtE4M3, FORM>(a, s);
+        case kFmtInt4: return launch_attn_qlen<kFmtInt4, FORM>(a, s);
+        default: return launch_attn_qlen<kFmtInt4 | kFmtE4M3, FORM>(a, s);
+    }
 }
 
 hipError_t launch_attn(const AttnArgs &a, hipStream_t s) {
     if (a.n_q == 0) return hipSuccess;
-    if (a.q_len) {
-        // a prefix per query: the staged kernel for the plain format (2-bit levels, binary16 scales,
-        // one smoothing stage, byte ids, up to 4 rounds, aligned chunks); else instances of the
-        // general kernel with run-time counts
-        const bool al = ((a.chunk_len % 8 == 0) || a.n_chunks == 1) &&
-            (reinterpret_cast<uintptr_t>(a.k_scales) & 15u) == 0 && (reinterpret_cast<uintptr_t>(a.v_scales) & 15u) == 0 &&
-            (a.H == 1 || (a.kv_stride * a.T * (kHeadDim / a.B) * 2) % 16 == 0);
-        if (a.fmt == 0 && a.S == 1 && !a.id_wide && al && a.T <= kStMaxT) {
-            switch (a.T) {
-                case 1: return launch_attn_staged_qlen<1>(a, s);
-                case 2: return launch_attn_staged_qlen<2>(a, s);
-                case 3: return launch_attn_staged_qlen<3>(a, s);
-                default: return launch_attn_staged_qlen<4>(a, s);
-            }
-        }
-        switch (a.fmt) {
-            case 0: return launch_attn_qlen<0>(a, s);
-            case kFmtE4M3: return launch_attn_qlen<kFmtE4M3>(a, s);
-            case kFmtInt4: return launch_attn_qlen<kFmtInt4>(a, s);
-            default: return launch_attn_qlen<kFmtInt4 | kFmtE4M3>(a, s);
-        }
-    }
+    // (one form for both spills more registers in the general kernel: 3 heads x 2242 queries over 231194 tokens, K = 512,
+    // 1671 us with an instance of its own, 1784 without; 4-bit levels 735 and 795)
+    if (a.q_len) return a.part_tiles ? launch_attn_lengths<kLengthsParted>(a, s) : launch_attn_lengths<kLengths>(a, s);
     // the staged kernel fetches scales in 16-byte pieces: every chunk must start on one
     // (binary16 scales: chunk_len * T * G * 2 bytes a multiple of 16; the test below is the sufficient
     // chunk_len % 8 == 0) and so must every unit's array (units are kv_stride tokens apart)

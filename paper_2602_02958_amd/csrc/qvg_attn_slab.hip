@@ -244,21 +244,24 @@ __device__ __forceinline__ void slab_rescale(float m_new, float &m, float &l, fl
     m = m_new;
 }
 
+// The running state of a workgroup's queries between slabs, or behind its part.
+template <bool PARTS>
+__device__ __forceinline__ float *slab_state(const AttnArgs &a, const SlabArgs &sl, int n_qblocks, const Place &at) {
+    if (PARTS) return part_state_of(a, n_qblocks, at.h, at.qblock, at.part);
+    return sl.state + ((int64_t)at.h * n_qblocks + at.qblock) * kStateFloats * kAtThreads + threadIdx.x;
+}
+
 // One workgroup = 8 wavefronts = 256 queries of one unit, over the tiles of one slab.
 // QL: a prefix length per query (a.q_len): scores beyond the lane's prefix are masked in the tiles
 // at or past the shortest prefix of the wavefront, and the workgroup stops at the longest prefix
 // among its 256 queries.
 // PARTS: the tiles are dealt to several workgroups per query block (a.parts).
 template <bool QL, bool PARTS>
-__global__ __launch_bounds__(kAtThreads, 2)
-void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int blocks_per_xcd) {
-    extern __shared__ __align__(16) unsigned char smem[];
+__device__ __forceinline__ void attend_slab(const AttnArgs &a, const SlabArgs &sl, int n_qblocks, Place at, Place &kept, unsigned char *smem) {
     uint16_t *Kt = reinterpret_cast<uint16_t *>(smem);                  // [3][64][136] bf16
     uint16_t *Vt = Kt + kSlabKBufs * kKtElems;                          // [2][128][72] f16, transposed
-
-    int parts = PARTS ? a.parts : 1, h, qblock, part;
-    if (!block_of<QL>(a, parts, n_qblocks, n_blocks, blocks_per_xcd, blockIdx.x, h, qblock, part)) return;      // uniform, before any barrier
-    const int w = h * n_qblocks + qblock;
+    if (threadIdx.x == 0) kept = at;                                    // for the end of the kernel
+    const int h = at.h, qblock = at.qblock;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
@@ -276,14 +279,13 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
     }
     floatx16_t O[4];
     float m = kNoScore, l = 0.0f;
-    float *st = PARTS && !(a.whole && parts == 1) ? part_state_of(a, n_qblocks, h, qblock, part)
-                            : sl.state ? sl.state + (int64_t)w * kStateFloats * kAtThreads + tid : nullptr;
     if (sl.first) {
 #pragma unroll
         for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) O[mb][r] = 0.0f;
     } else {
+        const float *st = slab_state<PARTS>(a, sl, n_qblocks, at);
 #pragma unroll
         for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
@@ -312,8 +314,9 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
         wgmax = bmax;
         wmin = __builtin_amdgcn_readfirstlane(wmin);
         if (PARTS) {                 // a part behind the longest prefix (its first tile is tile `part`): the join does not read it
-            parts = block_parts(a, wgmax);
-            if (part >= parts || (parts > 1 && part >= tiles_of(a, wgmax))) return;                             // uniform
+            at.parts = __builtin_amdgcn_readfirstlane(block_parts(a, wgmax));
+            if (at.part >= at.parts || (at.parts > 1 && at.part >= tiles_of(a, wgmax))) return;                 // uniform
+            if (tid == 0) kept.parts = at.parts;
         }
     }
 
@@ -334,8 +337,9 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
         const int64_t e = rel <= 0 ? 0 : full * sl.tpc + (rel - full * a.chunk_len + kAtKv - 1) / kAtKv;
         ne = e < n ? (int)e : n;
     }
+    const int parts = PARTS ? at.parts : 1;
     // this part's share of them: tiles i0, i0 + parts, ... of the slab (part g % parts has tile g of the cache)
-    const int i0 = !PARTS ? 0 : (int)(((int64_t)part + parts - (int64_t)sl.c0 * sl.tpc % parts) % parts);
+    const int i0 = !PARTS ? 0 : (int)(((int64_t)at.part + parts - (int64_t)sl.c0 * sl.tpc % parts) % parts);
     const int count = i0 < ne ? (ne - i0 + parts - 1) / parts : 0;
     // the slab's index of the part's j-th tile; past the end: the last tile (never used)
     auto clampt = [&](int j) { return j < count ? i0 + j * parts : n - 1; };
@@ -507,9 +511,26 @@ void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int 
             finish(Sa, 0);
         }
     }
-    if (idle) return;
-    if (sl.last && parts == 1) store_result(a, h, qrow, qvalid && (!QL || qlen > 0), qvalid, half, O, m, l);
-    else store_state(st, O, m, l);
+    if (count == 0) __syncthreads();                                    // uniform: `kept` has been written
+    const Place end = kept.uniform();
+    const AttnArgs &e = late_args();
+    const int te = late_thread();
+    const int64_t row = (int64_t)end.qblock * kAtQPerBlock + (te >> 6) * 32 + (te & 31);
+    const bool stored = row < e.n_q;
+    if (sl.last && end.parts == 1) store_result(e, end.h, row, stored && (!QL || qlen > 0), stored, (te >> 5) & 1, O, m, l);
+    else store_state(slab_state<PARTS>(e, sl, n_qblocks, end), O, m, l);
+}
+
+// A whole block takes the form that has no parts.
+template <bool QL, bool PARTS>
+__global__ __launch_bounds__(kAtThreads, 2)
+void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int blocks_per_xcd) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ Place kept;
+    Place at;
+    if (!block_of<QL ? kLengthsParted : kPlain>(a, n_qblocks, n_blocks, blocks_per_xcd, blockIdx.x, at)) return;     // uniform, before any barrier
+    if (PARTS && at.parts > 1) attend_slab<QL, PARTS>(a, sl, n_qblocks, at, kept, smem);
+    else attend_slab<QL, false>(a, sl, n_qblocks, at, kept, smem);
 }
 
 // ---- host side ---------------------------------------------------------------------------------

@@ -80,33 +80,54 @@ __host__ __device__ __forceinline__ Tile next_tile(const Span &a, Tile t) {
     return place_tile(a, t.chunk, (int)(((int64_t)t.t0 - (int64_t)t.chunk * a.chunk_len) >> 6) + a.parts);
 }
 
-// Which query block and part a workgroup has, b: its number.  Workgroups are dealt to the 8 XCDs round-robin; they are
-// re-numbered so that the query blocks of one unit run on one XCD, whose L2 then serves the unit's cache to all of them.
-// Prefixes of different lengths (a.part_tiles) are dealt the other way, all units' last queries first: what is left
-// when the chip runs empty is short, and the XCDs have equal shares of every length.  The first a.whole workgroups (a
-// multiple of 8) have a block each.  False: none.  parts: a.parts, 1 for a whole block.
-template <bool QL>
-__device__ __forceinline__ bool block_of(const AttnArgs &a, int &parts, int n_qblocks, int n_blocks, int blocks_per_xcd, unsigned b,
-                                         int &h, int &qblock, int &part) {
-    if (QL && a.part_tiles) {                                            // uniform
-        const int i = (int)(b / (unsigned)a.H), last = i / parts;
-        h = (int)(b % (unsigned)a.H); part = i - last * parts; qblock = n_qblocks - 1 - last;
-        return (int)b < n_blocks;
-    }
-    int first = 0;
-    if (!QL && a.whole) {                                                // uniform
-        if (b < (unsigned)a.whole) { parts = 1; blocks_per_xcd = a.whole / 8; n_blocks = a.whole; }
-        else { first = a.whole; b -= (unsigned)a.whole; }
-    }
-    const int w = (int)(b % 8u) * blocks_per_xcd + (int)(b / 8u), wq = w / parts, block = first + wq;
-    h = block / n_qblocks; qblock = block - h * n_qblocks; part = w - wq * parts;
-    return w < n_blocks;
-}
 // Tiles of the cache's first n tokens.
 __device__ __forceinline__ int64_t tiles_of(const AttnArgs &a, int n) {
     const int nk = (int)a.n_kv, clen = a.chunk_len < a.n_kv ? (int)a.chunk_len : nk;
     const int full = n / clen, rest = n - full * clen;
     return (int64_t)full * (((int64_t)clen + kAtKv - 1) / kAtKv) + ((int64_t)rest + kAtKv - 1) / kAtKv;
+}
+
+// A workgroup's unit, query block, part, and the parts of its block.
+struct Place {
+    int h, qblock, part, parts;
+    __device__ __forceinline__ Place uniform() const {                   // (values that went through LDS or a division)
+        return Place{__builtin_amdgcn_readfirstlane(h), __builtin_amdgcn_readfirstlane(qblock),
+                     __builtin_amdgcn_readfirstlane(part), __builtin_amdgcn_readfirstlane(parts)};
+    }
+};
+
+// Which query block and part a workgroup has, b: its number.  Workgroups are dealt to the 8 XCDs round-robin; they are
+// re-numbered so that the query blocks of one unit run on one XCD, whose L2 then serves the unit's cache to all of them.
+// Prefixes of different lengths (a.part_tiles) are dealt the other way, all units' last queries first: what is left
+// when the chip runs empty is short, and the XCDs have equal shares of every length.  The first a.whole workgroups (a
+// multiple of 8) have a block each.  False: none.  at.parts: at most.
+// FORM: a template parameter, so that what a call does not need takes no registers from its tile loop.
+enum BlockForm { kPlain, kLengths, kLengthsParted };                     // no q_len; q_len; q_len, and a.part_tiles may be set
+template <int FORM>
+__device__ __forceinline__ bool block_of(const AttnArgs &a, int n_qblocks, int n_blocks, int blocks_per_xcd, unsigned b, Place &at) {
+    if (FORM == kLengths) {
+        const int w = (int)(b % 8u) * blocks_per_xcd + (int)(b / 8u);
+        at.h = w / (n_qblocks * a.parts);
+        at.qblock = (w - at.h * n_qblocks * a.parts) / a.parts;
+        at.part = w % a.parts; at.parts = a.parts;
+        return w < n_blocks;
+    }
+    int parts = a.parts, h, qblock, part;
+    if (FORM == kLengthsParted && a.part_tiles) {                        // uniform
+        const int i = (int)(b / (unsigned)a.H), last = i / parts;
+        h = (int)(b % (unsigned)a.H); part = i - last * parts; qblock = n_qblocks - 1 - last;
+        at = Place{h, qblock, part, parts}.uniform();
+        return (int)b < n_blocks;
+    }
+    int first = 0;
+    if (FORM == kPlain && a.whole) {                                     // uniform
+        if (b < (unsigned)a.whole) { parts = 1; blocks_per_xcd = a.whole / 8; n_blocks = a.whole; }
+        else { first = a.whole; b -= (unsigned)a.whole; }
+    }
+    const int w = (int)(b % 8u) * blocks_per_xcd + (int)(b / 8u), wq = w / parts, block = first + wq;
+    h = block / n_qblocks; qblock = block - h * n_qblocks; part = w - wq * parts;
+    at = Place{h, qblock, part, parts}.uniform();
+    return w < n_blocks;
 }
 
 // Parts of a block whose longest prefix is `longest` tokens.  Where the first query sees about as much, all blocks
@@ -139,22 +160,27 @@ __device__ __forceinline__ float *part_state_of(const AttnArgs &a, int n_qblocks
     return a.part_state + (part * blocks + block) * kStateFloats * kAtThreads + threadIdx.x;
 }
 
-// The one-kernel forms' arguments (their kernels' first), read anew where they are called for, and the state's
-// place worked out anew from the workgroup's number: what only the end of the kernel needs would otherwise
-// be loaded at its start and carried through the tile loop, and scalar registers spill there (general
-// kernel, 40 heads x 1560 queries over 8192 tokens with prefix lengths, 1.30 ms instead of 1.20).
+// A kernel's arguments (the first parameter), read anew where they are called for, the workgroup's block and
+// part, which wait in LDS, and the thread's query, worked out anew: what only the end of the kernel needs
+// would otherwise be carried through the tile loop, and registers spill there (general kernel, 40 heads x 1560 queries over
+// 8192 tokens with prefix lengths, 1.30 ms instead of 1.20 with the arguments alone carried).
 __device__ __forceinline__ const AttnArgs &late_args() {
     auto p = __builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(p));
     return *(const AttnArgs *)p;
 }
-template <bool QL>
-__device__ __forceinline__ float *part_state_of_block(const AttnArgs &a, int n_qblocks, int blocks_per_xcd) {
+__device__ __forceinline__ int late_thread() {
+    int t = (int)threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+template <int FORM>
+__device__ __forceinline__ Place late_place(const AttnArgs &a, int n_qblocks, int blocks_per_xcd) {
     unsigned b = blockIdx.x;
     asm volatile("" : "+s"(b));
-    int h, qblock, part, parts = a.parts;
-    block_of<QL>(a, parts, n_qblocks, 0, blocks_per_xcd, b, h, qblock, part);
-    return part_state_of(a, n_qblocks, h, qblock, part);
+    Place at;
+    block_of<FORM>(a, n_qblocks, 0, blocks_per_xcd, b, at);
+    return at;
 }
 
 // Normalise and store one query's result: the lane holds channels 32*mb + 8*g + 4*half + 0..3 of its
