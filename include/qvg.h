@@ -307,12 +307,15 @@ int qvg_attn_decode_f32(const qvg_params *p, int64_t n_q, const void *q_bf16,
  * qvg_attn_decode_causal (out_bf16) or qvg_attn_decode_f32 (out_f32; exactly one of the two is given)
  * with scratch memory for calls of few query blocks, of prefixes of different lengths, or with a few blocks beyond a
  * multiple of 256.  Such a call fills, or ends with, a fraction of the chip while
- * every workgroup walks the whole cache; with scratch of at least qvg_attn_scratch_bytes bytes
- * (16-byte aligned) the cache's tiles are dealt to several workgroups per query block, and one
+ * every workgroup walks the whole cache; with scratch of at least qvg_attn_scratch_bytes bytes, or with q_kv_len
+ * qvg_attn_scratch_bytes_causal bytes (16-byte aligned), the cache's tiles are dealt to several workgroups per query block, and one
  * more launch joins their partial results (fp32).  How many depends on n_heads, n_q, n_kv_tokens, chunk_len
  * and the prefix lengths only, so equal calls give equal bits, with and without `workspace`.  They differ from the undivided
  * result by the order of fp32 sums and by the maxima that the binary16 probabilities are taken
  * against.  Without scratch (NULL, 0) or with less, this is the undivided call.
+ * Prefix lengths may come in any order.  Calls of more than 128 blocks of 256 queries over 192 tiles or more read off
+ * the first and the last query's what the others are like: where these two see about as much no block is divided, else the
+ * blocks at the end that sees more run first.  Any other order gets the same results, not the best time.
  */
 int qvg_attn_decode_parts(const qvg_params *p, int64_t n_q, const void *q_bf16,
                           int64_t n_kv_tokens, int64_t chunk_len, int64_t kv_capacity_tokens,
@@ -325,7 +328,7 @@ int qvg_attn_decode_parts(const qvg_params *p, int64_t n_q, const void *q_bf16,
                           void *workspace, size_t workspace_bytes,
                           void *scratch, size_t scratch_bytes, void *stream);
 
-/* Bytes of scratch that let qvg_attn_decode_parts divide this call; 0 when it would not be divided. */
+/* Bytes of scratch that let qvg_attn_decode_parts divide this call without q_kv_len; 0 when it would not be divided. */
 int qvg_attn_scratch_bytes(const qvg_params *p, int64_t n_q, int64_t n_kv_tokens, int64_t chunk_len, size_t *out);
 /* The same for a call with a prefix length per query: calls of up to 256 blocks of 256 queries are divided too, since
  * their blocks' shares of the cache differ. */

@@ -934,7 +934,9 @@ hipError_t launch_attn(const AttnArgs &a, hipStream_t s) {
 // blocks are divided too, those of 96 tiles or more in up to three parts, the longest first.  37440 tokens, four groups of
 // queries that see a quarter of them more each, 12 heads x 4680 queries 1010 -> 850 us, with queries that are new to the caches 1010 ->
 // 921 (two parts 887, four 847; parts of at least 96 tiles 920), 7 heads 938 -> 524 (two parts 577), without a tile workspace 1720 -> 1330.  More blocks are taken whole, the
-// longest first: 20 heads x 4680 over 14040 tokens 762 -> 614 us (in two parts 704).
+// longest first: 20 heads x 4680 over 14040 tokens 762 -> 614 us (in two parts 704).  Lengths that are about the same are
+// neither divided nor re-ordered (block_of): the unit's blocks then share an XCD's L2 as without lengths (12 x 4680 over 37440 tokens,
+// all full, 1673 us in the order of unequal ones, 1110 so, 1097 before there was a division; without a tile workspace 3437, 1690, 1684).
 // ---------------------------------------------------------------------------------------------
 constexpr int kCus = 256;
 constexpr int kLenMinBlocks = 129, kLenMinTiles = 192, kLenParts = 3, kLenPartTiles = 48;

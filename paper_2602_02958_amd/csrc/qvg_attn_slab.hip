@@ -521,7 +521,7 @@ __device__ __forceinline__ void attend_slab(const AttnArgs &a, const SlabArgs &s
     else store_state(slab_state<PARTS>(e, sl, n_qblocks, end), O, m, l);
 }
 
-// A whole block takes the form that has no parts.
+// A whole block takes the form that has no parts (12 heads x 4680 queries that all see 37440 tokens 1090 us, 1126 with parts).
 template <bool QL, bool PARTS>
 __global__ __launch_bounds__(kAtThreads, 2)
 void attn_slab_kernel(AttnArgs a, SlabArgs sl, int n_qblocks, int n_blocks, int blocks_per_xcd) {

@@ -87,6 +87,21 @@ __device__ __forceinline__ int64_t tiles_of(const AttnArgs &a, int n) {
     return (int64_t)full * (((int64_t)clen + kAtKv - 1) / kAtKv) + ((int64_t)rest + kAtKv - 1) / kAtKv;
 }
 
+// A call with a prefix length per query (a.part_tiles): what its first and its last query see.  Lengths need not be in
+// any order, but where these two see about as much, all blocks are taken to.
+struct PrefixEnds {
+    int first, last;
+    __device__ __forceinline__ explicit PrefixEnds(const AttnArgs &a) {
+        const int nk = (int)a.n_kv, f = a.q_len[0], l = a.q_len[a.n_q - 1];
+        first = f < 0 ? 0 : (f > nk ? nk : f);
+        last = l < 0 ? 0 : (l > nk ? nk : l);
+    }
+    __device__ __forceinline__ bool covers(int longest) const {          // the shorter one about as long as `longest`
+        return (int64_t)(first < last ? first : last) * 8 >= (int64_t)longest * 7;
+    }
+    __device__ __forceinline__ bool equal() const { return covers(first < last ? last : first); }
+};
+
 // A workgroup's unit, query block, part, and the parts of its block.
 struct Place {
     int h, qblock, part, parts;
@@ -98,9 +113,9 @@ struct Place {
 
 // Which query block and part a workgroup has, b: its number.  Workgroups are dealt to the 8 XCDs round-robin; they are
 // re-numbered so that the query blocks of one unit run on one XCD, whose L2 then serves the unit's cache to all of them.
-// Prefixes of different lengths (a.part_tiles) are dealt the other way, all units' last queries first: what is left
-// when the chip runs empty is short, and the XCDs have equal shares of every length.  The first a.whole workgroups (a
-// multiple of 8) have a block each.  False: none.  at.parts: at most.
+// Prefixes of different lengths (a.part_tiles) are dealt the other way, the queries of all units from the end that sees
+// more on: what is left when the chip runs empty is short, and the XCDs have equal shares of every length.  The first
+// a.whole workgroups (a multiple of 8) have a block each.  False: none.  at.parts: at most.
 // FORM: a template parameter, so that what a call does not need takes no registers from its tile loop.
 enum BlockForm { kPlain, kLengths, kLengthsParted };                     // no q_len; q_len; q_len, and a.part_tiles may be set
 template <int FORM>
@@ -114,10 +129,15 @@ __device__ __forceinline__ bool block_of(const AttnArgs &a, int n_qblocks, int n
     }
     int parts = a.parts, h, qblock, part;
     if (FORM == kLengthsParted && a.part_tiles) {                        // uniform
-        const int i = (int)(b / (unsigned)a.H), last = i / parts;
-        h = (int)(b % (unsigned)a.H); part = i - last * parts; qblock = n_qblocks - 1 - last;
-        at = Place{h, qblock, part, parts}.uniform();
-        return (int)b < n_blocks;
+        const PrefixEnds ends(a);
+        if (!ends.equal()) {
+            const int i = (int)(b / (unsigned)a.H), n = i / parts;
+            h = (int)(b % (unsigned)a.H); part = i - n * parts; qblock = ends.first < ends.last ? n_qblocks - 1 - n : n;
+            at = Place{h, qblock, part, parts}.uniform();
+            return (int)b < n_blocks;
+        }
+        parts = 1; n_blocks = n_qblocks * a.H; blocks_per_xcd = (n_blocks + 7) / 8;
+        if ((int)(b / 8u) >= blocks_per_xcd) return false;
     }
     int first = 0;
     if (FORM == kPlain && a.whole) {                                     // uniform
@@ -130,12 +150,13 @@ __device__ __forceinline__ bool block_of(const AttnArgs &a, int n_qblocks, int n
     return w < n_blocks;
 }
 
-// Parts of a block whose longest prefix is `longest` tokens.  Where the first query sees about as much, all blocks
-// are taken to, and dividing them only costs (228 blocks of 592 tiles each 1102 us, in two parts 1180, in three 1240).
+// Parts of a block whose longest prefix is `longest` tokens.  Dividing blocks that all see about as much only costs (228
+// blocks of 592 tiles each 1102 us, in two parts 1180, in three 1240).
 __device__ __forceinline__ int block_parts(const AttnArgs &a, int longest) {
     if (!a.part_tiles || a.parts == 1) return a.parts;
     const int64_t n = tiles_of(a, longest) / a.part_tiles;
-    if (n < 2 || (int64_t)a.q_len[0] * 8 >= (int64_t)longest * 7) return 1;
+    const PrefixEnds ends(a);
+    if (n < 2 || ends.equal() || ends.covers(longest)) return 1;
     return n < a.parts ? (int)n : a.parts;
 }
 

@@ -279,7 +279,8 @@ struct AttnArgs {
     float *part_state;     // with more than one, each leaves its running state here and launch_attn_join makes the result
     int whole;             // the first blocks, in the order of unit and block, that are not divided (without q_len; a multiple of 8)
     int part_tiles;        // with q_len, not 0: a block has as many parts as its longest prefix has this many tiles (1 .. parts); a
-                           // block of one part stores its result itself; the longest prefixes (the last queries') are taken first
+                           // block of one part stores its result itself; unless the first and the last query see about as much: then
+                           // no block is divided, else the blocks at the end that sees more are taken first
 };
 hipError_t launch_attn(const AttnArgs &a, hipStream_t s);
 // parts for a call of these sizes (with_len: with a prefix length per query), and the bytes of their state (0 for a single part)

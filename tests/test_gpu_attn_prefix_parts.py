@@ -82,3 +82,34 @@ def test_blocks_of_long_prefixes_are_divided(caches, Nq, n, prefixes, divided):
             ok, max_abs, worst = P.attn_tolerance_ok(P.to_np_u16(out[h, i:i + 1]), want)
             assert ok, (h, i, seen, max_abs, worst)
             assert abs(float(lse[h, i]) - lse_w[0]) < 2e-3
+
+
+def _lengths_call(caches, q, lens, n):
+    """The result, and which parts' states the divided call left: [3, H, blocks]."""
+    kd, vd = (B.Encoded(c.centroids[:, :13].contiguous(), c.ids[:, :n].contiguous(), c.codes[:, :n].contiguous(),
+                        c.scales[:, :n].contiguous(), c.chunk_len) for c in caches)
+    blocks = q.shape[1] // 256
+    scratch = torch.full((3 * 66 * 512 * 4 * H * blocks,), 0x7F, dtype=torch.uint8, device=DEV)
+    out = _decode_parts(q, kd, vd, lens.to(DEV), scratch)
+    torch.cuda.synchronize()
+    return out, (scratch.view(3, H, blocks, -1) != 0x7F).any(-1).cpu(), _decode_parts(q, kd, vd, lens.to(DEV), None)
+
+
+def test_lengths_that_fall_are_divided_as_those_that_rise(caches):
+    n, blocks = 12500, 3
+    q = synth.queries(CONFIGS["cfg2_window21"], H, 256 * blocks, DEV)
+    lens = torch.tensor([40, 5935, 12500], dtype=torch.int32)[:, None] - torch.arange(256, dtype=torch.int32) % 40
+    out, touched, _ = _lengths_call(caches, q, lens.flatten(), n)
+    assert touched.all(1).sum(0).tolist() == [0, 0, 3]
+    fell, touched, _ = _lengths_call(caches, q.view(H, blocks, 256, 128).flip(1).reshape(q.shape).contiguous(), lens.flip(0).flatten(), n)
+    assert touched.all(1).sum(0).tolist() == [3, 0, 0]
+    assert torch.equal(fell.view(H, blocks, 256, 128).flip(1).reshape(q.shape), out)
+
+
+@pytest.mark.parametrize("first,last", [(12500, 12500), (12500, 11000), (10940, 12500)])
+def test_lengths_about_the_same_are_not_divided(caches, first, last):
+    q = synth.queries(CONFIGS["cfg2_window21"], H, 768, DEV)
+    lens = torch.full((768,), 12500, dtype=torch.int32)
+    lens[:256], lens[-1] = first, last
+    out, touched, one = _lengths_call(caches, q, lens, 12500)
+    assert not touched.any() and torch.equal(out, one)
