@@ -974,15 +974,19 @@ size_t attn_parts_bytes(int H, int64_t n_q, const AttnParts &p) {
 // 64 values, threads as in the kernels that left the states.  A part whose first tile lies behind
 // the query's prefix saw none of its tokens and is left out (its sums may be anything; behind all prefixes of the
 // block it leaves none: 64 queries of one head that see one of 74880 tokens, 256 parts, 54 us when all of them were
-// written and read).  A chain of loads: many parts are requested before the first is used, and the requests are kept from
-// moving into the branches that use them; few blocks (the ones with many parts) take four values to a workgroup, which
-// doubles the workgroups.  (64 queries of one head over 4096 tokens, 16 parts, the call 21.5 -> 20.3 us; 204 over 103473, 256
-// parts 102 -> 81; 168 over 223961 126 -> 106.)
-constexpr int kJoinAhead = 16;
-constexpr int kJoinFewBlocks = 32;      // up to this many take NV = 4
-template <bool QL, int NV>         // QL: with a.q_len; NV: 4 or 8
+// written and read).  A chain of loads: AHEAD parts' maxima, 32 / NV parts' values are requested before the first is used, and
+// the requests are kept from moving into the branches that use them (with prefixes only where NV = 4: in more than 16 blocks
+// that costs 0.3 us).  Few blocks take four values to a workgroup, which doubles the workgroups and reads the maxima and
+// sums twice as often, and from 16 parts on AHEAD = 16.  The whole call in us, one head's 250 queries or more heads' (a block each):
+//   blocks x parts      1x4   1x16  1x256  4x16  8x8   16x4  16x16  21x5  21x11  32x8  64x4  128x2
+//   NV 8, AHEAD 8       21.3  25.1  100.8  27.9  22.6  24.7  36.4   30.7  35.3   36.7  35.1  53.7
+//   NV 4, AHEAD 8       20.8  24.0   89.2  26.6  22.1  24.5  35.9   31.8  36.1   36.3  34.8  54.1
+//   NV 4, AHEAD 16      21.7  23.4   79.6  26.1  22.6  25.1  35.6   31.9  36.9   37.6  36.5  59.3
+constexpr int kJoinFewBlocks = 16, kJoinManyParts = 16;
+template <bool QL, int NV, int AHEAD>         // QL: with a.q_len; NV: 4 or 8
 __global__ __launch_bounds__(kAtThreads)
 void attn_join_kernel(AttnArgs a, int n_qblocks) {
+    constexpr bool kPin = NV == 4 || !QL;
     const unsigned block = blockIdx.x + (unsigned)a.whole;
     const int h = (int)(block / (unsigned)n_qblocks), qblock = (int)(block - (unsigned)h * n_qblocks);
     const int v0 = blockIdx.y * NV;                                      // channels 32 * (v0 / 16) + 8 * (v / 4 % 4) + 4 * half + v % 4
@@ -1021,14 +1025,14 @@ void attn_join_kernel(AttnArgs a, int n_qblocks) {
     float m = -INFINITY, l = 0.0f, o[NV];
 #pragma unroll
     for (int i = 0; i < NV; ++i) o[i] = 0.0f;
-    for (int p0 = 0; p0 < read; p0 += kJoinAhead) {
-        float mp[kJoinAhead];
+    for (int p0 = 0; p0 < read; p0 += AHEAD) {
+        float mp[AHEAD];
 #pragma unroll
-        for (int u = 0; u < kJoinAhead; ++u) mp[u] = st[(p0 + u < read ? p0 + u : 0) * pitch + 64 * kAtThreads];
+        for (int u = 0; u < AHEAD; ++u) mp[u] = st[(p0 + u < read ? p0 + u : 0) * pitch + 64 * kAtThreads];
 #pragma unroll
-        for (int u = 0; u < kJoinAhead; ++u) asm volatile("" : "+v"(mp[u]));
+        for (int u = 0; u < AHEAD; ++u) if (kPin) asm volatile("" : "+v"(mp[u]));
 #pragma unroll
-        for (int u = 0; u < kJoinAhead; ++u) m = p0 + u < seen ? fmaxf(m, mp[u]) : m;
+        for (int u = 0; u < AHEAD; ++u) m = p0 + u < seen ? fmaxf(m, mp[u]) : m;
     }
     constexpr int kRows = 32 / NV;
     for (int p0 = 0; p0 < read; p0 += kRows) {
@@ -1043,7 +1047,7 @@ void attn_join_kernel(AttnArgs a, int n_qblocks) {
 #pragma unroll
         for (int u = 0; u < kRows; ++u)
 #pragma unroll
-            for (int i = 0; i < NV + 2; ++i) asm volatile("" : "+v"(x[u][i]));
+            for (int i = 0; i < NV + 2; ++i) if (kPin) asm volatile("" : "+v"(x[u][i]));
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
             if (p0 + u < seen) {
@@ -1075,11 +1079,12 @@ hipError_t launch_attn_join(const AttnArgs &a, hipStream_t s) {
     const int64_t nqb = (a.n_q + kAtQPerBlock - 1) / kAtQPerBlock;
     if (nqb * a.H > 0x7fffffff) return hipErrorInvalidValue;
     const int64_t blocks = nqb * a.H - a.whole;
-    const bool few = blocks <= kJoinFewBlocks;
-    const dim3 grid((unsigned)blocks, few ? 16 : 8);
+    const int form = blocks > kJoinFewBlocks ? 0 : a.parts < kJoinManyParts ? 2 : 4;
+    const dim3 grid((unsigned)blocks, form ? 16 : 8);
     typedef void (*join_kernel_t)(AttnArgs, int);
-    static const join_kernel_t kernels[4] = {attn_join_kernel<false, 8>, attn_join_kernel<true, 8>, attn_join_kernel<false, 4>, attn_join_kernel<true, 4>};
-    hipLaunchKernelGGL(kernels[(a.q_len ? 1 : 0) + (few ? 2 : 0)], grid, dim3(kAtThreads), 0, s, a, (int)nqb);
+    static const join_kernel_t kernels[6] = {attn_join_kernel<false, 8, 8>, attn_join_kernel<true, 8, 8>, attn_join_kernel<false, 4, 8>,
+                                             attn_join_kernel<true, 4, 8>, attn_join_kernel<false, 4, 16>, attn_join_kernel<true, 4, 16>};
+    hipLaunchKernelGGL(kernels[form + (a.q_len ? 1 : 0)], grid, dim3(kAtThreads), 0, s, a, (int)nqb);
     return hipGetLastError();
 }
 

@@ -167,3 +167,32 @@ def test_parts_behind_every_prefix_leave_no_state(Nq, L, lend, longest):
         assert not out.any()
     # one output's rounding and the order of the sums apart
     assert (out.float() - one.float()).abs().max() <= 2 ** -8 * one.float().abs().max() + 2e-3
+
+
+@pytest.mark.parametrize("H,tiles,parts", [(16, 63, 15), (16, 64, 16), (17, 64, 15)])
+def test_join_of_few_and_many_blocks_and_parts(H, tiles, parts):
+    """Each side of the rules that choose the join's form; with lengths, some of which only the first parts see."""
+    L, Nq = 1024, 200
+    n = tiles * 64
+    kc, vc = _filled_caches(H, L, 4, n, 16, 64, 1)
+    assert _scratch_bytes(H, Nq, n, L) == parts * H * 66 * 512 * 4
+    q = synth.queries(CONFIGS["cfg2_window21"], H, Nq, DEV)
+    lens = torch.full((Nq,), n, dtype=torch.int32)
+    lens[:32], lens[32:64], lens[64], lens[65] = 130, 65 * parts, 0, 1
+    khat, vhat = B.decode(kc), B.decode(vc)
+    for ql in (None, lens.to(DEV)):
+        out, lse = B.attn_decode(q, kc, vc, want_lse=True, n_kv=n, q_kv_len=ql)
+        f32 = B.attn_decode(q, kc, vc, n_kv=n, q_kv_len=ql, f32_out=True)
+        torch.cuda.synchronize()
+        assert torch.equal(f32.to(torch.bfloat16), out)
+        for h in (0, H - 1):
+            kb, vb = P.to_np_u16(khat[h, :n]), P.to_np_u16(vhat[h, :n])
+            for i in (0, 40, 64, 65, 199):
+                seen = n if ql is None else int(lens[i])
+                if seen == 0:
+                    assert not out[h, i].any() and lse[h, i] == -float("inf")
+                    continue
+                want, lse_w = O.attention(bf16_bits(q[h, i:i + 1]), kb[:seen], vb[:seen], want_lse=True)
+                ok, max_abs, worst = P.attn_tolerance_ok(P.to_np_u16(out[h, i:i + 1]), want)
+                assert ok, (h, i, seen, max_abs, worst)
+                assert abs(float(lse[h, i]) - lse_w[0]) < 2e-3
