@@ -558,8 +558,10 @@ int attn_call(const qvg_params *p, int64_t n_q, const void *q, int64_t n_kv_toke
     const AttnParts parts = attn_parts(a.H, n_q, n_kv_tokens, a.chunk_len, q_kv_len != nullptr);
     const size_t part_bytes = attn_parts_bytes(a.H, n_q, parts);
     a.parts = parts.parts; a.part_tiles = parts.part_tiles; a.whole = parts.whole;
-    if (a.parts > 1 && scratch && scratch_bytes >= part_bytes) {
-        if (!aligned16(scratch)) return QVG_ERR_ALIGN;
+    // (calls of more than 128 query blocks were not divided at first and took any scratch: one that they cannot use is ignored)
+    const bool unaligned = !aligned16(scratch), ignored = unaligned && (a.whole || a.part_tiles);
+    if (a.parts > 1 && scratch && scratch_bytes >= part_bytes && !ignored) {
+        if (unaligned) return QVG_ERR_ALIGN;
         a.part_state = static_cast<float *>(scratch);
     } else {
         a.parts = 1; a.whole = 0;                      // no room for the parts' states: every workgroup walks the whole cache
