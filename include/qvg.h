@@ -120,6 +120,9 @@ typedef struct qvg_params {
  *                  holds several chunks per unit: point the outputs at the chunk's first token
  *                  and table, and pass the cache's tokens and table elements per unit.
  *   workspace      qvg_workspace_bytes(p, QVG_ENTRY_ENCODE, N, 0) bytes (a few KB per unit when I == 0)
+ * A call that the free chip holds at once (up to 6144 tokens per unit, 512 workgroups of 256 tokens) runs all its iterations in one launch, whose
+ * workgroups wait for each other.  Where another stream's kernel holds part of the chip, a unit is done by those of its
+ * workgroups that have a place: same results, 1.1 to 2 times the time that one launch per step takes beside the same kernel.
  * n_tokens in 0 .. 2^20.  n_tokens == 0 only copies the centroids.
  * Rounding rules that fix the stored integers: a group's scale is max|r| / qmax (one fp32
  * division; qmax = 2^(b-1) - 1, so 1 for b = 2), saturated at the scale format's largest finite

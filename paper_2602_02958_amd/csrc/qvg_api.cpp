@@ -102,12 +102,12 @@ bool tables_overlap(const qvg_params *p, const void *init, const void *out, int6
     return a < b + (uintptr_t)(p->n_heads - 1) * out_stride * sizeof(bf16_t) + unit && b < a + (uintptr_t)p->n_heads * unit;
 }
 
-// wait_ticks: the longest wait of a workgroup in the one-launch form, of 10 ns
+// wanted: how many workgroups a unit's first barrier waits for in the one-launch form, 0: all
 int encode_call(const qvg_params *p, int64_t n_tokens, const void *x, int64_t stride_head,
                 int64_t stride_token, const void *init_centroids, void *centroids_out,
                 int64_t cent_out_stride_head, uint8_t *ids_out, uint8_t *codes_out,
                 void *scales_out, int64_t out_stride_head_tokens, void *workspace,
-                size_t workspace_bytes, uint32_t wait_ticks, void *stream) {
+                size_t workspace_bytes, int wanted, void *stream) {
     int st = check_params(p);
     if (st != QVG_OK) return st;
     if (n_tokens < 0 || n_tokens > kMaxTokensPerChunk) return QVG_ERR_BAD_PARAM;
@@ -151,6 +151,7 @@ int encode_call(const qvg_params *p, int64_t n_tokens, const void *x, int64_t st
         l.H = p->n_heads; l.K = p->n_clusters; l.B = p->group_size; l.T = p->n_stages; l.S = S; l.iters = I;
         l.cent_out = static_cast<bf16_t *>(centroids_out); l.cent_out_stride = cent_out_stride_head;
         l.ids = ids_out; l.codes = codes_out; l.scales = static_cast<f16_t *>(scales_out);
+        l.codes_stride = out_stride_head_tokens * p->n_stages * (kHeadDim * p->bits / 8);
         l.out_stride = out_stride_head_tokens; l.id_wide = id_wide(p); l.fused = fmt == 0;
         l.init_norms = reinterpret_cast<const uint2 *>(ws + w.init_norms);
         l.meet = reinterpret_cast<uint32_t *>(ws + w.cent[1]);           // 256 bytes per unit; a table has at least one row
@@ -158,7 +159,7 @@ int encode_call(const qvg_params *p, int64_t n_tokens, const void *x, int64_t st
         l.table = reinterpret_cast<bf16_t *>(ws + w.cent[0]); l.norms = reinterpret_cast<uint2 *>(ws + w.norms);
         for (int i = 0; i < 2; ++i) l.resid[i] = reinterpret_cast<bf16_t *>(ws + w.resid[i]);
         l.n_blocks = (int)((n_tokens + 255) / 256); l.groups = groups;
-        l.wait_ticks = wait_ticks;
+        l.wanted = wanted > 0 ? wanted : groups;
         if (launch_lloyd(l, s) != hipSuccess) return QVG_ERR_LAUNCH;
         if (fmt == 0) return QVG_OK;
         QuantArgs q{};
@@ -355,18 +356,19 @@ int qvg_encode_chunk(const qvg_params *p, int64_t n_tokens, const void *x, int64
                      void *scales_out, int64_t out_stride_head_tokens, void *workspace,
                      size_t workspace_bytes, void *stream) {
     return encode_call(p, n_tokens, x, stride_head, stride_token, init_centroids, centroids_out, cent_out_stride_head, ids_out,
-                       codes_out, scales_out, out_stride_head_tokens, workspace, workspace_bytes, kLloydWaitTicks, stream);
+                       codes_out, scales_out, out_stride_head_tokens, workspace, workspace_bytes, 0, stream);
 }
 
-// qvg_encode_chunk with another bound on the one-launch encoder's waits (0: every workgroup but the last to arrive gives up
-// at once), so that a test reaches what follows a wait that lasts too long.  Not part of the interface.
+// qvg_encode_chunk with another number of workgroups that the one-launch encoder's units wait for, so that a test reaches
+// the teams of a busy chip: up to a unit's workgroups, those that come first do the unit (0: one alone); beyond them, the wait for
+// more ends by the clock.  Not part of the interface.
 int qvg_encode_chunk_wait(const qvg_params *p, int64_t n_tokens, const void *x, int64_t stride_head,
                           int64_t stride_token, const void *init_centroids, void *centroids_out,
                           int64_t cent_out_stride_head, uint8_t *ids_out, uint8_t *codes_out,
                           void *scales_out, int64_t out_stride_head_tokens, void *workspace,
-                          size_t workspace_bytes, void *stream, uint32_t wait_ticks) {
+                          size_t workspace_bytes, void *stream, uint32_t wanted) {
     return encode_call(p, n_tokens, x, stride_head, stride_token, init_centroids, centroids_out, cent_out_stride_head, ids_out,
-                       codes_out, scales_out, out_stride_head_tokens, workspace, workspace_bytes, wait_ticks, stream);
+                       codes_out, scales_out, out_stride_head_tokens, workspace, workspace_bytes, wanted > 0 ? (int)wanted : 1, stream);
 }
 
 }  // extern "C"

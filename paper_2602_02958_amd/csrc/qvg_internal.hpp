@@ -232,18 +232,19 @@ struct LloydArgs {
     int H, K, B, T, S, iters;
     bf16_t *cent_out; int64_t cent_out_stride;     // unit h's tables at cent_out + h * stride elements
     uint8_t *ids; uint8_t *codes; f16_t *scales; int64_t out_stride; int id_wide;
+    int64_t codes_stride;                    // bytes of a unit's codes, out_stride tokens
     int fused;                               // codes and scales are written (2-bit levels, binary16 scales)
     // scratch
     const uint2 *init_norms;                 // [H][S][Kpad]
-    uint32_t *meet;                          // [H][64]: arrivals, workgroups that gave the unit up
+    uint32_t *meet;                          // [H][64]: the words that a unit's workgroups meet at
     uint16_t *ids_x;                         // [H][n_blocks * 256]
     bf16_t *table; uint2 *norms;             // [H][K][d], [H][Kpad]
     bf16_t *resid[2];                        // stage s leaves the next one's input [H][N][d] in resid[s & 1]
     int n_blocks, groups;                    // blocks of 256 tokens per unit; workgroups per unit
-    uint32_t wait_ticks;                     // of 10 ns: the longest wait of a workgroup
+    int wanted;                              // workgroups that a unit's first barrier waits for: `groups`
+    uint32_t wait_ticks;                     // set by launch_lloyd
     int by_xcd;                              // set by launch_lloyd
 };
-constexpr uint32_t kLloydWaitTicks = 200000;
 int lloyd_groups(int H, int K, int64_t n_tokens, int64_t stride_token, int iters);      // workgroups per unit, 0: not for this call
 hipError_t launch_lloyd(const LloydArgs &a, hipStream_t s);
 

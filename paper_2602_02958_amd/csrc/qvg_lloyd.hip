@@ -16,18 +16,25 @@
 // loads at agent scope (64 KB to each of 456 workgroups, barrier included: 5.4 us; with fences, which write back and
 // invalidate whole caches, 52).
 //
-// The barrier.  Only workgroups that run at the same time can meet, so the launch is taken only where the chip
-// holds all of them (lloyd_groups), and no wait is unbounded: one that lasts 2 ms (another stream's work
-// may hold the CUs) marks the unit.  A barrier that is complete cannot be marked any more (compare and swap): behind the
-// last one nobody gives up, and all workgroups of a marked unit leave, at that barrier or at the one before.  The
-// last to leave does the unit over alone, without anybody to wait for (the inputs are untouched).  (A second launch for the marked units, which ended at once where
-// there were none, took 4.8 us: 24 units x 4680 tokens, K = 256, T = 4, I = 3 116.4 us with it, 115.8 without; 10 x 1571, INT4 69.1 and 67.7.)
+// The barrier.  Only workgroups that run at the same time can meet.  The launch is taken only where the chip holds all of
+// them (lloyd_groups), but another stream's work may hold part of it for long.  So the workgroups that arrive at the first
+// barrier are the unit's team: all of them, or, where some have not even started in time, those that have arrived by then.
+// Such a team is closed; it begins anew, the unit's blocks and rows dealt among its members, and a workgroup that
+// arrives later leaves.  What that one has written, the first ids, is not read: a closed team has its ids in the codes' place
+// in the output.  Behind the first barrier only members are waited for, and they never wait for anybody else.
+// How long the first barrier waits for workgroups that have not started: half of what the run takes with the members
+// there are, so that it costs little where none comes and few members do not go on alone where others come soon.
+// Beside an attention of 130 / 170 / 200 workgroups on another stream that lasts 3 ms, us (launches per iteration; this; as it was
+// when a unit waited 2 ms and one workgroup did it over): 24 units x 4680 tokens, K = 256, T = 4, I = 3 295 / 420 / 760; 350 / 860 / 1255; 359 / - / 3190;
+// four stages 1205 / 1820 / 2370; 1520 / 2390 / 3000; 1500 / - / 6500; INT4, 10 x 1571 101 / 116 / 174; 158 / 163 / 370; 143 / - / 2520.  Two streams of
+// encodes, a pair of them: 225, 213, 214; 900, 931, 953; 123, 102, 104.  (A wait half as long: 200 workgroups 1070, two
+// streams of four stages 1000; twice as long 1610, 928.)
 #include "qvg_assign.hpp"
 
 namespace qvg {
 
-constexpr uint32_t kUnitFailed = 0x80000000u;
 constexpr int kMeetWords = 64;                   // a 256-byte line per unit
+constexpr uint32_t kWaitTicks = 1500;            // of 10 ns: half an iteration over one block per workgroup
 constexpr int kLloydMaxBlocks = 24;              // blocks of 256 tokens per unit (lloyd_groups; token numbers have 16 bits)
 constexpr int kListLong = 128;                   // lists at least this long are summed by the whole workgroup,
 constexpr int kListShared = 32;                  // where it has one or two rows, at least this long
@@ -67,45 +74,76 @@ struct Shared {                                  // a buffer of one unit; loads 
     }
 };
 
-// All workgroups of the unit: everything stored before is seen by all after.  False: the unit is given up.
-// `word` counts the arrivals since the launch began; target: workgroups x barriers so far, this one included.
+// A unit's words: the arrivals at the first barrier (and, once the team is closed, bit 31 and the members from bit 16 on), the
+// arrivals at all later ones, and (in a cache line of their own) a byte per workgroup that has started.
+constexpr uint32_t kTeamClosed = 0x80000000u, kArrivedMask = 0xffffu;
+constexpr int kMembersShift = 16, kLaterWord = 4, kStartedAt = 128;
+static_assert(kMaxClusters / 8 <= kMeetWords * 4 - kStartedAt && kLloydMaxBlocks <= kMeetWords * 4 - kStartedAt, "a byte per workgroup");
+
+__device__ __forceinline__ void set_started(uint32_t *words, int g) {
+    const Shared s(words, kMeetWords * 4);
+    __builtin_amdgcn_raw_buffer_store_b8((unsigned char)1, s.r, kStartedAt + g, 0, kAgentScope);
+}
+__device__ __forceinline__ bool all_started(const uint32_t *words) {     // (bytes that nobody sets are set from the start)
+    const Shared s(words, kMeetWords * 4);
+    uint4 v[(kMeetWords * 4 - kStartedAt) / 16];                         // (all requested before the first is looked at)
+#pragma unroll
+    for (int i = 0; i < (kMeetWords * 4 - kStartedAt) / 16; ++i) v[i] = s.load16((uint32_t)(kStartedAt + i * 16));
+    uint32_t all = 0x01010101u;
+#pragma unroll
+    for (int i = 0; i < (kMeetWords * 4 - kStartedAt) / 16; ++i) all &= v[i].x & v[i].y & v[i].z & v[i].w;
+    return all == 0x01010101u;
+}
+// Thread 0 at the first barrier, which waits for `wanted` workgroups: 0 where all have come, else the members of the closed team, -1
+// where this one has come too late.  number: of this one, in the order of arrival.
+// ticks: the wait for workgroups that have not started, for each block that a member has.
+__device__ __forceinline__ int team_meet(uint32_t *words, int wanted, int groups, int nb, uint32_t ticks, int &number) {
+    uint32_t v = __hip_atomic_fetch_add(words, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    number = (int)(v & kArrivedMask);
+    if ((v & kTeamClosed) || number >= wanted) return -1;
+    ++v;
+    uint64_t t0 = 0;
+    for (uint32_t polls = 0; ; ++polls) {
+        if (v & kTeamClosed) return (int)(v >> kMembersShift) & 0x7fff;
+        const int there = (int)(v & kArrivedMask);                       // at least this one
+        if (there >= wanted) {                                           // (more: they left)
+            if (wanted == groups) return 0;
+            __hip_atomic_fetch_or(words, kTeamClosed | (uint32_t)wanted << kMembersShift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return wanted;
+        }
+        if (polls % 16 == 15) {                                          // (reading the clock at every poll costs 1.5 us)
+            const uint64_t now = __builtin_amdgcn_s_memrealtime();
+            if (t0 == 0) t0 = now;
+            if (now - t0 >= (uint64_t)ticks * (uint32_t)((nb + there - 1) / there)) {
+                t0 = now;
+                // (the exchange fails only where another workgroup has arrived or closed the team meanwhile)
+                if (!all_started(words) && __hip_atomic_compare_exchange_strong(words, &v, v | kTeamClosed | (uint32_t)there << kMembersShift,
+                                                                                __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                    return there;
+            }
+        }
+        __builtin_amdgcn_s_sleep(8);
+        v = __hip_atomic_load(words, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// All members of the team: everything stored before is seen by all after.
+// `word` counts the arrivals; target: members x barriers so far, this one included.
 // fresh: data of this launch is going to be read by plain loads.
-__device__ __forceinline__ bool meet(uint32_t *word, uint32_t groups, uint32_t target, uint32_t ticks, bool fresh, int *flag) {
+__device__ __forceinline__ void meet(uint32_t *word, uint32_t members, uint32_t target, bool fresh) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                     // this wavefront's stores have arrived
     __syncthreads();
     if (threadIdx.x == 0) {
-        int ok = 1;
-        if (groups > 1) {                                                // uniform
+        if (members > 1) {                                               // uniform
             uint32_t v = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
-            if (v < target) {                                            // (a failed unit's word is above every target)
-                const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-                for (;;) {
-                    v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (v >= target) break;
-                    if (__builtin_amdgcn_s_memrealtime() - t0 >= ticks) {
-                        // (fails only where another workgroup has arrived or marked the unit: at most `groups` times)
-                        if (__hip_atomic_compare_exchange_strong(word, &v, v | kUnitFailed, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                                 __HIP_MEMORY_SCOPE_AGENT)) v = kUnitFailed;
-                        if (v >= target) break;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
-                }
+            while (v < target) {
+                __builtin_amdgcn_s_sleep(2);
+                v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            ok = !(v & kUnitFailed);
         }
         if (fresh) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        *flag = ok;
     }
     __syncthreads();
-    return *flag != 0;
-}
-
-// A workgroup of a unit that was given up, behind its last barrier: true for the last one of them.
-__device__ __forceinline__ bool last_to_leave(uint32_t *left, uint32_t groups, int *flag) {
-    __syncthreads();                                                     // the flag of the barrier has been read
-    if (threadIdx.x == 0) *flag = __hip_atomic_fetch_add(left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == groups;
-    __syncthreads();
-    return __builtin_amdgcn_readfirstlane(*flag) != 0;
 }
 
 // LDS of the update, over the staged table
@@ -364,8 +402,10 @@ __device__ __forceinline__ Shared norms_of(const LloydArgs &a, int h) {
 __device__ __forceinline__ Shared init_of(const LloydArgs &a, int h, int stage) {
     return Shared(a.init + ((int64_t)h * a.S + stage) * a.K * kHeadDim, (uint32_t)a.K * kHeadDim * 2);
 }
-__device__ __forceinline__ Shared ids_of(const LloydArgs &a, int h) {
-    return Shared(a.ids_x + (int64_t)h * a.n_blocks * kAsgThreads, (uint32_t)a.n_blocks * kAsgThreads * 2);
+// the unit's ids; apart: those of a closed team
+__device__ __forceinline__ Shared ids_of(const LloydArgs &a, int h, bool apart) {
+    const void *p = apart ? static_cast<const void *>(a.codes + h * a.codes_stride) : a.ids_x + (int64_t)h * a.n_blocks * kAsgThreads;
+    return Shared(p, (uint32_t)a.n_blocks * kAsgThreads * 2);
 }
 // the stage's input
 __device__ __forceinline__ const bf16_t *input_of(const LloydArgs &a, int h, int stage) {
@@ -446,33 +486,44 @@ __global__ __launch_bounds__(kAsgThreads, 2)
 void lloyd_kernel(LloydArgs a0) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t smax;
-    __shared__ int flag;
+    __shared__ int number, members;
     const int nb = a0.n_blocks;
-    int groups = a0.groups;                                              // 1 where the unit is done over
-    int h, g;
-    if (a0.by_xcd) { const int i = (int)(blockIdx.x >> 3); h = (int)(blockIdx.x & 7u) + 8 * (i / groups); g = i % groups; }
-    else { h = (int)blockIdx.x / groups; g = (int)blockIdx.x % groups; }
+    int h, g0;
+    if (a0.by_xcd) { const int i = (int)(blockIdx.x >> 3); h = (int)(blockIdx.x & 7u) + 8 * (i / a0.groups); g0 = i % a0.groups; }
+    else { h = (int)blockIdx.x / a0.groups; g0 = (int)blockIdx.x % a0.groups; }
     if (h >= a0.H) return;                                               // uniform
-    bool resident = groups >= nb;                                        // one block per workgroup: its tokens stay in registers
+    // What a team changes waits in LDS and is read anew where a phase begins, as the arguments are.
+    __shared__ int lds_groups, lds_g, lds_apart;                         // members, this one's number, a closed team
+    if (threadIdx.x == 0) { lds_groups = a0.groups; lds_g = g0; lds_apart = 0; }
+    __syncthreads();
+    auto groups_now = [&] { return __builtin_amdgcn_readfirstlane(lds_groups); };
+    auto g_now = [&] { return __builtin_amdgcn_readfirstlane(lds_g); };
+    bool formed = a0.groups == 1;                                        // uniform
     uint32_t met = 0;
     auto meet_unit = [&](bool fresh) {
-        const LloydArgs &a = args_again();
         ++met;
-        return meet(a.meet + (int64_t)h * kMeetWords, (uint32_t)groups, met * (uint32_t)groups, a.wait_ticks, fresh, &flag);
+        const uint32_t groups = (uint32_t)groups_now();
+        meet(args_again().meet + (int64_t)h * kMeetWords + kLaterWord, groups, met * groups, fresh);
     };
 
     uint4 xa[2][8];
 begin:
-    if (g < nb) load_tokens(h, 0, g, xa);                                // on their way while the table is staged
-    if (threadIdx.x == 0) smax = 0u;
+    {
+        const int g = g_now();
+        if (g < nb) load_tokens(h, 0, g, xa);                            // on their way while the table is staged
+        if (thread_id() == 0) {
+            smax = 0u;
+            set_started(args_again().meet + (int64_t)h * kMeetWords, g);
+        }
+    }
     __syncthreads();
     for (int stage = 0; stage < a0.S; ++stage) {
         for (int it = 0; ; ++it) {
             const bool last = it == args_again().iters;                  // uniform: the stage's final assignment
-            stage_table(h, stage, it == 0, last && g == 0, smem, &smax);
+            stage_table(h, stage, it == 0, last && g_now() == 0, smem, &smax);
             // ---- this workgroup's tokens ----
-            for (int blk = g; blk < nb; blk += groups) {
-                if (!resident) load_tokens(h, stage, blk, xa);
+            for (int blk = g_now(), groups = groups_now(); blk < nb; blk += groups) {
+                if (groups < nb) load_tokens(h, stage, blk, xa);
                 const LloydArgs &a = args_again();
                 const int tid = thread_id(), lane = tid & 63, wave = tid >> 6, half = lane >> 5, col = lane & 31;
                 const int K = a.K, Kpad = k_padded(K), N = a.n_tokens;
@@ -500,7 +551,7 @@ begin:
                     const int p0 = __shfl(id[0], from, 64), p1 = __shfl(id[0], from + 1, 64);
                     const int q0 = __shfl(id[1], from, 64), q1 = __shfl(id[1], from + 1, 64);
                     const uint32_t lo = (uint32_t)(lane & 16 ? q0 : p0), hi = (uint32_t)(lane & 16 ? q1 : p1);
-                    if (half == 0) ids_of(a, h).store4((uint32_t)n0 * 2u + lane * 4u, lo | hi << 16);
+                    if (half == 0) ids_of(a, h, __builtin_amdgcn_readfirstlane(lds_apart) != 0).store4((uint32_t)n0 * 2u + lane * 4u, lo | hi << 16);
                     continue;
                 }
 #pragma unroll
@@ -545,34 +596,47 @@ begin:
                 }
             }
             if (last) break;
-            if (!meet_unit(stage > 0 && it == 0)) goto given_up;         // uniform
+            if (!formed) {                                               // uniform: the first barrier of all
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wavefront's stores have arrived
+                __syncthreads();
+                if (threadIdx.x == 0) {
+                    const LloydArgs &a = args_again();
+                    members = team_meet(a.meet + (int64_t)h * kMeetWords, a.wanted, a.groups, nb, a.wait_ticks, number);
+                }
+                __syncthreads();
+                formed = true;
+                const int k = __builtin_amdgcn_readfirstlane(members);
+                if (k < 0) return;                                       // uniform
+                if (k > 0) {                                             // uniform: a closed team, from the beginning
+                    if (threadIdx.x == 0) { lds_groups = k; lds_g = number; lds_apart = 1; }
+                    __syncthreads();
+                    goto begin;
+                }
+            } else {
+                meet_unit(stage > 0 && it == 0);
+            }
             if (threadIdx.x == 0) smax = 0u;
             {
                 const LloydArgs &a = args_again();
-                const int K = a.K, c_max = (K + groups - 1) / groups, j0 = g * c_max, end = j0 + c_max < K ? j0 + c_max : K;
+                const int K = a.K, groups = groups_now(), g = g_now(), c_max = (K + groups - 1) / groups, j0 = g * c_max, end = j0 + c_max < K ? j0 + c_max : K;
                 const int rows = rows_at_once(K, a.groups);              // (the launch's: what its LDS holds)
                 for (int j = j0; j < end; j += rows) {                   // uniform
                     if (j > j0) __syncthreads();                         // the lists of the rows before are no longer read
                     update_rows(input_of(a, h, stage), stage == 0 ? (uint32_t)a.stride_token * 2u : kHeadDim * 2u, a.n_tokens, nb, j,
-                                end - j < rows ? end - j : rows, ids_of(a, h), it == 0 ? init_of(a, h, stage) : table_of(a, h),
+                                end - j < rows ? end - j : rows, ids_of(a, h, __builtin_amdgcn_readfirstlane(lds_apart) != 0), it == 0 ? init_of(a, h, stage) : table_of(a, h),
                                 table_of(a, h), norms_of(a, h), smem);
                 }
             }
-            if (!meet_unit(false)) goto given_up;                        // uniform
+            meet_unit(false);
         }
         if (stage + 1 < a0.S) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();                                             // the staged table is overwritten by the next stage's
             if (threadIdx.x == 0) smax = 0u;
-            if (!resident) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            if (groups_now() < nb) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             __syncthreads();
         }
     }
-    return;
-given_up:
-    if (!last_to_leave(args_again().meet + (int64_t)h * kMeetWords + 1, (uint32_t)groups, &flag)) return;       // uniform
-    groups = 1; g = 0; met = 0; resident = nb == 1;
-    goto begin;
 }
 
 static size_t lloyd_smem_bytes(int K, int groups, int nb) {
@@ -584,11 +648,11 @@ static size_t lloyd_smem_bytes(int K, int groups, int nb) {
 
 // Norms of the start tables, and the units' meeting words cleared.  16 lanes per centroid, grid: x = rows, y = stage, z = unit.
 __global__ __launch_bounds__(kAsgThreads)
-void lloyd_prepare_kernel(const bf16_t *init, int K, int Kpad, uint2 *init_norms, uint32_t *meet) {
+void lloyd_prepare_kernel(const bf16_t *init, int K, int Kpad, uint2 *init_norms, uint32_t *meet, int wanted) {
     const int row = (int)blockIdx.x * 16 + (int)(threadIdx.x >> 4), c16 = threadIdx.x & 15;
     const int64_t t = (int64_t)blockIdx.z * gridDim.y + blockIdx.y;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
-        *reinterpret_cast<uint2 *>(meet + (int64_t)blockIdx.z * kMeetWords) = make_uint2(0u, 0u);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && (int)threadIdx.x < kMeetWords * 4)
+        reinterpret_cast<unsigned char *>(meet + (int64_t)blockIdx.z * kMeetWords)[threadIdx.x] = (int)threadIdx.x >= kStartedAt + wanted;
     uint4 v = make_uint4(0u, 0u, 0u, 0u);
     if (row < K) v = *reinterpret_cast<const uint4 *>(init + (t * K + row) * kHeadDim + c16 * 8);
     const double s = row_sumsq(v);
@@ -604,9 +668,10 @@ static hipError_t launch_lloyd_t(LloydArgs a, hipStream_t s) {
     hipError_t e = ensure_dynamic_lds(kernel, smem, lds_limit);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(lloyd_prepare_kernel, dim3((unsigned)((a.K + 15) / 16), (unsigned)S, (unsigned)a.H), dim3(kAsgThreads), 0, s,
-                       a.init, a.K, Kpad, const_cast<uint2 *>(a.init_norms), a.meet);
+                       a.init, a.K, Kpad, const_cast<uint2 *>(a.init_norms), a.meet, a.wanted);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     a.by_xcd = a.H >= 8;
+    a.wait_ticks = kWaitTicks * (uint32_t)(a.S * a.iters);
     const int64_t grid = a.by_xcd ? (int64_t)8 * a.groups * ((a.H + 7) / 8) : (int64_t)a.groups * a.H;
     hipLaunchKernelGGL((lloyd_kernel<B_, FUSED, T_>), dim3((unsigned)grid), dim3(kAsgThreads), smem, s, a);
     return hipGetLastError();
@@ -645,6 +710,7 @@ int lloyd_groups(int H, int K, int64_t n_tokens, int64_t stride_token, int iters
     // and at most one workgroup to a CU in all (10 units x 1571 tokens, K = 256: 78 -> 69 us)
     const int64_t spare = (int64_t)n / units, useful = (K + 7) / 8, more = spare < useful ? spare : useful;
     const int64_t groups = more > nb ? more : nb;
+    if (n_tokens < 16) return 1;                                         // (a closed team's ids do not fit the codes of fewer tokens)
     return nb < 6 && K > 31 * groups ? 0 : (int)groups;
 }
 

@@ -142,3 +142,72 @@ def test_graph_replays_equal_the_eager_call():
         torch.cuda.synchronize()
         for a, b in zip(_bytes(cache, slice(None)), _bytes(want, slice(None))):
             assert np.array_equal(a, b)
+
+
+def _team_call(shape, wanted):
+    """The encode with units that wait for `wanted` workgroups -> (cache, the units' words: arrived | members << 16, top bit:
+    closed).  The words lie behind the norms and the first table."""
+    H, N, K, S, I, T, Bg, bits, fp8, wide = shape
+    x, init = (t.to(DEV) for t in _inputs(H, N, K, S, 7 * N + K, wide))
+    fmt = B.SCALE_E4M3 if fp8 else B.SCALE_F16
+    got = B.alloc_cache(H, N, N, K, Bg, T, device=DEV, n_smooth=S, bits=bits, scale_format=fmt)
+    for t in (got.centroids, got.ids, got.codes, got.scales):
+        t.view(torch.uint8).fill_(0xA5)
+    p = B.make_params(H, K, Bg, T, I, bits=bits, n_smooth_stages=S, scale_format=fmt)
+    ws = torch.full((B.workspace_bytes(p, B.ENTRY_ENCODE, N),), 0x5A, dtype=torch.uint8, device=DEV)
+    ptr = lambda t: C.c_void_p(t.data_ptr())
+    i64 = C.c_int64
+    st = B.lib().qvg_encode_chunk_wait(C.byref(p), i64(N), ptr(x), i64(x.stride(0)), i64(128), ptr(init), ptr(got.centroids), i64(0),
+                                       ptr(got.ids), ptr(got.codes), ptr(got.scales), i64(0), ptr(ws), C.c_size_t(ws.numel()),
+                                       C.c_void_p(torch.cuda.current_stream().cuda_stream), C.c_uint32(wanted))
+    torch.cuda.synchronize()
+    assert st == 0
+    r256 = lambda v: -(-v // 256) * 256
+    norms = r256(H * (-(-K // 64) * 64) * 8)
+    at = norms * S + r256(H * 4) + norms + r256(H * K * 256)
+    words = ws[at:at + H * 256].view(torch.int32).reshape(H, 64)[:, 0]
+    return B.encode_chunk(x, init, Bg, T, I, bits=bits, scale_format=fmt), got, words.cpu()
+
+
+TEAMS = SHAPES + [(24, 1200, 256, 4, 3, 1, 16, 2, True, False), (26, 3000, 64, 3, 3, 2, 64, 2, False, True)]
+
+
+@pytest.mark.parametrize("wanted", [2, 3, 5, 1000])
+@pytest.mark.parametrize("shape", [s for s in TEAMS if 512 < s[1]], ids=lambda s: "x".join(str(v) for v in s))
+def test_teams_of_fewer_workgroups_make_the_same_bits(shape, wanted):
+    """A team of two, three and five (blocks and rows dealt anew, tokens not kept in registers, residuals of several stages
+    read back), and one closed by the clock because the last of the wanted does not exist."""
+    want, got, words = _team_call(shape, wanted)
+    closed = words < 0
+    if wanted < 5 or wanted == 1000:
+        assert bool(closed.all())
+    members = (words[closed] >> 16) & 0x7fff
+    assert bool((members >= 1).all() if wanted == 1000 else (members == wanted).all())
+    for a, b in zip(_bytes(got, slice(None)), _bytes(want, slice(None))):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("shape", [(24, 4680, 256, 1, 3, 4, 64, 2, False, False), (24, 2000, 64, 4, 3, 1, 16, 2, True, False)],
+                         ids=lambda s: "x".join(str(v) for v in s))
+def test_beside_a_kernel_that_holds_most_of_the_chip(shape):
+    """An attention of 200 workgroups on another stream: units whose workgroups have no place are done by those that have."""
+    from test_gpu_attn_integration import _filled_caches
+    from paper_2602_02958_amd.configs import CONFIGS
+    H, N, K, S, I, T, Bg, bits, fp8, wide = shape
+    x, init = (t.to(DEV) for t in _inputs(H, N, K, S, 3, wide))
+    fmt = B.SCALE_E4M3 if fp8 else B.SCALE_F16
+    want = B.encode_chunk(x, init, Bg, T, I, bits=bits, scale_format=fmt)
+    kc, vc = _filled_caches(20, 4680, 4, 18720, 64, 64, 1)
+    q = synth.queries(CONFIGS["cfg2_window21"], 20, 2560, DEV)
+    B.attn_decode(q, kc, vc)
+    torch.cuda.synchronize()
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(one):
+        outs = [B.attn_decode(q, kc, vc) for _ in range(3)]
+    with torch.cuda.stream(two):
+        got = [B.encode_chunk(x, init, Bg, T, I, bits=bits, scale_format=fmt) for _ in range(3)]
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[2])
+    for g in got:
+        for a, b in zip(_bytes(g, slice(None)), _bytes(want, slice(None))):
+            assert np.array_equal(a, b)
