@@ -92,6 +92,15 @@ __device__ __forceinline__ bool mean_exact(uint32_t mx, uint32_t mn, int lg) {
     return ok;
 }
 
+// s / n correctly rounded, r = 1 / n, for a sum s of bf16 numbers in fp64 and a whole n from 1 to 2^13.  q = s r is within 3/2 ulp
+// of the quotient; s - n q is a multiple of q's last place below 2^14 of them, so the inner fma is exact, and what the
+// outer one rounds is within 2^-52 ulp of s / n.  That rounds alike: s / n is no midpoint between two numbers (n times its 54
+// significant bits does not fit s) and differs from each by 1 / 2n ulp at least.
+__host__ __device__ __forceinline__ double quotient(double s, double n, double r) {
+    const double q = s * r;
+    return __builtin_fma(__builtin_fma(-n, q, s), r, q);
+}
+
 // Upper bound (one ulp up) of ||c||^2 from the split of -||c||^2 / 2; -0 for a zero row.
 __host__ __device__ __forceinline__ float norm_bound(uint2 split) {
     const float hi = __builtin_bit_cast(float, split.x << 16), mid = __builtin_bit_cast(float, split.x & 0xffff0000u);

@@ -167,16 +167,14 @@ struct UpdateLds {
     }
 };
 
-// The 8 channels' sums over n, rounded as one division each would be: with r the correctly rounded 1 / n, q = s r is
-// within an ulp and fma(s - n q, r, q) is the correctly rounded quotient (Markstein; neither term leaves fp64's range
-// here).  Infinite sums and NaN stay what they are.
+// The 8 channels' sums over n, rounded as one division each would be (Markstein's correction).  Infinite sums and NaN
+// stay what they are.
 __device__ __forceinline__ uint4 mean_row(const double s[8], int n) {
     const double d = (double)n, r = 1.0 / d;
     float m[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const double q = s[e] * r, v = __builtin_fma(__builtin_fma(-d, q, s[e]), r, q);
-        m[e] = (float)(__builtin_fabs(s[e]) < INFINITY ? v : s[e]);
+        m[e] = (float)(__builtin_fabs(s[e]) < INFINITY ? quotient(s[e], d, r) : s[e]);
     }
     return make_uint4(pack_bf16x2(m[0], m[1]), pack_bf16x2(m[2], m[3]), pack_bf16x2(m[4], m[5]), pack_bf16x2(m[6], m[7]));
 }

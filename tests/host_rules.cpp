@@ -64,7 +64,26 @@ static const char *norm_reaches() {
     return "ok";
 }
 
+// sums just below a power of two (the largest relative errors of s r), above one, and in between, over every count
+static const char *quotients() {
+    uint64_t state = 1;
+    for (int n = 1; n <= 8192; ++n) {
+        const double r = 1.0 / n;
+        for (int i = 0; i < 400; ++i) {
+            state = state * 6364136223846793005ull + 1442695040888963407ull;
+            const uint64_t some = state >> 12, top = (1ull << 52) - 1;
+            const uint64_t m = i < 100 ? top - i : i < 150 ? i - 100 : i < 250 ? top - (some >> (i % 40)) : some;
+            const double s = ldexp((double)((1ull << 52) | (m & top)), i % 2 ? -133 : 40);
+            if (quotient(s, n, r) != s / n || quotient(-s, n, r) != -s / n) return "not the rounded quotient";
+            const double whole = (double)(m & 0xffffffffu) * n;      // exact ones
+            if (quotient(whole, n, r) != whole / n) return "not the exact quotient";
+        }
+    }
+    return "ok";
+}
+
 int main() {
+    std::printf("quotients %s\n", quotients());
     std::printf("norm_reaches %s\n", norm_reaches());
     std::printf("norm_bounds %s\n", norm_bounds());
     std::printf("tiles_small %s\n", tiles_of(1000, 130, 3, false));

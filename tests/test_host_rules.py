@@ -1,6 +1,6 @@
 """Rules of the device code that are plain arithmetic, compiled for the host and run on the CPU: where
 the tiles of an attention's part lie, up to the largest cache; the bounds on a table's
-norms."""
+norms; the means' division."""
 import os
 import subprocess
 
@@ -21,6 +21,6 @@ def rules(tmp_path_factory):
     return dict(line.split(" ", 1) for line in text.splitlines())
 
 
-@pytest.mark.parametrize("name", ["norm_bounds", "norm_reaches", "tiles_small", "tiles_one_chunk", "tiles_top", "tiles_top_one_chunk", "tiles_top_undivided"])
+@pytest.mark.parametrize("name", ["quotients", "norm_bounds", "norm_reaches", "tiles_small", "tiles_one_chunk", "tiles_top", "tiles_top_one_chunk", "tiles_top_undivided"])
 def test_host_rule(rules, name):
     assert rules[name] == "ok"
