@@ -1,7 +1,7 @@
 """The encoder that runs all Lloyd iterations in one launch, at the sizes where its division of the work has edges:
 blocks of 256 tokens, more workgroups than blocks, more than 64 rows per workgroup, lists summed by a wavefront and by a
-workgroup (with sums that depend on the order), 16-bit ids, several stages; and the same calls with every wait between
-workgroups given up at once, which leaves the units to the last of their workgroups to leave.  Stored arrays against the oracle, bit for bit."""
+workgroup (with sums that depend on the order), 16-bit ids, several stages; and the same calls done by fewer workgroups
+than a unit has, down to one.  Stored arrays against the oracle, bit for bit."""
 import ctypes as C
 
 import numpy as np
@@ -99,7 +99,7 @@ def test_units_given_up_by_their_workgroups_are_done_over(shape):
                                        C.c_void_p(torch.cuda.current_stream().cuda_stream), C.c_uint32(0))
     torch.cuda.synchronize()
     assert st == 0
-    # the units' words, behind the norms and the first table: the top bit says that a unit was given up
+    # the units' words, behind the norms and the first table: the top bit says that a unit's team was closed
     r256 = lambda v: -(-v // 256) * 256
     norms = r256(H * (-(-K // 64) * 64) * 8)
     at = norms * S + r256(H * 4) + norms + r256(H * K * 256)
@@ -211,3 +211,15 @@ def test_beside_a_kernel_that_holds_most_of_the_chip(shape):
     for g in got:
         for a, b in zip(_bytes(g, slice(None)), _bytes(want, slice(None))):
             assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("shape", [(2, 6200, 256, 4, 2, 1, 16, 2, True, False),     # one block too many for the launch
+                                   (2, 2500, 300, 3, 2, 2, 64, 2, False, True)],     # too few workgroups; 16-bit ids
+                         ids=lambda s: "x".join(str(v) for v in s))
+def test_stages_in_launches_of_their_own(shape):
+    """Several stages with Lloyd iterations where the one launch is not taken: residuals, start norms and ids by stage."""
+    H, N, K, S, I, T, Bg, bits, fp8, wide = shape
+    x, init = _inputs(H, N, K, S, N + K, wide)
+    enc = B.encode_chunk(x.to(DEV), init.to(DEV), Bg, T, I, bits=bits, scale_format=B.SCALE_E4M3 if fp8 else B.SCALE_F16)
+    torch.cuda.synchronize()
+    _check(enc, _oracle(x, init, K, Bg, T, I, S, bits, fp8, slice(None)), slice(None))
