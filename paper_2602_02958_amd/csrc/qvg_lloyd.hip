@@ -685,8 +685,11 @@ static hipError_t launch_lloyd_t(LloydArgs a, hipStream_t s) {
 //   61 -> 59 us, K = 16 62 -> 70).  Every workgroup looks through its whole unit's ids, and few units with long
 //   lists have too few wavefronts for the sums: 2 units x 10800, K = 64 65 -> 84 us.
 // For the same reason units of more than 24 blocks are left out (I = 10: 8 units x 10800, K = 16 274 -> 324 us, K = 64 257 -> 284, K = 256
-// 304 -> 316), and those of more than 21, which only calls of up to 16 units have, where lists are long (16 x 6000, K = 16
-// 282 -> 309, K = 64 242 -> 254, but K = 256 325 -> 285; 22 x 4500, K = 16 317 -> 233).
+// 304 -> 316), and, where lists have more than 64 members on average, those of more than 19 blocks: I = 10, K = 64: 16 units x 20
+// blocks 250 -> 258, 24 x 20 257 -> 277, 24 x 21 265 -> 276, K = 16: 16 x 20 298 -> 331, 16 x 21 268 -> 348; but K = 128: 24 x 20 298
+// -> 245, K = 256: 326 -> 290, and 19 blocks, K = 64: 24 units 243 -> 242, 16 224 -> 223.  Three iterations lie on the same side each
+// time.  Lists of more than 256 stay where the chip is nearly full (400 workgroups: K = 16, 24 x 20 362 -> 316, 24 x 21 398 -> 354).
+// (Left in though slower: 24 x 13, K = 64 224 -> 228 us; 32 x 13 231 -> 216, 24 x 16 232 -> 230; 24 x 13, K = 16 310 -> 250.)
 // A workgroup with many rows and few blocks to share them is slower too (80 x 800, K = 256: 64 rows each, 111 -> 119 us; 80 x
 // 1536, 43 rows, 142 -> 122).
 int lloyd_groups(int H, int K, int64_t n_tokens, int64_t stride_token, int iters) {
@@ -702,7 +705,7 @@ int lloyd_groups(int H, int K, int64_t n_tokens, int64_t stride_token, int iters
     }
     const int64_t units = H >= 8 ? (H + 7) / 8 * 8 : H;                  // by_xcd: whole rounds of the eight XCDs
     if (units * nb > (int64_t)n * (K > 256 ? 1 : 2)) return 0;
-    if (nb > 21 && n_tokens > (int64_t)64 * K) return 0;
+    if (nb > 19 && n_tokens > (int64_t)64 * K && (H * nb < 400 || n_tokens <= (int64_t)256 * K)) return 0;
     if (H * nb < 300 && (nb > 8 || n_tokens > (int64_t)40 * K)) return 0;
     // A chip that is not full: more workgroups than blocks, which take rows of the update only, at least eight of them,
     // and at most one workgroup to a CU in all (10 units x 1571 tokens, K = 256: 78 -> 69 us)

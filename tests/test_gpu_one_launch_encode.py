@@ -223,3 +223,16 @@ def test_stages_in_launches_of_their_own(shape):
     enc = B.encode_chunk(x.to(DEV), init.to(DEV), Bg, T, I, bits=bits, scale_format=B.SCALE_E4M3 if fp8 else B.SCALE_F16)
     torch.cuda.synchronize()
     _check(enc, _oracle(x, init, K, Bg, T, I, S, bits, fp8, slice(None)), slice(None))
+
+
+@pytest.mark.parametrize("H,N,K,one_launch", [(24, 5100, 64, False), (16, 5100, 16, False), (24, 5376, 83, False), (20, 5100, 19, True),
+                                              (24, 5376, 84, True), (24, 5100, 16, True), (24, 4864, 64, True), (16, 6144, 95, False)])
+def test_long_lists_of_many_blocks_keep_launches_of_their_own(H, N, K, one_launch):
+    """Which form a call takes: with one iteration only the one launch writes the second table's place, where its units meet;
+    same bytes as the oracle in both."""
+    got, words = _team_call((H, N, K, 1, 1, 1, 64, 2, False, False), 2)[1:]
+    assert bool((words < 0).all()) == one_launch and bool((words == 0x5A5A5A5A).all()) != one_launch
+    x, init = _inputs(H, N, K, 1, 7 * N + K)
+    units = [0, H - 1]
+    ref = _oracle(x, init, K, 64, 1, 1, 1, 2, False, units)
+    _check(got, ref, units)
