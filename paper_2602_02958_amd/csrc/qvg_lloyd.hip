@@ -5,7 +5,7 @@
 // iteration of 24 units x 4680 tokens, K = 256 takes 35 us, of which the tokens' way from memory to the CUs, twice,
 // is 11 (nothing stays in the L2s from one launch to the next: 30 MB fetched by each) and the launches themselves 3 to 4.  Here a unit's
 // workgroups stay: each keeps its 256 tokens in registers through all iterations, the update's gathers find the
-// unit's tokens in the L2 that served the assignment (47 MB fetched in all), and the steps are kept apart by a barrier among the
+// unit's tokens in the L2 that served the assignment (23 MB fetched by a launch where the L2s hold some from the one before, FETCH_SIZE), and the steps are kept apart by a barrier among the
 // workgroups of a UNIT (1.2 us among 16 or 19 of them) instead of the end of a launch.
 //
 // Every iteration: assign (table staged in LDS, qvg_assign.hpp), publish the tokens' ids; meet; update: a
