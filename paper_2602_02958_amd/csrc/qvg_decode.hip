@@ -32,7 +32,8 @@ constexpr int kDecThreads = 1024;
 constexpr int kDecRows = kDecThreads / 16;       // token rows per pass of a block (64)
 constexpr int kDecUnroll = 4;
 constexpr int kDecTokPerIter = kDecRows * kDecUnroll;      // 256 tokens per pass
-constexpr int kXcds = 8;                         // MI355X: 8 XCDs, each with its own L2
+constexpr int kXcds = 8;                         // MI355X: 8 XCDs, each with its own L2,
+constexpr int64_t kDecCus = 256;                 // and 256 CUs in all
 
 // One pass of a block: 256 tokens, 4 rows per thread.  CHECK = false is the fast path for a pass
 // whose tokens all exist (no per-row predication).  tab: the chunk's centroid table in LDS.
@@ -238,19 +239,30 @@ void decode_kernel(DecodeArgs a, int slices, uint32_t slice_len, int n_blocks, i
     }
 }
 
+// Tokens per workgroup.  A workgroup of sixteen wavefronts has a CU to itself (two share one with one round of 2-bit
+// levels), so a call of one to five rounds of workgroups pays for the round that is nearly empty, and every workgroup
+// waits for its table before it writes.  Where slices of up to eight passes make one round that fills at least 208 CUs, each CU gets one slice,
+// us before and after (back to back): 24 units x 4680 tokens, K = 256, T = 2 (456 slices -> 240) 9.5 -> 8.4, T = 4 11.6 ->
+// 10.4; 24 x 10800, K = 64, T = 3 (1032 -> 240) 23.7 -> 17.8; 80 x 4680, T = 4 33 -> 27; 2 x 200000 in chunks of 10800 35 -> 30; with one round 1.02 to 1.2 times.
+// On fewer CUs it loses (130 units x 2000 tokens, T = 2 16.4 -> 18.9).  Otherwise enough workgroups to fill 256 CUs x 2
+// twice over, but as few as possible beyond that (every workgroup re-reads the chunk's table; measured flat from 512 to 4096).
+static int64_t decode_slice_len(int64_t unit_chunks, int64_t chunk) {
+    const int64_t max_slices = (chunk + kDecTokPerIter - 1) / kDecTokPerIter;
+    const int64_t per_cu = unit_chunks <= kDecCus ? kDecCus / unit_chunks : 0;
+    if (unit_chunks * max_slices > kDecCus && unit_chunks * per_cu >= kDecCus * 13 / 16 && per_cu * 8 * kDecTokPerIter >= chunk)
+        return ((chunk + per_cu - 1) / per_cu + 15) / 16 * 16;
+    int64_t slices = (4 * kDecCus + unit_chunks - 1) / unit_chunks;
+    if (slices > max_slices) slices = max_slices;
+    const int64_t len = (chunk + slices - 1) / slices;
+    return (len + kDecTokPerIter - 1) / kDecTokPerIter * kDecTokPerIter;
+}
+
 template <int T_, int SM, int FMT, int SC, bool WIDE>
 static hipError_t launch_decode_w(const DecodeArgs &a, hipStream_t s) {
-    // slices per chunk: enough workgroups to fill 256 CUs x 2 twice over, but as few as possible
-    // beyond that (every workgroup re-reads the chunk's table; measured flat from 512 to 4096)
     const int64_t unit_chunks = (int64_t)a.H * a.n_chunks;
     const int64_t chunk = a.chunk_len < a.n_tokens ? a.chunk_len : a.n_tokens;
-    int64_t slices = (1024 + unit_chunks - 1) / unit_chunks;
-    const int64_t max_slices = (chunk + kDecTokPerIter - 1) / kDecTokPerIter;
-    if (slices > max_slices) slices = max_slices;
-    if (slices < 1) slices = 1;
-    int64_t slice_len = (chunk + slices - 1) / slices;
-    slice_len = (slice_len + kDecTokPerIter - 1) / kDecTokPerIter * kDecTokPerIter;
-    slices = (chunk + slice_len - 1) / slice_len;
+    const int64_t slice_len = decode_slice_len(unit_chunks, chunk);
+    const int64_t slices = (chunk + slice_len - 1) / slice_len;
     const int64_t nb = unit_chunks * slices;
     if (nb > 0x7fffffff - kXcds) return hipErrorInvalidValue;
     const int bpx = (int)((nb + kXcds - 1) / kXcds);
@@ -271,7 +283,8 @@ static hipError_t launch_decode_t(const DecodeArgs &a, hipStream_t s) {
     return launch_decode_w<T_, SM, FMT, SC, false>(a, s);
 }
 
-// the other stored formats: run-time round count, except the paper's own 2-bit / E4M3 / one round
+// the other stored formats: run-time round count, except the paper's own single round (with 4-bit levels, eight rounds' loads
+// in a loop of one had cost 24 units x 4680 tokens 14.0 instead of 8.1 us, 80 x 10800 59 instead of 46)
 template <int FMT>
 static hipError_t launch_decode_fmt(const DecodeArgs &a, hipStream_t s) {
     if (a.S > 1) {
@@ -280,7 +293,7 @@ static hipError_t launch_decode_fmt(const DecodeArgs &a, hipStream_t s) {
         if ((FMT & kFmtE4M3) && a.S == 4 && a.T == 1) return launch_decode_t<1, 3, FMT, 4>(a, s);
         return launch_decode_t<0, 3, FMT>(a, s);
     }
-    if (FMT == kFmtE4M3 && a.T == 1) return launch_decode_t<(FMT == kFmtE4M3 ? 1 : 0), 1, FMT>(a, s);
+    if (a.T == 1) return launch_decode_t<1, 1, FMT>(a, s);
     return launch_decode_t<0, 1, FMT>(a, s);
 }
 
