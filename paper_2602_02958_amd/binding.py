@@ -282,9 +282,9 @@ def _scratch(nbytes: int, device):
 
 
 def _may_divide(n_kv, chunk_len):
-    """False for caches of fewer than eight tiles, which are never divided: a call over them is host time (11.7 us,
+    """False for caches of fewer than four tiles, which are never divided: a call over them is host time (11.7 us,
     12.5 with the question asked)."""
-    return n_kv // 64 + n_kv // chunk_len >= 6
+    return n_kv // 64 + n_kv // chunk_len >= 3
 
 
 # An attn_decode that is lent no workspace takes one for itself when a unit has three query blocks or more:

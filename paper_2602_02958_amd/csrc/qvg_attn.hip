@@ -917,14 +917,14 @@ hipError_t launch_attn(const AttnArgs &a, hipStream_t s) {
 
 // ---------------------------------------------------------------------------------------------
 // Parts.  A call of few query blocks leaves most of the 256 CUs idle while each workgroup walks the
-// whole cache, 1.5-2.5 us a tile.  Its tiles are dealt out (tile g to part g % parts, so that every slab
-// of the shared-tile form and every prefix is spread evenly) until the chip is full once, with at
-// least four tiles to a part: fewer do not repay the part's start and its 132 KB of state.  64 queries
-// of one head over 4096 tokens 160 -> 28 us (2, 3 and 6 tiles at least: 28, 29, 30); 12 heads x
-// 1560 queries over 31997 tokens 795 -> 430 us; twice the chip's worth of parts is 5 % slower there.
-// More than 64 query blocks are not divided below ten tiles: the states are 132 KB each to write and to read, and two
-// parts of four tiles do not repay them (12 heads x 1560 queries over 512 tokens 30 us undivided, 34 divided; 40 x 700
-// 30.5 and 35; with 36 blocks 30 and 27; 40 x 300 over twelve tiles 32 in three parts, 36 in two).
+// whole cache, 1.5-3 us a tile.  Its tiles are dealt out (tile g to part g % parts, so that every slab
+// of the shared-tile form and every prefix is spread evenly), at most until the chip is full once (twice the chip's worth of parts
+// is 5 % slower).  How far is what costs least: the longest part's tiles, the join, and the states, 528 bytes per query and part
+// to write and to read.  With four tiles to a part at least, us before and after: 64 queries x 1 head over 500 tokens 19.3 -> 11.4, 4096 20.3 ->
+// 12.5, 8 heads over 2000 19.5 -> 12.7; 250 x 8 over 1000 22.3 -> 19.9 (one tile to a part 18.1), 400 x 2 over 3000 26.6 -> 20.9 (one tile
+// 24.0); 300 x 40 over 700 36.7 -> 33.5; 500 the same undivided (31.1), 1560 x 12 over 512 26.7 (divided 34).  More than
+// eight blocks over 48 tiles or more have as many parts as the chip holds, of four tiles at least: the cost of one more or less is about the same there
+// (16 blocks over 74 tiles in 16 parts 38.7, in 15 39.3; 12 x 64 queries over 74 tiles in 18 27.8, in 19 26.7).
 // From 129 query blocks on nothing is dealt: 160 blocks in three parts gain nothing (1.09 against 1.08 ms).
 // More than 256 are taken whole up to the last round of 256, and that one is dealt out if at most 128 are left for it: the
 // call would end with a few blocks on an idle chip.  266 blocks over 293 tiles 1025 -> 655 us (all blocks in four parts
@@ -941,7 +941,21 @@ hipError_t launch_attn(const AttnArgs &a, hipStream_t s) {
 constexpr int kCus = 256;
 constexpr int kLenMinBlocks = 129, kLenMinTiles = 192, kLenParts = 3, kLenPartTiles = 48;
 constexpr int kTailMaxBlocks = 4096, kTailMinTiles = 16;
-constexpr int kPartMinTiles = 4, kPartManyBlocks = 64, kPartManyMinTiles = 10;
+constexpr int kPartTiles = 4;                     // tiles of a part at least where the parts are as many as the chip holds
+constexpr int kCostBlocks = 8, kCostTiles = 48;   // up to that many blocks, or below that many tiles, parts are chosen by cost
+constexpr int64_t kTileNs = 2300, kJoinNs = 4700, kStateNsBy100 = 21;
+// Parts of `tiles` tiles of a call of `queries` queries, `most` at most: by what the longest part's tiles, the join's launch and
+// the states of all parts take.  Among equal longest parts the fewest.
+static int parts_by_cost(int64_t tiles, int64_t most, int64_t queries) {
+    int64_t parts = 1, best = tiles * kTileNs;
+    if (most > tiles) most = tiles;
+    if (most < 2) return 1;
+    for (int64_t longest = (tiles + most - 1) / most; longest * kTileNs + kJoinNs < best; ++longest) {
+        const int64_t p = (tiles + longest - 1) / longest, cost = longest * kTileNs + kJoinNs + p * queries * kStateNsBy100 / 100;
+        if (cost < best) { best = cost; parts = p; }
+    }
+    return (int)parts;
+}
 AttnParts attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool with_len) {
     AttnParts p{1, 0, 0};
     if (n_q < 1 || n_kv < 1) return p;
@@ -954,20 +968,40 @@ AttnParts attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool w
         return p;
     }
     if (nb > kCus && nb <= kTailMaxBlocks) {
-        const int64_t rest = nb % kCus, most = tiles / kPartMinTiles;
+        const int64_t rest = nb % kCus, most = tiles / kPartTiles;
         if (with_len || rest == 0 || rest > kCus / 2 || tiles < kTailMinTiles) return p;
         p.parts = (int)(kCus / rest < most ? kCus / rest : most);
         p.whole = (int)(nb - rest);
         return p;
     }
-    const int64_t most = nb > kPartManyBlocks && tiles < kPartManyMinTiles ? 1 : tiles / kPartMinTiles;
-    const int64_t parts = kCus / nb < most ? kCus / nb : most;
-    if (parts > 1) p.parts = (int)parts;
+    if (nb > kCus) return p;
+    if (nb <= kCostBlocks || tiles < kCostTiles) p.parts = parts_by_cost(tiles, kCus / nb, H * n_q);
+    else p.parts = (int)(kCus / nb < tiles / kPartTiles ? kCus / nb : tiles / kPartTiles);
     return p;
 }
 size_t attn_parts_bytes(int H, int64_t n_q, const AttnParts &p) {
     const int64_t nqb = (n_q + kAtQPerBlock - 1) / kAtQPerBlock;
     return p.parts > 1 ? (size_t)p.parts * (nqb * H - p.whole) * kStateFloats * kAtThreads * sizeof(float) : 0;
+}
+
+// The end of a join: a lane's NV values from value v0 on (channels 32 * (v0 / 16) + 8 * (v / 4 % 4) + 4 * half + v % 4) of
+// its query, normalised; any: some part saw a token of the query.
+template <int NV>
+__device__ __forceinline__ void join_store(const AttnArgs &a, int h, int64_t qrow, int half, int v0, bool any, const float (&o)[NV], float m, float l) {
+    const float ltot = l + __shfl_xor(l, 32, 64);
+    const float inv = any ? 1.0f / ltot : 0.0f;
+    const int64_t at = ((int64_t)h * a.n_q + qrow) * kHeadDim + half * 4 + (v0 >> 4) * 32 + ((v0 >> 2) & 3) * 8;
+#pragma unroll
+    for (int g = 0; g < NV / 4; ++g) {
+        if (a.out_f32)
+            *reinterpret_cast<float4 *>(a.out_f32 + at + g * 8) =
+                make_float4(o[4 * g] * inv, o[4 * g + 1] * inv, o[4 * g + 2] * inv, o[4 * g + 3] * inv);
+        else
+            *reinterpret_cast<uint2 *>(a.out + at + g * 8) = make_uint2(pack_bf16x2(o[4 * g] * inv, o[4 * g + 1] * inv),
+                                                                        pack_bf16x2(o[4 * g + 2] * inv, o[4 * g + 3] * inv));
+    }
+    if (a.lse && half == 0 && v0 == 0)
+        a.lse[(int64_t)h * a.n_q + qrow] = any ? (m + __builtin_log2f(ltot)) * 0.6931471805599453f : -INFINITY;
 }
 
 // The result of a query from the states of its parts: one workgroup per query block and NV of a lane's
@@ -982,7 +1016,8 @@ size_t attn_parts_bytes(int H, int64_t n_q, const AttnParts &p) {
 //   NV 8, AHEAD 8       21.3  25.1  100.8  27.9  22.6  24.7  36.4   30.7  35.3   36.7  35.1  53.7
 //   NV 4, AHEAD 8       20.8  24.0   89.2  26.6  22.1  24.5  35.9   31.8  36.1   36.3  34.8  54.1
 //   NV 4, AHEAD 16      21.7  23.4   79.6  26.1  22.6  25.1  35.6   31.9  36.9   37.6  36.5  59.3
-constexpr int kJoinFewBlocks = 16, kJoinManyParts = 16;
+// (From 8 parts of up to 8 blocks on: attn_join_many_kernel.)
+constexpr int kJoinFewBlocks = 16, kJoinManyParts = 16, kJoinSplitBlocks = 8, kJoinSplitParts = 8;
 template <bool QL, int NV, int AHEAD>         // QL: with a.q_len; NV: 4 or 8
 __global__ __launch_bounds__(kAtThreads)
 void attn_join_kernel(AttnArgs a, int n_qblocks) {
@@ -1058,27 +1093,107 @@ void attn_join_kernel(AttnArgs a, int n_qblocks) {
             }
         }
     }
-    const float ltot = l + __shfl_xor(l, 32, 64);
-    const bool any = seen > 0;
-    const float inv = any ? 1.0f / ltot : 0.0f;
-    const int64_t at = ((int64_t)h * a.n_q + qrow) * kHeadDim + half * 4 + (v0 >> 4) * 32 + ((v0 >> 2) & 3) * 8;
+    join_store<NV>(a, h, qrow, half, v0, seen > 0, o, m, l);
+}
+
+// The same for many parts: one workgroup per 32 queries and four of a lane's values, whose eight wavefronts take the parts in
+// turn (a running maximum each) and meet in LDS.  One wavefront's chain of all parts was the larger part of a small call:
+// one head's 64 queries over 100000 tokens in 223 parts 70 -> 37 us a call, 100 over 20000 in 157 35 -> 22; 2 heads x 400 over 3000 in 24 22.2
+// (the other join 25).  More than 8 blocks read too much for that: 12 x 200 over 31997 in 21 parts 109 (this one 112).
+// QL: with a.q_len and no a.part_tiles (more than three parts).
+template <bool QL>
+__global__ __launch_bounds__(kAtThreads)
+void attn_join_many_kernel(AttnArgs a, int n_qblocks) {
+    constexpr int NV = 4, AHEAD = 8;
+    __shared__ float met[kAtWaves][NV + 2][64];
+    const unsigned block = blockIdx.x + (unsigned)a.whole;
+    const int h = (int)(block / (unsigned)n_qblocks), qblock = (int)(block - (unsigned)h * n_qblocks);
+    const int v0 = blockIdx.y * NV, group = blockIdx.z;
+    const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if ((int64_t)qblock * kAtQPerBlock + group * 32 >= a.n_q) return;   // uniform
+    const int64_t qrow = (int64_t)qblock * kAtQPerBlock + group * 32 + col;
+    const bool qvalid = qrow < a.n_q;                                    // (what is read for the others lies inside the state and is not used)
+    const float *st = part_state_of(a, n_qblocks, h, qblock, 0) - threadIdx.x + group * 64 + lane;
+    const int64_t pitch = ((int64_t)a.H * n_qblocks - a.whole) * kStateFloats * kAtThreads;
+    // (as in attn_join_kernel)
+    int seen = a.parts, read = a.parts;
+    if (QL) {
+        const int nk = (int)a.n_kv;
+        int qlen = 0;
+        if (qvalid) { const int v = a.q_len[qrow]; qlen = v < 0 ? 0 : (v > nk ? nk : v); }
+        int longest = qlen;
 #pragma unroll
-    for (int g = 0; g < NV / 4; ++g) {
-        if (a.out_f32)
-            *reinterpret_cast<float4 *>(a.out_f32 + at + g * 8) =
-                make_float4(o[4 * g] * inv, o[4 * g + 1] * inv, o[4 * g + 2] * inv, o[4 * g + 3] * inv);
-        else
-            *reinterpret_cast<uint2 *>(a.out + at + g * 8) = make_uint2(pack_bf16x2(o[4 * g] * inv, o[4 * g + 1] * inv),
-                                                                        pack_bf16x2(o[4 * g + 2] * inv, o[4 * g + 3] * inv));
+        for (int off = 16; off >= 1; off >>= 1) { const int o = __shfl_xor(longest, off, 64); longest = o > longest ? o : longest; }
+        longest = __builtin_amdgcn_readfirstlane(longest);
+        const int64_t tiles = tiles_of(a, qlen), most = tiles_of(a, longest);
+        seen = tiles < a.parts ? (int)tiles : a.parts;
+        read = most < a.parts ? (int)most : a.parts;
     }
-    if (a.lse && half == 0 && v0 == 0)
-        a.lse[(int64_t)h * a.n_q + qrow] = any ? (m + __builtin_log2f(ltot)) * 0.6931471805599453f : -INFINITY;
+    float m = kNoScore, l = 0.0f, o[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) o[i] = 0.0f;
+    for (int p0 = wave; p0 < read; p0 += AHEAD * kAtWaves) {             // uniform
+        float x[AHEAD][NV + 2];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const float *sp = st + (p0 + u * kAtWaves < read ? p0 + u * kAtWaves : p0) * pitch;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) x[u][i] = sp[(v0 + i) * kAtThreads];
+            x[u][NV] = sp[64 * kAtThreads]; x[u][NV + 1] = sp[65 * kAtThreads];
+        }
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u)
+#pragma unroll
+            for (int i = 0; i < NV + 2; ++i) asm volatile("" : "+v"(x[u][i]));        // requested before the first is used
+        float top = m;
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) top = p0 + u * kAtWaves < seen ? fmaxf(top, x[u][NV]) : top;
+        const float alpha = __builtin_amdgcn_exp2f(m - top);
+        m = top;
+        l *= alpha;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) o[i] *= alpha;
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            if (p0 + u * kAtWaves < seen) {
+                const float wgt = __builtin_amdgcn_exp2f(x[u][NV] - m);
+                l = __builtin_fmaf(wgt, x[u][NV + 1], l);
+#pragma unroll
+                for (int i = 0; i < NV; ++i) o[i] = __builtin_fmaf(wgt, x[u][i], o[i]);
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) met[wave][i][lane] = o[i];
+    met[wave][NV][lane] = m; met[wave][NV + 1][lane] = l;
+    __syncthreads();
+    if (wave != 0) return;                                               // uniform
+#pragma unroll
+    for (int r = 1; r < kAtWaves; ++r) m = fmaxf(m, met[r][NV][lane]);
+    l = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) o[i] = 0.0f;
+#pragma unroll
+    for (int r = 0; r < kAtWaves; ++r) {
+        const float wgt = __builtin_amdgcn_exp2f(met[r][NV][lane] - m);
+        l = __builtin_fmaf(wgt, met[r][NV + 1][lane], l);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) o[i] = __builtin_fmaf(wgt, met[r][i][lane], o[i]);
+    }
+    if (qvalid) join_store<NV>(a, h, qrow, half, v0, seen > 0, o, m, l);
 }
 
 hipError_t launch_attn_join(const AttnArgs &a, hipStream_t s) {
     const int64_t nqb = (a.n_q + kAtQPerBlock - 1) / kAtQPerBlock;
     if (nqb * a.H > 0x7fffffff) return hipErrorInvalidValue;
     const int64_t blocks = nqb * a.H - a.whole;
+    if (blocks <= kJoinSplitBlocks && a.parts >= kJoinSplitParts) {
+        const dim3 grid((unsigned)blocks, 16, nqb > 1 ? kAtWaves : (unsigned)(a.n_q + 31) / 32u);
+        if (a.q_len) hipLaunchKernelGGL(attn_join_many_kernel<true>, grid, dim3(kAtThreads), 0, s, a, (int)nqb);
+        else hipLaunchKernelGGL(attn_join_many_kernel<false>, grid, dim3(kAtThreads), 0, s, a, (int)nqb);
+        return hipGetLastError();
+    }
     const int form = blocks > kJoinFewBlocks ? 0 : a.parts < kJoinManyParts ? 2 : 4;
     const dim3 grid((unsigned)blocks, form ? 16 : 8);
     typedef void (*join_kernel_t)(AttnArgs, int);
