@@ -8,6 +8,7 @@ a missing library raises at the first call.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from dataclasses import dataclass
 
@@ -122,7 +123,8 @@ def compressed_bytes(p: QvgParams, n_tokens: int) -> int:
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    # (torch.cuda.current_stream().cuda_stream without the Stream object, which costs more than all pointers of a call)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t):
@@ -168,6 +170,18 @@ def id_dtype(n_clusters):
     """Cluster ids are bytes up to 256 centroids and 16-bit words beyond (int16 tensors here: the
     values stay below 512)."""
     return torch.uint8 if n_clusters <= 256 else torch.int16
+
+
+def _check_stored(cent, ids, codes, scales, K):
+    if (cent.dtype is torch.bfloat16 and ids.dtype is id_dtype(K) and codes.dtype is torch.uint8 and
+            cent.is_cuda and ids.is_cuda and codes.is_cuda and scales.is_cuda and
+            cent.is_contiguous() and ids.is_contiguous() and codes.is_contiguous() and scales.is_contiguous()):
+        return
+    for t, dt, nm in ((cent, torch.bfloat16, "centroids"), (ids, id_dtype(K), "ids"),
+                      (codes, torch.uint8, "codes"), (scales, scales.dtype, "scales")):
+        _check(t, dt, nm)
+        if not t.is_contiguous():
+            raise ValueError(f"{nm} must be contiguous")
 
 
 def alloc_cache(n_heads, n_tokens, chunk_len, n_clusters, group_size, n_stages, head_dim=128,
@@ -239,24 +253,20 @@ def encode_chunk(x, init_centroids, group_size, n_stages, kmeans_iters, cache: E
 def decode(enc: Encoded, out=None, n_tokens=None, first_token=0) -> torch.Tensor:
     """qvg_decode_ex -> bf16 [H, n_tokens, d]: the whole cache, or n_tokens tokens starting at
     first_token (a multiple of the chunk length)."""
-    H, cap = enc.ids.shape[:2]
+    cent, ids, codes, scales = enc.centroids, enc.ids, enc.codes, enc.scales
+    H, cap = ids.shape[:2]
     N = cap - first_token if n_tokens is None else int(n_tokens)
     if first_token < 0 or N < 0 or first_token + N > cap:
         raise ValueError("token range outside the cache")
-    K, d = enc.centroids.shape[-2:]
-    T, G = enc.codes.shape[2], enc.scales.shape[3]
-    p = make_params(H, K, d // G, T, 0, head_dim=d, n_smooth_stages=enc.n_smooth, bits=enc.bits,
-                    scale_format=enc.scale_format)
+    K, d = cent.shape[-2:]
+    T, code_bytes = codes.shape[2:]
+    p = QvgParams(H, d, K, d // scales.shape[3], T, code_bytes * 8 // d, enc.n_smooth, 0, enc.scale_format)
     if out is None:
-        out = torch.empty(H, N, d, dtype=torch.bfloat16, device=enc.ids.device)
+        out = torch.empty(H, N, d, dtype=torch.bfloat16, device=ids.device)
     sh, st_ = _view3(out, "out")
-    for t, dt, nm in ((enc.centroids, torch.bfloat16, "centroids"), (enc.ids, id_dtype(K), "ids"),
-                      (enc.codes, torch.uint8, "codes"), (enc.scales, enc.scales.dtype, "scales")):
-        _check(t, dt, nm)
-        if not t.is_contiguous():
-            raise ValueError(f"{nm} must be contiguous")
-    st = lib().qvg_decode_ex(C.byref(p), N, enc.chunk_len, cap, first_token, _ptr(enc.centroids), _ptr(enc.ids),
-                             _ptr(enc.codes), _ptr(enc.scales), _ptr(out), sh, st_, _stream())
+    _check_stored(cent, ids, codes, scales, K)
+    st = lib().qvg_decode_ex(p, N, enc.chunk_len, cap, first_token, cent.data_ptr(), ids.data_ptr(), codes.data_ptr(),
+                             scales.data_ptr(), out.data_ptr(), sh, st_, _stream())
     if st != 0:
         raise QvgError(st, "qvg_decode_ex")
     return out
@@ -285,6 +295,18 @@ def _may_divide(n_kv, chunk_len):
     """False for caches of fewer than four tiles, which are never divided: a call over them is host time (11.7 us,
     12.5 with the question asked)."""
     return n_kv // 64 + n_kv // chunk_len >= 3
+
+
+@functools.lru_cache(maxsize=256)
+def _parts_bytes(H, d, K, group_size, T, bits, n_smooth, scale_format, n_q, n_kv, chunk_len, with_len) -> int:
+    """Bytes of scratch that let a call of these sizes be divided: a function of its arguments alone, so a call like
+    the one before does not ask the library again."""
+    need = C.c_size_t()
+    ask = lib().qvg_attn_scratch_bytes_causal if with_len else lib().qvg_attn_scratch_bytes
+    st = ask(QvgParams(H, d, K, group_size, T, bits, n_smooth, 0, scale_format), n_q, n_kv, chunk_len, C.byref(need))
+    if st != 0:
+        raise QvgError(st, "qvg_attn_scratch_bytes")
+    return need.value
 
 
 # An attn_decode that is lent no workspace takes one for itself when a unit has three query blocks or more:
@@ -352,10 +374,10 @@ def _attn(q, k: Encoded, kp, vp, softmax_scale, want_lse, out, n_kv, k_rope, q_k
         if tuple(k_rope.shape) != (Nk, d // 2, 2) or not k_rope.is_contiguous():
             raise ValueError("k_rope: need a contiguous [n_kv, d/2, 2] float16 tensor")
     K = k.centroids.shape[-2]
-    T, G = k.codes.shape[2], k.scales.shape[3]
+    T, code_bytes = k.codes.shape[2:]
+    G = k.scales.shape[3]
     _check(k.ids, id_dtype(K), "k.ids")
-    p = make_params(H, K, d // G, T, 0, head_dim=d, n_smooth_stages=k.n_smooth, bits=k.bits,
-                    scale_format=k.scale_format)
+    p = QvgParams(H, d, K, d // G, T, code_bytes * 8 // d, k.n_smooth, 0, k.scale_format)
     if softmax_scale is None:
         softmax_scale = 1.0 / (d ** 0.5)
     if out is None:
@@ -371,12 +393,8 @@ def _attn(q, k: Encoded, kp, vp, softmax_scale, want_lse, out, n_kv, k_rope, q_k
             raise ValueError("out must be contiguous")
     scratch = None
     if _may_divide(Nk, k.chunk_len):
-        need = C.c_size_t()
-        ask = lib().qvg_attn_scratch_bytes if q_kv_len is None else lib().qvg_attn_scratch_bytes_causal
-        st = ask(C.byref(p), Nq, Nk, k.chunk_len, C.byref(need))
-        if st != 0:
-            raise QvgError(st, "qvg_attn_scratch_bytes")
-        scratch = _scratch(need.value, q.device)
+        scratch = _scratch(_parts_bytes(H, d, K, d // G, T, p.bits, k.n_smooth, p.scale_format, Nq, Nk, k.chunk_len,
+                                        q_kv_len is not None), q.device)
     if workspace is None and q_kv_len is None and Nq > TILE_SCRATCH_MIN_QUERIES and Nk >= TILE_SCRATCH_MIN_TOKENS:
         workspace = _scratch(_tile_scratch_bytes(H, Nq, k.chunk_len, -(-Nk // k.chunk_len)), q.device)
     st = lib().qvg_attn_decode_parts(C.byref(p), Nq, _ptr(q), Nk, k.chunk_len, cap,
@@ -513,9 +531,11 @@ class StreamingCache:
         # the two halves of the cache by address: views of both sides (self.k, self.v) cost more than the
         # smallest attention's launches
         c = self.cache
-        ts = (c.centroids, c.ids, c.codes, c.scales)
-        vp = tuple(t.data_ptr() + self.heads * t.stride(0) * t.element_size() for t in ts)
-        return _attn(q, c, tuple(_ptr(t) for t in ts), vp, softmax_scale, want_lse, out, self.n_tokens, k_rope, None,
+        h = self.heads
+        kp = (c.centroids.data_ptr(), c.ids.data_ptr(), c.codes.data_ptr(), c.scales.data_ptr())
+        vp = (kp[0] + h * c.centroids.stride(0) * 2, kp[1] + h * c.ids.stride(0) * c.ids.element_size(),
+              kp[2] + h * c.codes.stride(0), kp[3] + h * c.scales.stride(0) * c.scales.element_size())
+        return _attn(q, c, kp, vp, softmax_scale, want_lse, out, self.n_tokens, k_rope, None,
                      False, workspace)
 
     def decode(self, out=None, first_chunk=0, n_tokens=None) -> torch.Tensor:
