@@ -243,7 +243,7 @@ struct LloydArgs {
     int n_blocks, groups;                    // blocks of 256 tokens per unit; workgroups per unit
     int wanted;                              // workgroups that a unit's first barrier waits for: `groups`
     uint32_t wait_ticks;                     // set by launch_lloyd
-    int by_xcd;                              // set by launch_lloyd
+    int by_xcd, rows, row_weight;            // set by launch_lloyd
 };
 int lloyd_groups(int H, int K, int64_t n_tokens, int64_t stride_token, int iters);      // workgroups per unit, 0: not for this call
 hipError_t launch_lloyd(const LloydArgs &a, hipStream_t s);

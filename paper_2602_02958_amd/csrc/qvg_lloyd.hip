@@ -193,201 +193,277 @@ __device__ __forceinline__ int thread_id() {
     return t;
 }
 
-// The new rows j0 .. j0 + c - 1 of a unit's table, 1 <= c <= 64.
+// The rows of a unit's new table are dealt in index order by their members, not by their number: a stage's largest
+// clusters can hold a tenth of a unit's tokens each (later smoothing stages), and the unit waits for the workgroup that has
+// most.  Every workgroup has to see the same members: those of the iteration before, which come with the table, and before the
+// first update of a stage they are counted from the ids (2 us).  The first stage's clusters are dealt by number: what the
+// dealing takes, 0.8 us an iteration, is not gained back there (24 units x 4680 tokens, K = 256, S = 1: 115.0 -> 115.8 us).
+struct DealLds {
+    int sums[kMaxClusters / 64];   // weights of 64 rows
+    int below[kMaxClusters / 64], upto[kMaxClusters / 64];               // of 64 rows: those before this workgroup's, and with them
+};
+constexpr int kRowsPerThread = kMaxClusters / kAsgThreads;
+
+// This workgroup's rows: those whose middle lies in its share of the weight.  members: of rows t and t + 256 (thread t).
+// The caller's barrier stands between this and dealt().
+__device__ __forceinline__ void deal_rows(const int (&members)[kRowsPerThread], int K, int weight, int g, int groups, DealLds &d) {
+    const int tid = thread_id(), lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int v[kRowsPerThread], upto[kRowsPerThread];
+#pragma unroll
+    for (int k = 0; k < kRowsPerThread; ++k) {
+        v[k] = k * kAsgThreads + tid < K ? weight + members[k] : 0;
+        upto[k] = scan64(v[k]);
+        if (lane == 63) d.sums[k * kAsgWaves + w] = upto[k];
+    }
+    __syncthreads();
+    int all = 0, before[kRowsPerThread] = {};
+#pragma unroll
+    for (int i = 0; i < kMaxClusters / 64; ++i) {
+#pragma unroll
+        for (int k = 0; k < kRowsPerThread; ++k) before[k] = i == k * kAsgWaves + w ? all : before[k];
+        all += d.sums[i];
+    }
+#pragma unroll
+    for (int k = 0; k < kRowsPerThread; ++k) {
+        const int at = v[k] ? (2 * (before[k] + upto[k]) - v[k]) * groups : 0x7fffffff;                // (the products are below 2^23)
+        const int below = __builtin_popcountll(__ballot(at < 2 * all * g)), with = __builtin_popcountll(__ballot(at < 2 * all * (g + 1)));
+        if (lane == 0) { d.below[k * kAsgWaves + w] = below; d.upto[k * kAsgWaves + w] = with; }
+    }
+}
+__device__ __forceinline__ void dealt(const DealLds &d, int &first, int &end) {
+    int a = 0, b = 0;
+#pragma unroll
+    for (int i = 0; i < kMaxClusters / 64; ++i) { a += d.below[i]; b += d.upto[i]; }
+    first = __builtin_amdgcn_readfirstlane(a); end = __builtin_amdgcn_readfirstlane(b);
+}
+
+// The workgroup's rows of a unit's new table, `rows` <= 64 at a time.
+// count: the members are not known yet.
 // x: the unit's tokens, row_bytes apart (below 2^31 bytes in all).
-__device__ __forceinline__ void update_rows(const void *x, uint32_t row_bytes, int n_tokens, int nb, int j0, int c, const Shared &ids_x,
-                                            const Shared &prev, const Shared &table, const Shared &norms, unsigned char *smem) {
+__device__ __forceinline__ void update_rows(const void *x, uint32_t row_bytes, int n_tokens, int nb, int K, int g, int groups, int rows, int weight, bool count,
+                                            const Shared &ids_x, const Shared &prev, const Shared &table, const Shared &norms, unsigned char *smem, DealLds &deal) {
     const int tid = thread_id(), lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const UpdateLds u(smem, nb, c);
-    // ---- the unit's ids, four pieces in flight per thread ----
-    for (int i0 = tid; i0 < nb * 32; i0 += 4 * kAsgThreads) {
-        uint4 v[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = ids_x.load16((uint32_t)(i0 + k * kAsgThreads) * 16u);        // (zero beyond the unit)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) if (i0 + k * kAsgThreads < nb * 32) *reinterpret_cast<uint4 *>(u.ids + (i0 + k * kAsgThreads) * 8) = v[k];
-    }
+    const UpdateLds u(smem, nb, rows);
     int *cnt = u.cnt + w * 64;
-    cnt[lane] = 0;
-    __syncthreads();
-    // ---- the members of these rows, a wavefront's quarter of the tokens at a time, in token order (no branches: what
-    // is no member goes to the place behind the last) ----
     uint32_t *own = u.own + w * (nb * 64 + 1);
-    const uint16_t *my = u.ids + w * nb * 64 + lane;
-    int n_own = 0;                                                       // uniform
-    for (int i0 = 0; i0 < nb; i0 += 4) {
-        uint32_t key[4];
+    const uint16_t *my = u.ids + w * nb * 64 + lane;                     // the wavefront's quarter of the tokens
+    // ---- the unit's ids, four pieces in flight per thread ----
+    auto load_ids = [&] {
+        for (int i0 = tid; i0 < nb * 32; i0 += 4 * kAsgThreads) {
+            uint4 v[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int i = i0 + k < nb ? i0 + k : nb - 1;
-            key[k] = ((uint32_t)my[i * 64] | (i0 + k < nb ? 0u : 0xffffu)) - (uint32_t)j0;
-        }
+            for (int k = 0; k < 4; ++k) v[k] = ids_x.load16((uint32_t)(i0 + k * kAsgThreads) * 16u);    // (zero beyond the unit)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const bool mine = key[k] < (uint32_t)c;
-            const uint64_t m = __ballot(mine);
-            const int at = n_own + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-            own[mine ? at : nb * 64] = (uint32_t)((w * nb + i0 + k) * 64 + lane) | key[k] << 16;
-            n_own += __builtin_popcountll(m);
+            for (int k = 0; k < 4; ++k) if (i0 + k * kAsgThreads < nb * 32) *reinterpret_cast<uint4 *>(u.ids + (i0 + k * kAsgThreads) * 8) = v[k];
         }
-    }
-    // ---- sorted by row: lanes with the same row are ranked by lane number ----
-    auto peers_of = [&](uint32_t key, bool mine) {
-        uint64_t peers = __ballot(mine);
-        for (int b = 0; (c - 1) >> b; ++b) {                             // uniform
-            const uint64_t m = __ballot((key >> b) & 1u);
-            peers &= ((key >> b) & 1u) ? m : ~m;
-        }
-        return peers;
     };
-    const uint64_t below = (1ull << lane) - 1ull;
-    __builtin_amdgcn_wave_barrier();
-    for (int e = 0; e < n_own; e += 64) {                                // uniform
-        const bool mine = e + lane < n_own;
-        const uint32_t key = mine ? own[e + lane] >> 16 : 0u;
-        const uint64_t peers = peers_of(key, mine);
-        if (mine && !(peers & below)) atomicAdd(&cnt[key], __builtin_popcountll(peers));
-    }
+    uint32_t *members = reinterpret_cast<uint32_t *>(u.part);            // [K], of the count
+    if (count) for (int i = tid; i < K; i += kAsgThreads) members[i] = 0u;
+    cnt[lane] = 0;
+    load_ids();
     __syncthreads();
-    // lane l: row l's members (len) and the first one's place in the list (start), the same in every wavefront
-    int len = 0, mine_from = 0;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) { const int n = u.cnt[r * 64 + lane]; if (r < w) mine_from += n; len += n; }
-    const int long_min = c <= 2 ? kListShared : kListLong;
-    const bool is_long = lane < c && len >= long_min;                    // the long rows' members come behind the others'
-    const int n_short = is_long ? 0 : len, upto = scan64(n_short), all_short = __builtin_amdgcn_readlane(upto, 63);
-    const int n_long = is_long ? len : 0, upto_long = scan64(n_long);
-    const int start = is_long ? all_short + upto_long - len : upto - n_short;
-    __syncthreads();                                                     // every wavefront has read the counts
-    cnt[lane] = start + mine_from;
-    __builtin_amdgcn_wave_barrier();
-    for (int e = 0; e < n_own; e += 64) {                                // uniform
-        const bool mine = e + lane < n_own;
-        const uint32_t v = mine ? own[e + lane] : 0u, key = v >> 16;
-        const uint64_t peers = peers_of(key, mine);
-        if (mine) {
-            const int rank = __builtin_popcountll(peers & below);
-            const int at = cnt[key];                                     // read by all peers before the write below
-            u.list[at + rank] = (uint16_t)v;
-            if (rank == 0) cnt[key] = at + __builtin_popcountll(peers);
+    if (count) {                                                         // uniform
+#pragma unroll 4
+        for (int i = 0; i < nb; ++i) {
+            const uint32_t id = my[i * 64];
+            if (id < (uint32_t)K) atomicAdd(&members[id], 1u);           // (0xffff: no token)
         }
-        __builtin_amdgcn_wave_barrier();
+        __syncthreads();
+        int n[kRowsPerThread];
+#pragma unroll
+        for (int k = 0; k < kRowsPerThread; ++k) n[k] = k * kAsgThreads + tid < K ? (int)members[k * kAsgThreads + tid] : 0;
+        deal_rows(n, K, weight, g, groups, deal);
+        __syncthreads();
     }
-    __syncthreads();
-
-    // ---- the rows' sums: lane = channels 2 lane, 2 lane + 1; a member is one load of the wavefront.  (Four rows at a
-    // time, 16 lanes with 8 channels each, takes a quarter of the loads and 6.1 instead of 4.4 us on 24 units x 4680 tokens, K =
-    // 256: rows of different lengths wait for each other, and the vector ALU is what a SIMD's two wavefronts share.)
-    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(x), 0, (int)((uint32_t)(n_tokens - 1) * row_bytes + kHeadDim * 2), 0x00020000);
-    // members m .. m + kRowsAhead - 1 of the list; those behind the end lie beyond the buffer and read as zero
-    auto request = [&](int m, int end, uint32_t (&row)[kRowsAhead]) {
-        const int i = m + (lane & (kRowsAhead - 1));
-        const int at = i < end ? (int)(u.list[i] * row_bytes) : (int)0x80000000u;
-#pragma unroll
-        for (int k = 0; k < kRowsAhead; ++k)
-            row[k] = __builtin_amdgcn_raw_buffer_load_b32(xr, lane * 4 + __builtin_amdgcn_readlane(at, k), 0, 0);
-    };
-    auto store_sums = [&](int j, double s0, double s1) {
-        u.sums[j * kHeadDim + 2 * lane] = s0; u.sums[j * kHeadDim + 2 * lane + 1] = s1;
-    };
-    // Short lists, a wavefront each, members in token order; the longest first, dealt to and fro.  The next row's first
-    // members are requested while this one's are added.
-    {
-        const bool is_short = n_short > 0;
-        int rank = 0;
-        for (int j = 0; j < c; ++j) {                                    // uniform
-            const int o = __builtin_amdgcn_readlane(is_short ? len : -1, j);
-            rank += o > len || (o == len && j < lane);
+    int first, end;                                                      // uniform
+    dealt(deal, first, end);
+    for (int j0 = first; j0 < end; j0 += rows) {                         // uniform
+        const int c = end - j0 < rows ? end - j0 : rows;
+        if (j0 > first) {                                                    // (the lists of the rows before are where the ids were)
+            __syncthreads();
+            cnt[lane] = 0;
+            load_ids();
+            __syncthreads();
         }
-        if (is_short) cnt[rank] = lane;                                  // this wavefront's copy of the order
-        __builtin_amdgcn_wave_barrier();
-        const int order = cnt[lane];
-        const int rows = __builtin_popcountll(__ballot(is_short));
-        auto rank_of = [&](int i) { return 4 * i + (i & 1 ? 3 - w : w); };       // the wavefront's i-th row
-        uint32_t row[kRowsAhead], nxt[kRowsAhead];
-        int j_n = 0, from_n = 0, n_n = 0;
-        auto first = [&](int i) {
-            const int r = rank_of(i);
-            n_n = 0;
-            if (r < rows) {                                              // uniform
-                j_n = __builtin_amdgcn_readlane(order, r);
-                from_n = __builtin_amdgcn_readlane(start, j_n); n_n = __builtin_amdgcn_readlane(len, j_n);
-                request(from_n, from_n + n_n, nxt);
+        // ---- the members of these rows, a wavefront's quarter of the tokens at a time, in token order (no branches: what
+        // is no member goes to the place behind the last) ----
+        int n_own = 0;                                                       // uniform
+        for (int i0 = 0; i0 < nb; i0 += 4) {
+            uint32_t key[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int i = i0 + k < nb ? i0 + k : nb - 1;
+                key[k] = ((uint32_t)my[i * 64] | (i0 + k < nb ? 0u : 0xffffu)) - (uint32_t)j0;
             }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const bool mine = key[k] < (uint32_t)c;
+                const uint64_t m = __ballot(mine);
+                const int at = n_own + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                own[mine ? at : nb * 64] = (uint32_t)((w * nb + i0 + k) * 64 + lane) | key[k] << 16;
+                n_own += __builtin_popcountll(m);
+            }
+        }
+        // ---- sorted by row: lanes with the same row are ranked by lane number ----
+        auto peers_of = [&](uint32_t key, bool mine) {
+            uint64_t peers = __ballot(mine);
+            for (int b = 0; (c - 1) >> b; ++b) {                             // uniform
+                const uint64_t m = __ballot((key >> b) & 1u);
+                peers &= ((key >> b) & 1u) ? m : ~m;
+            }
+            return peers;
         };
-        first(0);
-        for (int i = 0; n_n > 0; ++i) {                                  // uniform
-            const int j = j_n, from = from_n, n = n_n;
+        const uint64_t below = (1ull << lane) - 1ull;
+        __builtin_amdgcn_wave_barrier();
+        for (int e = 0; e < n_own; e += 64) {                                // uniform
+            const bool mine = e + lane < n_own;
+            const uint32_t key = mine ? own[e + lane] >> 16 : 0u;
+            const uint64_t peers = peers_of(key, mine);
+            if (mine && !(peers & below)) atomicAdd(&cnt[key], __builtin_popcountll(peers));
+        }
+        __syncthreads();
+        // lane l: row l's members (len) and the first one's place in the list (start), the same in every wavefront
+        int len = 0, mine_from = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { const int n = u.cnt[r * 64 + lane]; if (r < w) mine_from += n; len += n; }
+        const int long_min = c <= 2 ? kListShared : kListLong;
+        const bool is_long = lane < c && len >= long_min;                    // the long rows' members come behind the others'
+        const int n_short = is_long ? 0 : len, upto = scan64(n_short), all_short = __builtin_amdgcn_readlane(upto, 63);
+        const int n_long = is_long ? len : 0, upto_long = scan64(n_long);
+        const int start = is_long ? all_short + upto_long - len : upto - n_short;
+        __syncthreads();                                                     // every wavefront has read the counts
+        cnt[lane] = start + mine_from;
+        __builtin_amdgcn_wave_barrier();
+        for (int e = 0; e < n_own; e += 64) {                                // uniform
+            const bool mine = e + lane < n_own;
+            const uint32_t v = mine ? own[e + lane] : 0u, key = v >> 16;
+            const uint64_t peers = peers_of(key, mine);
+            if (mine) {
+                const int rank = __builtin_popcountll(peers & below);
+                const int at = cnt[key];                                     // read by all peers before the write below
+                u.list[at + rank] = (uint16_t)v;
+                if (rank == 0) cnt[key] = at + __builtin_popcountll(peers);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();
+
+        // ---- the rows' sums: lane = channels 2 lane, 2 lane + 1; a member is one load of the wavefront.  (Four rows at a
+        // time, 16 lanes with 8 channels each, takes a quarter of the loads and 6.1 instead of 4.4 us on 24 units x 4680 tokens, K =
+        // 256: rows of different lengths wait for each other, and the vector ALU is what a SIMD's two wavefronts share.)
+        const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(x), 0, (int)((uint32_t)(n_tokens - 1) * row_bytes + kHeadDim * 2), 0x00020000);
+        // members m .. m + kRowsAhead - 1 of the list; those behind the end lie beyond the buffer and read as zero
+        auto request = [&](int m, int end, uint32_t (&row)[kRowsAhead]) {
+            const int i = m + (lane & (kRowsAhead - 1));
+            const int at = i < end ? (int)(u.list[i] * row_bytes) : (int)0x80000000u;
+#pragma unroll
+            for (int k = 0; k < kRowsAhead; ++k)
+                row[k] = __builtin_amdgcn_raw_buffer_load_b32(xr, lane * 4 + __builtin_amdgcn_readlane(at, k), 0, 0);
+        };
+        auto store_sums = [&](int j, double s0, double s1) {
+            u.sums[j * kHeadDim + 2 * lane] = s0; u.sums[j * kHeadDim + 2 * lane + 1] = s1;
+        };
+        // Short lists, a wavefront each, members in token order; the longest first, dealt to and fro.  The next row's first
+        // members are requested while this one's are added.
+        {
+            const bool is_short = n_short > 0;
+            int rank = 0;
+            for (int j = 0; j < c; ++j) {                                    // uniform
+                const int o = __builtin_amdgcn_readlane(is_short ? len : -1, j);
+                rank += o > len || (o == len && j < lane);
+            }
+            if (is_short) cnt[rank] = lane;                                  // this wavefront's copy of the order
+            __builtin_amdgcn_wave_barrier();
+            const int order = cnt[lane];
+            const int rows = __builtin_popcountll(__ballot(is_short));
+            auto rank_of = [&](int i) { return 4 * i + (i & 1 ? 3 - w : w); };       // the wavefront's i-th row
+            uint32_t row[kRowsAhead], nxt[kRowsAhead];
+            int j_n = 0, from_n = 0, n_n = 0;
+            auto first = [&](int i) {
+                const int r = rank_of(i);
+                n_n = 0;
+                if (r < rows) {                                              // uniform
+                    j_n = __builtin_amdgcn_readlane(order, r);
+                    from_n = __builtin_amdgcn_readlane(start, j_n); n_n = __builtin_amdgcn_readlane(len, j_n);
+                    request(from_n, from_n + n_n, nxt);
+                }
+            };
+            first(0);
+            for (int i = 0; n_n > 0; ++i) {                                  // uniform
+                const int j = j_n, from = from_n, n = n_n;
+                double s0 = 0.0, s1 = 0.0;
+                for (int m = 0; m < n; m += kRowsAhead) {                    // uniform
+#pragma unroll
+                    for (int k = 0; k < kRowsAhead; ++k) row[k] = nxt[k];
+                    if (m + kRowsAhead < n) request(from + m + kRowsAhead, from + n, nxt); else first(i + 1);
+#pragma unroll
+                    for (int k = 0; k < kRowsAhead; ++k) {                   // (a row that is not there adds +0)
+                        if (k == kRowsAhead / 2 && m + k >= n) break;        // uniform
+                        s0 += (double)bf16_lo(row[k]); s1 += (double)bf16_hi(row[k]);
+                    }
+                }
+                store_sums(j, s0, s1);
+            }
+        }
+        // Long lists, one after the other, by all wavefronts: partial sums, exact unless the test on the exponents fails (see
+        // qvg_kmeans.hip)
+        for (uint64_t longs = __ballot(is_long); longs; longs &= longs - 1) {                               // uniform
+            const int j = __builtin_ctzll(longs), from = __builtin_amdgcn_readlane(start, j), n = __builtin_amdgcn_readlane(len, j);
+            const int m0 = from + n * w / 4, end = from + n * (w + 1) / 4;   // (n >= 32: none is empty)
             double s0 = 0.0, s1 = 0.0;
-            for (int m = 0; m < n; m += kRowsAhead) {                    // uniform
+            uint32_t mx = 0u, mn = ~0u;
+            uint32_t row[kRowsAhead], nxt[kRowsAhead];
+            request(m0, end, nxt);
+            for (int m = m0; m < end; m += kRowsAhead) {                     // uniform
 #pragma unroll
                 for (int k = 0; k < kRowsAhead; ++k) row[k] = nxt[k];
-                if (m + kRowsAhead < n) request(from + m + kRowsAhead, from + n, nxt); else first(i + 1);
+                if (m + kRowsAhead < end) request(m + kRowsAhead, end, nxt);
 #pragma unroll
-                for (int k = 0; k < kRowsAhead; ++k) {                   // (a row that is not there adds +0)
-                    if (k == kRowsAhead / 2 && m + k >= n) break;        // uniform
-                    s0 += (double)bf16_lo(row[k]); s1 += (double)bf16_hi(row[k]);
-                }
+                for (int k = 0; k < kRowsAhead; ++k) add_pair(row[k], s0, s1, mx, mn);
             }
-            store_sums(j, s0, s1);
-        }
-    }
-    // Long lists, one after the other, by all wavefronts: partial sums, exact unless the test on the exponents fails (see
-    // qvg_kmeans.hip)
-    for (uint64_t longs = __ballot(is_long); longs; longs &= longs - 1) {                               // uniform
-        const int j = __builtin_ctzll(longs), from = __builtin_amdgcn_readlane(start, j), n = __builtin_amdgcn_readlane(len, j);
-        const int m0 = from + n * w / 4, end = from + n * (w + 1) / 4;   // (n >= 32: none is empty)
-        double s0 = 0.0, s1 = 0.0;
-        uint32_t mx = 0u, mn = ~0u;
-        uint32_t row[kRowsAhead], nxt[kRowsAhead];
-        request(m0, end, nxt);
-        for (int m = m0; m < end; m += kRowsAhead) {                     // uniform
+            u.part[w][lane][0] = s0; u.part[w][lane][1] = s1;
+            u.pmx[w][lane] = mx; u.pmn[w][lane] = mn;
+            __syncthreads();
+            if (w == (j & 3)) {
+                s0 = 0.0; s1 = 0.0; mx = 0u; mn = ~0u;
 #pragma unroll
-            for (int k = 0; k < kRowsAhead; ++k) row[k] = nxt[k];
-            if (m + kRowsAhead < end) request(m + kRowsAhead, end, nxt);
+                for (int r = 0; r < 4; ++r) {
+                    s0 += u.part[r][lane][0]; s1 += u.part[r][lane][1];
+                    mx = pk_max_u16(mx, u.pmx[r][lane]); mn = pk_min_u16(mn, u.pmn[r][lane]);
+                }
+                if (!__all(mean_exact(mx, mn, 32 - __builtin_clz(n - 1)))) {
+                    s0 = 0.0; s1 = 0.0;
+                    for (int m = from; m < from + n; m += kRowsAhead) {
+                        request(m, from + n, row);
 #pragma unroll
-            for (int k = 0; k < kRowsAhead; ++k) add_pair(row[k], s0, s1, mx, mn);
+                        for (int k = 0; k < kRowsAhead; ++k) { s0 += (double)bf16_lo(row[k]); s1 += (double)bf16_hi(row[k]); }
+                    }
+                }
+                store_sums(j, s0, s1);
+            }
+            __syncthreads();                      // the partial results are overwritten by the next list
         }
-        u.part[w][lane][0] = s0; u.part[w][lane][1] = s1;
-        u.pmx[w][lane] = mx; u.pmn[w][lane] = mn;
+        // ---- the rows: means and norms, 16 lanes each, 8 channels per lane ----
+        if (w == 0) cnt[lane] = len;
         __syncthreads();
-        if (w == (j & 3)) {
-            s0 = 0.0; s1 = 0.0; mx = 0u; mn = ~0u;
+        for (int j = tid >> 4; j < c; j += kAsgThreads / 16) {
+            const int c8 = tid & 15, n = u.cnt[j];
+            uint4 v;
+            if (n > 0) {
+                double s[8];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                s0 += u.part[r][lane][0]; s1 += u.part[r][lane][1];
-                mx = pk_max_u16(mx, u.pmx[r][lane]); mn = pk_min_u16(mn, u.pmn[r][lane]);
+                for (int e = 0; e < 8; ++e) s[e] = u.sums[j * kHeadDim + c8 * 8 + e];
+                v = mean_row(s, n);
+            } else {
+                v = prev.load16((uint32_t)(j0 + j) * (kHeadDim * 2) + c8 * 16);      // an empty group keeps its centroid
             }
-            if (!__all(mean_exact(mx, mn, 32 - __builtin_clz(n - 1)))) {
-                s0 = 0.0; s1 = 0.0;
-                for (int m = from; m < from + n; m += kRowsAhead) {
-                    request(m, from + n, row);
-#pragma unroll
-                    for (int k = 0; k < kRowsAhead; ++k) { s0 += (double)bf16_lo(row[k]); s1 += (double)bf16_hi(row[k]); }
-                }
-            }
-            store_sums(j, s0, s1);
+            const double q = row_sumsq(v);
+            table.store16((uint32_t)(j0 + j) * (kHeadDim * 2) + c8 * 16, v);
+            uint2 nh = split_half_norm(q);
+            nh.y |= (uint32_t)n << 16;                                       // and the members
+            if (c8 == 0) norms.store8((uint32_t)(j0 + j) * 8u, nh);
         }
-        __syncthreads();                      // the partial results are overwritten by the next list
-    }
-    // ---- the rows: means and norms, 16 lanes each, 8 channels per lane ----
-    if (w == 0) cnt[lane] = len;
-    __syncthreads();
-    for (int j = tid >> 4; j < c; j += kAsgThreads / 16) {
-        const int c8 = tid & 15, n = u.cnt[j];
-        uint4 v;
-        if (n > 0) {
-            double s[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) s[e] = u.sums[j * kHeadDim + c8 * 8 + e];
-            v = mean_row(s, n);
-        } else {
-            v = prev.load16((uint32_t)(j0 + j) * (kHeadDim * 2) + c8 * 16);      // an empty group keeps its centroid
-        }
-        const double q = row_sumsq(v);
-        table.store16((uint32_t)(j0 + j) * (kHeadDim * 2) + c8 * 16, v);
-        if (c8 == 0) norms.store8((uint32_t)(j0 + j) * 8u, split_half_norm(q));
     }
 }
 
@@ -425,19 +501,22 @@ __device__ __forceinline__ void load_tokens(int h, int stage, int blk, uint4 (&x
 }
 
 // The current table (the stage's start table, or the update's) into LDS, rows and norms, eight pieces in flight per
-// thread.  out: the table's way to the caller, or nullptr.  smax (zero before): the largest norm.
-__device__ __forceinline__ void stage_table(int h, int stage, bool start, bool out, unsigned char *smem, uint32_t *smax) {
+// thread.  out: the table goes to the caller.  smax (zero before): the largest norm.
+// Deals the rows of the next update among the unit's workgroups.
+__device__ __forceinline__ void stage_table(int h, int stage, bool start, bool out, int g, int groups, unsigned char *smem, DealLds &deal, uint32_t *smax) {
     const LloydArgs &a = args_again();
     const int tid = thread_id(), K = a.K, Kpad = k_padded(K);
     bf16_t *lc = reinterpret_cast<bf16_t *>(smem);                       // [Kpad][kCPitch]
     const Shared src = start ? init_of(a, h, stage) : table_of(a, h);
     const Shared srcn = start ? Shared(a.init_norms + ((int64_t)h * a.S + stage) * Kpad, (uint32_t)K * 8) : norms_of(a, h);
     bf16_t *dst = a.cent_out + (int64_t)h * a.cent_out_stride + (int64_t)stage * K * kHeadDim;
-    uint2 nh[kMaxClusters / kAsgThreads];
+    uint2 nh[kRowsPerThread];
+    int members[kRowsPerThread];                                         // (a start table: none)
 #pragma unroll
     for (int k = 0; k < kMaxClusters / kAsgThreads; ++k) {
         const int row = tid + k * kAsgThreads;
         nh[k] = srcn.load8((uint32_t)row * 8u);
+        members[k] = (int)(nh[k].y >> 16); nh[k].y &= 0xffffu;
         if (row >= K) nh[k] = make_uint2(__float_as_uint(-3.0e38f) >> 16, 0u);     // rows K.. never win
     }
     constexpr int kBatch = 8;
@@ -468,12 +547,9 @@ __device__ __forceinline__ void stage_table(int h, int stage, bool start, bool o
             if ((tid & 63) == 0) atomicMax(smax, norm_order(up));
         }
     }
+    if (stage > 0) deal_rows(members, K, a.row_weight, g, groups, deal); // uniform
+    else { if (tid < kMaxClusters / 64) { deal.below[tid] = tid ? 0 : K * g / groups; deal.upto[tid] = tid ? 0 : K * (g + 1) / groups; } }
     __syncthreads();
-}
-
-__host__ __device__ __forceinline__ int rows_at_once(int K, int groups) {
-    const int c = (K + groups - 1) / groups;
-    return c < kLloydRows ? c : kLloydRows;
 }
 
 // blockIdx.x -> (unit, workgroup of the unit).  With eight units or more a unit's workgroups are 8 apart, on one
@@ -485,6 +561,7 @@ void lloyd_kernel(LloydArgs a0) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t smax;
     __shared__ int number, members;
+    __shared__ DealLds deal;
     const int nb = a0.n_blocks;
     int h, g0;
     if (a0.by_xcd) { const int i = (int)(blockIdx.x >> 3); h = (int)(blockIdx.x & 7u) + 8 * (i / a0.groups); g0 = i % a0.groups; }
@@ -518,7 +595,7 @@ begin:
     for (int stage = 0; stage < a0.S; ++stage) {
         for (int it = 0; ; ++it) {
             const bool last = it == args_again().iters;                  // uniform: the stage's final assignment
-            stage_table(h, stage, it == 0, last && g_now() == 0, smem, &smax);
+            stage_table(h, stage, it == 0, last && g_now() == 0, g_now(), groups_now(), smem, deal, &smax);
             // ---- this workgroup's tokens ----
             for (int blk = g_now(), groups = groups_now(); blk < nb; blk += groups) {
                 if (groups < nb) load_tokens(h, stage, blk, xa);
@@ -616,14 +693,10 @@ begin:
             if (threadIdx.x == 0) smax = 0u;
             {
                 const LloydArgs &a = args_again();
-                const int K = a.K, groups = groups_now(), g = g_now(), c_max = (K + groups - 1) / groups, j0 = g * c_max, end = j0 + c_max < K ? j0 + c_max : K;
-                const int rows = rows_at_once(K, a.groups);              // (the launch's: what its LDS holds)
-                for (int j = j0; j < end; j += rows) {                   // uniform
-                    if (j > j0) __syncthreads();                         // the lists of the rows before are no longer read
-                    update_rows(input_of(a, h, stage), stage == 0 ? (uint32_t)a.stride_token * 2u : kHeadDim * 2u, a.n_tokens, nb, j,
-                                end - j < rows ? end - j : rows, ids_of(a, h, __builtin_amdgcn_readfirstlane(lds_apart) != 0), it == 0 ? init_of(a, h, stage) : table_of(a, h),
-                                table_of(a, h), norms_of(a, h), smem);
-                }
+                update_rows(input_of(a, h, stage), stage == 0 ? (uint32_t)a.stride_token * 2u : kHeadDim * 2u, a.n_tokens, nb, a.K, g_now(), groups_now(),
+                            a.rows, a.row_weight, stage > 0 && it == 0,
+                            ids_of(a, h, __builtin_amdgcn_readfirstlane(lds_apart) != 0), it == 0 ? init_of(a, h, stage) : table_of(a, h),
+                            table_of(a, h), norms_of(a, h), smem, deal);
             }
             meet_unit(false);
         }
@@ -637,10 +710,26 @@ begin:
     }
 }
 
-static size_t lloyd_smem_bytes(int K, int groups, int nb) {
+// A row costs what its members cost and as much as this many.
+static int row_weight(int K, int nb) {
+    const int mean = nb * kAsgThreads / K;
+    return mean < 8 ? 8 : mean > 16 ? 16 : mean;
+}
+static size_t assign_bytes(int K) {
     const int Kpad = k_padded(K);
-    const size_t assign = (size_t)Kpad * kCPitch * 2 + (size_t)kAsgWaves * (kHeadDim * 2 + Kpad * sizeof(float));
-    const size_t update = UpdateLds::bytes(nb, rows_at_once(K, groups));
+    return (size_t)Kpad * kCPitch * 2 + (size_t)kAsgWaves * (kHeadDim * 2 + Kpad * sizeof(float));
+}
+// Rows that a workgroup makes at a time: as many as can have their middle in one share of the weight, where the LDS holds
+// them beside a second workgroup's; never fewer than an equal share.
+static int rows_at_once(int K, int groups, int nb) {
+    const size_t room = assign_bytes(K) > 65536 ? assign_bytes(K) : 65536;
+    const int share = (nb * kAsgThreads / row_weight(K, nb) + K) / groups + 2, fit = (int)((room - UpdateLds::bytes(nb, 0)) / 1024);
+    const int equal = (K + groups - 1) / groups, most = share < fit ? share : fit;
+    const int c = most > equal ? most : equal, rows = c < K ? c : K;
+    return rows < kLloydRows ? rows : kLloydRows;
+}
+static size_t lloyd_smem_bytes(int K, int rows, int nb) {
+    const size_t assign = assign_bytes(K), update = UpdateLds::bytes(nb, rows);
     return assign > update ? assign : update;
 }
 
@@ -662,7 +751,9 @@ static hipError_t launch_lloyd_t(LloydArgs a, hipStream_t s) {
     const int Kpad = k_padded(a.K), S = a.S;
     static LdsHighWater lds_limit = {};
     const void *kernel = reinterpret_cast<const void *>(&lloyd_kernel<B_, FUSED, T_>);
-    const size_t smem = lloyd_smem_bytes(a.K, a.groups, a.n_blocks);
+    a.row_weight = row_weight(a.K, a.n_blocks);
+    a.rows = rows_at_once(a.K, a.groups, a.n_blocks);
+    const size_t smem = lloyd_smem_bytes(a.K, a.rows, a.n_blocks);
     hipError_t e = ensure_dynamic_lds(kernel, smem, lds_limit);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(lloyd_prepare_kernel, dim3((unsigned)((a.K + 15) / 16), (unsigned)S, (unsigned)a.H), dim3(kAsgThreads), 0, s,
