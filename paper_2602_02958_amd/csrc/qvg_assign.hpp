@@ -9,6 +9,50 @@ namespace qvg {
 constexpr int kCPitch = 136;                    // bf16 elements per LDS centroid row (272 B): 128 + (hi, mid, lo of -||c||^2/2) + 5 zeros
 constexpr int kScanPairs = 24;                  // candidates up to which fp64 distances are taken two at a time
 
+// Rows of zeros but the first are taken out of a staged table: of equal rows only the lowest can be a token's nearest.
+// The residuals of clusters of one token are zero, so a later smoothing stage has a dozen such rows among its centroids, and
+// every token near zero had as many candidates: each a scan of the table and their fp64 distances, one after the
+// other (K = 256, four stages: 24 units x 4680 tokens, in one launch, 495 -> 455 us; 6 x 1560 814 -> 297; 80 x 4680, in launches of their
+// own, 1504 -> 1294).
+__device__ __forceinline__ uint2 never_wins() { return make_uint2(__float_as_uint(-3.0e38f) >> 16, 0u); }      // a norm's split
+// zero: an LDS word, kMaxClusters while no row with a norm of zero is known
+__device__ __forceinline__ void note_zero_norm(uint2 nh, int row, int *zero) {
+    if (!((nh.x | nh.y) & 0x7fff7fffu)) atomicMin(zero, row);
+}
+// By the whole workgroup, behind a barrier after the table, its norms nh (of rows t and t + 256, thread t) and the notes.  A barrier
+// precedes the table's use.
+__device__ __forceinline__ void drop_zero_rows(bf16_t *lc, int K, const uint2 (&nh)[kMaxClusters / kAsgThreads], int *zero) {
+    if (*zero >= K) return;                                              // uniform
+    const int tid = (int)threadIdx.x;
+    bool is_zero[kMaxClusters / kAsgThreads];
+#pragma unroll
+    for (int k = 0; k < kMaxClusters / kAsgThreads; ++k) {
+        const int row = tid + k * kAsgThreads;
+        is_zero[k] = row < K && !((nh[k].x | nh[k].y) & 0x7fff7fffu);
+        if (!is_zero[k]) continue;                                       // (the norm of a tiny row is zero as well)
+        uint32_t any = 0u;
+        for (int c16 = 0; c16 < kHeadDim / 8; ++c16) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(lc + row * kCPitch + c16 * 8);
+            any |= v.x | v.y | v.z | v.w;
+        }
+        is_zero[k] = !(any & 0x7fff7fffu);
+    }
+    __syncthreads();
+    if (tid == 0) *zero = kMaxClusters;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kMaxClusters / kAsgThreads; ++k) if (is_zero[k]) atomicMin(zero, tid + k * kAsgThreads);
+    __syncthreads();
+    const int keep = *zero;
+    const uint2 never = never_wins();
+#pragma unroll
+    for (int k = 0; k < kMaxClusters / kAsgThreads; ++k)
+        if (is_zero[k] && tid + k * kAsgThreads != keep)
+            *reinterpret_cast<uint4 *>(lc + (tid + k * kAsgThreads) * kCPitch + kHeadDim) = make_uint4(never.x, never.y, 0u, 0u);
+    __syncthreads();
+    if (tid == 0) *zero = kMaxClusters;                                  // (for the next table)
+}
+
 __device__ __forceinline__ void insert3(float v, int idx, float &b1, float &b2, float &b3,
                                         int &i1, int &i2) {
     if (v > b1) { b3 = b2; b2 = b1; i2 = i1; b1 = v; i1 = idx; }

@@ -74,13 +74,14 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
     // -||c||^2 / 2; rows K..Kpad-1 get a huge negative value so that they never win.  The largest
     // ||c||^2 of the unit (one ulp up) is needed for the error band of the certification.
     __shared__ uint32_t smax;
-    if (tid == 0) smax = 0u;
+    __shared__ int zero_row;
+    if (tid == 0) { smax = 0u; zero_row = kMaxClusters; }
     const bf16_t *cg = a.cent + (int64_t)h * a.cent_stride;
     uint2 nh[kMaxClusters / kAsgThreads];
 #pragma unroll
     for (int u = 0; u < kMaxClusters / kAsgThreads; ++u) {
         const int row = tid + u * kAsgThreads;
-        nh[u] = make_uint2(__float_as_uint(-3.0e38f) >> 16, 0u);
+        nh[u] = never_wins();
         if (row < K && a.nh3) nh[u] = a.nh3[(int64_t)h * a.nh3_stride + row];
     }
     const int64_t blk0 = (int64_t)blockIdx.y * tiles_per_wave * (kAsgWaves * kAsgTile);
@@ -138,7 +139,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
         const int c16 = tid & 15;
         for (int row = tid >> 4; row < Kpad; row += kAsgThreads / 16) {  // 16 lanes per row, sums as in half_norm_kernel
             const double sq = row_sumsq(*reinterpret_cast<const uint4 *>(lc + row * kCPitch + c16 * 8));
-            if (c16 == 0) up = fmaxf(up, place_norm(row, row < K ? split_half_norm(sq) : make_uint2(__float_as_uint(-3.0e38f) >> 16, 0u)));
+            if (c16 == 0) up = fmaxf(up, place_norm(row, row < K ? split_half_norm(sq) : never_wins()));
         }
 #pragma unroll
         for (int off = 32; off >= 16; off >>= 1) up = fmaxf(up, __shfl_xor(up, off, 64));
@@ -148,7 +149,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
         for (int u = 0; u < kMaxClusters / kAsgThreads; ++u) {
             const int row = tid + u * kAsgThreads;
             float up = 0.0f;
-            if (row < Kpad) up = place_norm(row, nh[u]);
+            if (row < Kpad) { up = place_norm(row, nh[u]); if (a.ids_off > 0) note_zero_norm(nh[u], row, &zero_row); }
             if (u * kAsgThreads < Kpad) {                               // uniform
 #pragma unroll
                 for (int off = 32; off >= 1; off >>= 1) up = fmaxf(up, __shfl_xor(up, off, 64));
@@ -157,6 +158,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
         }
     }
     __syncthreads();
+    if (a.ids_off > 0 && a.nh3) drop_zero_rows(lc, K, nh, &zero_row);   // uniform: a later smoothing stage
     const float cmax = __uint_as_float(smax);
     bf16_t *scr = lscr + wave * kHeadDim;
     float *sscr = lsscr + wave * Kpad;

@@ -201,6 +201,7 @@ __device__ __forceinline__ int thread_id() {
 struct DealLds {
     int sums[kMaxClusters / 64];   // weights of 64 rows
     int below[kMaxClusters / 64], upto[kMaxClusters / 64];               // of 64 rows: those before this workgroup's, and with them
+    int zero;                      // a row whose norm is zero, kMaxClusters: none
 };
 constexpr int kRowsPerThread = kMaxClusters / kAsgThreads;
 
@@ -502,7 +503,7 @@ __device__ __forceinline__ void load_tokens(int h, int stage, int blk, uint4 (&x
 
 // The current table (the stage's start table, or the update's) into LDS, rows and norms, eight pieces in flight per
 // thread.  out: the table goes to the caller.  smax (zero before): the largest norm.
-// Deals the rows of the next update among the unit's workgroups.
+// Deals the rows of the next update among the unit's workgroups.  deal.zero is kMaxClusters before and after.
 __device__ __forceinline__ void stage_table(int h, int stage, bool start, bool out, int g, int groups, unsigned char *smem, DealLds &deal, uint32_t *smax) {
     const LloydArgs &a = args_again();
     const int tid = thread_id(), K = a.K, Kpad = k_padded(K);
@@ -517,7 +518,7 @@ __device__ __forceinline__ void stage_table(int h, int stage, bool start, bool o
         const int row = tid + k * kAsgThreads;
         nh[k] = srcn.load8((uint32_t)row * 8u);
         members[k] = (int)(nh[k].y >> 16); nh[k].y &= 0xffffu;
-        if (row >= K) nh[k] = make_uint2(__float_as_uint(-3.0e38f) >> 16, 0u);     // rows K.. never win
+        if (row >= K) nh[k] = never_wins();            // rows K..
     }
     constexpr int kBatch = 8;
     for (int i0 = tid; i0 < Kpad * 16; i0 += kAsgThreads * kBatch) {
@@ -539,7 +540,10 @@ __device__ __forceinline__ void stage_table(int h, int stage, bool start, bool o
         float up = 0.0f;
         if (row < Kpad) {
             *reinterpret_cast<uint4 *>(lc + row * kCPitch + kHeadDim) = make_uint4(nh[k].x, nh[k].y, 0u, 0u);
-            if (row < K) up = norm_bound(nh[k]);
+            if (row < K) {
+                up = norm_bound(nh[k]);
+                if (stage > 0) note_zero_norm(nh[k], row, &deal.zero);
+            }
         }
         if (k * kAsgThreads < Kpad) {                                    // uniform
 #pragma unroll
@@ -550,6 +554,7 @@ __device__ __forceinline__ void stage_table(int h, int stage, bool start, bool o
     if (stage > 0) deal_rows(members, K, a.row_weight, g, groups, deal); // uniform
     else { if (tid < kMaxClusters / 64) { deal.below[tid] = tid ? 0 : K * g / groups; deal.upto[tid] = tid ? 0 : K * (g + 1) / groups; } }
     __syncthreads();
+    if (stage > 0) drop_zero_rows(lc, K, nh, &deal.zero);                // uniform
 }
 
 // blockIdx.x -> (unit, workgroup of the unit).  With eight units or more a unit's workgroups are 8 apart, on one
@@ -569,7 +574,7 @@ void lloyd_kernel(LloydArgs a0) {
     if (h >= a0.H) return;                                               // uniform
     // What a team changes waits in LDS and is read anew where a phase begins, as the arguments are.
     __shared__ int lds_groups, lds_g, lds_apart;                         // members, this one's number, a closed team
-    if (threadIdx.x == 0) { lds_groups = a0.groups; lds_g = g0; lds_apart = 0; }
+    if (threadIdx.x == 0) { lds_groups = a0.groups; lds_g = g0; lds_apart = 0; deal.zero = kMaxClusters; }
     __syncthreads();
     auto groups_now = [&] { return __builtin_amdgcn_readfirstlane(lds_groups); };
     auto g_now = [&] { return __builtin_amdgcn_readfirstlane(lds_g); };

@@ -1,5 +1,5 @@
-"""The one-launch encoder's stages behind the first: rows dealt to a unit's workgroups by their members (clusters that hold
-most of the tokens next to empty ones, more rows for a workgroup than it makes at a time), and tables with several rows of
+"""The encoder's stages behind the first: in one launch, rows dealt to a unit's workgroups by their members (clusters that hold
+most of the tokens next to empty ones, more rows for a workgroup than it makes at a time); tables with several rows of
 zeros, of which only the first can be nearest (with rows beside them whose norm is zero in fp32 though they are not).
 Stored arrays against the oracle, bit for bit."""
 import numpy as np
@@ -47,6 +47,8 @@ def _inputs(H, N, K, S, zeros, seed):
     (2, 700, 512, 64, 2, 1),
     (1, 15, 12, 64, 2, 2),             # one workgroup
     (27, 3000, 64, 64, 2, 1),          # a full chip, units of twelve blocks
+    (2, 1300, 256, 16, 3, 0),          # launches of their own
+    (1, 6300, 64, 64, 2, 1),
 ])
 def test_stages_with_unequal_clusters(H, N, K, Bg, S, I, zeros):
     x, init = _inputs(H, N, K, S, zeros, 1000 + N + K)
