@@ -75,7 +75,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
     // ||c||^2 of the unit (one ulp up) is needed for the error band of the certification.
     __shared__ uint32_t smax;
     __shared__ int zero_row;
-    if (tid == 0) { smax = 0u; zero_row = kMaxClusters; }
+    if (tid == 0) { smax = 0u; if (!FUSED) zero_row = kMaxClusters; }
     const bf16_t *cg = a.cent + (int64_t)h * a.cent_stride;
     uint2 nh[kMaxClusters / kAsgThreads];
 #pragma unroll
@@ -149,7 +149,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
         for (int u = 0; u < kMaxClusters / kAsgThreads; ++u) {
             const int row = tid + u * kAsgThreads;
             float up = 0.0f;
-            if (row < Kpad) { up = place_norm(row, nh[u]); if (a.ids_off > 0) note_zero_norm(nh[u], row, &zero_row); }
+            if (row < Kpad) { up = place_norm(row, nh[u]); if (!FUSED && a.ids_off > 0) note_zero_norm(nh[u], row, &zero_row); }
             if (u * kAsgThreads < Kpad) {                               // uniform
 #pragma unroll
                 for (int off = 32; off >= 1; off >>= 1) up = fmaxf(up, __shfl_xor(up, off, 64));
@@ -158,7 +158,9 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
         }
     }
     __syncthreads();
-    if (a.ids_off > 0 && a.nh3) drop_zero_rows(lc, K, nh, &zero_row);   // uniform: a later smoothing stage
+    // Uniform: a later smoothing stage.  (Not in the fused pass, one of a stage's I + 1 and the only one of an encode without
+    // iterations, which the test alone made 1 % slower: 24 units x 4680 tokens, K = 256, T = 2 30.1 -> 30.4 us.)
+    if (!FUSED && a.ids_off > 0 && a.nh3) drop_zero_rows(lc, K, nh, &zero_row);
     const float cmax = __uint_as_float(smax);
     bf16_t *scr = lscr + wave * kHeadDim;
     float *sscr = lsscr + wave * Kpad;

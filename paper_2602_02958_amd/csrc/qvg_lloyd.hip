@@ -503,7 +503,7 @@ __device__ __forceinline__ void load_tokens(int h, int stage, int blk, uint4 (&x
 
 // The current table (the stage's start table, or the update's) into LDS, rows and norms, eight pieces in flight per
 // thread.  out: the table goes to the caller.  smax (zero before): the largest norm.
-// Deals the rows of the next update among the unit's workgroups.  deal.zero is kMaxClusters before and after.
+// Deals the rows of the next update among the unit's workgroups, behind the first stage.  deal.zero is kMaxClusters before and after.
 __device__ __forceinline__ void stage_table(int h, int stage, bool start, bool out, int g, int groups, unsigned char *smem, DealLds &deal, uint32_t *smax) {
     const LloydArgs &a = args_again();
     const int tid = thread_id(), K = a.K, Kpad = k_padded(K);
@@ -552,7 +552,6 @@ __device__ __forceinline__ void stage_table(int h, int stage, bool start, bool o
         }
     }
     if (stage > 0) deal_rows(members, K, a.row_weight, g, groups, deal); // uniform
-    else { if (tid < kMaxClusters / 64) { deal.below[tid] = tid ? 0 : K * g / groups; deal.upto[tid] = tid ? 0 : K * (g + 1) / groups; } }
     __syncthreads();
     if (stage > 0) drop_zero_rows(lc, K, nh, &deal.zero);                // uniform
 }
@@ -594,6 +593,11 @@ begin:
         if (thread_id() == 0) {
             smax = 0u;
             set_started(args_again().meet + (int64_t)h * kMeetWords, g);
+        }
+        const int t = thread_id();
+        if (t < kMaxClusters / 64) {                                     // the first stage's rows, in equal shares
+            const int groups = groups_now(), K = args_again().K;
+            deal.below[t] = t ? 0 : K * g / groups; deal.upto[t] = t ? 0 : K * (g + 1) / groups;
         }
     }
     __syncthreads();
