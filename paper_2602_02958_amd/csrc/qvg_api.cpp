@@ -150,9 +150,10 @@ int encode_call(const qvg_params *p, int64_t n_tokens, const void *x, int64_t st
         l.n_tokens = (int)n_tokens; l.init = static_cast<const bf16_t *>(init_centroids);
         l.H = p->n_heads; l.K = p->n_clusters; l.B = p->group_size; l.T = p->n_stages; l.S = S; l.iters = I;
         l.cent_out = static_cast<bf16_t *>(centroids_out); l.cent_out_stride = cent_out_stride_head;
-        l.ids = ids_out; l.codes = codes_out; l.scales = static_cast<f16_t *>(scales_out);
+        l.ids = ids_out; l.codes = codes_out; l.scales = scales_out;
         l.codes_stride = out_stride_head_tokens * p->n_stages * (kHeadDim * p->bits / 8);
-        l.out_stride = out_stride_head_tokens; l.id_wide = id_wide(p); l.fused = fmt == 0;
+        l.out_stride = out_stride_head_tokens; l.id_wide = id_wide(p);
+        l.fmt = fmt; l.fused = lloyd_fuses(fmt, p->group_size, p->n_stages);
         l.init_norms = reinterpret_cast<const uint2 *>(ws + w.init_norms);
         l.meet = reinterpret_cast<uint32_t *>(ws + w.cent[1]);           // 256 bytes per unit; a table has at least one row
         l.ids_x = reinterpret_cast<uint16_t *>(ws + w.perm);
@@ -161,7 +162,7 @@ int encode_call(const qvg_params *p, int64_t n_tokens, const void *x, int64_t st
         l.n_blocks = (int)((n_tokens + 255) / 256); l.groups = groups;
         l.wanted = wanted > 0 ? wanted : groups;
         if (launch_lloyd(l, s) != hipSuccess) return QVG_ERR_LAUNCH;
-        if (fmt == 0) return QVG_OK;
+        if (l.fused) return QVG_OK;
         QuantArgs q{};
         q.x = l.x; q.stride_head = stride_head; q.stride_token = stride_token;
         if (S > 1) { q.x = l.resid[S & 1]; q.stride_head = n_tokens * kHeadDim; q.stride_token = kHeadDim; }   // stage S - 2 left it

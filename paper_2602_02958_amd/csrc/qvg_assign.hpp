@@ -164,6 +164,35 @@ __device__ __forceinline__ void quantize_token(float *r, int T, bool valid, int 
     }
 }
 
+// The same for one round with E4M3 scales, 2- or 4-bit levels (the rules of qvg_quant.hip).  B_ <= 64.
+template <int B_, int BITS>
+__device__ __forceinline__ void quantize_token_e4m3(const float *r, bool valid, int half, uint8_t *codes_tok, uint8_t *scales_tok) {
+    constexpr int GL = 64 / B_;                      // groups held by this lane
+    constexpr float qmax = BITS == 4 ? 7.0f : 1.0f;
+    uint32_t word[2 * BITS] = {}, scales = 0u;
+#pragma unroll
+    for (int g = 0; g < GL; ++g) {
+        const float *rg = r + g * B_;
+        float m = 0.0f;
+#pragma unroll
+        for (int i = 0; i < B_; i += 2) m = fmaxf(fmaxf(m, fabsf(rg[i])), fabsf(rg[i + 1]));
+        const uint32_t sbits = f32_to_e4m3_bits(m / qmax);
+        const float sf = e4m3_bits_to_f32(sbits), inv = (sf == 0.0f) ? 0.0f : 1.0f / sf;
+        scales |= sbits << (8 * g);
+#pragma unroll
+        for (int i = 0; i < B_; ++i) {
+            const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(rg[i] * inv), -qmax, qmax);
+            const int at = (g * B_ + i) * BITS;
+            word[at >> 5] |= ((uint32_t)(int)q & ((1u << BITS) - 1u)) << (at & 31);
+        }
+    }
+    if (!valid) return;
+#pragma unroll
+    for (int i = 0; i < BITS / 2; ++i)
+        *reinterpret_cast<uint4 *>(codes_tok + half * 8 * BITS + i * 16) = make_uint4(word[4 * i], word[4 * i + 1], word[4 * i + 2], word[4 * i + 3]);
+    __builtin_memcpy(scales_tok + half * GL, &scales, GL);              // (they may lie at any address)
+}
+
 // One wavefront's search of the staged table.  A wavefront works on 64 tokens at a time, lane (col, half) holding
 // channels 64 half .. of tokens col and 32 + col (the MFMA B operands).
 struct TokenSearch {

@@ -231,9 +231,9 @@ struct LloydArgs {
     const bf16_t *init;                      // [H][S][K][d]; not written, and disjoint from cent_out
     int H, K, B, T, S, iters;
     bf16_t *cent_out; int64_t cent_out_stride;     // unit h's tables at cent_out + h * stride elements
-    uint8_t *ids; uint8_t *codes; f16_t *scales; int64_t out_stride; int id_wide;
+    uint8_t *ids; uint8_t *codes; void *scales; int64_t out_stride; int id_wide;
     int64_t codes_stride;                    // bytes of a unit's codes, out_stride tokens
-    int fused;                               // codes and scales are written (2-bit levels, binary16 scales)
+    int fmt, fused;                          // fused: codes and scales are written (lloyd_fuses)
     // scratch
     const uint2 *init_norms;                 // [H][S][Kpad]
     uint32_t *meet;                          // [H][64]: the words that a unit's workgroups meet at
@@ -246,6 +246,7 @@ struct LloydArgs {
     int by_xcd, rows, row_weight;            // set by launch_lloyd
 };
 int lloyd_groups(int H, int K, int64_t n_tokens, int64_t stride_token, int iters);      // workgroups per unit, 0: not for this call
+bool lloyd_fuses(int fmt, int B, int T);
 hipError_t launch_lloyd(const LloydArgs &a, hipStream_t s);
 
 // member lists of a given assignment, ids [H][ids_stride]; ids at or above K are left out

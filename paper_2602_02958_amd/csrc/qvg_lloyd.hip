@@ -1,5 +1,5 @@
 // The whole encoder of a chunk in one launch: every smoothing stage's Lloyd iterations (paper Sec. 4.1, 4.3), its
-// last assignment and, for 2-bit levels with binary16 scales, the quantization rounds.
+// last assignment and, in the formats of lloyd_fuses, the quantization rounds.
 //
 // What bounds the launches of qvg_encode.hip / qvg_kmeans.hip on one layer's chunk is not their work: an
 // iteration of 24 units x 4680 tokens, K = 256 takes 35 us, of which the tokens' way from memory to the CUs, twice,
@@ -559,7 +559,8 @@ __device__ __forceinline__ void stage_table(int h, int stage, bool start, bool o
 // blockIdx.x -> (unit, workgroup of the unit).  With eight units or more a unit's workgroups are 8 apart, on one
 // XCD, whose L2 then holds the unit's tokens; they follow each other there, so that workgroups that start in
 // order complete one unit after the other.  Fewer units spread over all XCDs.
-template <int B_, bool FUSED, int T_>
+// FMT: the stored format of the fused rounds (0, or E4M3 scales with one round)
+template <int B_, bool FUSED, int T_, int FMT>
 __global__ __launch_bounds__(kAsgThreads, 2)
 void lloyd_kernel(LloydArgs a0) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -674,7 +675,10 @@ begin:
                             }
                         }
                         const int T = T_ > 0 ? T_ : a.T;
-                        quantize_token<B_, T_>(r, T, valid, half, a.codes + hn * T * 32, a.scales + hn * T * (kHeadDim / B_));
+                        if constexpr (FMT != 0) {
+                            constexpr int BITS = (FMT & kFmtInt4) ? 4 : 2;
+                            quantize_token_e4m3<B_, BITS>(r, valid, half, a.codes + hn * (kHeadDim * BITS / 8), static_cast<uint8_t *>(a.scales) + hn * (kHeadDim / B_));
+                        } else quantize_token<B_, T_>(r, T, valid, half, a.codes + hn * T * 32, static_cast<f16_t *>(a.scales) + hn * T * (kHeadDim / B_));
                         __builtin_amdgcn_sched_barrier(0);               // keep the two tokens' passes apart: each needs most registers
                     }
                 }
@@ -755,11 +759,11 @@ void lloyd_prepare_kernel(const bf16_t *init, int K, int Kpad, uint2 *init_norms
     if (row < K && c16 == 0) init_norms[t * Kpad + row] = split_half_norm(s);
 }
 
-template <int B_, bool FUSED, int T_>
+template <int B_, bool FUSED, int T_, int FMT = 0>
 static hipError_t launch_lloyd_t(LloydArgs a, hipStream_t s) {
     const int Kpad = k_padded(a.K), S = a.S;
     static LdsHighWater lds_limit = {};
-    const void *kernel = reinterpret_cast<const void *>(&lloyd_kernel<B_, FUSED, T_>);
+    const void *kernel = reinterpret_cast<const void *>(&lloyd_kernel<B_, FUSED, T_, FMT>);
     a.row_weight = row_weight(a.K, a.n_blocks);
     a.rows = rows_at_once(a.K, a.groups, a.n_blocks);
     const size_t smem = lloyd_smem_bytes(a.K, a.rows, a.n_blocks);
@@ -771,7 +775,7 @@ static hipError_t launch_lloyd_t(LloydArgs a, hipStream_t s) {
     a.by_xcd = a.H >= 8;
     a.wait_ticks = kWaitTicks * (uint32_t)(a.S * a.iters);
     const int64_t grid = a.by_xcd ? (int64_t)8 * a.groups * ((a.H + 7) / 8) : (int64_t)a.groups * a.H;
-    hipLaunchKernelGGL((lloyd_kernel<B_, FUSED, T_>), dim3((unsigned)grid), dim3(kAsgThreads), smem, s, a);
+    hipLaunchKernelGGL((lloyd_kernel<B_, FUSED, T_, FMT>), dim3((unsigned)grid), dim3(kAsgThreads), smem, s, a);
     return hipGetLastError();
 }
 
@@ -815,8 +819,18 @@ int lloyd_groups(int H, int K, int64_t n_tokens, int64_t stride_token, int iters
     return nb < 6 && K > 31 * groups ? 0 : (int)groups;
 }
 
+// The formats whose rounds the launch writes itself: 2-bit levels with binary16 scales, and the paper's presets with E4M3 scales (one
+// round of 2-bit levels in groups of 64 or, QVG-Pro, 16, of 4-bit levels in groups of 64).  The others have quantize_kernel after it,
+// a launch that reads the tokens, ids and rows once more.
+bool lloyd_fuses(int fmt, int B, int T) {
+    if (fmt == 0) return true;
+    return T == 1 && ((fmt == kFmtE4M3 && (B == 16 || B == 64)) || (fmt == (kFmtE4M3 | kFmtInt4) && B == 64));
+}
+
 hipError_t launch_lloyd(const LloydArgs &a, hipStream_t s) {
     if (!a.fused) return launch_lloyd_t<64, false, 0>(a, s);
+    if (a.fmt == kFmtE4M3) return a.B == 16 ? launch_lloyd_t<16, true, 1, kFmtE4M3>(a, s) : launch_lloyd_t<64, true, 1, kFmtE4M3>(a, s);
+    if (a.fmt != 0) return launch_lloyd_t<64, true, 1, kFmtE4M3 | kFmtInt4>(a, s);
     switch (a.B) {
         case 16: return launch_lloyd_t<16, true, 0>(a, s);
         case 32: return a.T == 3 ? launch_lloyd_t<32, true, 3>(a, s) : launch_lloyd_t<32, true, 0>(a, s);
