@@ -249,8 +249,11 @@ __device__ __forceinline__ void update_rows(const void *x, uint32_t row_bytes, i
     int *cnt = u.cnt + w * 64;
     uint32_t *own = u.own + w * (nb * 64 + 1);
     const uint16_t *my = u.ids + w * nb * 64 + lane;                     // the wavefront's quarter of the tokens
-    // ---- the unit's ids, four pieces in flight per thread ----
-    auto load_ids = [&] {
+    uint32_t *members = reinterpret_cast<uint32_t *>(u.part);            // [K], of the count
+    if (count) for (int i = tid; i < K; i += kAsgThreads) members[i] = 0u;
+    for (int j0 = -1, end = 0; ; ) {                                     // uniform; from -1 on: its rows are not known yet
+        // ---- the unit's ids, four pieces in flight per thread (again for the next rows: the lists of those before are
+        // where the ids were) ----
         for (int i0 = tid; i0 < nb * 32; i0 += 4 * kAsgThreads) {
             uint4 v[4];
 #pragma unroll
@@ -258,35 +261,26 @@ __device__ __forceinline__ void update_rows(const void *x, uint32_t row_bytes, i
 #pragma unroll
             for (int k = 0; k < 4; ++k) if (i0 + k * kAsgThreads < nb * 32) *reinterpret_cast<uint4 *>(u.ids + (i0 + k * kAsgThreads) * 8) = v[k];
         }
-    };
-    uint32_t *members = reinterpret_cast<uint32_t *>(u.part);            // [K], of the count
-    if (count) for (int i = tid; i < K; i += kAsgThreads) members[i] = 0u;
-    cnt[lane] = 0;
-    load_ids();
-    __syncthreads();
-    if (count) {                                                         // uniform
+        cnt[lane] = 0;
+        __syncthreads();
+        if (j0 < 0) {
+            if (count) {                                                 // uniform
 #pragma unroll 4
-        for (int i = 0; i < nb; ++i) {
-            const uint32_t id = my[i * 64];
-            if (id < (uint32_t)K) atomicAdd(&members[id], 1u);           // (0xffff: no token)
-        }
-        __syncthreads();
-        int n[kRowsPerThread];
+                for (int i = 0; i < nb; ++i) {
+                    const uint32_t id = my[i * 64];
+                    if (id < (uint32_t)K) atomicAdd(&members[id], 1u);   // (0xffff: no token)
+                }
+                __syncthreads();
+                int n[kRowsPerThread];
 #pragma unroll
-        for (int k = 0; k < kRowsPerThread; ++k) n[k] = k * kAsgThreads + tid < K ? (int)members[k * kAsgThreads + tid] : 0;
-        deal_rows(n, K, weight, g, groups, deal);
-        __syncthreads();
-    }
-    int first, end;                                                      // uniform
-    dealt(deal, first, end);
-    for (int j0 = first; j0 < end; j0 += rows) {                         // uniform
-        const int c = end - j0 < rows ? end - j0 : rows;
-        if (j0 > first) {                                                    // (the lists of the rows before are where the ids were)
-            __syncthreads();
-            cnt[lane] = 0;
-            load_ids();
-            __syncthreads();
+                for (int k = 0; k < kRowsPerThread; ++k) n[k] = k * kAsgThreads + tid < K ? (int)members[k * kAsgThreads + tid] : 0;
+                deal_rows(n, K, weight, g, groups, deal);
+                __syncthreads();
+            }
+            dealt(deal, j0, end);
         }
+        const int c = end - j0 < rows ? end - j0 : rows;
+        if (c <= 0) break;
         // ---- the members of these rows, a wavefront's quarter of the tokens at a time, in token order (no branches: what
         // is no member goes to the place behind the last) ----
         int n_own = 0;                                                       // uniform
@@ -465,6 +459,9 @@ __device__ __forceinline__ void update_rows(const void *x, uint32_t row_bytes, i
             nh.y |= (uint32_t)n << 16;                                       // and the members
             if (c8 == 0) norms.store8((uint32_t)(j0 + j) * 8u, nh);
         }
+        j0 += c;
+        if (j0 == end) break;
+        __syncthreads();
     }
 }
 
