@@ -56,7 +56,9 @@ hipError_t launch_half_norms(const bf16_t *cent, int64_t cent_stride, int H, int
 // grid: x = unit, y = block of 256 * tiles_per_wave tokens.  With the unit as the fastest grid
 // index and H a multiple of 8, all blocks of a unit run on one XCD and share its table in L2.
 // T_: number of quantization rounds of the fused pass when known at compile time (0: a.T)
-template <int B_, bool FUSED, int T_>
+// LATER: the tokens are residuals, the table may have several rows of zeros.  (An instance of its own, so that the first
+// stage's launches stay as they are.  Not with FUSED, one of a stage's I + 1 passes.)
+template <int B_, bool FUSED, int T_, bool LATER>
 __global__ __launch_bounds__(kAsgThreads, 2)
 void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -75,7 +77,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
     // ||c||^2 of the unit (one ulp up) is needed for the error band of the certification.
     __shared__ uint32_t smax;
     __shared__ int zero_row;
-    if (tid == 0) { smax = 0u; if (!FUSED) zero_row = kMaxClusters; }
+    if (tid == 0) { smax = 0u; if (LATER) zero_row = kMaxClusters; }
     const bf16_t *cg = a.cent + (int64_t)h * a.cent_stride;
     uint2 nh[kMaxClusters / kAsgThreads];
 #pragma unroll
@@ -149,7 +151,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
         for (int u = 0; u < kMaxClusters / kAsgThreads; ++u) {
             const int row = tid + u * kAsgThreads;
             float up = 0.0f;
-            if (row < Kpad) { up = place_norm(row, nh[u]); if (!FUSED && a.ids_off > 0) note_zero_norm(nh[u], row, &zero_row); }
+            if (row < Kpad) { up = place_norm(row, nh[u]); if (LATER) note_zero_norm(nh[u], row, &zero_row); }
             if (u * kAsgThreads < Kpad) {                               // uniform
 #pragma unroll
                 for (int off = 32; off >= 1; off >>= 1) up = fmaxf(up, __shfl_xor(up, off, 64));
@@ -158,9 +160,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
         }
     }
     __syncthreads();
-    // Uniform: a later smoothing stage.  (Not in the fused pass, one of a stage's I + 1 and the only one of an encode without
-    // iterations, which the test alone made 1 % slower: 24 units x 4680 tokens, K = 256, T = 2 30.1 -> 30.4 us.)
-    if (!FUSED && a.ids_off > 0 && a.nh3) drop_zero_rows(lc, K, nh, &zero_row);
+    if (LATER && a.nh3) drop_zero_rows(lc, K, nh, &zero_row);           // uniform
     const float cmax = __uint_as_float(smax);
     bf16_t *scr = lscr + wave * kHeadDim;
     float *sscr = lsscr + wave * Kpad;
@@ -277,18 +277,18 @@ bool assign_takes_norms(int H, int K, int64_t n_tokens, bool fused) {
     return kp <= 128 && wgs * kp * kp <= ((int64_t)1 << 23);
 }
 
-template <int B_, bool FUSED, int T_>
+template <int B_, bool FUSED, int T_, bool LATER = false>
 static hipError_t launch_assign_t(const AssignArgs &a, hipStream_t s) {
     const int Kpad = k_padded(a.K);
     const size_t smem = assign_smem_bytes(Kpad);
     static LdsHighWater lds_limit = {};
-    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&assign_kernel<B_, FUSED, T_>), smem, lds_limit);
+    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&assign_kernel<B_, FUSED, T_, LATER>), smem, lds_limit);
     if (e != hipSuccess) return e;
     const int tpw = assign_tiles_per_wave(a.H, a.n_tokens);
     const int64_t gy = (a.n_tokens + kAsgThreads * tpw - 1) / (kAsgThreads * tpw);
     if (gy > 65535) return hipErrorInvalidValue;
     if (a.lists.perm && (a.lists.block != kAsgThreads * tpw || a.lists.n_blocks != gy)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((assign_kernel<B_, FUSED, T_>), dim3((unsigned)a.H, (unsigned)gy), dim3(kAsgThreads), smem, s, a,
+    hipLaunchKernelGGL((assign_kernel<B_, FUSED, T_, LATER>), dim3((unsigned)a.H, (unsigned)gy), dim3(kAsgThreads), smem, s, a,
                        Kpad, tpw);
     return hipGetLastError();
 }
@@ -306,7 +306,7 @@ static hipError_t launch_fused(const AssignArgs &a, hipStream_t s) {
 
 hipError_t launch_assign(const AssignArgs &a, hipStream_t s) {
     if (a.n_tokens == 0) return hipSuccess;
-    if (!a.fused) return launch_assign_t<64, false, 0>(a, s);
+    if (!a.fused) return a.ids_off > 0 ? launch_assign_t<64, false, 0, true>(a, s) : launch_assign_t<64, false, 0>(a, s);
     switch (a.B) {
         case 16: return launch_fused<16>(a, s);
         case 32: return launch_fused<32>(a, s);
