@@ -28,7 +28,8 @@
 // when a unit waited 2 ms and one workgroup did it over): 24 units x 4680 tokens, K = 256, T = 4, I = 3 295 / 420 / 760; 350 / 860 / 1255; 359 / - / 3190;
 // four stages 1205 / 1820 / 2370; 1520 / 2390 / 3000; 1500 / - / 6500; INT4, 10 x 1571 101 / 116 / 174; 158 / 163 / 370; 143 / - / 2520.  Two streams of
 // encodes, a pair of them: 225, 213, 214; 900, 931, 953; 123, 102, 104.  (A wait half as long: 200 workgroups 1070, two
-// streams of four stages 1000; twice as long 1610, 928.)
+// streams of four stages 1000; twice as long 1610, 928.)  The figures of four stages are from before update_rows dealt later stages' rows
+// by their members (alone 540 us then, 449 now).
 #include "qvg_assign.hpp"
 
 namespace qvg {
@@ -263,7 +264,7 @@ __device__ __forceinline__ void update_rows(const void *x, uint32_t row_bytes, i
         }
         cnt[lane] = 0;
         __syncthreads();
-        if (j0 < 0) {
+        if (j0 < 0) {                                                    // uniform
             if (count) {                                                 // uniform
 #pragma unroll 4
                 for (int i = 0; i < nb; ++i) {
@@ -779,7 +780,7 @@ static hipError_t launch_lloyd_t(LloydArgs a, hipStream_t s) {
 // Workgroups of a unit, 0: the call is left to the launches of their own.
 //
 // All workgroups have to run at the same time: two to a CU by registers and LDS, one with more than 256 centroids.  Then
-// the launch is taken where it measured faster (24 units x 4680 tokens, K = 256, I = 3: 131 -> 117 us; 10: 346 -> 294; S = 4: 1004 -> 767;
+// the launch is taken where it measured faster (24 units x 4680 tokens, K = 256, I = 3: 131 -> 117 us; 10: 346 -> 294; S = 4: 1004 -> 767, 449 since;
 // 80 x 1536, K = 64, I = 10: 269 -> 198; 24 x 780, K = 64: 59 -> 50):
 // - the chip is more than half full (300 workgroups; at 190 of them, 10 units x 4680, K = 64, 70 -> 84 us);
 // - or a unit has up to eight blocks and its lists are short on average (up to 40 members: 6 units x 2000 tokens, K = 64
