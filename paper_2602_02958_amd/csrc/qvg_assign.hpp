@@ -470,7 +470,9 @@ struct TokenSearch {
         // (the last term: the tag of a score that is zero, where all norms are)
         const float thr = (K > 256 ? 0x1.8p-14f : 0x1p-14f) * (0.5f * xn + fminf(cmax, reach)) + 0x1p-126f;
         int id = i1;
-        const bool amb = valid && (i2 < K) && !(c1 - c2 > thr);
+        // (rows K.. and rows of zeros but the first are not candidates.  A band that is not finite: scores of tokens or rows
+        // whose norm fp32 does not hold may be missing from the ranking, so there the second best says nothing)
+        const bool amb = valid && (i2 < K || !(thr < pinf)) && !(c1 - c2 > thr);
         const bool full = !(c1 - c3 > thr);
 
         // ---- fp64 re-evaluation of tokens the fp32 scores cannot decide ----

@@ -61,3 +61,28 @@ def test_stages_with_unequal_clusters(H, N, K, Bg, S, I, zeros):
     assert np.array_equal(ids, ref["ids"].transpose(0, 2, 1))
     assert np.array_equal(P.to_np_u8(enc.codes[units]), ref["codes"])
     assert np.array_equal(P.to_np_u16(enc.scales[units]), ref["scales"])
+
+
+@pytest.mark.parametrize("N,I", [(640, 1), (1300, 2), (640, 0)])
+@pytest.mark.parametrize("K,zeros", [(3, [0, 1]), (4, [0, 1, 3]), (4, [0]), (2, [0]), (130, [0, 1, 129])])
+def test_scores_beyond_fp32(N, I, K, zeros):
+    """Finite tokens and rows whose squared norms are not: a score that overflows decides nothing, also where the only row with
+    a finite one is a row of zeros and the rows behind it are the table's padding.  (Half of the tokens are + a, half - a, so
+    that the first stage, all rows zero, leaves them as they are.)"""
+    a = 2.0 ** 66
+    g = torch.Generator().manual_seed(N + K)
+    x = torch.full((2, N, 128), a)
+    x[:, ::2] *= -1.0
+    init = torch.zeros(2, 2, K, 128)
+    init[:, 1] = -8.0 * a * (1.0 + torch.rand(2, K, 1, generator=g))     # further than zero from every token
+    init[:, 1, zeros] = 0.0
+    init[:, 1, min(2, K - 1)] = 0.75 * a
+    x, init = x.to(torch.bfloat16), init.to(torch.bfloat16)
+    enc = B.encode_chunk(x.to(DEV), init.to(DEV), 64, 1, I)
+    torch.cuda.synchronize()
+    ref = O.encode_batch(bf16_bits(x), bf16_bits(init), K, 64, 1, I, S=2)
+    assert len(set(ref["ids"][0, 1])) == 2
+    assert np.array_equal(P.to_np_u8(enc.ids), ref["ids"].transpose(0, 2, 1))
+    assert np.array_equal(P.to_np_u16(enc.centroids[:, 0]), ref["cent"])
+    assert np.array_equal(P.to_np_u8(enc.codes), ref["codes"])
+    assert np.array_equal(P.to_np_u16(enc.scales), ref["scales"])
