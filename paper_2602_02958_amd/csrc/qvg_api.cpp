@@ -561,10 +561,9 @@ int attn_call(const qvg_params *p, int64_t n_q, const void *q, int64_t n_kv_toke
     const AttnParts parts = attn_parts(a.H, n_q, n_kv_tokens, a.chunk_len, q_kv_len != nullptr);
     const size_t part_bytes = attn_parts_bytes(a.H, n_q, parts);
     a.parts = parts.parts; a.part_tiles = parts.part_tiles; a.whole = parts.whole;
-    // (calls of more than 128 query blocks were not divided at first and took any scratch: one that they cannot use is ignored)
-    const bool unaligned = !aligned16(scratch), ignored = unaligned && (a.whole || a.part_tiles);
-    if (a.parts > 1 && scratch && scratch_bytes >= part_bytes && !ignored) {
-        if (unaligned) return QVG_ERR_ALIGN;
+    const bool unaligned = !aligned16(scratch);
+    if (unaligned && parts.aligned && scratch_bytes >= attn_parts_bytes(a.H, n_q, AttnParts{parts.aligned, 0, 0, 0})) return QVG_ERR_ALIGN;
+    if (a.parts > 1 && scratch && !unaligned && scratch_bytes >= part_bytes) {
         a.part_state = static_cast<float *>(scratch);
     } else {
         a.parts = 1; a.whole = 0;                      // no room for the parts' states: every workgroup walks the whole cache

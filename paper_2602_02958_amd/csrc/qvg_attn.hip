@@ -956,8 +956,14 @@ static int parts_by_cost(int64_t tiles, int64_t most, int64_t queries) {
     }
     return (int)parts;
 }
+// Parts of four tiles at least until the chip is full, and of more than 64 blocks not below ten tiles: the calls that were divided
+// at first.  They refuse scratch that is not aligned; the others took any, and one that they cannot use is ignored.
+static int parts_at_first(int64_t nb, int64_t tiles) {
+    const int64_t most = nb > 64 && tiles < 10 ? 1 : tiles / kPartTiles, p = kCus / nb < most ? kCus / nb : most;
+    return p > 1 ? (int)p : 1;
+}
 AttnParts attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool with_len) {
-    AttnParts p{1, 0, 0};
+    AttnParts p{1, 0, 0, 0};
     if (n_q < 1 || n_kv < 1) return p;
     const int64_t nb = (n_q + kAtQPerBlock - 1) / kAtQPerBlock * H;
     const int64_t full = n_kv / chunk_len, rest = n_kv - full * chunk_len;
@@ -975,8 +981,10 @@ AttnParts attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool w
         return p;
     }
     if (nb > kCus) return p;
+    const int first = parts_at_first(nb, tiles);
+    if (first > 1) p.aligned = first;
     if (nb <= kCostBlocks || tiles < kCostTiles) p.parts = parts_by_cost(tiles, kCus / nb, H * n_q);
-    else p.parts = (int)(kCus / nb < tiles / kPartTiles ? kCus / nb : tiles / kPartTiles);
+    else p.parts = first;
     return p;
 }
 size_t attn_parts_bytes(int H, int64_t n_q, const AttnParts &p) {

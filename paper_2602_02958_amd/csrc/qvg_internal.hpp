@@ -286,7 +286,8 @@ struct AttnArgs {
 };
 hipError_t launch_attn(const AttnArgs &a, hipStream_t s);
 // parts for a call of these sizes (with_len: with a prefix length per query), and the bytes of their state (0 for a single part)
-struct AttnParts { int parts, part_tiles, whole; };                      // as in AttnArgs
+// aligned: not 0: scratch of at least this many parts' states has to be 16-byte aligned
+struct AttnParts { int parts, part_tiles, whole, aligned; };             // (the first three as in AttnArgs)
 AttnParts attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool with_len);
 size_t attn_parts_bytes(int H, int64_t n_q, const AttnParts &p);
 hipError_t launch_attn_join(const AttnArgs &a, hipStream_t s);
