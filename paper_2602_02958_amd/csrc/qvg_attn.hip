@@ -922,7 +922,8 @@ hipError_t launch_attn(const AttnArgs &a, hipStream_t s) {
 // is 5 % slower).  How far is what costs least: the longest part's tiles, the join, and the states, 528 bytes per query and part
 // to write and to read.  With four tiles to a part at least, us before and after: 64 queries x 1 head over 500 tokens 19.3 -> 11.4, 4096 20.3 ->
 // 12.5, 8 heads over 2000 19.5 -> 12.7; 250 x 8 over 1000 22.3 -> 19.9 (one tile to a part 18.1), 400 x 2 over 3000 26.6 -> 20.9 (one tile
-// 24.0); 300 x 40 over 700 36.7 -> 33.5; 500 the same undivided (31.1), 1560 x 12 over 512 26.7 (divided 34).  More than
+// 24.0); 300 x 40 over 700 36.7 -> 33.5; 500 the same undivided (31.1), 1560 x 12 over 512 26.7 (divided 34).  Calls that had parts of four
+// tiles at least keep parts no longer than that (parts_at_first).  More than
 // eight blocks over 48 tiles or more have as many parts as the chip holds, of four tiles at least: the cost of one more or less is about the same there
 // (16 blocks over 74 tiles in 16 parts 38.7, in 15 39.3; 12 x 64 queries over 74 tiles in 18 27.8, in 19 26.7).
 // From 129 query blocks on nothing is dealt: 160 blocks in three parts gain nothing (1.09 against 1.08 ms).
@@ -945,12 +946,16 @@ constexpr int kPartTiles = 4;                     // tiles of a part at least wh
 constexpr int kCostBlocks = 8, kCostTiles = 48;   // up to that many blocks, or below that many tiles, parts are chosen by cost
 constexpr int64_t kTileNs = 2300, kJoinNs = 4700, kStateNsBy100 = 21;
 // Parts of `tiles` tiles of a call of `queries` queries, `most` at most: by what the longest part's tiles, the join's launch and
-// the states of all parts take.  Among equal longest parts the fewest.
-static int parts_by_cost(int64_t tiles, int64_t most, int64_t queries) {
-    int64_t parts = 1, best = tiles * kTileNs;
+// the states of all parts take.  Among equal longest parts the fewest.  No part is longer than in `first` parts (1: the call may stay
+// whole): the cost is that of two rounds of levels without rotary keys, and four stages take up to three times that a tile (40
+// heads x 700 queries over 768 tokens, E4M3 scales, whole and in two parts: 59 us, 46; with rotary keys 79, 55; with prefix lengths
+// 146, 95; two rounds of levels 42, 42).
+static int parts_by_cost(int64_t tiles, int64_t most, int64_t queries, int64_t first) {
     if (most > tiles) most = tiles;
     if (most < 2) return 1;
-    for (int64_t longest = (tiles + most - 1) / most; longest * kTileNs + kJoinNs < best; ++longest) {
+    const int64_t limit = (tiles + first - 1) / first;
+    int64_t parts = first, best = first > 1 ? INT64_MAX : tiles * kTileNs;
+    for (int64_t longest = (tiles + most - 1) / most; longest <= limit && longest * kTileNs + kJoinNs < best; ++longest) {
         const int64_t p = (tiles + longest - 1) / longest, cost = longest * kTileNs + kJoinNs + p * queries * kStateNsBy100 / 100;
         if (cost < best) { best = cost; parts = p; }
     }
@@ -983,7 +988,7 @@ AttnParts attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool w
     if (nb > kCus) return p;
     const int first = parts_at_first(nb, tiles);
     if (first > 1) p.aligned = first;
-    if (nb <= kCostBlocks || tiles < kCostTiles) p.parts = parts_by_cost(tiles, kCus / nb, H * n_q);
+    if (nb <= kCostBlocks || tiles < kCostTiles) p.parts = parts_by_cost(tiles, kCus / nb, H * n_q, first);
     else p.parts = first;
     return p;
 }

@@ -1,0 +1,30 @@
+"""Which attention calls are divided, and the scratch that they ask for: the library's host arithmetic, no GPU."""
+import pytest
+
+from paper_2602_02958_amd import binding as B
+
+STATE = 66 * 512 * 4                             # bytes of a query block's state
+SHAPES = [(1, 1), (1, 64), (1, 300), (2, 64), (8, 64), (3, 700), (9, 64), (16, 200), (5, 600), (12, 600), (64, 64), (65, 64), (40, 700),
+          (12, 1560), (128, 256), (129, 64), (256, 64)]
+
+
+def _scratch(H, Nq, tiles, lengths=False):
+    need, p = B.C.c_size_t(), B.make_params(H, 16, 64, 2)
+    ask = B.lib().qvg_attn_scratch_bytes_causal if lengths else B.lib().qvg_attn_scratch_bytes
+    assert ask(B.C.byref(p), Nq, tiles * 64 - 3, 1 << 20, B.C.byref(need)) == 0
+    return need.value
+
+
+def _parts_of_four_tiles(blocks, tiles):
+    """The parts of a call that has always been divided: four tiles to a part at least, until 256 workgroups are there; of
+    more than 64 blocks not below ten tiles."""
+    return 1 if blocks > 64 and tiles < 10 else min(256 // blocks, tiles // 4)
+
+
+@pytest.mark.parametrize("lengths", [False, True])
+@pytest.mark.parametrize("H,Nq", SHAPES)
+def test_calls_that_were_divided_are(H, Nq, lengths):
+    blocks = H * -(-Nq // 256)
+    for tiles in range(1, 192):
+        if blocks <= 256 and _parts_of_four_tiles(blocks, tiles) > 1:
+            assert _scratch(H, Nq, tiles, lengths) >= 2 * blocks * STATE, tiles
