@@ -927,6 +927,9 @@ hipError_t launch_attn(const AttnArgs &a, hipStream_t s) {
 // eight blocks over 48 tiles or more have as many parts as the chip holds, of four tiles at least: the cost of one more or less is about the same there
 // (16 blocks over 74 tiles in 16 parts 38.7, in 15 39.3; 12 x 64 queries over 74 tiles in 18 27.8, in 19 26.7).
 // From 129 query blocks on nothing is dealt: 160 blocks in three parts gain nothing (1.09 against 1.08 ms).
+// With a prefix length per query those that have always been whole stay so: only the device knows the prefixes, and where they end
+// in the first tile the division is lost (64 queries x 1 head over 448 tokens 8.1 us whole, 12.2 divided, 128 heads over 512 9.4 and
+// 16.0; four stages 13.4 and 17.3).
 // More than 256 are taken whole up to the last round of 256, and that one is dealt out if at most 128 are left for it: the
 // call would end with a few blocks on an idle chip.  266 blocks over 293 tiles 1025 -> 655 us (all blocks in four parts
 // 779), over 32 tiles 137 -> 100; 320 blocks 1048 -> 790, 384 1066 -> 945; 792 over 148 tiles 1108 -> 952; 16 x 6108 queries over 34483
@@ -988,6 +991,7 @@ AttnParts attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool w
     if (nb > kCus) return p;
     const int first = parts_at_first(nb, tiles);
     if (first > 1) p.aligned = first;
+    if (with_len && first == 1) return p;
     if (nb <= kCostBlocks || tiles < kCostTiles) p.parts = parts_by_cost(tiles, kCus / nb, H * n_q, first);
     else p.parts = first;
     return p;

@@ -28,3 +28,12 @@ def test_calls_that_were_divided_are(H, Nq, lengths):
     for tiles in range(1, 192):
         if blocks <= 256 and _parts_of_four_tiles(blocks, tiles) > 1:
             assert _scratch(H, Nq, tiles, lengths) >= 2 * blocks * STATE, tiles
+
+
+@pytest.mark.parametrize("H,Nq", SHAPES)
+def test_prefix_lengths_over_a_few_tiles_are_taken_whole(H, Nq):
+    """Where the prefixes end in the first tile, the launch that joins the parts is half of such a call."""
+    blocks = H * -(-Nq // 256)
+    for tiles in range(1, 48):
+        if blocks <= 256 and _parts_of_four_tiles(blocks, tiles) <= 1:
+            assert _scratch(H, Nq, tiles, True) == 0, tiles
