@@ -947,19 +947,24 @@ constexpr int kLenMinBlocks = 129, kLenMinTiles = 192, kLenParts = 3, kLenPartTi
 constexpr int kTailMaxBlocks = 4096, kTailMinTiles = 16;
 constexpr int kPartTiles = 4;                     // tiles of a part at least where the parts are as many as the chip holds
 constexpr int kCostBlocks = 8, kCostTiles = 48;   // up to that many blocks, or below that many tiles, parts are chosen by cost
-constexpr int64_t kTileNs = 2300, kJoinNs = 4700, kStateNsBy100 = 21;
+struct PartCost { int64_t tile, join, state_by_100; };                   // ns; the last for each query and part
+constexpr PartCost kOwnTiles{2300, 4700, 21}, kSharedTiles{1500, 3000, 30};
+constexpr int64_t kSharedMinQueries = 513;        // queries per unit from which a workspace for the tiles is the rule
 // Parts of `tiles` tiles of a call of `queries` queries, `most` at most: by what the longest part's tiles, the join's launch and
 // the states of all parts take.  Among equal longest parts the fewest.  No part is longer than in `first` parts (1: the call may stay
 // whole): the cost is that of two rounds of levels without rotary keys, and four stages take up to three times that a tile (40
 // heads x 700 queries over 768 tokens, E4M3 scales, whole and in two parts: 59 us, 46; with rotary keys 79, 55; with prefix lengths
 // 146, 95; two rounds of levels 42, 42).
-static int parts_by_cost(int64_t tiles, int64_t most, int64_t queries, int64_t first) {
+// Units of more than 512 queries read tiles that a workspace holds, decoded by a launch of its own (whether one is lent may not change
+// the parts): a tile is cheaper there and a state dearer.  12 heads x 600 queries over 445 tokens whole 24.9 us, in the four
+// parts of the other cost 28.1; over 637 in two parts 29.0, in five 30.8; 5 x 600 over 2045 in eight 30.6, in eleven 31.6.
+static int parts_by_cost(const PartCost &c, int64_t tiles, int64_t most, int64_t queries, int64_t first) {
     if (most > tiles) most = tiles;
     if (most < 2) return 1;
     const int64_t limit = (tiles + first - 1) / first;
-    int64_t parts = first, best = first > 1 ? INT64_MAX : tiles * kTileNs;
-    for (int64_t longest = (tiles + most - 1) / most; longest <= limit && longest * kTileNs + kJoinNs < best; ++longest) {
-        const int64_t p = (tiles + longest - 1) / longest, cost = longest * kTileNs + kJoinNs + p * queries * kStateNsBy100 / 100;
+    int64_t parts = first, best = first > 1 ? INT64_MAX : tiles * c.tile;
+    for (int64_t longest = (tiles + most - 1) / most; longest <= limit && longest * c.tile + c.join < best; ++longest) {
+        const int64_t p = (tiles + longest - 1) / longest, cost = longest * c.tile + c.join + p * queries * c.state_by_100 / 100;
         if (cost < best) { best = cost; parts = p; }
     }
     return (int)parts;
@@ -992,7 +997,7 @@ AttnParts attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool w
     const int first = parts_at_first(nb, tiles);
     if (first > 1) p.aligned = first;
     if (with_len && first == 1) return p;
-    if (nb <= kCostBlocks || tiles < kCostTiles) p.parts = parts_by_cost(tiles, kCus / nb, H * n_q, first);
+    if (nb <= kCostBlocks || tiles < kCostTiles) p.parts = parts_by_cost(n_q < kSharedMinQueries ? kOwnTiles : kSharedTiles, tiles, kCus / nb, H * n_q, first);
     else p.parts = first;
     return p;
 }

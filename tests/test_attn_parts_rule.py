@@ -37,3 +37,10 @@ def test_prefix_lengths_over_a_few_tiles_are_taken_whole(H, Nq):
     for tiles in range(1, 48):
         if blocks <= 256 and _parts_of_four_tiles(blocks, tiles) <= 1:
             assert _scratch(H, Nq, tiles, True) == 0, tiles
+
+
+def test_shared_tiles_have_a_cost_of_their_own():
+    """More than 512 queries per unit read tiles that another launch has decoded: a part's start is dear for what it saves."""
+    assert _scratch(12, 600, 7) == 0
+    assert _scratch(12, 512, 7) > 0
+    assert _scratch(1, 600, 7) > 0
