@@ -122,13 +122,6 @@ def test_null_and_alignment_errors_are_reported_before_any_launch():
                                     None, C.c_void_p(0x1002), C.c_float(0.1), fake, None, None, 0, None) == -5
     assert L.qvg_attn_decode_causal(C.byref(p), 0, None, 10, 10, 0, None, None, None, None, None, None, None, None,
                                     None, None, C.c_float(0.1), None, None, None, 0, None) == 0
-    # scratch of a call that has always been divided, with room for its parts of four tiles, but misaligned
-    parts = lambda H, Nq, n, room: L.qvg_attn_decode_parts(
-        C.byref(B.make_params(H, 16, 64, 2)), Nq, fake, n, n, 0, fake, fake, fake, fake, fake, fake, fake, fake, None, None,
-        C.c_float(0.1), fake, None, None, None, 0, odd, room, None)
-    state = 66 * 512 * 4
-    assert parts(1, 64, 512, 2 * state) == -5 and parts(1, 64, 4096, 16 * state) == -5
-    assert parts(64, 200, 512, 64 * 2 * state) == -5 and parts(65, 1, 640, 65 * 2 * state) == -5
     # merge
     assert L.qvg_attn_merge(4, 64, fake, fake, fake, fake, fake, None, None) == -3
     assert L.qvg_attn_merge(-1, 128, fake, fake, fake, fake, fake, None, None) == -2

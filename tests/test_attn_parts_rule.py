@@ -44,3 +44,16 @@ def test_shared_tiles_have_a_cost_of_their_own():
     assert _scratch(12, 600, 7) == 0
     assert _scratch(12, 512, 7) > 0
     assert _scratch(1, 600, 7) > 0
+
+
+def test_misaligned_scratch_of_calls_that_have_always_been_divided_is_refused():
+    """With room for their parts of four tiles; the calls below that were ignored it."""
+    at = B.C.c_void_p
+    fake, odd = at(0x1000), at(0x1008)               # never dereferenced: the call fails first
+
+    def call(H, Nq, n, room):
+        return B.lib().qvg_attn_decode_parts(
+            B.C.byref(B.make_params(H, 16, 64, 2)), Nq, fake, n, n, 0, fake, fake, fake, fake, fake, fake, fake, fake, None, None,
+            B.C.c_float(0.1), fake, None, None, None, 0, odd, room, None)
+    assert call(1, 64, 512, 2 * STATE) == -5 and call(1, 64, 4096, 16 * STATE) == -5
+    assert call(64, 200, 512, 64 * 2 * STATE) == -5 and call(65, 1, 640, 65 * 2 * STATE) == -5
