@@ -315,7 +315,9 @@ int qvg_attn_decode_f32(const qvg_params *p, int64_t n_q, const void *q_bf16,
  * more launch joins their partial results (fp32).  How many depends on n_heads, n_q, n_kv_tokens, chunk_len
  * and the prefix lengths only, so equal calls give equal bits, with and without `workspace`.  They differ from the undivided
  * result by the order of fp32 sums and by the maxima that the binary16 probabilities are taken
- * against.  Without scratch (NULL, 0) or with less, this is the undivided call.
+ * against.  Without scratch (NULL, 0) or with less, this is the undivided call; except that of up to 256 blocks of 256 queries the
+ * number of parts may fall as the cache grows, and scratch for a longer cache (n_kv_tokens larger, all else equal) divides a
+ * shorter one into as many parts as it holds.
  * Prefix lengths may come in any order.  Calls of more than 128 blocks of 256 queries over 192 tiles or more read off
  * the first and the last query's what the others are like: where these two see about as much no block is divided, else the
  * blocks at the end that sees more run first.  Any other order gets the same results, not the best time.

@@ -558,16 +558,12 @@ int attn_call(const qvg_params *p, int64_t n_q, const void *q, int64_t n_kv_toke
     if (!ids_aligned(p, k_ids) || !ids_aligned(p, v_ids)) return QVG_ERR_ALIGN;
     if (q_kv_len && (reinterpret_cast<uintptr_t>(q_kv_len) & 3u)) return QVG_ERR_ALIGN;
     a.q_len = q_kv_len;
-    const AttnParts parts = attn_parts(a.H, n_q, n_kv_tokens, a.chunk_len, q_kv_len != nullptr);
-    const size_t part_bytes = attn_parts_bytes(a.H, n_q, parts);
-    a.parts = parts.parts; a.part_tiles = parts.part_tiles; a.whole = parts.whole;
+    // (without room for parts every workgroup walks the whole cache)
     const bool unaligned = !aligned16(scratch);
-    if (unaligned && parts.aligned && scratch_bytes >= attn_parts_bytes(a.H, n_q, AttnParts{parts.aligned, 0, 0, 0})) return QVG_ERR_ALIGN;
-    if (a.parts > 1 && scratch && !unaligned && scratch_bytes >= part_bytes) {
-        a.part_state = static_cast<float *>(scratch);
-    } else {
-        a.parts = 1; a.whole = 0;                      // no room for the parts' states: every workgroup walks the whole cache
-    }
+    const AttnParts parts = attn_parts(a.H, n_q, n_kv_tokens, a.chunk_len, q_kv_len != nullptr, scratch && !unaligned ? scratch_bytes : 0);
+    if (unaligned && parts.aligned && scratch_bytes >= attn_state_bytes(a.H, n_q, AttnParts{parts.aligned, 0, 0, 0})) return QVG_ERR_ALIGN;
+    a.parts = parts.parts; a.part_tiles = parts.part_tiles; a.whole = parts.whole;
+    if (a.parts > 1) a.part_state = static_cast<float *>(scratch);
     hipStream_t s = static_cast<hipStream_t>(stream);
     // a workspace that holds at least one chunk's decoded tiles switches to the shared-tile path
     if (workspace && attn_slab_applicable(a, workspace, workspace_bytes)) {
@@ -600,7 +596,7 @@ int qvg_attn_scratch_bytes(const qvg_params *p, int64_t n_q, int64_t n_kv_tokens
     if (st != QVG_OK) return st;
     if (!out) return QVG_ERR_NULL;
     if (n_q < 0 || n_kv_tokens < 1 || n_kv_tokens > 0x7fffffff || chunk_len < 1) return QVG_ERR_BAD_PARAM;
-    *out = attn_parts_bytes(p->n_heads, n_q, attn_parts(p->n_heads, n_q, n_kv_tokens, bounded_chunk_len(chunk_len), false));
+    *out = attn_state_bytes(p->n_heads, n_q, attn_parts(p->n_heads, n_q, n_kv_tokens, bounded_chunk_len(chunk_len), false));
     return QVG_OK;
 }
 
@@ -609,7 +605,7 @@ int qvg_attn_scratch_bytes_causal(const qvg_params *p, int64_t n_q, int64_t n_kv
     if (st != QVG_OK) return st;
     if (!out) return QVG_ERR_NULL;
     if (n_q < 0 || n_kv_tokens < 1 || n_kv_tokens > 0x7fffffff || chunk_len < 1) return QVG_ERR_BAD_PARAM;
-    *out = attn_parts_bytes(p->n_heads, n_q, attn_parts(p->n_heads, n_q, n_kv_tokens, bounded_chunk_len(chunk_len), true));
+    *out = attn_state_bytes(p->n_heads, n_q, attn_parts(p->n_heads, n_q, n_kv_tokens, bounded_chunk_len(chunk_len), true));
     return QVG_OK;
 }
 

@@ -947,6 +947,7 @@ constexpr int kLenMinBlocks = 129, kLenMinTiles = 192, kLenParts = 3, kLenPartTi
 constexpr int kTailMaxBlocks = 4096, kTailMinTiles = 16;
 constexpr int kPartTiles = 4;                     // tiles of a part at least where the parts are as many as the chip holds
 constexpr int kCostBlocks = 8, kCostTiles = 48;   // up to that many blocks, or below that many tiles, parts are chosen by cost
+constexpr size_t kStateBytes = (size_t)kStateFloats * kAtThreads * sizeof(float);                // of a query block's part
 struct PartCost { int64_t tile, join, state_by_100; };                   // ns; the last for each query and part
 constexpr PartCost kOwnTiles{2300, 4700, 21}, kSharedTiles{1500, 3000, 30};
 constexpr int64_t kSharedMinQueries = 513;        // queries per unit from which a workspace for the tiles is the rule
@@ -971,39 +972,45 @@ static int parts_by_cost(const PartCost &c, int64_t tiles, int64_t most, int64_t
 }
 // Parts of four tiles at least until the chip is full, and of more than 64 blocks not below ten tiles: the calls that were divided
 // at first.  They refuse scratch that is not aligned; the others took any, and one that they cannot use is ignored.
+// They grow with the cache, the parts by cost do not (8 heads x 64 queries: 32 tiles in 32 parts, 33 in 17).  So that scratch for a long
+// cache serves every shorter one, as many parts are taken as it holds, and these at least are asked for.
 static int parts_at_first(int64_t nb, int64_t tiles) {
     const int64_t most = nb > 64 && tiles < 10 ? 1 : tiles / kPartTiles, p = kCus / nb < most ? kCus / nb : most;
     return p > 1 ? (int)p : 1;
 }
-AttnParts attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool with_len) {
+AttnParts attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool with_len, size_t room) {
     AttnParts p{1, 0, 0, 0};
     if (n_q < 1 || n_kv < 1) return p;
     const int64_t nb = (n_q + kAtQPerBlock - 1) / kAtQPerBlock * H;
+    const int64_t states = (int64_t)(room / kStateBytes < 0x7fffffff ? room / kStateBytes : 0x7fffffff);
     const int64_t full = n_kv / chunk_len, rest = n_kv - full * chunk_len;
     const int64_t tiles = full * ((chunk_len + kAtKv - 1) / kAtKv) + (rest + kAtKv - 1) / kAtKv;
     if (with_len && nb >= kLenMinBlocks && tiles >= kLenMinTiles) {
         p.part_tiles = kLenPartTiles;
-        p.parts = nb <= kCus ? kLenParts : 1;
+        p.parts = nb <= kCus && states >= kLenParts * nb ? kLenParts : 1;
         return p;
     }
     if (nb > kCus && nb <= kTailMaxBlocks) {
         const int64_t rest = nb % kCus, most = tiles / kPartTiles;
         if (with_len || rest == 0 || rest > kCus / 2 || tiles < kTailMinTiles) return p;
-        p.parts = (int)(kCus / rest < most ? kCus / rest : most);
+        const int64_t parts = kCus / rest < most ? kCus / rest : most;
+        if (states < parts * rest) return p;
+        p.parts = (int)parts;
         p.whole = (int)(nb - rest);
         return p;
     }
     if (nb > kCus) return p;
     const int first = parts_at_first(nb, tiles);
+    const int64_t fit = states / nb, most = kCus / nb < fit ? kCus / nb : fit;
     if (first > 1) p.aligned = first;
-    if (with_len && first == 1) return p;
-    if (nb <= kCostBlocks || tiles < kCostTiles) p.parts = parts_by_cost(n_q < kSharedMinQueries ? kOwnTiles : kSharedTiles, tiles, kCus / nb, H * n_q, first);
+    if ((with_len && first == 1) || fit < first) return p;
+    if (nb <= kCostBlocks || tiles < kCostTiles) p.parts = parts_by_cost(n_q < kSharedMinQueries ? kOwnTiles : kSharedTiles, tiles, most, H * n_q, first);
     else p.parts = first;
     return p;
 }
-size_t attn_parts_bytes(int H, int64_t n_q, const AttnParts &p) {
-    const int64_t nqb = (n_q + kAtQPerBlock - 1) / kAtQPerBlock;
-    return p.parts > 1 ? (size_t)p.parts * (nqb * H - p.whole) * kStateFloats * kAtThreads * sizeof(float) : 0;
+size_t attn_state_bytes(int H, int64_t n_q, const AttnParts &p) {
+    const int64_t nqb = (n_q + kAtQPerBlock - 1) / kAtQPerBlock, most = p.parts > p.aligned ? p.parts : p.aligned;
+    return most > 1 ? (size_t)most * (nqb * H - p.whole) * kStateBytes : 0;
 }
 
 // The end of a join: a lane's NV values from value v0 on (channels 32 * (v0 / 16) + 8 * (v / 4 % 4) + 4 * half + v % 4) of

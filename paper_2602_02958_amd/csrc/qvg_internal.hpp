@@ -285,11 +285,12 @@ struct AttnArgs {
                            // no block is divided, else the blocks at the end that sees more are taken first
 };
 hipError_t launch_attn(const AttnArgs &a, hipStream_t s);
-// parts for a call of these sizes (with_len: with a prefix length per query), and the bytes of their state (0 for a single part)
-// aligned: not 0: scratch of at least this many parts' states has to be 16-byte aligned
+// parts for a call of these sizes (with_len: with a prefix length per query) whose states `room` bytes hold, and the bytes that a
+// call is told to bring for them
+// aligned: not 0: scratch of at least this many parts' states has to be 16-byte aligned, and with less the call is not divided
 struct AttnParts { int parts, part_tiles, whole, aligned; };             // (the first three as in AttnArgs)
-AttnParts attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool with_len);
-size_t attn_parts_bytes(int H, int64_t n_q, const AttnParts &p);
+AttnParts attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool with_len, size_t room = SIZE_MAX);
+size_t attn_state_bytes(int H, int64_t n_q, const AttnParts &p);
 hipError_t launch_attn_join(const AttnArgs &a, hipStream_t s);
 // The same attention with every tile decoded once per unit into a caller-lent workspace and shared
 // by all query blocks (qvg_attn_slab.hip).  Workspace = running state of the queries (only when the

@@ -1,7 +1,11 @@
 """Which attention calls are divided, and the scratch that they ask for: the library's host arithmetic, no GPU."""
+import os
+import subprocess
+
 import pytest
 
 from paper_2602_02958_amd import binding as B
+from paper_2602_02958_amd import build as qbuild
 
 STATE = 66 * 512 * 4                             # bytes of a query block's state
 SHAPES = [(1, 1), (1, 64), (1, 300), (2, 64), (8, 64), (3, 700), (9, 64), (16, 200), (5, 600), (12, 600), (64, 64), (65, 64), (40, 700),
@@ -57,3 +61,18 @@ def test_misaligned_scratch_of_calls_that_have_always_been_divided_is_refused():
             B.C.c_float(0.1), fake, None, None, None, 0, odd, room, None)
     assert call(1, 64, 512, 2 * STATE) == -5 and call(1, 64, 4096, 16 * STATE) == -5
     assert call(64, 200, 512, 64 * 2 * STATE) == -5 and call(65, 1, 640, 65 * 2 * STATE) == -5
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("host_parts") / "host_parts")
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    subprocess.run([hipcc, *qbuild.FLAGS, "--offload-host-only", os.path.join(os.path.dirname(os.path.abspath(__file__)), "host_parts.cpp"),
+                    "-x", "none", qbuild.LIB, "-Wl,-rpath," + os.path.dirname(qbuild.LIB), "-o", exe], check=True, stderr=subprocess.DEVNULL)
+    text = subprocess.run([exe], check=True, capture_output=True, text=True).stdout
+    return dict(line.split(" ", 1) for line in text.splitlines())
+
+
+@pytest.mark.parametrize("name", ["longer_caches", "what_is_asked_for"])
+def test_parts_by_the_scratch_that_is_lent(rules, name):
+    assert rules[name] == "ok"
