@@ -19,11 +19,10 @@ __device__ __forceinline__ uint2 never_wins() { return make_uint2(__float_as_uin
 __device__ __forceinline__ void note_zero_norm(uint2 nh, int row, int *zero) {
     if (!((nh.x | nh.y) & 0x7fff7fffu)) atomicMin(zero, row);
 }
-// By the whole workgroup, behind a barrier after the table, its norms nh (of rows t and t + 256, thread t) and the notes.  A barrier
-// precedes the table's use.
-__device__ __forceinline__ void drop_zero_rows(bf16_t *lc, int K, const uint2 (&nh)[kMaxClusters / kAsgThreads], int *zero) {
+// By the whole workgroup (tid: the thread's number; in a loop over tables one that the compiler cannot carry through it), behind a barrier
+// after the table, its norms nh (of rows t and t + 256, thread t) and the notes.  A barrier precedes the table's use.
+__device__ __forceinline__ void drop_zero_rows(int tid, bf16_t *lc, int K, const uint2 (&nh)[kMaxClusters / kAsgThreads], int *zero) {
     if (*zero >= K) return;                                              // uniform
-    const int tid = (int)threadIdx.x;
     bool is_zero[kMaxClusters / kAsgThreads];
 #pragma unroll
     for (int k = 0; k < kMaxClusters / kAsgThreads; ++k) {

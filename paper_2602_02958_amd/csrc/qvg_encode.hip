@@ -160,7 +160,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
         }
     }
     __syncthreads();
-    if (LATER && a.nh3) drop_zero_rows(lc, K, nh, &zero_row);           // uniform
+    if (LATER && a.nh3) drop_zero_rows(tid, lc, K, nh, &zero_row);           // uniform
     const float cmax = __uint_as_float(smax);
     bf16_t *scr = lscr + wave * kHeadDim;
     float *sscr = lsscr + wave * Kpad;

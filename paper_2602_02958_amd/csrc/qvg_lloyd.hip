@@ -551,7 +551,7 @@ __device__ __forceinline__ void stage_table(int h, int stage, bool start, bool o
     }
     if (stage > 0) deal_rows(members, K, a.row_weight, g, groups, deal); // uniform
     __syncthreads();
-    if (stage > 0) drop_zero_rows(lc, K, nh, &deal.zero);                // uniform
+    if (stage > 0) drop_zero_rows(thread_id(), lc, K, nh, &deal.zero);                // uniform
 }
 
 // blockIdx.x -> (unit, workgroup of the unit).  With eight units or more a unit's workgroups are 8 apart, on one
