@@ -189,7 +189,7 @@ __device__ __forceinline__ void decode_pass(int T, int S_, uint32_t ln0, uint32_
 // in LDS once (the only shared operand) and then streams its tokens.
 template <int T_, int SM, int FMT, int SC, bool WIDE>   // T_ > 0: compile-time stage count; T_ == 0: run-time.  SM, FMT, SC, WIDE: see decode_pass
 __global__ __launch_bounds__(kDecThreads)
-void decode_kernel(DecodeArgs a, int slices, uint32_t slice_len, int n_blocks, int blocks_per_xcd) {
+void decode_kernel(DecodeArgs a, int slices, int per_unit, uint32_t slice_len, int n_blocks, int blocks_per_xcd) {
     extern __shared__ __align__(16) unsigned char smem[];
     bf16_t *tab = reinterpret_cast<bf16_t *>(smem);                 // [K][128]
     // Workgroups are dealt to the XCDs round-robin by their linear id; re-number them so that
@@ -197,8 +197,7 @@ void decode_kernel(DecodeArgs a, int slices, uint32_t slice_len, int n_blocks, i
     // region of the output.
     const int w = (int)(blockIdx.x % kXcds) * blocks_per_xcd + (int)(blockIdx.x / kXcds);
     if (w >= n_blocks) return;
-    const int per_unit = a.n_chunks * slices;
-    const int h = w / per_unit;
+    const int h = w / per_unit;                                     // (in a single round a unit's last chunk may have fewer slices)
     const int c = (w - h * per_unit) / slices;
     const int sl = w - h * per_unit - c * slices;
     const int64_t cbeg = (int64_t)c * a.chunk_len;
@@ -246,24 +245,35 @@ void decode_kernel(DecodeArgs a, int slices, uint32_t slice_len, int n_blocks, i
 // 10.4; 24 x 10800, K = 64, T = 3 (1032 -> 240) 23.7 -> 17.8; 80 x 4680, T = 4 33 -> 27; 2 x 200000 in chunks of 10800 35 -> 30; with one round 1.02 to 1.2 times.
 // On fewer CUs it loses (130 units x 2000 tokens, T = 2 16.4 -> 18.9).  Otherwise enough workgroups to fill 256 CUs x 2
 // twice over, but as few as possible beyond that (every workgroup re-reads the chunk's table; measured flat from 512 to 4096).
-static int64_t decode_slice_len(int64_t unit_chunks, int64_t chunk) {
-    const int64_t max_slices = (chunk + kDecTokPerIter - 1) / kDecTokPerIter;
-    const int64_t per_cu = unit_chunks <= kDecCus ? kDecCus / unit_chunks : 0;
-    if (unit_chunks * max_slices > kDecCus && unit_chunks * per_cu >= kDecCus * 13 / 16 && per_cu * 8 * kDecTokPerIter >= chunk)
-        return ((chunk + per_cu - 1) / per_cu + 15) / 16 * 16;
+// A last chunk that is not full counts with the slices that it has (24 x 4688 in chunks of 4680, QVG-Pro: nine slices of a chunk 12.0, five, as if
+// both were full, 16.1, 256 tokens each 13.4; 24 x 9368, T = 4: a round would have 192 busy CUs, 23.6, and is not taken, 19.5).
+struct DecodeCall {
+    int64_t units, full, chunk, rest;            // full chunks of `chunk` tokens, and the tokens of one that is not
+    int64_t slices(int64_t len) const { return full * ((chunk + len - 1) / len) + (rest + len - 1) / len; }       // of a unit
+};
+static int64_t decode_slice_len(const DecodeCall &c) {
+    if (c.units * c.slices(kDecTokPerIter) > kDecCus) {
+        for (int64_t n = kDecCus / (c.units * c.full); n > 0; --n) {
+            const int64_t len = ((c.chunk + n - 1) / n + 15) / 16 * 16, last = c.rest * kDecCus / len;            // (in 256ths)
+            if (len > 8 * kDecTokPerIter || c.units * (c.full * n * kDecCus + last) < kDecCus * kDecCus * 13 / 16) break;
+            if (c.units * c.slices(len) <= kDecCus) return len;
+        }
+    }
+    const int64_t unit_chunks = c.units * (c.full + (c.rest > 0)), max_slices = (c.chunk + kDecTokPerIter - 1) / kDecTokPerIter;
     int64_t slices = (4 * kDecCus + unit_chunks - 1) / unit_chunks;
     if (slices > max_slices) slices = max_slices;
-    const int64_t len = (chunk + slices - 1) / slices;
+    const int64_t len = (c.chunk + slices - 1) / slices;
     return (len + kDecTokPerIter - 1) / kDecTokPerIter * kDecTokPerIter;
 }
 
 template <int T_, int SM, int FMT, int SC, bool WIDE>
 static hipError_t launch_decode_w(const DecodeArgs &a, hipStream_t s) {
-    const int64_t unit_chunks = (int64_t)a.H * a.n_chunks;
     const int64_t chunk = a.chunk_len < a.n_tokens ? a.chunk_len : a.n_tokens;
-    const int64_t slice_len = decode_slice_len(unit_chunks, chunk);
-    const int64_t slices = (chunk + slice_len - 1) / slice_len;
-    const int64_t nb = unit_chunks * slices;
+    const DecodeCall call{a.H, a.n_tokens / chunk, chunk, a.n_tokens % chunk};
+    const int64_t slice_len = decode_slice_len(call);
+    const int64_t slices = (chunk + slice_len - 1) / slice_len, one = call.slices(slice_len);
+    // (in a single round no workgroup is without a slice; in more the numbers of a last chunk go as far as those of the others)
+    const int64_t per_unit = one * a.H <= kDecCus ? one : slices * a.n_chunks, nb = per_unit * a.H;
     if (nb > 0x7fffffff - kXcds) return hipErrorInvalidValue;
     const int bpx = (int)((nb + kXcds - 1) / kXcds);
     const size_t smem = (SM == 3) ? 16 : (size_t)(SM == 1 ? 1 : a.S) * a.K * kHeadDim * sizeof(bf16_t);
@@ -271,7 +281,7 @@ static hipError_t launch_decode_w(const DecodeArgs &a, hipStream_t s) {
     hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&decode_kernel<T_, SM, FMT, SC, WIDE>), smem, lds_limit);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((decode_kernel<T_, SM, FMT, SC, WIDE>), dim3((unsigned)(bpx * kXcds)), dim3(kDecThreads), smem, s, a,
-                       (int)slices, (uint32_t)slice_len, (int)nb, bpx);
+                       (int)slices, (int)per_unit, (uint32_t)slice_len, (int)nb, bpx);
     return hipGetLastError();
 }
 
