@@ -471,7 +471,7 @@ struct TokenSearch {
         int id = i1;
         // (rows K.. and rows of zeros but the first are not candidates.  A band that is not finite: scores of tokens or rows
         // whose norm fp32 does not hold may be missing from the ranking, so there the second best says nothing)
-        const bool amb = valid && (i2 < K || !(thr < pinf)) && !(c1 - c2 > thr);
+        const bool amb = valid && !((i2 < K ? c1 - c2 : pinf) > thr);
         const bool full = !(c1 - c3 > thr);
 
         // ---- fp64 re-evaluation of tokens the fp32 scores cannot decide ----
