@@ -952,7 +952,8 @@ struct PartCost { int64_t tile, join, state_by_100; };                   // ns; 
 constexpr PartCost kOwnTiles{2300, 4700, 21}, kSharedTiles{1500, 3000, 30};
 constexpr int64_t kSharedMinQueries = 513;        // queries per unit from which a workspace for the tiles is the rule
 // Parts of `tiles` tiles of a call of `queries` queries, `most` at most: by what the longest part's tiles, the join's launch and
-// the states of all parts take.  Among equal longest parts the fewest.  No part is longer than in `first` parts (1: the call may stay
+// the states of all parts take.  Among equal longest parts the fewest, but never fewer than `first` (16 heads x 490 queries over 35 tiles, 4-bit
+// levels, in eight parts of which three have five tiles 37.4 us, in seven of five 40.2).  No part is longer than in `first` parts (1: the call may stay
 // whole): the cost is that of two rounds of levels without rotary keys, and four stages take up to three times that a tile (40
 // heads x 700 queries over 768 tokens, E4M3 scales, whole and in two parts: 59 us, 46; with rotary keys 79, 55; with prefix lengths
 // 146, 95; two rounds of levels 42, 42).
@@ -965,7 +966,7 @@ static int parts_by_cost(const PartCost &c, int64_t tiles, int64_t most, int64_t
     const int64_t limit = (tiles + first - 1) / first;
     int64_t parts = first, best = first > 1 ? INT64_MAX : tiles * c.tile;
     for (int64_t longest = (tiles + most - 1) / most; longest <= limit && longest * c.tile + c.join < best; ++longest) {
-        const int64_t p = (tiles + longest - 1) / longest, cost = longest * c.tile + c.join + p * queries * c.state_by_100 / 100;
+        const int64_t p = longest < limit ? (tiles + longest - 1) / longest : first, cost = longest * c.tile + c.join + p * queries * c.state_by_100 / 100;
         if (cost < best) { best = cost; parts = p; }
     }
     return (int)parts;
@@ -973,7 +974,7 @@ static int parts_by_cost(const PartCost &c, int64_t tiles, int64_t most, int64_t
 // Parts of four tiles at least until the chip is full, and of more than 64 blocks not below ten tiles: the calls that were divided
 // at first.  They refuse scratch that is not aligned; the others took any, and one that they cannot use is ignored.
 // They grow with the cache, the parts by cost do not (8 heads x 64 queries: 32 tiles in 32 parts, 33 in 17).  So that scratch for a long
-// cache serves every shorter one, as many parts are taken as it holds, and these at least are asked for.
+// cache serves every shorter one, as many parts are taken as it holds, and never fewer than these are asked for.
 static int parts_at_first(int64_t nb, int64_t tiles) {
     const int64_t most = nb > 64 && tiles < 10 ? 1 : tiles / kPartTiles, p = kCus / nb < most ? kCus / nb : most;
     return p > 1 ? (int)p : 1;
@@ -1009,8 +1010,8 @@ AttnParts attn_parts(int H, int64_t n_q, int64_t n_kv, int64_t chunk_len, bool w
     return p;
 }
 size_t attn_state_bytes(int H, int64_t n_q, const AttnParts &p) {
-    const int64_t nqb = (n_q + kAtQPerBlock - 1) / kAtQPerBlock, most = p.parts > p.aligned ? p.parts : p.aligned;
-    return most > 1 ? (size_t)most * (nqb * H - p.whole) * kStateBytes : 0;
+    const int64_t nqb = (n_q + kAtQPerBlock - 1) / kAtQPerBlock;
+    return p.parts > 1 ? (size_t)p.parts * (nqb * H - p.whole) * kStateBytes : 0;
 }
 
 // The end of a join: a lane's NV values from value v0 on (channels 32 * (v0 / 16) + 8 * (v / 4 % 4) + 4 * half + v % 4) of

@@ -33,6 +33,7 @@ static const char *longer_caches() {
                     }
                     const int64_t four = blocks(s) > 64 && tiles < 10 ? 1 : 256 / blocks(s) < tiles / 4 ? 256 / blocks(s) : tiles / 4;
                     if (four > 1 && longest(tiles, p.parts) > longest(tiles, four)) return "longer parts than of four tiles";
+                    if (best.parts < four) return "fewer parts than of four tiles";
                     if (p.parts > best.parts && longest(tiles, p.parts) < longest(tiles, best.parts)) return "more than the best";
                 }
             }
