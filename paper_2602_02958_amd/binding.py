@@ -292,8 +292,8 @@ def _scratch(nbytes: int, device):
 
 
 def _may_divide(n_kv, chunk_len):
-    """False for caches of fewer than four tiles, which are never divided: a call over them is host time (11.7 us,
-    12.5 with the question asked)."""
+    """False for caches of fewer than four tiles, which are never divided: a call over them is host time and does without
+    the question (which a call of sizes that were not there before puts to the library)."""
     return n_kv // 64 + n_kv // chunk_len >= 3
 
 

@@ -12,8 +12,8 @@ constexpr int kScanPairs = 24;                  // candidates up to which fp64 d
 // Rows of zeros but the first are taken out of a staged table: of equal rows only the lowest can be a token's nearest.
 // The residuals of clusters of one token are zero, so a later smoothing stage has a dozen such rows among its centroids, and
 // every token near zero had as many candidates: each a scan of the table and their fp64 distances, one after the
-// other (K = 256, four stages: 24 units x 4680 tokens, in one launch, 495 -> 455 us; 6 x 1560 814 -> 297; 80 x 4680, in launches of their
-// own, 1504 -> 1294).
+// other (K = 256, four stages: 24 units x 4680 tokens, in one launch, 495 -> 455 us; 6 x 1560 783 -> 295; 80 x 4680, in launches of their
+// own, 1492 -> 1354).
 __device__ __forceinline__ uint2 never_wins() { return make_uint2(__float_as_uint(-3.0e38f) >> 16, 0u); }      // a norm's split
 // zero: an LDS word, kMaxClusters while no row with a norm of zero is known
 __device__ __forceinline__ void note_zero_norm(uint2 nh, int row, int *zero) {

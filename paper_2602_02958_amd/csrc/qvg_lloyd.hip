@@ -26,10 +26,8 @@
 // there are, so that it costs little where none comes and few members do not go on alone where others come soon.
 // Beside an attention of 130 / 170 / 200 workgroups on another stream that lasts 3 ms, us (launches per iteration; this; as it was
 // when a unit waited 2 ms and one workgroup did it over): 24 units x 4680 tokens, K = 256, T = 4, I = 3 295 / 420 / 760; 350 / 860 / 1255; 359 / - / 3190;
-// four stages 1205 / 1820 / 2370; 1520 / 2390 / 3000; 1500 / - / 6500; INT4, 10 x 1571 101 / 116 / 174; 158 / 163 / 370; 143 / - / 2520.  Two streams of
-// encodes, a pair of them: 225, 213, 214; 900, 931, 953; 123, 102, 104.  (A wait half as long: 200 workgroups 1070, two
-// streams of four stages 1000; twice as long 1610, 928.)  The figures of four stages are from before update_rows dealt later stages' rows
-// by their members (alone 540 us then, 449 now).
+// INT4, 10 x 1571 101 / 116 / 174; 158 / 163 / 370; 143 / - / 2520.  Two streams of encodes, a pair of them: 225, 213, 214; 123, 102, 104.  (A
+// wait half as long: 200 workgroups 1070; twice as long 1610.)
 #include "qvg_assign.hpp"
 
 namespace qvg {
@@ -817,9 +815,10 @@ int lloyd_groups(int H, int K, int64_t n_tokens, int64_t stride_token, int iters
     return nb < 6 && K > 31 * groups ? 0 : (int)groups;
 }
 
-// The formats whose rounds the launch writes itself: 2-bit levels with binary16 scales, and the paper's presets with E4M3 scales (one
-// round of 2-bit levels in groups of 64 or, QVG-Pro, 16, of 4-bit levels in groups of 64).  The others have quantize_kernel after it,
-// a launch that reads the tokens, ids and rows once more.
+// The formats whose rounds the launch writes itself: 2-bit levels with binary16 scales, and with E4M3 scales one
+// round of 2-bit levels in groups of 64 or 16 or of 4-bit levels in groups of 64: the paper's presets but QVG-Pro INT4 (4
+// of 461 us, 24 units x 4680 tokens: not worth one more instance).  The others have quantize_kernel after it, a launch that reads the tokens,
+// ids and rows once more.
 bool lloyd_fuses(int fmt, int B, int T) {
     if (fmt == 0) return true;
     return T == 1 && ((fmt == kFmtE4M3 && (B == 16 || B == 64)) || (fmt == (kFmtE4M3 | kFmtInt4) && B == 64));

@@ -2,7 +2,8 @@
 // applied progressively as in Sec. 4.2) for a GIVEN assignment, in every stored format:
 // 2-bit or 4-bit levels (Sec. 5: INT2 / INT4), binary16 or FP8 E4M3 scales (Sec. 5
 // "Implementation").  The encoder uses it after the assignment kernel whenever the format is
-// not the one the fused assignment kernel writes (2-bit levels with binary16 scales).
+// not the one the fused assignment kernel writes (2-bit levels with binary16 scales), and after the one launch of
+// qvg_lloyd.hip for the formats that this one does not write itself (lloyd_fuses).
 //
 // Per token it reads 256 B of x, one id and one centroid row (L2) and writes T*(d*b/8 + d/B
 // scales): a streaming kernel.  Mapping: 16 lanes per token, 8 channels per lane, so a group of

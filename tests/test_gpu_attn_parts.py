@@ -1,6 +1,6 @@
 """Attention of few query blocks: the cache's tiles are dealt to several workgroups per query block and
-their partial results joined.  Against the oracle at the existing bound, at sizes where the deal is
-ragged (a last part with fewer tiles, chunks of one tile, parts that lie behind every prefix);
+their partial results joined.  Against the oracle at the existing bound, with chunks of one tile and parts that lie behind
+every prefix (most with a tile to a part; several tiles to a part: test_gpu_attn_several_tiles_per_part.py);
 equal bits with a tile workspace, without one and in the fp32 result; NaN stays in its row."""
 import numpy as np
 import pytest
@@ -26,7 +26,7 @@ def _scratch_bytes(H, Nq, n_kv, L):
 
 
 @pytest.mark.parametrize("H,Nq,L,chunks,n_kv,T,Bg,S,bits,fmt,K", [
-    (1, 1, 520, 1, 511, 2, 64, 1, 2, B.SCALE_F16, 16),       # eight tiles, two parts, the last tile one short
+    (1, 1, 520, 1, 511, 2, 64, 1, 2, B.SCALE_F16, 16),       # eight tiles, eight parts, the last tile one short
     (1, 64, 520, 3, 1173, 3, 32, 1, 2, B.SCALE_F16, 64),     # staged kernel, chunks of 8 tiles + 8 tokens
     (2, 33, 516, 2, 1000, 2, 64, 1, 2, B.SCALE_F16, 16),     # general kernel
     (3, 256, 40, 20, 793, 2, 64, 1, 2, B.SCALE_F16, 16),     # chunks of one short tile

@@ -41,7 +41,7 @@ def _check(H, N, L, K, Bg, T, bits, fmt):
 
 
 @pytest.mark.parametrize("H,N,L", [
-    (1, 65537, 65537),       # 256 slices of 272 tokens, the last with 1
+    (1, 65537, 65537),       # 241 slices of 272 tokens, the last with 257
     (1, 524288, 524288),     # eight whole passes each: the longest slices of the rule
     (24, 4680, 4680),        # ten slices of 480, the last 360
     (2, 40001, 4680),        # 14 slices of 336 per chunk, the last chunk 2561 tokens
