@@ -469,10 +469,12 @@ struct TokenSearch {
         // (the last term: the tag of a score that is zero, where all norms are)
         const float thr = (K > 256 ? 0x1.8p-14f : 0x1p-14f) * (0.5f * xn + fminf(cmax, reach)) + 0x1p-126f;
         int id = i1;
-        // (rows K.. and rows of zeros but the first are not candidates.  A band that is not finite: scores of tokens or rows
-        // whose norm fp32 does not hold may be missing from the ranking, so there the second best says nothing)
-        const bool amb = valid && !((i2 < K ? c1 - c2 : pinf) > thr);
-        const bool full = !(c1 - c3 > thr);
+        // Rows K.. and rows of zeros but the first, which score never_wins(), lie below `none` and are no candidates.  But where the best itself
+        // does, the scores of all rows that could be have overflowed; and where the band is not finite, those of tokens or rows
+        // whose norm fp32 does not hold may be missing from the ranking: both mean the exact distances of all rows.
+        constexpr float none = -2.9e38f;
+        const bool amb = valid && !(c1 - fmaxf(c2, none) > thr);
+        const bool full = !(c1 - fmaxf(c3, none) > thr);
 
         // ---- fp64 re-evaluation of tokens the fp32 scores cannot decide ----
         uint64_t mask = __ballot(amb) & 0xffffffffull;
