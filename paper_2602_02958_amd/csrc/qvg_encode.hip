@@ -56,9 +56,11 @@ hipError_t launch_half_norms(const bf16_t *cent, int64_t cent_stride, int H, int
 // grid: x = unit, y = block of 256 * tiles_per_wave tokens.  With the unit as the fastest grid
 // index and H a multiple of 8, all blocks of a unit run on one XCD and share its table in L2.
 // T_: number of quantization rounds of the fused pass when known at compile time (0: a.T)
-// LATER: the tokens are residuals, the table may have several rows of zeros.  (An instance of its own, so that the first
-// stage's launches stay as they are.  Not with FUSED, one of a stage's I + 1 passes.)
-template <int B_, bool FUSED, int T_, bool LATER>
+// ZEROS: a call of several smoothing stages, whose later tables may have several rows of zeros.  (An instance of its own, so that calls of
+// one stage stay as they are; for all stages, as a second kernel is cold when it is first launched: 6 units x 2000 tokens, two stages 136.7
+// us without the search, 137.7, 139.3 with the first stage's launches left out; 40 x 10800, K = 256 711, 715, 720.  Not with FUSED, one of a
+// stage's I + 1 passes.)
+template <int B_, bool FUSED, int T_, bool ZEROS>
 __global__ __launch_bounds__(kAsgThreads, 2)
 void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -77,7 +79,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
     // ||c||^2 of the unit (one ulp up) is needed for the error band of the certification.
     __shared__ uint32_t smax;
     __shared__ int zero_row;
-    if (tid == 0) { smax = 0u; if (LATER) zero_row = kMaxClusters; }
+    if (tid == 0) { smax = 0u; if (ZEROS) zero_row = kMaxClusters; }
     const bf16_t *cg = a.cent + (int64_t)h * a.cent_stride;
     uint2 nh[kMaxClusters / kAsgThreads];
 #pragma unroll
@@ -151,7 +153,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
         for (int u = 0; u < kMaxClusters / kAsgThreads; ++u) {
             const int row = tid + u * kAsgThreads;
             float up = 0.0f;
-            if (row < Kpad) { up = place_norm(row, nh[u]); if (LATER) note_zero_norm(nh[u], row, &zero_row); }
+            if (row < Kpad) { up = place_norm(row, nh[u]); if (ZEROS) note_zero_norm(nh[u], row, &zero_row); }
             if (u * kAsgThreads < Kpad) {                               // uniform
 #pragma unroll
                 for (int off = 32; off >= 1; off >>= 1) up = fmaxf(up, __shfl_xor(up, off, 64));
@@ -160,7 +162,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
         }
     }
     __syncthreads();
-    if (LATER && a.nh3) drop_zero_rows(tid, lc, K, nh, &zero_row);           // uniform
+    if (ZEROS && a.nh3) drop_zero_rows(tid, lc, K, nh, &zero_row);      // uniform
     const float cmax = __uint_as_float(smax);
     bf16_t *scr = lscr + wave * kHeadDim;
     float *sscr = lsscr + wave * Kpad;
@@ -277,18 +279,18 @@ bool assign_takes_norms(int H, int K, int64_t n_tokens, bool fused) {
     return kp <= 128 && wgs * kp * kp <= ((int64_t)1 << 23);
 }
 
-template <int B_, bool FUSED, int T_, bool LATER = false>
+template <int B_, bool FUSED, int T_, bool ZEROS = false>
 static hipError_t launch_assign_t(const AssignArgs &a, hipStream_t s) {
     const int Kpad = k_padded(a.K);
     const size_t smem = assign_smem_bytes(Kpad);
     static LdsHighWater lds_limit = {};
-    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&assign_kernel<B_, FUSED, T_, LATER>), smem, lds_limit);
+    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(&assign_kernel<B_, FUSED, T_, ZEROS>), smem, lds_limit);
     if (e != hipSuccess) return e;
     const int tpw = assign_tiles_per_wave(a.H, a.n_tokens);
     const int64_t gy = (a.n_tokens + kAsgThreads * tpw - 1) / (kAsgThreads * tpw);
     if (gy > 65535) return hipErrorInvalidValue;
     if (a.lists.perm && (a.lists.block != kAsgThreads * tpw || a.lists.n_blocks != gy)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((assign_kernel<B_, FUSED, T_, LATER>), dim3((unsigned)a.H, (unsigned)gy), dim3(kAsgThreads), smem, s, a,
+    hipLaunchKernelGGL((assign_kernel<B_, FUSED, T_, ZEROS>), dim3((unsigned)a.H, (unsigned)gy), dim3(kAsgThreads), smem, s, a,
                        Kpad, tpw);
     return hipGetLastError();
 }
@@ -306,7 +308,7 @@ static hipError_t launch_fused(const AssignArgs &a, hipStream_t s) {
 
 hipError_t launch_assign(const AssignArgs &a, hipStream_t s) {
     if (a.n_tokens == 0) return hipSuccess;
-    if (!a.fused) return a.ids_off > 0 ? launch_assign_t<64, false, 0, true>(a, s) : launch_assign_t<64, false, 0>(a, s);
+    if (!a.fused) return a.ids_step > 1 ? launch_assign_t<64, false, 0, true>(a, s) : launch_assign_t<64, false, 0>(a, s);
     switch (a.B) {
         case 16: return launch_fused<16>(a, s);
         case 32: return launch_fused<32>(a, s);
