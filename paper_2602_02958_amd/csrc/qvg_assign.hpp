@@ -276,7 +276,7 @@ struct TokenSearch {
             }
         }
         if (left >= 0 && bj < K) return bj;
-        bd = INFINITY; bj = 0x7fffffff;
+        bd = INFINITY; bj = 0xffff;           // (stays where no distance is a number: near no row, and every list leaves it out)
         // many candidates (equal centroids): one per lane, the channels summed in index order
         for (int j = lane; j < K; j += 64) {
             const bf16_t *cr = lc + j * kCPitch;

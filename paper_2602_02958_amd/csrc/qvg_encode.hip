@@ -199,7 +199,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
             if (!FUSED) {
                 if (a.lists.perm && half == 0) lid[(k * kAsgWaves + wave) * kAsgTile + tb * 32 + col] = valid[tb] ? (uint16_t)id : 0xffffu;
                 if (a.resid && valid[tb]) {                              // Eq. 5, rounded to bf16: the next smoothing stage's input
-                    const bf16_t *crow = lc + id * kCPitch + half * 64;
+                    const bf16_t *crow = lc + (id != 0xffff ? id : 0) * kCPitch + half * 64;
                     bf16_t *rp = a.resid + ((int64_t)h * N + n[tb]) * kHeadDim + half * 64;
 #pragma unroll
                     for (int kk = 0; kk < 8; ++kk) {
@@ -216,7 +216,7 @@ void assign_kernel(AssignArgs a, int Kpad, int tiles_per_wave) {
 
             // ---- Eq. 5: residual against the assigned centroid, then the T rounds ----
             float r[64];
-            const bf16_t *crow = lc + id * kCPitch + half * 64;
+            const bf16_t *crow = lc + (id != 0xffff ? id : 0) * kCPitch + half * 64;
 #pragma unroll
             for (int kk = 0; kk < 8; ++kk) {
                 const uint4 cv = *reinterpret_cast<const uint4 *>(crow + kk * 8);

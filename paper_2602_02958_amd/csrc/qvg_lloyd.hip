@@ -642,7 +642,7 @@ begin:
                     const int S = a.S;
                     const int64_t hn = (int64_t)h * a.out_stride + n;
                     if (valid && half == 0) store_id(a.ids, hn * S + stage, a.id_wide, (uint32_t)id[tb]);
-                    const bf16_t *crow = lc + (valid ? id[tb] : 0) * kCPitch + half * 64;
+                    const bf16_t *crow = lc + (id[tb] != 0xffff ? id[tb] : 0) * kCPitch + half * 64;
                     if (stage + 1 < S) {                                 // Eq. 5, rounded to bf16: the next stage's input
                         const Shared resid(a.resid[stage & 1] + (int64_t)h * N * kHeadDim, (uint32_t)N * kHeadDim * 2);
 #pragma unroll
