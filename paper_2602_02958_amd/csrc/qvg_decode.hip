@@ -240,22 +240,34 @@ void decode_kernel(DecodeArgs a, int slices, int per_unit, uint32_t slice_len, i
 
 // Tokens per workgroup.  A workgroup of sixteen wavefronts has a CU to itself (two share one with one round of 2-bit
 // levels), so a call of one to five rounds of workgroups pays for the round that is nearly empty, and every workgroup
-// waits for its table before it writes.  Where slices of up to eight passes make one round that fills at least 208 CUs, each CU gets one slice,
+// waits for its table before it writes.  Where slices of up to eight passes make one round that keeps enough CUs busy, each CU gets one slice,
 // us before and after (back to back): 24 units x 4680 tokens, K = 256, T = 2 (456 slices -> 240) 9.5 -> 8.4, T = 4 11.6 ->
-// 10.4; 24 x 10800, K = 64, T = 3 (1032 -> 240) 23.7 -> 17.8; 80 x 4680, T = 4 33 -> 27; 2 x 200000 in chunks of 10800 35 -> 30; with one round 1.02 to 1.2 times.
-// On fewer CUs it loses (130 units x 2000 tokens, T = 2 16.4 -> 18.9).  Otherwise enough workgroups to fill 256 CUs x 2
+// 10.4; 24 x 10800, K = 64, T = 3 (1032 -> 240) 23.7 -> 17.8; 80 x 4680, T = 4 33 -> 27; 2 x 200000 in chunks of 10800 35 -> 30.
+// 60 sizes of each format, ratio: T = 3 0.80, 4 0.85, 2 0.92, several stages 0.84, 4-bit levels 0.95.  Not
+// - on too few CUs (130 units x 2000 tokens, T = 2 16.4 -> 18.9): from 152 busy ones on with more than 128 rows, whose table a workgroup
+//   waits for (152 to 207: 0.67 to 1.02), from 184 on with fewer (below, T = 4 and 5 up to 1.10), from 192 on with several stages (below up to
+//   1.07), from 208 on with one round of 2-bit levels;
+// - where a token has few bytes, and many small workgroups do as well: one round of 2-bit levels, two workgroups to a CU, from 2.5 passes
+//   on (up to there 0.82 to 1.03; beyond 0.93 to 1.22, 10 units x 34738 tokens 19.1 -> 21.1), 64 bytes of levels from 2.5
+//   with tables of up to 32 rows (T = 2, K = 16: up to there 0.77 to 0.86, beyond 1.0 to 1.12) and from 4.5 with up to 128 (K = 64: up to
+//   there 0.73 to 1.04, beyond 0.90 to 1.08);
+// - where the tables that an XCD's 32 workgroups gather from, several stages' from global memory, do not fit its L2 (four stages, K = 256, a
+//   workgroup per chunk, 8 MB: 40 units x 8760 tokens in chunks of 1544 38 -> 44; two, 4 MB: 0.82 to 1.04).
+// Otherwise enough workgroups to fill 256 CUs x 2
 // twice over, but as few as possible beyond that (every workgroup re-reads the chunk's table; measured flat from 512 to 4096).
 // A last chunk that is not full counts with the slices that it has (24 x 4688 in chunks of 4680, QVG-Pro: nine slices of a chunk 12.0, five, as if
-// both were full, 16.1, 256 tokens each 13.4; 24 x 9368, T = 4: a round would have 192 busy CUs, 23.6, and is not taken, 19.5).
+// both were full, 16.1, 256 tokens each 13.4).
+constexpr int64_t kXcdL2 = (int64_t)4 << 20;
 struct DecodeCall {
     int64_t units, full, chunk, rest;            // full chunks of `chunk` tokens, and the tokens of one that is not
     int64_t slices(int64_t len) const { return full * ((chunk + len - 1) / len) + (rest + len - 1) / len; }       // of a unit
 };
-static int64_t decode_slice_len(const DecodeCall &c) {
+// longest: tokens of a slice at most, fewest: slices of a chunk at least, busy: CUs at least, where each CU gets one
+static int64_t decode_slice_len(const DecodeCall &c, int64_t longest, int64_t fewest, int64_t busy) {
     if (c.units * c.slices(kDecTokPerIter) > kDecCus) {
-        for (int64_t n = kDecCus / (c.units * c.full); n > 0; --n) {
+        for (int64_t n = kDecCus / (c.units * c.full); n >= fewest; --n) {
             const int64_t len = ((c.chunk + n - 1) / n + 15) / 16 * 16, last = c.rest * kDecCus / len;            // (in 256ths)
-            if (len > 8 * kDecTokPerIter || c.units * (c.full * n * kDecCus + last) < kDecCus * kDecCus * 13 / 16) break;
+            if (len > longest || c.units * (c.full * n * kDecCus + last) < kDecCus * busy) break;
             if (c.units * c.slices(len) <= kDecCus) return len;
         }
     }
@@ -270,7 +282,12 @@ template <int T_, int SM, int FMT, int SC, bool WIDE>
 static hipError_t launch_decode_w(const DecodeArgs &a, hipStream_t s) {
     const int64_t chunk = a.chunk_len < a.n_tokens ? a.chunk_len : a.n_tokens;
     const DecodeCall call{a.H, a.n_tokens / chunk, chunk, a.n_tokens % chunk};
-    const int64_t slice_len = decode_slice_len(call);
+    constexpr int64_t most = 8 * kDecTokPerIter;
+    constexpr int level_bytes = SM == 1 ? T_ * ((FMT & kFmtInt4) ? 64 : 32) : 0;                        // (0: many, or not known here)
+    const int64_t longest = level_bytes == 32 || (level_bytes == 64 && a.K <= 32) ? most * 5 / 16 : level_bytes == 64 && a.K <= 128 ? most * 9 / 16 : most;
+    const int64_t tables = (SM == 3 ? (int64_t)a.S * a.K * kHeadDim * 2 : 1) * (kDecCus / kXcds);       // of an XCD's workgroups
+    const int64_t busy = level_bytes == 32 ? 208 : SM != 1 ? 192 : a.K <= 128 ? 184 : 152;
+    const int64_t slice_len = decode_slice_len(call, longest, (tables + kXcdL2 - 1) / kXcdL2, busy);
     const int64_t slices = (chunk + slice_len - 1) / slice_len, one = call.slices(slice_len);
     // (in a single round no workgroup is without a slice; in more the numbers of a last chunk go as far as those of the others)
     const int64_t per_unit = one * a.H <= kDecCus ? one : slices * a.n_chunks, nb = per_unit * a.H;
