@@ -245,9 +245,9 @@ void decode_kernel(DecodeArgs a, int slices, int per_unit, uint32_t slice_len, i
 // 10.4; 24 x 10800, K = 64, T = 3 (1032 -> 240) 23.7 -> 17.8; 80 x 4680, T = 4 33 -> 27; 2 x 200000 in chunks of 10800 35 -> 30.
 // 60 sizes of each format, ratio: T = 3 0.80, 4 0.85, 2 0.92, several stages 0.84, 4-bit levels 0.95.  Not
 // - on too few CUs (130 units x 2000 tokens, T = 2 16.4 -> 18.9): from 152 busy ones on with more than 128 rows, whose table a workgroup
-//   waits for (152 to 207: 0.67 to 1.02), from 184 on with fewer (below, T = 4 and 5 up to 1.10), from 192 on with several stages (below up to
+//   waits for (152 to 207: 0.67 to 1.02), 128 with more than 320 (114 x 1987 in chunks of 1568, 145 busy ones, 28.5 -> 17.2), from 184 on with fewer (below, T = 4 and 5 up to 1.10), from 192 on with several stages (below up to
 //   1.07), from 208 on with one round of 2-bit levels;
-// - where a token has few bytes, and many small workgroups do as well: one round of 2-bit levels, two workgroups to a CU, from 2.5 passes
+// - where a token has few bytes, and many small workgroups do as well: one round of 2-bit levels, two workgroups to a CU (up to 320 rows), from 2.5 passes
 //   on (up to there 0.82 to 1.03; beyond 0.93 to 1.22, 10 units x 34738 tokens 19.1 -> 21.1), 64 bytes of levels from 2.5
 //   with tables of up to 32 rows (T = 2, K = 16: up to there 0.77 to 0.86, beyond 1.0 to 1.12) and from 4.5 with up to 128 (K = 64: up to
 //   there 0.73 to 1.04, beyond 0.90 to 1.08);
@@ -284,9 +284,10 @@ static hipError_t launch_decode_w(const DecodeArgs &a, hipStream_t s) {
     const DecodeCall call{a.H, a.n_tokens / chunk, chunk, a.n_tokens % chunk};
     constexpr int64_t most = 8 * kDecTokPerIter;
     constexpr int level_bytes = SM == 1 ? T_ * ((FMT & kFmtInt4) ? 64 : 32) : 0;                        // (0: many, or not known here)
-    const int64_t longest = level_bytes == 32 || (level_bytes == 64 && a.K <= 32) ? most * 5 / 16 : level_bytes == 64 && a.K <= 128 ? most * 9 / 16 : most;
+    const bool two = level_bytes == 32 && a.K <= 320;                    // workgroups to a CU, by registers and tables
+    const int64_t longest = two || (level_bytes == 64 && a.K <= 32) ? most * 5 / 16 : level_bytes == 64 && a.K <= 128 ? most * 9 / 16 : most;
     const int64_t tables = (SM == 3 ? (int64_t)a.S * a.K * kHeadDim * 2 : 1) * (kDecCus / kXcds);       // of an XCD's workgroups
-    const int64_t busy = level_bytes == 32 ? 208 : SM != 1 ? 192 : a.K <= 128 ? 184 : 152;
+    const int64_t busy = two ? 208 : SM != 1 ? 192 : a.K <= 128 ? 184 : a.K <= 320 ? 152 : 128;
     const int64_t slice_len = decode_slice_len(call, longest, (tables + kXcdL2 - 1) / kXcdL2, busy);
     const int64_t slices = (chunk + slice_len - 1) / slice_len, one = call.slices(slice_len);
     // (in a single round no workgroup is without a slice; in more the numbers of a last chunk go as far as those of the others)
